@@ -157,10 +157,13 @@ typedef struct {
   int32_t cg_max_iter;         /* >= 1                                                   */
   int32_t eig_max_sweeps;      /* Jacobi sweep cap, >= 1                                 */
   double eig_tol;              /* Jacobi column-orthogonality threshold; 0 = dtype default */
-  int32_t eig_refine;          /* 1: refine the float32 eigenpairs of every PSD block
-                                  once (Ogita-Aishima step with float64-accumulated
-                                  residual products) and form the projection by
-                                  Rayleigh-Ritz on the positive subspace; 0: use
+  int32_t eig_refine;          /* float32 plans.  1: eigenpairs and projection to better
+                                  than float32 accuracy: blocks up to order 128 sweep
+                                  in float64 until the couplings left are below 1e-11;
+                                  larger ones are refined after their float32 sweeps
+                                  (Ogita-Aishima steps with float64-accumulated residual
+                                  products, projection by Rayleigh-Ritz on the positive
+                                  subspace).  0: stop at the float32 threshold and use
                                   the Jacobi eigenpairs as they are.  Must be 0 or 1;
                                   ignored for COSMO_F64, whose sweeps run in float64. */
   int32_t eig_warm_start;      /* 1: start every step's Jacobi sweeps from the same
@@ -184,8 +187,10 @@ typedef struct {
   int32_t cg_iters_total;      /* PCG iterations summed over the solves                */
   int32_t cg_passes_total;     /* float64 true-residual passes summed over the solves
                                   (each is one more operator application)               */
-  int32_t eig_refine_steps_total; /* float32 eigenpair refinement steps summed over the
-                                  PSD block solves (1 to 3 per solve)                   */
+  int32_t eig_refine_steps_total; /* refinement steps of float32 plans summed over the PSD
+                                  block solves: the sweeps after the column cosines fell
+                                  below 1e-3 (orders up to 128), or the Ogita-Aishima
+                                  steps (larger orders)                                 */
 } cosmo_stats;
 
 const char *cosmo_status_string(cosmo_status s);

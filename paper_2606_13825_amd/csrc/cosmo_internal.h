@@ -261,6 +261,7 @@ struct PsdLaunchCfg {
   int32_t refine;          // float64 refinement steps after the Jacobi sweeps
   int32_t max_p;           // largest order in the list
   int32_t threads = 0;     // threads per workgroup of the eigensolve; 0 = the class default
+  bool keep_warm = false;  // keep the float64 eigenvectors in the scratch for the next step's warm start
 };
 // Eigensolve threads per workgroup of order class c (orders <= 32, <= 64,
 // <= 128, larger): the default and the one alternative the autotuner times

@@ -10,12 +10,7 @@
 // eigenvalues.  Rotations never mix columns that are already orthogonal, so
 // exactly or nearly repeated eigenvalues need no special treatment: the
 // eigenvectors come out orthonormal to working precision regardless of
-// gaps.  The whole p x p block stays in LDS (<= 160 KiB).
-//
-// One round pairs every column once (round-robin "circle" schedule, p-1
-// rounds per sweep); G consecutive lanes own one pair, reduce the three dot
-// products with a butterfly and rotate the two columns.  One barrier per
-// round.
+// gaps.  The sweeps are in jacobi_sweeps.h.
 //
 // Reconstruction Pi = U diag(max(lam, 0)) U' and the four products of the DK
 // rule U (L o (U' T U)) U' run on the matrix cores (v_mfma 16x16x4, FP32 or
@@ -23,6 +18,7 @@
 #include <type_traits>
 
 #include "cosmo_internal.h"
+#include "jacobi_sweeps.h"
 #include "mma_tiles.h"
 
 namespace cosmo {
@@ -44,65 +40,16 @@ template <typename T, int NT> __device__ inline T wg_max(T v, T *red) {
   return t;
 }
 
-// Jacobi lanes move 16 bytes per LDS access in the padded classes.
-template <typename T> struct Vec16;
-template <> struct Vec16<float> { typedef float type __attribute__((ext_vector_type(4))); };
-template <> struct Vec16<double> { typedef double type __attribute__((ext_vector_type(2))); };
-
-// Leading dimension of a p x p block held in LDS.  In order classes up to
-// 128 the G lanes of a Jacobi pair read a column in 16-byte pieces (VE
-// elements per lane, VE G rows per access of the group) without masks:
-// columns are padded with zero rows to a multiple of VE G, then by 8 more
-// elements, so ld is an odd multiple of 8 and the groups of a wave, which
-// work on consecutive columns in the circle schedule, hit different LDS
-// banks.  In the largest class a block alone nearly fills the LDS: even
-// orders pad to the next odd one, lanes read single elements and reads past
-// row p are clamped.  p * eig_ld(p) does not decrease with p.
-template <typename T, int G, int PMAX> __host__ __device__ constexpr int eig_rows(int p) {
-  return PMAX <= 128 ? (16 / (int)sizeof(T)) * G * ((p + (16 / (int)sizeof(T)) * G - 1) / ((16 / (int)sizeof(T)) * G))
-                     : p;
-}
-template <typename T, int G, int PMAX> __host__ __device__ constexpr int eig_ld(int p) {
-  return PMAX <= 128 ? eig_rows<T, G, PMAX>(p) + 8 : (p | 1);
-}
-
-// Cross-lane moves inside rows of 16 lanes (DPP): quad_perm [1,0,3,2] and
-// [2,3,0,1], row_half_mirror, row_mirror.
-template <int CTRL> __device__ inline float dpp_mov(float x) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, false));
-}
-template <int CTRL> __device__ inline double dpp_mov(double x) {
-  const long long b = __double_as_longlong(x);
-  const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffLL), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-// Sum over aligned groups of G = 4, 8 or 16 lanes, in every lane of the group.
-template <int G, typename T> __device__ inline T group_sum(T x) {
-  static_assert(G == 4 || G == 8 || G == 16, "group of 4, 8 or 16 lanes");
-  x += dpp_mov<0xB1>(x);
-  x += dpp_mov<0x4E>(x);
-  if constexpr (G >= 8) x += dpp_mov<0x141>(x);
-  if constexpr (G >= 16) x += dpp_mov<0x140>(x);
-  return x;
-}
-
-// Jacobi rotation (cs, sn) that makes columns with squared norms al, be and
-// inner product ga orthogonal (smaller angle, |tan| <= 1).  Float32 uses the
-// hardware reciprocal and reciprocal square root: any rotation with
-// cs^2 + sn^2 = 1 to working precision is valid, a slightly inexact angle only
-// leaves a little more for the next sweep.
-__device__ inline void jacobi_rot(float al, float be, float ga, float &cs, float &sn) {
-  const float zeta = (be - al) * __builtin_amdgcn_rcpf(2.f * ga);
-  const float tt = __builtin_amdgcn_rcpf(fabsf(zeta) + __builtin_amdgcn_sqrtf(1.f + zeta * zeta));
-  cs = __builtin_amdgcn_rsqf(1.f + tt * tt);
-  sn = copysignf(cs * tt, zeta);
-}
-__device__ inline void jacobi_rot(double al, double be, double ga, double &cs, double &sn) {
-  const double zeta = (be - al) / (2.0 * ga);
-  const double tt = 1.0 / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-  cs = 1.0 / sqrt(1.0 + tt * tt);
-  sn = copysign(cs * tt, zeta);
+// A p x p block in LDS is column-major; its columns are padded to whole pairs
+// of Jacobi blocks (zero columns).  The leading dimension makes the groups of
+// a wave, which work on consecutive column blocks, hit different LDS banks:
+// 4 modulo 8 doubles (8 modulo 16 for two-column blocks of 16-lane groups),
+// 8 modulo 16 floats.  Rows p to ld - 1 are zero.  Where that does not fit a
+// workgroup's LDS (float64 orders 137 to 140) ld is p.  p * ld does not
+// decrease with p.
+template <typename C, int G, int NB, int PMAX> __host__ __device__ constexpr int eig_ld(int p) {
+  if (sizeof(C) == 8 && PMAX > 128 && p > 136) return p;
+  return sizeof(C) == 8 && (NB == 4 || G == 8) ? ((p + 3) & ~7) + 4 : ((p + 7) & ~15) + 8;
 }
 
 // Two 16 x 16 tiles C1 = A B1, C2 = A B2 sharing the A operand.
@@ -176,76 +123,80 @@ __device__ inline float pair_tag(float e, bool rotated) {
 __device__ inline bool pair_rotated(float e) { return (__float_as_uint(e) & 1u) != 0; }
 
 // mode 0: COSMO step on the block (s+ and y+ rows); mode 1: projection only.
-template <typename T, int NT, int G, int PMAX>
-__global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ descs, int32_t max_sweeps, T tol_base,
+// T: type of the data, C: type the sweeps run in.  Orders up to 128 of a
+// float32 plan sweep in float64: the vector units issue float64 multiply-adds
+// at the rate of (unpacked) float32 ones, a sweep costs about a quarter more
+// (LDS traffic, cross-lane moves), and the eigenpairs need no refinement
+// afterwards (245 us of 979 at order 100 when they were swept in float32).
+// Larger float32 blocks do not fit the LDS in float64: they sweep in float32
+// and are refined (below).
+//   warm: this plan's float64 eigenvectors (row-major) of the previous step
+//   (read when warm_read, written when warm_write; C = double), in the
+//   block's part of the scratch; Uprev: the same from the tape (C = float).
+template <typename T, typename C, int NT, int G, int NB, int PE, int PMAX>
+__global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ descs, int32_t max_sweeps, double tol_base,
                                                 int32_t mode, const T *__restrict__ rho_hat,
                                                 const T *__restrict__ vin, const T *__restrict__ sh,
                                                 const T *__restrict__ y, T *__restrict__ s_new,
                                                 T *__restrict__ y_new, T *__restrict__ Uout,
                                                 T *__restrict__ lamout, cosmo_stats *stats, int32_t refine,
                                                 double *__restrict__ rscratch, const T *__restrict__ Uprev,
-                                                int32_t attempt) {
+                                                int32_t warm_read, int32_t warm_write) {
+  constexpr bool WIDE = std::is_same<C, double>::value;   // float64 sweeps, no refinement
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  T *W = reinterpret_cast<T *>(smem_raw);
-  __shared__ T red[NT / 64];
+  C *W = reinterpret_cast<C *>(smem_raw);
+  __shared__ C red[NT / 64];
   __shared__ double redd[2 * (NT / 64)];
-  __shared__ double lamd[PMAX];
-  __shared__ short pos_idx[PMAX];
-  __shared__ short posof[PMAX];
-  __shared__ signed char cls[PMAX];
-  __shared__ int flags[3];
-  __shared__ int bigf[3];
+  // eigenvalues; during the sweeps the scalars that travel with the columns
+  __shared__ double lamd[PMAX * sizeof(C) / 4];
+  __shared__ short pos_idx[PMAX + 16];
+  __shared__ short posof[WIDE ? 1 : PMAX];
+  __shared__ signed char cls[WIDE ? 1 : PMAX];
+  __shared__ int mx_s[6];
   __shared__ int npos_s;
-  __shared__ int redo_s;
   __shared__ int again_s;
 
   const PsdDesc d = descs[blockIdx.x];
   const int p = d.p;
-  // Early-stopped sweeps (float32, orders up to 128, with refinement) can
-  // leave a pair across the positive / non-positive split too coupled for
-  // the refinement's first-order rotation; such a block writes only its
-  // current eigenvectors (to the eigenvector output, when there is one), sets
-  // its flag (a slot of the refinement scratch these classes do not use
-  // otherwise), and a second launch (attempt 1) solves only the flagged
-  // blocks, started from those eigenvectors, with the sweeps run to
-  // convergence.
-  constexpr bool EARLY = std::is_same<T, float>::value && PMAX <= 128;
-  int *redo_g = (EARLY && refine > 0 && rscratch) ? reinterpret_cast<int *>(rscratch + 3 * (size_t)d.uoff) : nullptr;
-  if (attempt == 1) {
-    if (!redo_g || *redo_g == 0) return;   // the same value in every thread
-  } else if (redo_g && threadIdx.x == 0) {
-    *redo_g = 0;
-  }
-  const T *Uwarm = (attempt == 1 && Uout) ? Uout : Uprev;   // warm start of this attempt
-  const int ld = eig_ld<T, G, PMAX>(p);
+  const int ld = eig_ld<C, G, NB, PMAX>(p), nc = jacobi_cols<NB>(p);
   const int nrows = p * (p + 1) / 2;
   const T *v = vin + d.row0;
   const int tid = threadIdx.x;
+  const int wave = tid >> 6, lane = tid & 63;
+  constexpr int NWv = NT / 64;
 
-  // S = smat(v) into W (column-major, full); ||S||_F^2 = ||v||^2 (svec is isometric)
-  T fro2 = 0;
-  for (int idx = tid; idx < nrows; idx += NT) {
-    const int j = svec_col(idx);
-    const int i = idx - j * (j + 1) / 2;
-    T val = v[idx];
-    fro2 += val * val;
-    if (i != j) val *= (T)RSQRT2;
-    W[i + j * ld] = val;
-    W[j + i * ld] = val;
-  }
-  constexpr bool PADDED = PMAX <= 128;   // zero rows up to eig_rows (see eig_ld)
-  const int ne = (p + G - 1) / G;         // column rows per Jacobi lane (unpadded class)
-  if constexpr (PADDED) {
-    const int npad = eig_rows<T, G, PMAX>(p) - p;
-    for (int e = tid; e < npad * p; e += NT) {
-      const int j = e / npad;
-      W[p + (e - j * npad) + j * ld] = (T)0;
+  // S = smat(v) into W (column-major, full); ||S||_F^2 = ||v||^2 (svec is
+  // isometric).  Four entries in flight per thread.
+  C fro2 = 0;
+  for (int base = tid; base < nrows; base += 4 * NT) {
+    T val[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) val[u] = v[min(base + u * NT, nrows - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int idx = base + u * NT;
+      if (idx < nrows) {
+        const int j = svec_col(idx);
+        const int i = idx - j * (j + 1) / 2;
+        C x = (C)val[u];
+        fro2 += x * x;
+        if (i != j) x *= (C)RSQRT2;
+        W[i + j * ld] = x;
+        W[j + i * ld] = x;
+      }
     }
   }
-  if (tid < 3) flags[tid] = bigf[tid] = 0;
-  if (tid == 0) redo_s = 0;
-  fro2 = wg_sum<T, NT>(fro2, red);   // contains barriers: W complete after this
-  if (!isfinite(fro2)) {
+  {   // zero rows p .. ld - 1 and columns p .. nc - 1
+    const int npad = ld - p;
+    for (int e = tid; e < npad * p; e += NT) {
+      const int j = e / npad;
+      W[p + (e - j * npad) + j * ld] = (C)0;
+    }
+    for (int e = p * ld + tid; e < nc * ld; e += NT) W[e] = (C)0;
+  }
+  if (tid < 6) mx_s[tid] = 0;
+  fro2 = wg_sum<C, NT>(fro2, red);   // contains barriers: W complete after this
+  if (!isfinite((T)fro2)) {
     // a non-finite block yields a non-finite projection (never a clipped one)
     for (int idx = tid; idx < nrows; idx += NT) {
       s_new[d.row0 + idx] = (T)NAN;
@@ -255,64 +206,60 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
       for (int i = tid; i < p; i += NT) lamout[d.loff + i] = (T)NAN;
     if (Uout)
       for (int e = tid; e < p * p; e += NT) Uout[d.uoff + e] = (T)NAN;
+    if (WIDE && warm_write) {
+      double *Ut = rscratch + 3 * (size_t)d.uoff;
+      for (int e = tid; e < p * p; e += NT) Ut[e] = NAN;
+    }
     return;   // fro2 is the same in every thread: the whole workgroup leaves
   }
-  T rowmax = 0;
-  for (int i = tid; i < p; i += NT) {
-    T a = 0;
-    for (int j = 0; j < p; ++j) a += fabs(W[i + j * ld]);
-    rowmax = fmax(rowmax, a);
+  // largest column sum of |S|: 16 lanes per column
+  C colmax = 0;
+  for (int j = tid / 16; j < (p + NT / 16 - 1) / (NT / 16) * (NT / 16); j += NT / 16) {
+    C a = 0;
+    if (j < p)
+      for (int i = tid % 16; i < p; i += 16) a += fabs(W[i + j * ld]);
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
+    colmax = fmax(colmax, a);
   }
-  const T inf = wg_max<T, NT>(rowmax, red);
-  T c = (T)1.1 * fmin(sqrt(fro2), inf);
-  if (!(c > (T)0)) c = (T)1;
+  const C inf = wg_max<C, NT>(colmax, red);
+  C c = (C)1.1 * fmin(sqrt(fro2), inf);
+  if (!(c > (C)0)) c = (C)1;
   // Warm start: W = (S + c I) U_prev, with U_prev the eigenvectors of the same
   // block at the previous unrolled step.  One-sided Jacobi on W computes the
   // same decomposition (W = G V with V orthogonal, W'W diagonal at the end);
   // a nearly diagonalising start only shortens the sweeps.
-  bool started = false;
-  if constexpr (std::is_same<T, float>::value && PMAX <= 128) {
-    if (Uwarm && refine > 0) {
-      // U_prev staged in the refinement buffer (free until the refinement);
+  const int nt = (p + 15) / 16;
+  constexpr int NTMAX = (PMAX + 15) / 16;
+  constexpr int HOLD = (NTMAX * NTMAX + NWv - 1) / NWv;
+  if constexpr (WIDE) {
+    if (warm_read) {
       // S is in W, so the products are held in registers until all are done
-      constexpr int NWs = NT / 64;
-      constexpr int NTM = (PMAX + 15) / 16;
-      constexpr int HOLDS = (NTM * NTM + NWs - 1) / NWs;
-      const float *Up = Uwarm + d.uoff;
-      float *Ub = W + p * ld;
-      for (int e = tid; e < p * p; e += NT) {
-        const int j = e / p;
-        Ub[(e - j * p) + j * ld] = Up[e];
-      }
-      __syncthreads();
-      const int nt0 = (p + 15) / 16;
-      const int wave0 = tid >> 6, lane0 = tid & 63;
-      tile_pass<HOLDS, true>(
-          nt0 * nt0, wave0, NWs,
+      const double *Ut = rscratch + 3 * (size_t)d.uoff;
+      tile_pass<HOLD, true>(
+          nt * nt, wave, NWv,
           [&](int t) {
-            const int I = t / nt0, J = t % nt0;
-            return tile_mma<float>(
-                I * 16, J * 16, p, [&](int i, int k) -> float { return (i < p && k < p) ? W[i + k * ld] : 0.f; },
-                [&](int k, int j) -> float { return (k < p && j < p) ? Ub[k + j * ld] : 0.f; });
+            const int I = t / nt, J = t % nt;
+            return tile_mma<double>(
+                I * 16, J * 16, p, [&](int i, int k) -> double { return W[min(i, ld - 1) + min(k, p - 1) * ld]; },
+                [&](int k, int j) -> double { return (k < p && j < p) ? Ut[k * p + j] : 0.0; });
           },
-          [&](int t, const Mma<float>::v4 &acc) {
-            const int I = t / nt0, J = t % nt0;
-            const int col = J * 16 + (lane0 & 15);
+          [&](int t, const Mma<double>::v4 &acc) {
+            const int I = t / nt, J = t % nt;
+            const int col = J * 16 + (lane & 15);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              const int row = I * 16 + Mma<float>::row(lane0, e);
-              if (row < p && col < p) W[row + col * ld] = acc[e] + c * Ub[row + col * ld];
+              const int row = I * 16 + Mma<double>::row(lane, e);
+              if (row < p && col < p) W[row + col * ld] = acc[e] + c * Ut[row * p + col];
             }
           });
-      started = true;
+    } else {
+      for (int i = tid; i < p; i += NT) W[i + i * ld] += c;
     }
-  }
-  if (!started && Uwarm) {
-    const T *Up = Uwarm + d.uoff;
-    const int nt0 = (p + 15) / 16;
-    const int wave0 = tid >> 6, lane0 = tid & 63;
-    for (int t = wave0; t < nt0 * nt0; t += NT / 64) {
-      const int I = t / nt0, J = t % nt0;
+  } else if (Uprev) {
+    const T *Up = Uprev + d.uoff;
+    for (int t = wave; t < nt * nt; t += NT / 64) {
+      const int I = t / nt, J = t % nt;
       const typename Mma<T>::v4 acc = tile_mma<T>(
           I * 16, J * 16, p,
           [&](int i, int k) -> T {
@@ -322,163 +269,39 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
             return a == b ? val : val * (T)RSQRT2;
           },
           [&](int k, int j) -> T { return (k < p && j < p) ? Up[k + j * p] : (T)0; });
-      const int col = J * 16 + (lane0 & 15);
+      const int col = J * 16 + (lane & 15);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int row = I * 16 + Mma<T>::row(lane0, e);
+        const int row = I * 16 + Mma<T>::row(lane, e);
         if (row < p && col < p) W[row + col * ld] = acc[e] + c * Up[row + col * p];
       }
     }
-  } else if (!started) {
+  } else {
     for (int i = tid; i < p; i += NT) W[i + i * ld] += c;
   }
+
+  // When the sweeps end (jacobi_sweeps.h).  tol is the column cosine that
+  // counts as orthogonal: the caller's, or 4 eps sqrt(p) of the data's type.
+  // A refined float32 solve in float64 sweeps to a cosine of 1e-3 within
+  // max_sweeps, then on until what is left is below 1e-11 (float32 eigenpairs
+  // would need three refinement steps for as much).
+  const double tol = tol_base > 0.0 ? tol_base : 4.0 * (double)Unit<T>::eps * sqrt((double)p);
+  SweepRule rule{(float)(tol * tol), (float)tol, 0.f, max_sweeps, 0};
+  if (WIDE && std::is_same<T, float>::value && refine > 0) {
+    const float fine = (float)fmin(tol_base > 0.0 ? tol_base : 1.0, 1e-11);
+    rule = SweepRule{fmaxf(1e-30f, 1e-4f * fine * fine), fine, 1e-6f, max_sweeps, 8};
+  }
+  int ce = 0;
+  (void)frexp((double)c, &ce);
+  const C scale = (C)ldexp(1.0, ce > 120 ? -120 : (ce < -120 ? 120 : -ce));
+  constexpr int PMIN = PMAX <= 32 ? 1 : (PMAX <= 64 ? 33 : (PMAX <= 128 ? 65 : 129));   // smallest order of the class
+  constexpr int NMIN = (PMIN + PE * G - 1) / (PE * G), NMAX = (PMAX + PE * G - 1) / (PE * G);
+  const SweepCount sw =
+      run_sweeps<C, G, NB, PE, NMIN, NMAX>(W, reinterpret_cast<C *>(lamd), scale, p, ld, rule, lamd, mx_s);
+  // eigenvalues: column norms minus the shift
+  for (int i = tid; i < p; i += NT) lamd[i] = lamd[i] / (double)scale - (double)c;
   __syncthreads();
 
-  const T tol = tol_base > (T)0 ? tol_base : (T)4 * Unit<T>::eps * sqrt((T)p);
-  const int P = p + (p & 1);
-  const int npairs = P / 2;
-  const int ngroups = NT / G;
-  const int grp = tid / G, gl = tid % G;
-  constexpr int MAXE = (PMAX + G - 1) / G;   // column elements held per lane
-  int sweep = 0;
-  bool converged = (p == 1);
-  const T tol2 = tol * tol;
-  // With the refinement behind them the sweeps of orders up to 128 can stop
-  // once a sweep's largest column cosine is below 1e-3: the couplings left
-  // are then of order 1e-6, well inside what one refinement step removes.
-  // The largest class converges fully (stopping early there left 1e-4
-  // errors on order-196 blocks).
-  const T stop2 = (redo_g && attempt == 0) ? (T)1e-6 : (T)0;
-  for (; sweep < max_sweeps && !converged; ++sweep) {
-    const int fslot = sweep % 3;
-    for (int r = 0; r < P - 1; ++r) {
-      for (int k = grp; k < npairs; k += ngroups) {
-        // circle schedule: column P-1 stays, the others rotate by one per round
-        int a, b;
-        if (k == 0) {
-          a = r;
-          b = P - 1;
-        } else {
-          a = r + k;
-          if (a >= P - 1) a -= P - 1;
-          b = r - k;
-          if (b < 0) b += P - 1;
-        }
-        const bool live = a < p && b < p;   // else the dummy column of an odd order
-        T *wa = W + (live ? a : 0) * ld;
-        T *wb = W + (live ? b : 0) * ld;
-        T al = 0, be = 0, ga = 0;
-        bool rot = false;
-        if constexpr (PADDED) {
-          // Pieces past the last (c >= nc) re-read the lane's last piece, are
-          // masked out of the sums, and their stores repeat that piece's.
-          typedef typename Vec16<T>::type V;
-          constexpr int VE = 16 / (int)sizeof(T);
-          constexpr int MAXC = (PMAX + VE * G - 1) / (VE * G);
-          const int nc = (p + VE * G - 1) / (VE * G);
-          V xa[MAXC], xb[MAXC];
-#pragma unroll
-          for (int c = 0; c < MAXC; ++c) {
-            const int rw = VE * (gl + (c < nc ? c : nc - 1) * G);
-            xa[c] = *reinterpret_cast<const V *>(wa + rw);
-            xb[c] = *reinterpret_cast<const V *>(wb + rw);
-          }
-#pragma unroll
-          for (int c = 0; c < MAXC; ++c) {
-            const T m = c < nc ? (T)1 : (T)0;
-#pragma unroll
-            for (int q = 0; q < VE; ++q) {
-              const T u = m * xa[c][q], w = m * xb[c][q];
-              al += u * u;
-              be += w * w;
-              ga += u * w;
-            }
-          }
-          al = group_sum<G>(al);
-          be = group_sum<G>(be);
-          ga = group_sum<G>(ga);
-          rot = live && ga * ga > tol2 * al * be;
-          if (rot) {
-            T cs, sn;
-            jacobi_rot(al, be, ga, cs, sn);
-#pragma unroll
-            for (int c = 0; c < MAXC; ++c) {
-              const int rw = VE * (gl + (c < nc ? c : nc - 1) * G);
-              *reinterpret_cast<V *>(wa + rw) = cs * xa[c] - sn * xb[c];
-              *reinterpret_cast<V *>(wb + rw) = sn * xa[c] + cs * xb[c];
-            }
-          }
-        } else {
-          // Rows past the lane's last one (e >= ne) re-read row p - 1 or the
-          // lane's last row and are masked out of the sums; their stores
-          // repeat the value stored for that row.
-          auto row_of = [&](int e) {
-            const int rw = gl + (e < ne ? e : ne - 1) * G;
-            return rw < p ? rw : p - 1;
-          };
-          T xa[MAXE], xb[MAXE];
-#pragma unroll
-          for (int e = 0; e < MAXE; ++e) {
-            xa[e] = wa[row_of(e)];
-            xb[e] = wb[row_of(e)];
-          }
-#pragma unroll
-          for (int e = 0; e < MAXE; ++e) {
-            const bool in = e < ne && gl + e * G < p;
-            const T u = in ? xa[e] : (T)0, w = in ? xb[e] : (T)0;
-            al += u * u;
-            be += w * w;
-            ga += u * w;
-          }
-          al = group_sum<G>(al);
-          be = group_sum<G>(be);
-          ga = group_sum<G>(ga);
-          rot = live && ga * ga > tol2 * al * be;
-          if (rot) {
-            T cs, sn;
-            jacobi_rot(al, be, ga, cs, sn);
-#pragma unroll
-            for (int e = 0; e < MAXE; ++e) {
-              wa[row_of(e)] = cs * xa[e] - sn * xb[e];
-              wb[row_of(e)] = sn * xa[e] + cs * xb[e];
-            }
-          }
-        }
-        if (rot && gl == 0) {
-          flags[fslot] = 1;
-          if (ga * ga > stop2 * al * be) bigf[fslot] = 1;
-        }
-      }
-      __syncthreads();
-    }
-    converged = (flags[fslot] == 0) || (stop2 > (T)0 && bigf[fslot] == 0);
-    if (tid == 0) flags[(sweep + 2) % 3] = bigf[(sweep + 2) % 3] = 0;
-  }
-  // every thread computed `converged` from the same flag after the same barrier
-
-  // eigenpairs: lam_i = ||w_i|| - c, u_i = w_i / ||w_i||
-  for (int i = tid; i < p; i += NT) {
-    const T *wi = W + i * ld;
-    double ss = 0;
-    for (int r = 0; r < p; ++r) ss += (double)wi[r] * (double)wi[r];
-    lamd[i] = sqrt(ss);
-  }
-  __syncthreads();
-  for (int e = tid; e < p * p; e += NT) {
-    const int j = e / p, i = e - j * p;
-    const double sg = lamd[j];
-    W[i + j * ld] = sg > 0.0 ? (T)((double)W[i + j * ld] / sg) : (T)0;
-  }
-  __syncthreads();
-  for (int i = tid; i < p; i += NT) lamd[i] -= (double)c;
-  __syncthreads();
-
-  const int nt = (p + 15) / 16;
-  const int wave = tid >> 6, lane = tid & 63;
-  constexpr int NWv = NT / 64;
-  constexpr int NTMAX = (PMAX + 15) / 16;
-  constexpr int HOLD = (NTMAX * NTMAX + NWv - 1) / NWv;
-  constexpr int HOLDU = (NTMAX * (NTMAX + 1) / 2 + NWv - 1) / NWv;
   const int ntiles = nt * (nt + 1) / 2;
   const T *yb = y + d.row0;
   const T *shb = sh + d.row0;
@@ -490,16 +313,36 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
     s_new[d.row0 + idx] = o;
     if (mode == 0) y_new[d.row0 + idx] = yb[idx] + rh * (shb[idx] - o);
   };
-  auto count = [&]() {
+  auto count = [&](int fine) {
     if (stats) {
-      atomicMax(&stats[d.inst].eig_sweeps_max, sweep);
-      atomicAdd(&stats[d.inst].eig_sweeps_total, sweep);
+      atomicMax(&stats[d.inst].eig_sweeps_max, sw.sweeps);
+      atomicAdd(&stats[d.inst].eig_sweeps_total, sw.sweeps);
       atomicAdd(&stats[d.inst].eig_solves, 1);
-      if (!converged) atomicAdd(&stats[d.inst].eig_not_converged, 1);
+      if (!sw.converged) atomicAdd(&stats[d.inst].eig_not_converged, 1);
+      if (fine) atomicAdd(&stats[d.inst].eig_refine_steps_total, fine);
+    }
+  };
+  // indices of the positive eigenvalues, in order, by the first wave; the list
+  // is padded to whole groups of 16 with the last column
+  auto list_positive = [&](auto positive) {
+    if (wave == 0) {
+      int np = 0;
+      for (int base = 0; base < p; base += 64) {
+        const int i = base + lane;
+        const bool on = i < p && positive(i);
+        const unsigned long long m = __ballot(on);
+        const int at = np + __popcll(m & ((1ull << lane) - 1));
+        if (on) pos_idx[at] = (short)i;
+        if constexpr (!WIDE)
+          if (i < p) posof[i] = on ? (short)at : (short)-1;
+        np += __popcll(m);
+      }
+      if (lane < 16) pos_idx[np + lane] = (short)(p - 1);
+      if (lane == 0) npos_s = np;
     }
   };
 
-  if constexpr (std::is_same<T, float>::value) {
+  if constexpr (!WIDE) {
     if (refine > 0) {
       // Refinement of the float32 eigenpairs (after Ogita & Aishima,
       // "Iterative refinement for symmetric eigenvalue decomposition", 2018)
@@ -537,25 +380,19 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
       // one side of the split) M_ij; for pairs on one side the lowest
       // mantissa bit of slot (j, i) says which (1: rotated, then M_ij = 0).
       // One unit in the last place of E is far below what E corrects.
-      constexpr bool INPL = PMAX <= 128;   // second p x p buffer in LDS, else global scratch
       constexpr int REFINE_STEPS = 3;
-      float *Db = INPL ? W + p * ld : reinterpret_cast<float *>(rscratch + 3 * (size_t)d.uoff);
-      float *SR = INPL ? Db : Db + p * ld;   // S~ (upper) and R (lower), then E and M
+      float *Db = reinterpret_cast<float *>(rscratch + 3 * (size_t)d.uoff);
+      float *SR = Db + p * ld;   // S~ (upper) and R (lower), then E and M
       auto Sget = [&](int i, int k) -> double {
-        if constexpr (INPL) {
-          return (double)Db[i + k * ld];
-        } else {
-          const int a = i < k ? i : k, b = i < k ? k : i;
-          const double val = (double)v[b * (b + 1) / 2 + a];
-          return a == b ? val : val * RSQRT2;
-        }
+        const int a = i < k ? i : k, b = i < k ? k : i;
+        const double val = (double)v[b * (b + 1) / 2 + a];
+        return a == b ? val : val * RSQRT2;
       };
       const double thr2 = 1e-7 * sqrt((double)fro2);
-      // This block's part of the refinement scratch (3 p^2 doubles) beyond
-      // the redo flag (orders up to 128) or beyond D, S~ and R (larger
-      // orders): the refined eigenvalues of a step (float64), then L+ and C
+      // This block's part of the refinement scratch (3 p^2 doubles) beyond D,
+      // S~ and R: the refined eigenvalues of a step (float64), then L+ and C
       // of the projection (below).
-      double *xs = rscratch + 3 * (size_t)d.uoff + (INPL ? 1 : (size_t)p * ld);
+      double *xs = rscratch + 3 * (size_t)d.uoff + (size_t)p * ld;
       // E_kj from the pair storage (see above)
       auto Eget = [&](int k, int j) -> float {
         if (k >= j || cls[k] * cls[j] < 0) return SR[k + j * ld];
@@ -572,19 +409,8 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
         int wave = wave_o, lane = lane_o;
         asm volatile("" : "+v"(wave), "+v"(lane));
         const bool last_allowed = rstep == REFINE_STEPS - 1;
-        if constexpr (INPL) {   // S into the second buffer (the D pass overwrites it in place)
-          for (int idx = tid; idx < nrows; idx += NT) {
-            const int j = svec_col(idx);
-            const int i = idx - j * (j + 1) / 2;
-            float val = v[idx];
-            if (i != j) val *= (float)RSQRT2;
-            Db[i + j * ld] = val;
-            Db[j + i * ld] = val;
-          }
-          __syncthreads();
-        }
         // D = S X - X diag(lam~)
-        tile_pass<HOLD, INPL>(
+        tile_pass<HOLD, false>(
             nt * nt, wave, NWv,
             [&](int t) {
               const int I = t / nt, J = t % nt;
@@ -603,7 +429,7 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
             });
         // S~ into the upper triangle, R into the lower, lam_i on the diagonal
         double nS = 0, nR = 0;
-        tile_pass<HOLDU, INPL>(
+        tile_pass<1, false>(
             ntiles, wave, NWv,
             [&](int t) {
               int I, J;
@@ -698,7 +524,6 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
           const float eij = (float)(rot ? (s + lj * r) / gap : 0.5 * r);
           const float eji = (float)(rot ? (s + li * r) / (-gap) : 0.5 * r);
           if (li * lj < 0.0) {
-            if (last && ok && !fin && stop2 > (T)0) redo_s = 1;   // resolvable, but not to first order
             SR[i + j * ld] = eij;
             SR[j + i * ld] = eji;
           } else {
@@ -707,15 +532,6 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
           }
         }
         __syncthreads();
-        if (last && redo_s) {   // read after the barrier above: the same in every thread
-          if (Uout)
-            for (int e = tid; e < p * p; e += NT) {
-              const int j = e / p, i = e - j * p;
-              Uout[d.uoff + e] = W[i + j * ld];
-            }
-          if (tid == 0) *redo_g = 1;
-          return;
-        }
         rsteps = rstep + 1;
         if (last) break;
         // X <- X + X E, in place in W (the last step's correction is kept apart, below)
@@ -737,18 +553,10 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
               }
             });
       }
-      if (stats && tid == 0) atomicAdd(&stats[d.inst].eig_refine_steps_total, rsteps);
       if (lamout)
         for (int i = tid; i < p; i += NT) lamout[d.loff + i] = (float)lamd[i];
-      if (tid == 0) {
-        int np = 0;
-        for (int i = 0; i < p; ++i) {
-          posof[i] = cls[i] > 0 ? (short)np : (short)-1;
-          if (cls[i] > 0) pos_idx[np++] = (short)i;
-        }
-        npos_s = np;
-        count();
-      }
+      list_positive([&](int i) { return cls[i] > 0; });
+      if (tid == 0) count(rsteps);
       __syncthreads();
       const int npos = npos_s;
       const int ntp = (npos + 15) / 16;
@@ -827,38 +635,43 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
     }
   }
 
-  // Unrefined: Pi = sum_{lam_k > 0} lam_k u_k u_k' (upper-triangle tiles)
+  // Pi = sum_{lam_k > 0} lam_k u_k u_k' (upper-triangle tiles)
   if (lamout)
     for (int i = tid; i < p; i += NT) lamout[d.loff + i] = (T)lamd[i];
   if (Uout)
     for (int e = tid; e < p * p; e += NT) {
       const int j = e / p, i = e - j * p;
-      Uout[d.uoff + e] = W[i + j * ld];
+      Uout[d.uoff + e] = (T)W[i + j * ld];
     }
-  if (tid == 0) {
-    int np = 0;
-    for (int i = 0; i < p; ++i)
-      if (lamd[i] > 0.0) pos_idx[np++] = (short)i;
-    npos_s = np;
-    count();
+  if constexpr (WIDE) {
+    if (warm_write) {
+      double *Ut = rscratch + 3 * (size_t)d.uoff;
+      for (int e = tid; e < p * p; e += NT) {
+        const int i = e / p, j = e - i * p;
+        Ut[e] = W[i + j * ld];
+      }
+    }
   }
+  list_positive([&](int i) { return lamd[i] > 0.0; });
+  if (tid == 0) count(sw.fine);
   __syncthreads();
   const int npos = npos_s;
   for (int t = wave; t < ntiles; t += NWv) {
     int I, J;
     upper_tile(t, I, J);
-    const typename Mma<T>::v4 acc = tile_mma<T>(
+    // rows past the block's end read the padding or its last row: only
+    // entries of the result that are not stored depend on them
+    const typename Mma<C>::v4 acc = tile_mma<C>(
         I * 16, J * 16, npos,
-        [&](int i, int k) -> T {
-          if (i >= p || k >= npos) return (T)0;
+        [&](int i, int k) -> C {
           const int c2 = pos_idx[k];
-          return W[i + c2 * ld] * (T)lamd[c2];
+          return W[min(i, ld - 1) + c2 * ld] * (k < npos ? (C)lamd[c2] : (C)0);
         },
-        [&](int k, int j) -> T { return (j >= p || k >= npos) ? (T)0 : W[j + pos_idx[k] * ld]; });
+        [&](int k, int j) -> C { return W[min(j, ld - 1) + pos_idx[k] * ld]; });
     const int col = J * 16 + (lane & 15);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int row = I * 16 + Mma<T>::row(lane, e);
+      const int row = I * 16 + Mma<C>::row(lane, e);
       if (row <= col && col < p) put(row, col, (double)acc[e]);
     }
   }
@@ -1021,31 +834,30 @@ size_t set_dyn_lds_cap(const void *fn) {
   return LDS_LIMIT - stat;
 }
 
-template <typename T, int NT, int G, int PMAX>
+template <typename T, typename C, int NT, int G, int NB, int PE, int PMAX>
 void run_eig(const PsdDesc *d, int32_t n, int32_t max_p, const PsdLaunchCfg &cfg, int32_t mode, const T *rho_hat,
              const T *vv, const T *sh, const T *y, T *s_new, T *y_new, T *U, T *lam, cosmo_stats *stats,
              double *rscratch, const T *Uprev, hipStream_t st) {
-  // The float32 refinement keeps a second p x ld buffer in LDS for classes up
-  // to order 128, in the global scratch above.
   const int refine = (std::is_same<T, float>::value && rscratch) ? cfg.refine : 0;
-  const size_t nbuf = (refine > 0 && PMAX <= 128) ? 2 : 1;
-  const size_t dyn = nbuf * (size_t)max_p * (size_t)eig_ld<T, G, PMAX>(max_p) * sizeof(T);
+  const size_t dyn = (size_t)jacobi_cols<NB>(max_p) * (size_t)eig_ld<C, G, NB, PMAX>(max_p) * sizeof(C);
   static bool attr_set = false;
   if (!attr_set) {
-    set_dyn_lds_cap(reinterpret_cast<const void *>(&k_psd_eig<T, NT, G, PMAX>));
+    set_dyn_lds_cap(reinterpret_cast<const void *>(&k_psd_eig<T, C, NT, G, NB, PE, PMAX>));
     attr_set = true;
   }
-  k_psd_eig<T, NT, G, PMAX><<<n, NT, dyn, st>>>(d, cfg.max_sweeps, (T)cfg.tol, mode, rho_hat, vv, sh, y, s_new,
-                                                y_new, U, lam, stats, refine, rscratch, Uprev, 0);
-  if (std::is_same<T, float>::value && PMAX <= 128 && refine > 0 && rscratch)   // the flagged blocks again
-    k_psd_eig<T, NT, G, PMAX><<<n, NT, dyn, st>>>(d, cfg.max_sweeps, (T)cfg.tol, mode, rho_hat, vv, sh, y, s_new,
-                                                  y_new, U, lam, stats, refine, rscratch, Uprev, 1);
+  k_psd_eig<T, C, NT, G, NB, PE, PMAX><<<n, NT, dyn, st>>>(
+      d, cfg.max_sweeps, cfg.tol, mode, rho_hat, vv, sh, y, s_new, y_new, U, lam, stats, refine, rscratch, Uprev,
+      Uprev && rscratch ? 1 : 0, cfg.keep_warm && rscratch ? 1 : 0);
 }
 
 }  // namespace
 
 // Blocks arrive sorted by order class (see the plan): callers pass one class
-// per call with its largest order.
+// per call with its largest order.  Lanes and column blocks per class: two
+// columns per block while that fills at most one wave per SIMD (a sweep is
+// then its ~p dependent steps, each as short as its rows are spread); four
+// above order 64, where the exchange of blocks between the groups costs as
+// much as the rotations (order 100: 51 us per sweep against 64 us with two).
 template <typename T>
 void launch_psd_step(const PsdDesc *d, int32_t n, const PsdLaunchCfg &cfg, const T *rho_hat, const T *vv,
                      const T *sh, const T *y, T *s_new, T *y_new, T *U, T *lam, double *rscratch,
@@ -1055,21 +867,22 @@ void launch_psd_step(const PsdDesc *d, int32_t n, const PsdLaunchCfg &cfg, const
   const int mp = cfg.max_p;
   const int cls = mp <= 32 ? 0 : mp <= 64 ? 1 : mp <= 128 ? 2 : 3;
   const bool alt = cfg.threads != 0 && cfg.threads == kEigThreadsAlt[cls] && cfg.threads != kEigThreads[cls];
-#define COSMO_EIG(NT_, G_, PMAX_) \
-  run_eig<T, NT_, G_, PMAX_>(d, n, mp, cfg, mode, rho_hat, vv, sh, y, s_new, y_new, U, lam, stats, rscratch, Uprev, st)
+#define COSMO_EIG(C_, NT_, G_, NB_, PE_, PMAX_)                                                                 \
+  run_eig<T, C_, NT_, G_, NB_, PE_, PMAX_>(d, n, mp, cfg, mode, rho_hat, vv, sh, y, s_new, y_new, U, lam, stats, \
+                                           rscratch, Uprev, st)
   static_assert(kEigThreads[0] == 64 && kEigThreads[1] == 256 && kEigThreads[2] == 512 && kEigThreads[3] == 1024,
                 "class defaults");
   static_assert(kEigThreadsAlt[0] == 128 && kEigThreadsAlt[1] == 512 && kEigThreadsAlt[2] == 1024, "class alternatives");
   if (cls == 0) {
-    if (alt) COSMO_EIG(128, 4, 32); else COSMO_EIG(64, 4, 32);
+    if (alt) COSMO_EIG(double, 128, 16, 2, 1, 32); else COSMO_EIG(double, 64, 8, 2, 1, 32);
   } else if (cls == 1) {
-    if (alt) COSMO_EIG(512, 8, 64); else COSMO_EIG(256, 8, 64);
+    if (alt) COSMO_EIG(double, 512, 16, 2, 1, 64); else COSMO_EIG(double, 256, 16, 2, 1, 64);
   } else if (cls == 2) {
-    if (alt) COSMO_EIG(1024, 8, 128); else COSMO_EIG(512, 8, 128);
+    if (alt) COSMO_EIG(double, 1024, 16, 2, 1, 128); else COSMO_EIG(double, 512, 16, 4, 1, 128);
   } else if constexpr (std::is_same<T, float>::value) {
-    COSMO_EIG(1024, 8, COSMO_MAX_PSD_ORDER_F32);
+    COSMO_EIG(float, 1024, 16, 2, 2, COSMO_MAX_PSD_ORDER_F32);
   } else {
-    COSMO_EIG(1024, 8, COSMO_MAX_PSD_ORDER_F64);
+    COSMO_EIG(double, 1024, 16, 2, 1, COSMO_MAX_PSD_ORDER_F64);
   }
 #undef COSMO_EIG
 }

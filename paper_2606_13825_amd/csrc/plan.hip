@@ -748,10 +748,10 @@ void launch_psd_classes(cosmo_plan *pl, const T *rho_hat, const T *vv, const T *
   fork_classes(pl, st, [&](int c, hipStream_t s) {
     const int n = pl->psd_cls_begin[c + 1] - pl->psd_cls_begin[c];
     PsdLaunchCfg cfg{pl->opt.eig_max_sweeps, pl->opt.eig_tol, refine ? pl->opt.eig_refine : 0, pl->psd_cls_maxp[c],
-                     pl->eig_threads[c]};
+                     pl->eig_threads[c], pl->opt.eig_warm_start != 0};
     ProfScope pc(pl, 4 + c, s);   // this class's kernel alone, on the stream it runs on
     launch_psd_step<T>(pl->d_psd + pl->psd_cls_begin[c], n, cfg, rho_hat, vv, sh, y, s_new, y_new, U, lam,
-                       refine ? rscratch : nullptr, Uprev, stats, s);
+                       rscratch, Uprev, stats, s);
   });
 }
 
@@ -2004,7 +2004,7 @@ cosmo_status psd_proj(int32_t nblk, const int32_t *order, const int64_t *offset,
     PsdLaunchCfg cfg{max_sweeps, eig_tol, rf, cm[c]};
     if (dtype == COSMO_F32)
       launch_psd_step<float>(d + cb[c], n, cfg, nullptr, (const float *)in, nullptr, nullptr, (float *)out, nullptr,
-                             (float *)eigvecs, (float *)eigvals, rf ? rs : nullptr, nullptr, nullptr, st);
+                             (float *)eigvecs, (float *)eigvals, rs, nullptr, nullptr, st);
     else
       launch_psd_step<double>(d + cb[c], n, cfg, nullptr, (const double *)in, nullptr, nullptr, (double *)out,
                               nullptr, (double *)eigvecs, (double *)eigvals, nullptr, nullptr, nullptr, st);
