@@ -559,7 +559,10 @@ struct GridBar {
 
 // Returns true once any wait of this solve has run out of time.
 __device__ inline bool grid_barrier(const GridBar &gb, uint32_t &gen, int32_t *shared_flag) {
-  __syncthreads();   // the workgroup's stores are complete (workgroup-scope release in every wave)
+  // every wave waits for its own stores (a workgroup barrier alone orders
+  // them inside the workgroup only); thread 0's release then publishes them
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+  __syncthreads();
   const uint32_t target = gen + 1;
   if (threadIdx.x == 0) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
