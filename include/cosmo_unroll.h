@@ -430,13 +430,16 @@ cosmo_status socp_proj_vjp(int32_t ncones, const int32_t *dim, const int64_t *of
                            const void *in, const void *gout, void *gin, void *ws, void *stream);
 
 /* Schedules of the CG solves (Table 2; Sec. "Matrix-Free Implicit
- * Differentiation"): form 0 = one workgroup per instance iterating to its own
- * tolerance (the default); form f = 1..4 = one cooperative launch over the
- * whole device with at most f workgroups per compute unit, the operator
- * passes of all instances spread over every workgroup and grid barriers
- * between phases (falls back to form 0 where cooperative launch is not
- * available).  Both forms compute the same iteration with the same stopping
- * rule; their sums are taken in different orders, each deterministic.
+ * Differentiation"): form 0 (the default) = every instance iterates to its own
+ * tolerance in one workgroup, or, on plans whose instances leave most of the
+ * device idle that way, in a team of up to 32 workgroups (chosen at plan
+ * creation from the instances' sizes); form f = 1..4 = one cooperative launch
+ * over the whole device with at most f workgroups per compute unit, the
+ * operator passes of all instances spread over every workgroup and grid
+ * barriers between phases, on plans where no instance or a very large one is
+ * in the teams' reach (else, and where cooperative launch is not available,
+ * as form 0).  All compute the same iteration with the same stopping rule;
+ * their sums are taken in different orders, each deterministic.
  * set_pcg_form: form outside 0..4 is COSMO_EINVAL; a cooperative form while
  * graph mode is on, or on a plan with dense blocks, is COSMO_EUNSUPPORTED.
  * With dense blocks, form 0 reads each block once per operator application:

@@ -245,6 +245,40 @@ template <typename T> void launch_pcg(const View<T> &v, const T *rho_hat, const 
                                       int32_t mode, cosmo_stats *stats, void *state, int32_t form,
                                       hipStream_t st);
 
+// PCG with a team of workgroups per instance (k_pcg_team.hip).  An instance's
+// rows and columns are cut into `slices` parts; rowsA / rowsAt list every
+// instance's rows of a length class slice by slice:
+// rowsA[sliceA[c (B slices + 1) + b slices + s] .. next) are slice s's, in the
+// longest class those up to TEAM_MID_ROW entries first (before
+// midA[b slices + s]); its columns are colcut[b slices + s] .. next.
+constexpr int32_t TEAM_XCDS = 8;            // accelerator dies of the device
+constexpr int32_t TEAM_MAX_SLICES = 32;     // compute units of one die
+constexpr int32_t TEAM_MID_ROW = 256;       // entries of a row 16 lanes still handle well
+constexpr uint32_t TEAM_NONE = 0xffffffffu;
+constexpr int32_t TEAM_MAX_LDS = 153600;    // dynamic LDS a team workgroup may use
+struct TeamView {
+  int32_t slices = 0;          // 0: no teams, one workgroup per instance
+  int32_t teams_per_xcd = 0;
+  int32_t grid = 0;            // workgroups of a launch
+  int64_t max_n = 0;           // columns of the largest instance
+  int64_t tcap = 0;            // bytes of a workgroup's LDS for the rows a slice's columns use
+  const int64_t *sliceA = nullptr, *sliceAt = nullptr, *midA = nullptr, *midAt = nullptr, *colcut = nullptr;
+  const int64_t *trange = nullptr;  // [2 (b slices + s)]: first row and end of the rows slice s's columns use
+  const int32_t *order = nullptr;   // instances, most work first
+  void *state = nullptr;       // control words (team_state_bytes), zeroed once per call
+  int64_t tl_off = 0;          // where tcap's bytes begin (set at the launch)
+  double *ecp = nullptr;       // per slice, the dense blocks' column products
+  int64_t ec_stride = 0;       // their length
+};
+size_t team_state_bytes(int32_t teams_per_xcd);
+size_t team_lds_bytes(size_t esz, int64_t max_n, int32_t dense_maxcols);   // without tcap
+void launch_team_reset(const TeamView &tv, hipStream_t st);
+template <typename T> void launch_pcg_team(const View<T> &v, const TeamView &tv, const T *rho_hat, const T *dg,
+                                           const double *rhs, T *x, T *r, T *z, T *Mp, T *t, double *t64,
+                                           double *c64, double tol, int32_t max_iter, const T *alpha_k, const T *xold, T *xnew,
+                                           const T *gx_in, T *gx_out, int32_t mode, cosmo_stats *stats,
+                                           hipStream_t st);
+
 // SOC (k_soc.hip)
 template <typename T> void launch_soc_step(const SocDesc *d, int32_t n, const T *rho_hat, const T *vv,
                                            const T *sh, const T *y, T *s_new, T *y_new, hipStream_t st);

@@ -1,0 +1,562 @@
+// The per-instance CG with a team of workgroups per instance (form 0 of plans
+// with fewer instances than compute units).  Same iteration and stopping rule
+// as k_pcg (see k_pcg.hip); an instance's rows and columns are cut into
+// `slices` parts, one per workgroup of a full team, and the workgroups meet at
+// team barriers: after the row half of the operator, with the sum of p'Mp,
+// and with the sums of r'z and r'r.
+//
+// Teams.  A team's workgroups run on one XCD: each reads its XCD's number
+// (the XCC_ID hardware register) and takes a ticket there, so what a team
+// exchanges stays in that XCD's L2, which its compute units share -- no L2
+// write-back or invalidation, which make a device-wide exchange several times
+// as expensive (measured, one barrier with 16 KB exchanged: 3.2 us here; 6.5
+// us with agent-scope release and acquire, which a team spread over XCDs
+// needs).  A store is in L2 when its wave's vmcnt reaches 0, which every wave
+// waits for before a team barrier; what other workgroups wrote is read with
+// agent-scope loads, which pass the compute unit's own cache by.
+//
+// A team starts with as many members as have arrived: it closes when it is
+// full, or when a member has waited FORM_TICKS for more; later arrivals leave
+// (a member does slices rank, rank + size, ..).  So the launch needs no
+// co-residency: whatever else runs on the device, the workgroups that are
+// running form teams and finish.  The teams of a launch take instances from
+// one queue, largest first, until it is empty.  Sums are formed per slice and
+// added in slice order: the result does not depend on the teams' sizes.
+// Waits inside a closed team end because all its members are running; each is
+// bounded in time all the same and then marks the solutions non-finite.
+//
+// p (in the residual pass: x) is kept whole in every workgroup's LDS: the row
+// half gathers from there, and p = z + beta p needs no barrier of its own.
+// The column half first copies the span of rows its columns use, where that
+// fits (a coalesced copy with all loads in flight; gathers of single entries
+// past the compute unit's cache took 10 us a pass on a slice of 300 columns of
+// 50 entries).
+//
+// What bounds it: latency.  Per iteration about 7 us are the three team
+// barriers with their sums, the rest dependent loads (row list, entries,
+// gathers) of the few rows a lane group has, which come from beyond the L2
+// (an instance's A and A' or dense block fill it); the operator's bytes at the
+// rate of one XCD are 4 to 8 us.  Measured per iteration, one workgroup per
+// instance or the device-wide form against teams of 32: 4 Huber instances of
+// 2000 x 500 in float64 137 -> 20 us; 16 covariance-steering instances 97 ->
+// 30 us; one program with 500,000 nonzeros 83 -> 28 us.
+#include <algorithm>
+
+#include "pcg_ops.h"
+
+namespace cosmo {
+namespace {
+
+constexpr uint64_t FORM_TICKS = 5000;           // 50 us of the 100 MHz real-time counter
+constexpr uint64_t WAIT_TICKS = 200000000ull;   // 2 s
+
+__device__ inline uint32_t ld_agent(const uint32_t *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void st_agent(uint32_t *p, uint32_t x) {
+  __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// An array other workgroups of the team write.
+template <typename T> struct Shared {
+  const T *p;
+  __device__ T operator[](int64_t i) const {
+    return __hip_atomic_load(p + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+};
+// The LDS copy of the instance's slice of a column vector.
+template <typename T> struct Local {
+  const T *p;
+  int32_t n0;
+  __device__ T operator[](int32_t c) const { return p[c - n0]; }
+};
+
+// Control words of one launch, zero before it and left zero by it.
+struct TeamHead {
+  uint32_t queue, exits;
+  uint32_t pad[62];
+  uint32_t ticket[TEAM_XCDS * 64];   // one line per XCD
+};
+struct TeamRec {
+  uint32_t joined;   // arrivals; CLOSED once the team has its members
+  uint32_t size;     // members, set by whoever closed it
+  uint32_t inst;     // queue position of the instance in work
+  uint32_t abort;
+  uint32_t pad0[60];
+  uint32_t count;    // arrivals at barriers
+  uint32_t pad1[63];
+  uint32_t gen;      // barriers passed
+  uint32_t pad2[63];
+  double sum[2][3][TEAM_MAX_SLICES];   // slices' partial sums, two sets in turn
+};
+constexpr uint32_t CLOSED = 0x80000000u;
+
+struct Team {
+  TeamRec *rec;
+  uint32_t rank, size, gen, parity;
+  bool aborted;
+};
+
+// All members' stores before it are visible to Shared reads after it.
+template <int NTH> __device__ inline void team_sync(Team &tm, int32_t *flag_s) {
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's stores are in L2
+  __syncthreads();
+  const uint32_t target = tm.gen + 1;
+  if (tm.size > 1) {
+    if (threadIdx.x == 0) {
+      if (__hip_atomic_fetch_add(&tm.rec->count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+          tm.size * target - 1) {
+        st_agent(&tm.rec->gen, target);
+      } else {
+        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+        while (ld_agent(&tm.rec->gen) < target) {
+          if (ld_agent(&tm.rec->abort) != 0) break;
+          if (__builtin_amdgcn_s_memrealtime() - t0 > WAIT_TICKS) {
+            st_agent(&tm.rec->abort, 1u);
+            break;
+          }
+        }
+      }
+      *flag_s = (int32_t)ld_agent(&tm.rec->abort);
+    }
+    __syncthreads();
+    tm.aborted = tm.aborted || *flag_s != 0;
+  }
+  tm.gen = target;
+}
+
+// Team sums of up to three values whose slice partials this workgroup has
+// stored (by thread 0) in the record's current set; same bits in every thread
+// of every member.
+template <int NTH, int NV> __device__ inline void team_sums(Team &tm, int slices, double (&out)[NV], double *sum_s,
+                                                            int32_t *flag_s) {
+  team_sync<NTH>(tm, flag_s);
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      double x = lane < slices ? Shared<double>{tm.rec->sum[tm.parity][k]}[lane] : 0.0;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+      if (lane == 0) sum_s[k] = x;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < NV; ++k) out[k] = sum_s[k];
+  tm.parity ^= 1;
+}
+
+// threads per workgroup: as in the one-workgroup form
+template <typename T, int DMP> constexpr int TT = (DMP == 0 && sizeof(T) == 4) ? 1024 : 512;
+
+template <typename T, int DMP, typename TG>
+__global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView tv, const T *__restrict__ rho_hat,
+                                                           const T *__restrict__ dg, const double *__restrict__ rhs,
+                                                           T *x, T *r, T *z, T *Mp, T *t, double *t64,
+                                                           double *c64, T tol, int32_t max_iter, const T *__restrict__ alpha_k,
+                                                           const T *__restrict__ xold, T *__restrict__ xnew,
+                                                           const T *__restrict__ gx_in, T *__restrict__ gx_out,
+                                                           int32_t mode, cosmo_stats *stats) {
+  constexpr int NTH = TT<T, DMP>;
+  extern __shared__ double dyn_lds[];
+  __shared__ T red[2 * (NTH / 64)];
+  __shared__ double redd[2 * (NTH / 64)];
+  __shared__ double sum_s[3];
+  __shared__ int32_t flag_s;
+  __shared__ uint32_t join_s[3];
+  __shared__ int64_t cuts[TEAM_MAX_SLICES][18];
+  const int tid = threadIdx.x;
+  const int V = tv.slices;
+  TeamHead *head = static_cast<TeamHead *>(tv.state);
+  TeamRec *recs = reinterpret_cast<TeamRec *>(head + 1);
+
+  // ---- join a team --------------------------------------------------------------
+  if (tid == 0) {
+    const uint32_t xcc = (uint32_t)__builtin_amdgcn_s_getreg(20 | (3 << 11)) % TEAM_XCDS;   // XCC_ID, bits 3:0
+    const uint32_t ticket = __hip_atomic_fetch_add(&head->ticket[64 * xcc], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t team = TEAM_NONE, rank = 0, size = 0;
+    if (ticket < (uint32_t)(tv.teams_per_xcd * V)) {
+      TeamRec *rec = recs + xcc * tv.teams_per_xcd + ticket / V;
+      const uint32_t old = __hip_atomic_fetch_add(&rec->joined, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (!(old & CLOSED)) {
+        team = xcc * tv.teams_per_xcd + ticket / V;
+        rank = old;
+        auto close = [&]() {
+          const uint32_t was = __hip_atomic_fetch_or(&rec->joined, CLOSED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (!(was & CLOSED)) st_agent(&rec->size, was);
+        };
+        if (rank == (uint32_t)V - 1) close();
+        const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+        while ((size = ld_agent(&rec->size)) == 0)
+          if (__builtin_amdgcn_s_memrealtime() - t0 > FORM_TICKS) close();
+      }
+    }
+    join_s[0] = team;
+    join_s[1] = rank;
+    join_s[2] = size;
+  }
+  __syncthreads();
+  Team tm{recs + (join_s[0] == TEAM_NONE ? 0 : join_s[0]), join_s[1], join_s[2], 0, 0, false};
+
+  T *pl = reinterpret_cast<T *>(dyn_lds);
+  auto all = [](int32_t) { return true; };
+  while (join_s[0] != TEAM_NONE) {
+    // ---- the next instance of the queue ------------------------------------------
+    if (tm.rank == 0 && tid == 0)
+      st_agent(&tm.rec->inst, __hip_atomic_fetch_add(&head->queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    team_sync<NTH>(tm, &flag_s);
+    if (tid == 0) sum_s[0] = (double)ld_agent(&tm.rec->inst);
+    __syncthreads();
+    const uint32_t pos = (uint32_t)sum_s[0];
+    __syncthreads();   // sum_s is written again below
+    if (pos >= (uint32_t)v.B || tm.aborted) break;
+    const int b = tv.order[pos];
+    const int64_t n0 = v.n_off[b], n1 = v.n_off[b + 1];
+    const int n = (int)(n1 - n0);
+    double *dl = dyn_lds + ((size_t)n * sizeof(T) + 7) / 8;   // the waves' partials of the dense product
+    const int64_t BV = (int64_t)v.B * V, bV = (int64_t)b * V;
+    const Local<T> pv{pl, (int32_t)n0};
+    char *tl = reinterpret_cast<char *>(dyn_lds) + tv.tl_off;   // the copied span of rows
+
+    // where this workgroup's slices begin and end: list ranges of the rows
+    // (0-6: three classes, the last one's short and long rows) and of the
+    // columns (7-13), the columns' span of rows (14, 15), the columns (16, 17)
+    for (int e = tid; e < 18 * V; e += NTH) {
+      const int s = e / 18, k = e % 18;
+      if (s % (int)tm.size != (int)tm.rank) continue;
+      const int64_t *sl = (k < 7 ? tv.sliceA : tv.sliceAt) + bV + s, *mid = (k < 7 ? tv.midA : tv.midAt) + bV + s;
+      const int q = k < 7 ? k : k - 7;
+      cuts[s][k] = k >= 16 ? tv.colcut[bV + s + k - 16] : k >= 14 ? tv.trange[2 * (bV + s) + k - 14]
+                   : q == 5 ? *mid : q == 6 ? sl[2 * (BV + 1) + 1] : sl[(q / 2) * (BV + 1) + (q & 1)];
+    }
+    __syncthreads();
+
+    // this workgroup's columns of slice s
+    auto own = [&](int s, auto f) {
+      for (int64_t j = cuts[s][16] + tid; j < cuts[s][17]; j += NTH) f(j);
+    };
+    auto sum_set = [&](int k, int s, double val) {
+      if (tid == 0) tm.rec->sum[tm.parity][k][s] = val;
+    };
+    // LDS copy of a vector the team's members wrote; f(old LDS value, new entry)
+    auto fill = [&](const T *src, auto f) {
+      const Shared<T> sv{src + n0};
+      for (int j = tid; j < n; j += 4 * NTH) {   // past the end: the last entry again, not stored
+        T e[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) e[u] = sv[min(j + u * NTH, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (j + u * NTH < n) pl[j + u * NTH] = f(pl[j + u * NTH], e[u]);
+      }
+      __syncthreads();
+    };
+    // All length classes of one slice's rows.  A team has few rows per lane
+    // group, so the time is the dependent loads of the rows one after another:
+    // few lanes per row, all of a row's pieces in flight at once.
+    auto class_rows_of = [&](auto zero, const int32_t *rows, const RowSpan *span, const int64_t *cut,
+                             const int32_t *col, const T *val, auto vin, auto emit) {
+      using AT = decltype(zero);
+      constexpr int U = 16 / sizeof(AT);
+      row_pass<1, AT>(rows, span, cut[0], cut[1], tid, NTH, col, val, vin, all, emit);
+      row_pass<4, AT, U>(rows, span, cut[2], cut[3], tid / 4, NTH / 4, col, val, vin, all, emit);
+      row_pass<16, AT, U>(rows, span, cut[4], cut[5], tid / 16, NTH / 16, col, val, vin, all, emit);
+      row_pass<64, AT>(rows, span, cut[5], cut[6], tid / 64, NTH / 64, col, val, vin, all, emit);
+    };
+    // The dense blocks' column products of slice s's columns, summed over the
+    // slices in order, into dl (by column of the slice): half a wave per column.
+    auto dense_columns = [&](int s) {
+      const int64_t c0 = cuts[s][16], c1 = cuts[s][17];
+      const int lane = tid % 32;
+      for (int64_t base = c0; base < c1; base += 4 * (NTH / 32)) {
+        int32_t e[4];
+        double x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int64_t j = base + u * (NTH / 32) + tid / 32;
+          e[u] = j < c1 ? v.dcol[j] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          x[u] = e[u] >= 0 && lane < V ? Shared<double>{tv.ecp + (int64_t)lane * tv.ec_stride}[e[u]] : 0.0;
+#pragma unroll
+        for (int off = 16; off > 0; off >>= 1)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) x[u] += __shfl_xor(x[u], off, 64);
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (e[u] >= 0 && lane == 0) dl[base + u * (NTH / 32) + tid / 32 - c0] = x[u];
+      }
+      __syncthreads();
+    };
+    // Row half: tt = rho_hat o (A p) on this workgroup's slices, sums in AT;
+    // rows of dense blocks are completed there and give the slice's G'w.
+    auto rows_half = [&](auto zero, auto *tt) {
+      using AT = decltype(zero);
+      for (int s = tm.rank; s < V; s += tm.size) {
+        auto emit = [&](int32_t i, AT acc) { tt[i] = (v.drow && v.drow[i] >= 0) ? acc : (AT)rho_hat[i] * acc; };
+        class_rows_of((AT)0, v.rowsA, v.spanA, cuts[s], v.A_col, v.A_val, pv, emit);
+        if constexpr (DMP > 0) {
+          __syncthreads();   // the CSR part of the slice's dense rows
+          for (int k = v.dense_inst[b]; k < v.dense_inst[b + 1]; ++k) {
+            const DenseDesc &d = v.dense[k];
+            const int rb = (int)((int64_t)d.rows * s / V), re = (int)((int64_t)d.rows * (s + 1) / V);
+            const T *vd = pl + (d.col0 - n0);
+            dense_block_fused<NTH, DMP, AT, TG>(d, rb, re, rho_hat, [&](int c) { return vd[c]; }, tt,
+                                                reinterpret_cast<AT *>(dl), tv.ecp + (int64_t)s * tv.ec_stride);
+          }
+        }
+      }
+    };
+    // (P p + sigma p)_j and the dense blocks' part of (A' t)_j, added to the
+    // column half's sum where the column's owner reads it (all loads of a
+    // column independent, none behind the sum).
+    auto col_rest = [&](auto acc, int64_t j, int s) {
+      using AT = decltype(acc);
+      if (v.P_rowptr)
+        for (int64_t k = v.P_rowptr[j]; k < v.P_rowptr[j + 1]; ++k) acc += (AT)v.P_val[k] * (AT)pv[v.P_col[k]];
+      if constexpr (DMP > 0) {
+        if (v.dcol[j] >= 0) acc += (AT)dl[j - cuts[s][16]];
+      }
+      return acc + (AT)v.sigma * (AT)pv[j];
+    };
+    // Column half: emit(j, (CSR part of A' tt)_j) on this workgroup's slices.
+    auto cols_half = [&](auto zero, auto *tt, auto emit) {
+      using AT = decltype(zero);
+      const Shared<AT> tsh{tt};
+      for (int s = tm.rank; s < V; s += tm.size) {
+        const int64_t i0 = cuts[s][14], i1 = cuts[s][15];
+        if ((i1 - i0) * (int64_t)sizeof(AT) <= tv.tcap) {
+          AT *tc = reinterpret_cast<AT *>(tl);
+          const int cnt = (int)(i1 - i0);
+          const Shared<AT> src{tt + i0};
+          for (int i = tid; i < cnt; i += 4 * NTH) {
+            AT e[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) e[u] = src[min(i + u * NTH, cnt - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (i + u * NTH < cnt) tc[i + u * NTH] = e[u];
+          }
+          __syncthreads();
+          class_rows_of((AT)0, v.rowsAt, v.spanAt, cuts[s] + 7, v.At_col, v.At_val, Local<AT>{tc, (int32_t)i0}, emit);
+          __syncthreads();   // the next slice's copy may overwrite it
+        } else {
+          class_rows_of((AT)0, v.rowsAt, v.spanAt, cuts[s] + 7, v.At_col, v.At_val, tsh, emit);
+        }
+      }
+      __syncthreads();   // the columns' results are read by other threads of this workgroup
+    };
+
+    for (int s = tm.rank; s < V; s += tm.size) {
+      double bb = 0, dd = 0;
+      own(s, [&](int64_t j) { bb += rhs[j] * rhs[j]; });
+      wg_sum2<NTH>(bb, dd, redd);
+      sum_set(0, s, bb);
+    }
+    double tot[3];
+    {
+      double one[1];
+      team_sums<NTH, 1>(tm, V, one, sum_s, &flag_s);
+      tot[0] = one[0];
+    }
+    const double thr = (double)tol * (double)tol * tot[0];
+    bool fail = !isfinite(tot[0]);
+    int it = 0, passes = 0;
+    double rrt = 0, rrt_prev = 0;
+    for (int restart = 0; !tm.aborted; ++restart) {
+      // true residual with float64 accumulation; z = r / diag M, p = z
+      fill(x, [](T, T e) { return e; });
+      rows_half(0.0, t64);
+      team_sync<NTH>(tm, &flag_s);
+      cols_half(0.0, t64, [&](int32_t j, double acc) { c64[j] = acc; });
+      ++passes;
+      for (int s = tm.rank; s < V; s += tm.size) {
+        if constexpr (DMP > 0) dense_columns(s);
+        T rz = 0, rr = 0;
+        double rt = 0, dd = 0;
+        own(s, [&](int64_t j) {
+          const T rj = (T)(rhs[j] - col_rest(c64[j], j, s));
+          r[j] = rj;
+          const T zj = rj / dg[j];
+          z[j] = zj;
+          rz += rj * zj;
+          rr += rj * rj;
+          rt += (double)rj * (double)rj;
+        });
+        wg_sum2<NTH>(rz, rr, red);
+        wg_sum2<NTH>(rt, dd, redd);
+        sum_set(0, s, (double)rz);
+        sum_set(1, s, (double)rr);
+        sum_set(2, s, rt);
+      }
+      team_sums<NTH, 3>(tm, V, tot, sum_s, &flag_s);
+      T rz = (T)tot[0], rr = (T)tot[1];
+      rrt = tot[2];
+      fail = fail || !isfinite(rrt);
+      const bool stalled = restart > 0 && rrt > STALL2 * rrt_prev;
+      if (fail || rrt <= thr || it >= max_iter || restart > NRESTART || stalled || tm.aborted) break;
+      rrt_prev = rrt;
+      const T target = (T)(restart == 0 ? thr : fmax(thr, ROUND_DROP2 * (double)rr));
+      fill(z, [](T, T e) { return e; });
+      while (rr > target && it < max_iter) {
+        rows_half((T)0, t);
+        team_sync<NTH>(tm, &flag_s);
+        cols_half((T)0, t, [&](int32_t j, T acc) { Mp[j] = acc; });
+        for (int s = tm.rank; s < V; s += tm.size) {
+          if constexpr (DMP > 0) dense_columns(s);
+          T pMp = 0, dummy = 0;
+          own(s, [&](int64_t j) {
+            const T m = col_rest(Mp[j], j, s);
+            Mp[j] = m;
+            pMp += pl[j - n0] * m;
+          });
+          wg_sum2<NTH>(pMp, dummy, red);
+          sum_set(0, s, (double)pMp);
+        }
+        double one[1];
+        team_sums<NTH, 1>(tm, V, one, sum_s, &flag_s);
+        if (tm.aborted) break;
+        const T pMp = (T)one[0];
+        if (!(pMp > (T)0)) {   // breakdown: restart from the true residual (or fail if non-finite)
+          fail = !isfinite(pMp);
+          break;
+        }
+        const T a = rz / pMp;
+        for (int s = tm.rank; s < V; s += tm.size) {
+          T rzn = 0, rrn = 0;
+          own(s, [&](int64_t j) {
+            x[j] += a * pl[j - n0];
+            const T rj = r[j] - a * Mp[j];
+            const T zj = rj / dg[j];
+            r[j] = rj;
+            z[j] = zj;
+            rzn += rj * zj;
+            rrn += rj * rj;
+          });
+          wg_sum2<NTH>(rzn, rrn, red);
+          sum_set(0, s, (double)rzn);
+          sum_set(1, s, (double)rrn);
+        }
+        double two[2];
+        team_sums<NTH, 2>(tm, V, two, sum_s, &flag_s);
+        if (tm.aborted) break;
+        const T rz_new = (T)two[0];
+        rr = (T)two[1];
+        const T beta = rz_new / rz;
+        rz = rz_new;
+        fill(z, [beta](T p, T e) { return e + beta * p; });
+        ++it;
+        if (!isfinite(rr)) {
+          fail = true;
+          break;
+        }
+      }
+      if (fail) break;
+    }
+    // ---- epilogue on this workgroup's columns --------------------------------------
+    if (tm.aborted) fail = true;
+    const T al = alpha_k ? alpha_k[b] : (T)1;
+    for (int s = tm.rank; s < V; s += tm.size)
+      own(s, [&](int64_t j) {
+        if (fail) x[j] = (T)NAN;   // a non-finite system marks its solution, never a finite warm start
+        if (mode == 0) {
+          if (xnew) xnew[j] = al * x[j] + ((T)1 - al) * xold[j];
+        } else {
+          gx_out[j] = ((T)1 - al) * gx_in[j] + v.sigma * x[j];
+        }
+      });
+    if (stats && tm.rank == 0 && tid == 0) {
+      atomicMax(&stats[b].cg_iters_max, it);
+      atomicAdd(&stats[b].cg_iters_total, it);
+      atomicAdd(&stats[b].cg_passes_total, passes);
+      if (!(rrt <= thr)) atomicAdd(&stats[b].cg_not_converged, 1);
+    }
+    if (tm.aborted) break;
+  }
+
+  // ---- the last workgroup out leaves the control words zero -------------------------
+  __syncthreads();
+  if (tid == 0)
+    flag_s = __hip_atomic_fetch_add(&head->exits, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+  __syncthreads();
+  if (flag_s) {
+    for (int i = tid; i < TEAM_XCDS * tv.teams_per_xcd; i += NTH) {
+      TeamRec &rec = recs[i];
+      st_agent(&rec.joined, 0);
+      st_agent(&rec.size, 0);
+      st_agent(&rec.abort, 0);
+      st_agent(&rec.count, 0);
+      st_agent(&rec.gen, 0);
+    }
+    for (int i = tid; i < TEAM_XCDS; i += NTH) st_agent(&head->ticket[64 * i], 0);
+    if (tid == 0) {
+      st_agent(&head->queue, 0);
+      st_agent(&head->exits, 0);
+    }
+  }
+}
+
+// Zeroes the control words (once per call of an unroll; a solve leaves them zero).
+__global__ __launch_bounds__(256) void k_team_reset(uint32_t *words, int64_t n) {
+  for (int64_t i = blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) words[i] = 0;
+}
+
+}  // namespace
+
+size_t team_state_bytes(int32_t teams_per_xcd) {
+  return sizeof(TeamHead) + (size_t)TEAM_XCDS * teams_per_xcd * sizeof(TeamRec);
+}
+
+void launch_team_reset(const TeamView &tv, hipStream_t st) {
+  const int64_t n = (int64_t)team_state_bytes(tv.teams_per_xcd) / 4;
+  k_team_reset<<<(int)std::min<int64_t>((n + 255) / 256, 64), 256, 0, st>>>(static_cast<uint32_t *>(tv.state), n);
+}
+
+// Dynamic LDS of a workgroup: the longest instance's vector, and the waves'
+// partials of the dense product (float64 in the residual pass).
+size_t team_lds_bytes(size_t esz, int64_t max_n, int32_t dense_maxcols) {
+  return (size_t)(max_n * (int64_t)esz + 7) / 8 * 8 + (dense_maxcols > 0 ? (size_t)(512 / 64) * dense_maxcols * 8 : 0);
+}
+
+template <typename T>
+void launch_pcg_team(const View<T> &v, const TeamView &tv, const T *rho_hat, const T *dg, const double *rhs, T *x, T *r,
+                     T *z, T *Mp, T *t, double *t64, double *c64, double tol, int32_t max_iter, const T *alpha_k,
+                     const T *xold, T *xnew, const T *gx_in, T *gx_out, int32_t mode, cosmo_stats *stats,
+                     hipStream_t st) {
+  TeamView tvl = tv;
+  tvl.tl_off = team_lds_bytes(sizeof(T), tv.max_n, v.n_dense > 0 ? v.dense_maxcols : 0);
+  auto go = [&](auto kern, int threads) {
+    static bool attr_set = false;   // more than the default 64 KiB of dynamic LDS may be needed
+    if (!attr_set) {
+      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                TEAM_MAX_LDS);
+      attr_set = true;
+    }
+    kern<<<tv.grid, threads, tvl.tl_off + tv.tcap, st>>>(v, tvl, rho_hat, dg, rhs, x, r, z, Mp, t, t64, c64, (T)tol,
+                                                         max_iter, alpha_k, xold, xnew, gx_in, gx_out, mode, stats);
+  };
+  if (v.n_dense <= 0) {
+    go(&k_pcg_team<T, 0, T>, TT<T, 0>);
+    return;
+  }
+  auto pick = [&](auto tg) {
+    using TG = decltype(tg);
+    constexpr int VE = 16 / sizeof(TG), MAXPC = COSMO_DENSE_MAX_COLS / (64 * VE);
+    const int pieces = (v.dense_maxcols + 64 * VE - 1) / (64 * VE);
+    if (pieces <= MAXPC / 4) go(&k_pcg_team<T, MAXPC / 4, TG>, 512);
+    else if (pieces <= MAXPC / 2) go(&k_pcg_team<T, MAXPC / 2, TG>, 512);
+    else go(&k_pcg_team<T, MAXPC, TG>, 512);
+  };
+  if (sizeof(T) == 8 && v.dense_g32) pick(float{});
+  else pick(T{});
+}
+
+#define INST(T)                                                                                                        \
+  template void launch_pcg_team<T>(const View<T> &, const TeamView &, const T *, const T *, const double *, T *, T *, \
+                                   T *, T *, T *, double *, double *, double, int32_t, const T *, const T *, T *,     \
+                                   const T *, T *, int32_t, cosmo_stats *, hipStream_t);
+INST(float)
+INST(double)
+
+}  // namespace cosmo

@@ -110,19 +110,22 @@ struct cosmo_plan {
   DenseDesc *d_dense = nullptr;
   int32_t *d_dense_inst = nullptr, *d_drow = nullptr, *d_dcol = nullptr;
   double *d_dscale = nullptr;
+  // teams of workgroups per instance in the CG (k_pcg_team.hip); slices = 0: none
+  TeamView team;
+  bool team_wide = false;   // the device-wide form reads the largest instance faster than one die does
   // M = P + sigma I + A' D A is diagonal when every row of A has at most one
   // nonzero and P is diagonal; the linear solves are then done in the
   // column kernels (x~ = xi / diag M) and the PCG kernel is not launched.
   bool diag_M = false;
   // layouts (element offsets of T)
   struct {
-    size_t rho_hat, dg, xi, r, z, p, Mp, t, t64, cg, sh, vv, itA, itB, xt, st, U, lam, rp, rd, rs, dn, ec, ed, total;
+    size_t rho_hat, dg, xi, r, z, p, Mp, t, t64, cg, tm, c64, ecp, sh, vv, itA, itB, xt, st, U, lam, rp, rd, rs, dn, ec, ed, total;
   } fw{};
   struct {
     size_t slot, step, xt, st, lam, U, total;  // per-slot / per-step sizes and offsets inside a step
   } tp{};
   struct {
-    size_t rho_hat, gA, gB, gsn, gv, gsh, gst, grh, gxt, w, dg, r, z, p, Mp, t, t64, cg, vv, dk, dn, ec, ed, zero, total;
+    size_t rho_hat, gA, gB, gsn, gv, gsh, gst, grh, gxt, w, dg, r, z, p, Mp, t, t64, cg, tm, c64, ecp, vv, dk, dn, ec, ed, zero, total;
   } bw{};
   bool profiling = false;
   void *tap = nullptr;   // cosmo_plan_set_tap: per-step projection input and output cotangent
@@ -353,6 +356,63 @@ void build_buckets(const std::vector<int64_t> &rowptr, int64_t nrows, std::vecto
   bk.lanes[2] = 64;
 }
 
+// How many workgroups share an instance's CG.  Time of one operator
+// application, from measurements: a workgroup walks the CSR entries at 2.8 ns
+// each (both passes) and dense blocks at 29 GB/s, with about 6 us of
+// dependent loads and barriers when it works alone and 15 us in a team; teams
+// of T work side by side, ncu / T of them, on the instances' queue.  The
+// smallest such estimate decides, and one workgroup per instance stays unless
+// teams are estimated at least a fifth faster.  (4 Huber instances of 2000 x
+// 500: 137 us per application alone; 256 of them fill the device with one
+// workgroup each.)
+int32_t team_slices(const std::vector<double> &work_us, int32_t ncu) {
+  double wmax = 0, sum = 0;
+  for (double w : work_us) {
+    wmax = std::max(wmax, w);
+    sum += w;
+  }
+  const double B = (double)work_us.size();
+  int32_t best = 0;
+  double best_us = 0.8 * std::max(6.0 + wmax, (6.0 * B + sum) / ncu);
+  for (int32_t T = 2; T <= TEAM_MAX_SLICES && T <= ncu; T *= 2) {
+    const double us = std::max(15.0 + wmax / T, (15.0 * B + sum / T) / (ncu / T));
+    if (us < best_us) {
+      best_us = us;
+      best = T;
+    }
+  }
+  return best;
+}
+
+// Lists an instance's rows of each length class slice by slice (rows of a
+// slice stay in increasing order, in the longest class those of up to
+// TEAM_MID_ROW entries first); returns the list ranges of (class, instance,
+// slice), mid: where the longest class's long rows begin.
+std::vector<int64_t> sort_by_slice(std::vector<int32_t> &rows, const RowBuckets &bk, const std::vector<int64_t> &ptr,
+                                   const std::vector<int32_t> &inst, const std::vector<int32_t> &slice, int32_t B,
+                                   int32_t V, std::vector<int64_t> &mid) {
+  const int64_t BV = (int64_t)B * V;
+  std::vector<int64_t> off(3 * (BV + 1), 0);
+  std::vector<int32_t> out(rows.size());
+  for (int c = 0; c < 3; ++c) {
+    // two keys per slice: rows up to TEAM_MID_ROW entries, longer ones
+    auto key = [&](int32_t r) {
+      return 2 * ((int64_t)inst[r] * V + slice[r]) + (ptr[r + 1] - ptr[r] > TEAM_MID_ROW ? 1 : 0);
+    };
+    std::vector<int64_t> at(2 * BV + 1, 0);
+    for (int64_t k = bk.begin[c]; k < bk.begin[c + 1]; ++k) at[key(rows[k]) + 1]++;
+    at[0] = bk.begin[c];
+    for (int64_t q = 0; q < 2 * BV; ++q) at[q + 1] += at[q];
+    int64_t *o = off.data() + c * (BV + 1);
+    for (int64_t q = 0; q <= BV; ++q) o[q] = at[2 * q];
+    if (c == 2)
+      for (int64_t q = 0; q < BV; ++q) mid.push_back(at[2 * q + 1]);
+    for (int64_t k = bk.begin[c]; k < bk.begin[c + 1]; ++k) out[at[key(rows[k])]++] = rows[k];
+  }
+  rows.swap(out);
+  return off;
+}
+
 template <typename T>
 cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   const int64_t n = pl->n_tot, m = pl->m_tot, nnz = p->A_nnz;
@@ -550,6 +610,91 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   };
   const std::vector<int64_t> instA = inst_ranges(rowsA, pl->bkA, pl->m_off);
   const std::vector<int64_t> instAt = inst_ranges(rowsAt, pl->bkAt, pl->n_off);
+  // CG teams: slices of every instance's rows and columns, cut by their
+  // entries; the rows of a dense block (all its placements) go with the
+  // block's row, so a slice completes its part of the block by itself
+  std::vector<int64_t> sliceA, sliceAt, midA, midAt, colcut, trange;
+  std::vector<int32_t> order;
+  if (!pl->diag_M) {
+    int dev = 0, ncu = 0;
+    HIPCHK(hipGetDevice(&dev));
+    HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    std::vector<double> work(pl->B, 0.0);
+    double bytes = 0;
+    int64_t max_n = 0;
+    for (int b = 0; b < pl->B; ++b) {
+      const double nz = (double)(rp[pl->m_off[b + 1]] - rp[pl->m_off[b]]);
+      double gb = 0;
+      for (int k = dinst[b]; k < dinst[b + 1]; ++k)
+        gb += (double)dens[k].rows * dens[k].cols * (pl->dense_g32 ? 4 : sizeof(T));
+      work[b] = 2.8e-3 * nz + gb / 29e3;
+      bytes = std::max(bytes, nz * 2 * (4 + sizeof(T)) + gb);
+      max_n = std::max(max_n, pl->n_off[b + 1] - pl->n_off[b]);
+    }
+    const bool fits = team_lds_bytes(sizeof(T), max_n, pl->dense_maxcols) <= (size_t)TEAM_MAX_LDS;
+    const int32_t V = fits ? team_slices(work, ncu) : 0;
+    if (V > 0) {
+      pl->team.slices = V;
+      pl->team.teams_per_xcd = (TEAM_MAX_SLICES + V - 1) / V;
+      pl->team.grid = (int32_t)std::min<int64_t>(ncu, (int64_t)TEAM_XCDS * V * ((pl->B + TEAM_XCDS - 1) / TEAM_XCDS));
+      pl->team.max_n = max_n;
+      pl->team.ec_stride = pl->dense_cols_tot;
+      // one die reads about 1 TB/s; the device-wide form reads the whole
+      // device's 4 TB/s but pays about 60 us of grid barriers per iteration
+      pl->team_wide = bytes > 64e6;
+      std::vector<int32_t> rslice(m), cslice(n);
+      colcut.assign((size_t)pl->B * V + 1, 0);
+      for (int b = 0; b < pl->B; ++b) {
+        auto cut = [&](int64_t i0, int64_t i1, auto weight, std::vector<int32_t> &out) {   // weight < 0: placed already
+          double tot = 0, at = 0;
+          for (int64_t i = i0; i < i1; ++i) tot += std::max(weight(i), 0.0);
+          for (int64_t i = i0; i < i1; ++i) {
+            if (weight(i) < 0) continue;
+            out[i] = std::min<int32_t>(V - 1, (int32_t)(at * V / tot));
+            at += weight(i);
+          }
+        };
+        for (int k = dinst[b]; k < dinst[b + 1]; ++k)
+          for (int q = 0; q < dens[k].nplace; ++q)
+            for (int32_t sl = 0; sl < V; ++sl)
+              for (int64_t r = (int64_t)dens[k].rows * sl / V; r < (int64_t)dens[k].rows * (sl + 1) / V; ++r)
+                rslice[dens[k].row0[q] + r] = sl;
+        cut(pl->m_off[b], pl->m_off[b + 1],
+            [&](int64_t i) { return !drow.empty() && drow[i] >= 0 ? -1.0 : 2.0 + (double)(rp[i + 1] - rp[i]); }, rslice);
+        cut(pl->n_off[b], pl->n_off[b + 1],
+            [&](int64_t j) {   // a dense column also sums its products over the slices
+              return 4.0 + (double)(trp[j + 1] - trp[j]) + (double)(prp[j + 1] - prp[j]) +
+                     (!dcolm.empty() && dcolm[j] >= 0 ? 12.0 : 0.0);
+            }, cslice);
+        int64_t j = pl->n_off[b];
+        for (int32_t sl = 0; sl < V; ++sl) {
+          colcut[(size_t)b * V + sl] = j;
+          while (j < pl->n_off[b + 1] && cslice[j] == sl) ++j;
+        }
+      }
+      colcut[(size_t)pl->B * V] = n;
+      // the span of rows each slice's columns use, and the LDS left for it
+      // (float64 in the residual pass; spans that do not fit are gathered)
+      const size_t room = (size_t)TEAM_MAX_LDS - team_lds_bytes(sizeof(T), max_n, pl->dense_maxcols);
+      for (size_t q = 0; q < (size_t)pl->B * V; ++q) {
+        int64_t lo = m, hi = 0;
+        for (int64_t j = colcut[q]; j < colcut[q + 1]; ++j)
+          if (trp[j + 1] > trp[j]) {   // rows of a column are in increasing order
+            lo = std::min<int64_t>(lo, tcol[trp[j]]);
+            hi = std::max<int64_t>(hi, tcol[trp[j + 1] - 1] + 1);
+          }
+        trange.push_back(std::min(lo, hi));
+        trange.push_back(hi);
+        const size_t wide = (size_t)std::max<int64_t>(hi - lo, 0) * 8, narrow = (size_t)std::max<int64_t>(hi - lo, 0) * sizeof(T);
+        pl->team.tcap = std::max<int64_t>(pl->team.tcap, (int64_t)(wide <= room ? wide : narrow <= room ? narrow : 0));
+      }
+      sliceA = sort_by_slice(rowsA, pl->bkA, rp, rinst, rslice, pl->B, V, midA);
+      sliceAt = sort_by_slice(rowsAt, pl->bkAt, trp, cinst, cslice, pl->B, V, midAt);
+      order.resize(pl->B);
+      std::iota(order.begin(), order.end(), 0);
+      std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return work[a] > work[b]; });
+    }
+  }
   // --- one device allocation for everything the plan owns
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -580,6 +725,13 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   const size_t o_drow = take(std::max<size_t>(drow.size(), 1) * sizeof(int32_t));
   const size_t o_dscale = take(std::max<size_t>(dscale.size(), 1) * sizeof(double));
   const size_t o_dcol = take(std::max<size_t>(dcolm.size(), 1) * sizeof(int32_t));
+  const size_t o_slA = take(std::max<size_t>(sliceA.size(), 1) * sizeof(int64_t));
+  const size_t o_slAt = take(std::max<size_t>(sliceAt.size(), 1) * sizeof(int64_t));
+  const size_t o_mA = take(std::max<size_t>(midA.size(), 1) * sizeof(int64_t));
+  const size_t o_mAt = take(std::max<size_t>(midAt.size(), 1) * sizeof(int64_t));
+  const size_t o_tr = take(std::max<size_t>(trange.size(), 1) * sizeof(int64_t));
+  const size_t o_cut = take(std::max<size_t>(colcut.size(), 1) * sizeof(int64_t));
+  const size_t o_ord = take(std::max<size_t>(order.size(), 1) * sizeof(int32_t));
   if (hipMalloc(&pl->mem.ptr, off) != hipSuccess) {
     pl->mem.ptr = nullptr;
     FAIL(COSMO_ENOMEM, "plan allocation of " + std::to_string(off) + " bytes failed");
@@ -612,6 +764,20 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   HIPCHK(up(o_drow, drow.data(), drow.size() * sizeof(int32_t)));
   HIPCHK(up(o_dscale, dscale.data(), dscale.size() * sizeof(double)));
   HIPCHK(up(o_dcol, dcolm.data(), dcolm.size() * sizeof(int32_t)));
+  HIPCHK(up(o_slA, sliceA.data(), sliceA.size() * sizeof(int64_t)));
+  HIPCHK(up(o_slAt, sliceAt.data(), sliceAt.size() * sizeof(int64_t)));
+  HIPCHK(up(o_mA, midA.data(), midA.size() * sizeof(int64_t)));
+  HIPCHK(up(o_mAt, midAt.data(), midAt.size() * sizeof(int64_t)));
+  HIPCHK(up(o_tr, trange.data(), trange.size() * sizeof(int64_t)));
+  HIPCHK(up(o_cut, colcut.data(), colcut.size() * sizeof(int64_t)));
+  HIPCHK(up(o_ord, order.data(), order.size() * sizeof(int32_t)));
+  pl->team.sliceA = reinterpret_cast<int64_t *>(base + o_slA);
+  pl->team.sliceAt = reinterpret_cast<int64_t *>(base + o_slAt);
+  pl->team.midA = reinterpret_cast<int64_t *>(base + o_mA);
+  pl->team.midAt = reinterpret_cast<int64_t *>(base + o_mAt);
+  pl->team.trange = reinterpret_cast<int64_t *>(base + o_tr);
+  pl->team.colcut = reinterpret_cast<int64_t *>(base + o_cut);
+  pl->team.order = reinterpret_cast<int32_t *>(base + o_ord);
   pl->d_n_off = reinterpret_cast<int64_t *>(base + o_noff);
   pl->d_m_off = reinterpret_cast<int64_t *>(base + o_moff);
   pl->d_At_rowptr = reinterpret_cast<int64_t *>(base + o_trp);
@@ -659,6 +825,11 @@ void build_layouts(cosmo_plan *pl) {
   f.t = take(m);
   f.t64 = take(2 * m);                     // float64 residual pass of the CG (m doubles)
   f.cg = take(16 * ((size_t)pl->B + 1) + 256);  // per-instance state of the CG (cooperative form)
+  const size_t team_elems = pl->team.slices > 0 ? team_state_bytes(pl->team.teams_per_xcd) / pl->esz : 0;
+  const size_t ecp_elems = (size_t)pl->team.slices * pl->dense_cols_tot * 8 / pl->esz;
+  f.tm = take(team_elems);                 // control words of the CG teams
+  f.c64 = take(pl->team.slices > 0 ? n * 8 / pl->esz : 0);   // float64 column sums of their residual pass
+  f.ecp = take(ecp_elems);                 // their dense column products, per slice
   f.sh = take(m);
   f.vv = take(m);
   // (x, s, y) triples laid out like a tape slot: each part starts 64-element aligned
@@ -706,6 +877,9 @@ void build_layouts(cosmo_plan *pl) {
   w.t = take(m);
   w.t64 = take(2 * m);
   w.cg = take(16 * ((size_t)pl->B + 1) + 256);
+  w.tm = take(team_elems);
+  w.c64 = take(pl->team.slices > 0 ? n * 8 / pl->esz : 0);
+  w.ecp = take(ecp_elems);
   w.vv = take(m);
   w.dk = take(pl->sum_p2_large);
   w.dn = take((size_t)pl->dense_rows_tot * 8 / pl->esz);
@@ -890,6 +1064,44 @@ void policy_bwd_at(cosmo_plan *pl, const View<T> &v, const PolRun<T> &P, int k, 
   launch_pol_resid_adjoint<T>(v, pl->bkA, pl->bkAt, ub, pb, wb, gx, gy, st);
 }
 
+// The CG solves of a call: a team of workgroups per instance where the plan
+// has teams and the device-wide form is not both asked for and faster.
+template <typename T> struct CgRun {
+  cosmo_plan *pl;
+  const View<T> &v;
+  TeamView tv;
+  T *r, *z, *p, *Mp, *t;
+  double *t64, *c64;
+  void *state;
+  hipStream_t st;
+  bool teams;
+  template <typename L>
+  CgRun(cosmo_plan *pl_, const View<T> &v_, T *ws, const L &f, hipStream_t st_) : pl(pl_), v(v_), tv(pl_->team), st(st_) {
+    r = ws + f.r;
+    z = ws + f.z;
+    p = ws + f.p;
+    Mp = ws + f.Mp;
+    t = ws + f.t;
+    t64 = reinterpret_cast<double *>(ws + f.t64);
+    c64 = reinterpret_cast<double *>(ws + f.c64);
+    state = ws + f.cg;
+    teams = tv.slices > 0 && (pl->pcg_form == 0 || !pl->team_wide);
+    tv.state = ws + f.tm;
+    tv.ecp = reinterpret_cast<double *>(ws + f.ecp);
+    if (teams) launch_team_reset(tv, st);
+  }
+  void operator()(const T *rho_hat, const T *dg, const double *rhs, T *x, const T *al, const T *xold, T *xnew,
+                  const T *gx_in, T *gx_out, int32_t mode, cosmo_stats *stats) const {
+    ProfScope ps(pl, 2, st);
+    if (teams)
+      launch_pcg_team<T>(v, tv, rho_hat, dg, rhs, x, r, z, Mp, t, t64, c64, pl->opt.cg_tol, pl->opt.cg_max_iter, al, xold, xnew,
+                         gx_in, gx_out, mode, stats, st);
+    else
+      launch_pcg<T>(v, rho_hat, dg, rhs, x, r, z, p, Mp, t, t64, pl->opt.cg_tol, pl->opt.cg_max_iter, al, xold, xnew, gx_in,
+                    gx_out, mode, stats, state, pl->pcg_form, st);
+  }
+};
+
 template <typename T>
 cosmo_status forward_impl(cosmo_plan *pl, const T *rho, const T *alpha, const T *x0, const T *s0, const T *y0, T *xK,
                           T *sK, T *yK, T *tape, T *ws, cosmo_stats *stats, hipStream_t st,
@@ -913,6 +1125,7 @@ cosmo_status forward_impl(cosmo_plan *pl, const T *rho, const T *alpha, const T 
   auto ST = [&](int k) -> T * { return tape ? tape + step_base(pl, k) + pl->tp.st : ws + f.st; };
   auto LAM = [&](int k) -> T * { return tape ? tape + step_base(pl, k) + pl->tp.lam : ws + f.lam; };
   auto UU = [&](int k) -> T * { return tape ? tape + step_base(pl, k) + pl->tp.U : ws + f.U; };
+  const CgRun<T> cg(pl, v, ws, f, st);
   if (x0) launch_copy<T>(X(0), x0, n, st); else launch_fill<T>(X(0), (T)0, n, st);
   if (s0) launch_copy<T>(S(0), s0, m, st); else launch_fill<T>(S(0), (T)0, m, st);
   if (y0) launch_copy<T>(Y(0), y0, m, st); else launch_fill<T>(Y(0), (T)0, m, st);
@@ -941,11 +1154,8 @@ cosmo_status forward_impl(cosmo_plan *pl, const T *rho, const T *alpha, const T 
       launch_dense_cols<T>(v, DC_XI, rh, y, s, st);
       launch_cols_pre<T>(v, pl->bkAt, rh, x, s, y, ws + f.dg, reinterpret_cast<double *>(ws + f.xi), ds, st);
     }
-    if (!pl->diag_M) {
-      ProfScope ps(pl, 2, st);
-      launch_pcg<T>(v, rh, ws + f.dg, reinterpret_cast<const double *>(ws + f.xi), xt, ws + f.r, ws + f.z, ws + f.p, ws + f.Mp, ws + f.t,
-                    reinterpret_cast<double *>(ws + f.t64), pl->opt.cg_tol, pl->opt.cg_max_iter, al, x, xn, nullptr, nullptr, 0, stats, ws + f.cg, pl->pcg_form, st);
-    }
+    if (!pl->diag_M)
+      cg(rh, ws + f.dg, reinterpret_cast<const double *>(ws + f.xi), xt, al, x, xn, nullptr, nullptr, 0, stats);
     {
       ProfScope ps(pl, 3, st);
       launch_dense_rows<T>(v, xt, st);
@@ -1116,6 +1326,7 @@ cosmo_status backward_impl(cosmo_plan *pl, const T *rho, const T *alpha, const T
     launch_fill<T>(pol->template at<T>(pol->L.parta), (T)0, (int64_t)pl->B * POL_ALPHA_PARAMS, st);
     policy_bwd_at<T>(pl, v, *pol, K, tape, grho, galpha, gA + on, gA + os, gA + oy, st);
   }
+  const CgRun<T> cg(pl, v, ws, w, st);
   launch_fill<T>(ws + w.w, (T)0, n, st);
   launch_fill<T>(ws + w.gsn, (T)0, m, st);
   T *scratch = ws + w.dk;
@@ -1157,12 +1368,8 @@ cosmo_status backward_impl(cosmo_plan *pl, const T *rho, const T *alpha, const T
       launch_dense_cols<T>(v, DC_GST, rh, ws + w.gst, nullptr, st);
       launch_bwd_cols<T>(v, pl->bkAt, rh, al, ws + w.gst, gx_in, reinterpret_cast<double *>(ws + w.gxt), ws + w.dg, ds, st);
     }
-    if (!pl->diag_M) {
-      ProfScope ps(pl, 2, st);
-      launch_pcg<T>(v, rh, ws + w.dg, reinterpret_cast<const double *>(ws + w.gxt), ws + w.w, ws + w.r, ws + w.z, ws + w.p, ws + w.Mp, ws + w.t,
-                    reinterpret_cast<double *>(ws + w.t64), pl->opt.cg_tol, pl->opt.cg_max_iter, al, nullptr, nullptr, gx_in, gx_out, 1, stats, ws + w.cg,
-                    pl->pcg_form, st);
-    }
+    if (!pl->diag_M)
+      cg(rh, ws + w.dg, reinterpret_cast<const double *>(ws + w.gxt), ws + w.w, al, nullptr, nullptr, gx_in, gx_out, 1, stats);
     {
       ProfScope ps(pl, 3, st);
       launch_dense_rows<T>(v, ws + w.w, st);
