@@ -2157,18 +2157,25 @@ cosmo_status psd_common(int32_t nblk, const int32_t *order, const int64_t *offse
   const int maxp = dt == COSMO_F32 ? COSMO_MAX_PSD_ORDER_F32 : COSMO_MAX_PSD_ORDER_F64;
   descs.resize(nblk);
   int64_t uo = 0, lo = 0;
+  // blocks that lie one behind the other, as they mostly do, show by one
+  // comparison each that none overlaps; only others are sorted
   std::vector<std::pair<int64_t, int64_t>> ranges;
+  ranges.reserve(nblk);
+  bool rising = true;
   for (int b = 0; b < nblk; ++b) {
     if (order[b] < 1 || order[b] > maxp) FAIL(order[b] < 1 ? COSMO_EINVAL : COSMO_EUNSUPPORTED, "PSD order out of range");
     if (offset[b] < 0) FAIL(COSMO_EINVAL, "negative offset");
     descs[b] = {offset[b], uo, lo, order[b], 0};
     uo += (int64_t)order[b] * order[b];
     lo += order[b];
+    if (b && offset[b] < ranges.back().second) rising = false;
     ranges.push_back({offset[b], offset[b] + (int64_t)order[b] * (order[b] + 1) / 2});
   }
-  std::sort(ranges.begin(), ranges.end());
-  for (size_t i = 1; i < ranges.size(); ++i)
-    if (ranges[i].first < ranges[i - 1].second) FAIL(COSMO_EINVAL, "PSD blocks overlap");
+  if (!rising) {
+    std::sort(ranges.begin(), ranges.end());
+    for (size_t i = 1; i < ranges.size(); ++i)
+      if (ranges[i].first < ranges[i - 1].second) FAIL(COSMO_EINVAL, "PSD blocks overlap");
+  }
   std::stable_sort(descs.begin(), descs.end(), [](const PsdDesc &a, const PsdDesc &b) {
     const int ca = psd_class(a.p), cb = psd_class(b.p);
     if (ca != cb) return ca < cb;
