@@ -157,15 +157,11 @@ typedef struct {
   int32_t cg_max_iter;         /* >= 1                                                   */
   int32_t eig_max_sweeps;      /* Jacobi sweep cap, >= 1                                 */
   double eig_tol;              /* Jacobi column-orthogonality threshold; 0 = dtype default */
-  int32_t eig_refine;          /* float32 plans.  1: eigenpairs and projection to better
-                                  than float32 accuracy: blocks up to order 128 sweep
-                                  in float64 until the couplings left are below 1e-11;
-                                  larger ones are refined after their float32 sweeps
-                                  (Ogita-Aishima steps with float64-accumulated residual
-                                  products, projection by Rayleigh-Ritz on the positive
-                                  subspace).  0: stop at the float32 threshold and use
-                                  the Jacobi eigenpairs as they are.  Must be 0 or 1;
-                                  ignored for COSMO_F64, whose sweeps run in float64. */
+  int32_t eig_refine;          /* float32 plans, whose sweeps run in float64.  1:
+                                  eigenpairs and projection to better than float32
+                                  accuracy: they go on until the couplings left are
+                                  below 2e-8.  0: stop at the float32 threshold.  Must
+                                  be 0 or 1; ignored for COSMO_F64.                     */
   int32_t eig_warm_start;      /* 1: start every step's Jacobi sweeps from the same
                                   block's eigenvectors of the previous step (same
                                   decomposition, fewer sweeps); 0: start from S.        */
@@ -189,8 +185,7 @@ typedef struct {
                                   (each is one more operator application)               */
   int32_t eig_refine_steps_total; /* refinement steps of float32 plans summed over the PSD
                                   block solves: the sweeps after the column cosines fell
-                                  below 1e-3 (orders up to 128), or the Ogita-Aishima
-                                  steps (larger orders)                                 */
+                                  below 1e-3                                            */
 } cosmo_stats;
 
 const char *cosmo_status_string(cosmo_status s);
@@ -487,7 +482,7 @@ cosmo_status cosmo_plan_autotune(cosmo_plan *plan, const void *rho, const void *
  * per workgroup of the eigensolve for the order classes p <= 32, <= 64,
  * <= 128 and larger; each is the class default {64, 256, 512, 1024} or twice
  * it for the three smaller classes {128, 512, 1024} (the largest class has
- * no alternative).  vjp_threads: 1024 (16 waves, default) or 512 (8 waves)
+ * no alternative; its 1024 names its one shape, of seven waves).  vjp_threads: 1024 (16 waves, default) or 512 (8 waves)
  * per workgroup of the DK VJP.  Other values are COSMO_EINVAL.  The VJP
  * gives bitwise the same result in both shapes; the eigensolve's workgroup
  * sums are taken in a different order (results agree to rounding).  Setting

@@ -1,5 +1,5 @@
-// One-sided (Hestenes) Jacobi sweeps over a block held in LDS, by one
-// workgroup.  Internal linkage: included by the eigensolver.
+// One-sided (Hestenes) Jacobi sweeps over a block, by one workgroup, in
+// float64.  Internal linkage: included by the eigensolver.
 //
 // A group of G lanes holds two blocks of NB columns (X: left, Y: right) in
 // registers, their rows in pieces of PE elements spread over its lanes, and
@@ -21,19 +21,31 @@
 // has met once and the row is reversed.  A block moves on in one direction,
 // so per phase a group keeps one block in registers and passes the other to
 // its neighbour through LDS: one block written, one read and one barrier for
-// NB^2 rotations.  The block's own storage is the exchange buffer (left half:
-// Y blocks moving left, right half: X blocks moving right).
+// NB^2 rotations.  Slot i of the exchange buffer belongs to group i after
+// every second phase: a group passes its left-moving block on in its own slot
+// and its right-moving one in the next group's, which it alone has read last,
+// so half of the block's storage and one barrier a phase are enough.  Slots
+// are interleaved lane by lane: every access of a wave is one contiguous row.
+//
+// Sweeps start from columns in descending order of their norms until the
+// couplings are small (ORDER2): equal eigenvalues then stand side by side,
+// without which the couplings of a cluster to the rest fall by a factor of a
+// few per sweep only, not quadratically.  Sweeps that a float32 solve of
+// order 160 takes, with and without: 10 and 14 with a quarter of the
+// eigenvalues equal, 8 and 9 for a Gaussian matrix; at order 60: 8 and 12, 7
+// and 8.
 //
 // What bounds it: the issue of 3 multiply-adds per element pair on the few
 // waves one block occupies (a wave issues a vector instruction every four
 // cycles), about as many instructions again for the reduction, the rotation
-// and the broadcasts, and their latency.  Measured per sweep in float64:
-// 51 us at order 100 (NB = 4, G = 16: one wave per SIMD), 24 us at 64 and
-// 10 us at 32 (NB = 2).  Reading and writing both columns of every pair in
-// LDS for each rotation (the circle schedule, which this replaces) took
-// 1542 us for the projection of an order-100 float64 block, this 690 us.
-// Two-column blocks at order 100 (twice the exchanges, two waves per SIMD)
-// took 64 us per sweep.
+// and the broadcasts, and their latency; above order 128, two waves to a
+// SIMD, also the LDS traffic of the exchange (320 KB a phase at order 200,
+// 2500 of its 10900 cycles).  Measured per sweep: 10 us at order 30, 23 us at
+// 60 (NB = 2), 55 us at 100, 73 us at 128, 150 us at 160, 230 us at 200 (NB =
+// 4).  Reading and writing both columns of every pair in LDS for each
+// rotation (the circle schedule, which this replaces) took 1542 us for the
+// projection of an order-100 float64 block, this 487 us; two-column blocks at
+// order 100 (twice the exchanges, two waves per SIMD) 64 us per sweep.
 #pragma once
 
 #include "cosmo_internal.h"
@@ -42,9 +54,6 @@ namespace cosmo {
 namespace {
 
 // Cross-lane moves inside rows of 16 lanes (DPP).
-template <int CTRL, int BANKS = 0xF> __device__ __forceinline__ float dpp_mov(float x, float old = 0.f) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(x), CTRL, 0xF, BANKS, BANKS == 0xF));
-}
 template <int CTRL, int BANKS = 0xF> __device__ __forceinline__ double dpp_mov(double x, double old = 0.0) {
   const long long b = __double_as_longlong(x), o = __double_as_longlong(old);
   const int lo = __builtin_amdgcn_update_dpp((int)o, (int)b, CTRL, 0xF, BANKS, BANKS == 0xF);
@@ -60,16 +69,16 @@ constexpr int quad_perm(int a, int b, int c, int d) { return a | b << 2 | c << 4
 // lanes with lane % NB == q.  Every step adds a lane and its partner (lane ^
 // 1, 2, 4, 8), so the lanes holding one total hold the same bits: the rows of
 // a column must be rotated by the same angle in all of them.
-template <int G, int NB, typename T> __device__ __forceinline__ T group_sums(const T (&v)[NB]) {
+template <int G, int NB> __device__ __forceinline__ double group_sums(const double (&v)[NB]) {
   static_assert((G == 8 || G == 16) && (NB == 2 || NB == 4), "group of 8 or 16 lanes, 2 or 4 values");
   const bool b0 = threadIdx.x & 1, b1 = threadIdx.x & 2;
-  T s;
+  double s;
   if constexpr (NB == 2) {
     s = (b0 ? v[1] : v[0]) + dpp_mov<DPP_XOR1>(b0 ? v[0] : v[1]);
     s += dpp_mov<DPP_XOR2>(s);
   } else {
-    const T lo = (b0 ? v[1] : v[0]) + dpp_mov<DPP_XOR1>(b0 ? v[0] : v[1]);
-    const T hi = (b0 ? v[3] : v[2]) + dpp_mov<DPP_XOR1>(b0 ? v[2] : v[3]);
+    const double lo = (b0 ? v[1] : v[0]) + dpp_mov<DPP_XOR1>(b0 ? v[0] : v[1]);
+    const double hi = (b0 ? v[3] : v[2]) + dpp_mov<DPP_XOR1>(b0 ? v[2] : v[3]);
     s = (b1 ? hi : lo) + dpp_mov<DPP_XOR2>(b1 ? lo : hi);
   }
   // lane i ^ 4: quads 0 and 2 of a row read upwards, 1 and 3 downwards
@@ -79,22 +88,20 @@ template <int G, int NB, typename T> __device__ __forceinline__ T group_sums(con
 }
 
 // The value held by the lanes of index Q, in every lane of their quad.
-template <int NB, int Q, typename T> __device__ __forceinline__ T from_lane(T x) {
+template <int NB, int Q> __device__ __forceinline__ double from_lane(double x) {
   if constexpr (NB == 4) return dpp_mov<quad_perm(Q, Q, Q, Q)>(x);
   else return dpp_mov<quad_perm(Q, Q, 2 + Q, 2 + Q)>(x);
 }
-template <int NB, typename T> __device__ __forceinline__ T lane_value(T x, int q) {   // q: known after unrolling
+template <int NB> __device__ __forceinline__ double lane_value(double x, int q) {   // q: known after unrolling
   return q == 0 ? from_lane<NB, 0>(x) : q == 1 ? from_lane<NB, 1>(x) : q == 2 ? from_lane<NB, 2 % NB>(x)
                                                                                 : from_lane<NB, 3 % NB>(x);
 }
 // Lane q receives lane (q + 1) % NB's value.
-template <int NB, typename T> __device__ __forceinline__ T next_lane(T x) {
+template <int NB> __device__ __forceinline__ double next_lane(double x) {
   return dpp_mov<NB == 4 ? quad_perm(1, 2, 3, 0) : DPP_XOR1>(x);
 }
 
-// 1 / x to working precision: the hardware's float32 reciprocal, or two
-// Newton steps on its float64 one.
-__device__ __forceinline__ float full_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+// 1 / x to working precision: two Newton steps on the hardware's reciprocal.
 __device__ __forceinline__ double full_rcp(double x) {
   double y = __builtin_amdgcn_rcp(x);
   y = fma(fma(-x, y, 1.0), y, y);
@@ -109,18 +116,18 @@ struct SweepMax {
 
 // Rotates NB disjoint pairs (a[q], b[q]); al, da, be, db: squared norms and D
 // of pair q's columns in the lanes of index q.
-template <int G, int NB, int E, typename C>
-__device__ __forceinline__ void rotate_pairs(C *const (&a)[NB], C *const (&b)[NB], C &al, C &da, C &be, C &db, float tol2,
+template <int G, int NB, int E>
+__device__ __forceinline__ void rotate_pairs(double *const (&a)[NB], double *const (&b)[NB], double &al, double &da, double &be, double &db, float tol2,
                                     SweepMax &mx) {
-  C dots[NB];
+  double dots[NB];
 #pragma unroll
   for (int q = 0; q < NB; ++q) dots[q] = a[q][0] * b[q][0];
 #pragma unroll
   for (int e = 1; e < E; ++e)
 #pragma unroll
     for (int q = 0; q < NB; ++q) dots[q] = fma(a[q][e], b[q][e], dots[q]);
-  const C g = group_sums<G, NB>(dots);
-  const C P = da * db, Pg = P * g;
+  const double g = group_sums<G, NB>(dots);
+  const double P = da * db, Pg = P * g;
   const float gf = (float)g, g2 = gf * (float)Pg;   // (a'b)^2
   const float ab = (float)al * (float)be;
   const bool rot = g2 > tol2 * ab;
@@ -131,19 +138,19 @@ __device__ __forceinline__ void rotate_pairs(C *const (&a)[NB], C *const (&b)[NB
   const float r2 = fmaf(4.f, g2, d * d);
   float tau = 2.f * gf * __builtin_amdgcn_rcpf(fmaf(r2, __builtin_amdgcn_rsqf(r2), fabsf(d)));
   tau = rot ? copysignf(1.f, d) * tau : 0.f;   // t / (d_a d_b); 0 where r2 = 0
-  const C cx = (C)tau * db, cy = (C)tau * da;
-  const C t2 = cx * cy, sec2 = (C)1 + t2, k = (C)tau * Pg;
-  const C cs2 = rot ? full_rcp(sec2) : (C)1;
-  const C cz = cy * cs2;
+  const double cx = (double)tau * db, cy = (double)tau * da;
+  const double t2 = cx * cy, sec2 = 1.0 + t2, k = (double)tau * Pg;
+  const double cs2 = rot ? full_rcp(sec2) : 1.0;
+  const double cz = cy * cs2;
 #pragma unroll
   for (int q = 0; q < NB; ++q) {
-    const C u = lane_value<NB>(cx, q);
+    const double u = lane_value<NB>(cx, q);
 #pragma unroll
     for (int e = 0; e < E; ++e) a[q][e] = fma(-u, b[q][e], a[q][e]);
   }
 #pragma unroll
   for (int q = 0; q < NB; ++q) {
-    const C u = lane_value<NB>(cz, q);
+    const double u = lane_value<NB>(cz, q);
 #pragma unroll
     for (int e = 0; e < E; ++e) b[q][e] = fma(u, a[q][e], b[q][e]);
   }
@@ -155,16 +162,16 @@ __device__ __forceinline__ void rotate_pairs(C *const (&a)[NB], C *const (&b)[NB
   mx.tan2 = fmaxf(mx.tan2, (float)t2);
 }
 
-template <typename C, int NB, int E> struct JacobiRegs {
-  C x[NB][E], y[NB][E];
-  C al, da;   // column X_q (q: lane index): squared norm, D
-  C be, db;   // column Y_q
+template <int NB, int E> struct JacobiRegs {
+  double x[NB][E], y[NB][E];
+  double al, da;   // column X_q (q: lane index): squared norm, D
+  double be, db;   // column Y_q
 };
 
 // The cross pairs of blocks X and Y: step S pairs (x_q, y_(q+S)).
-template <int G, int NB, int E, int S, typename C>
-__device__ __forceinline__ void cross_step(JacobiRegs<C, NB, E> &R, float tol2, SweepMax &mx) {
-  C *a[NB], *b[NB];
+template <int G, int NB, int E, int S>
+__device__ __forceinline__ void cross_step(JacobiRegs<NB, E> &R, float tol2, SweepMax &mx) {
+  double *a[NB], *b[NB];
 #pragma unroll
   for (int q = 0; q < NB; ++q) {
     a[q] = R.x[q];
@@ -174,8 +181,8 @@ __device__ __forceinline__ void cross_step(JacobiRegs<C, NB, E> &R, float tol2, 
   R.be = next_lane<NB>(R.be);
   R.db = next_lane<NB>(R.db);
 }
-template <int G, int NB, int E, typename C>
-__device__ __forceinline__ void cross_pairs(JacobiRegs<C, NB, E> &R, float tol2, SweepMax &mx) {
+template <int G, int NB, int E>
+__device__ __forceinline__ void cross_pairs(JacobiRegs<NB, E> &R, float tol2, SweepMax &mx) {
   cross_step<G, NB, E, 0>(R, tol2, mx);
   cross_step<G, NB, E, 1>(R, tol2, mx);
   if constexpr (NB == 4) {
@@ -186,30 +193,30 @@ __device__ __forceinline__ void cross_pairs(JacobiRegs<C, NB, E> &R, float tol2,
 
 // The pairs (I0, J0), (I1, J1) of X and of Y at once (NB = 4); lanes 0 and 1
 // of a quad take X's scalars, lanes 2 and 3 Y's.
-template <int G, int E, int I0, int J0, int I1, int J1, typename C>
-__device__ __forceinline__ void inside_step4(JacobiRegs<C, 4, E> &R, float tol2, SweepMax &mx) {
+template <int G, int E, int I0, int J0, int I1, int J1>
+__device__ __forceinline__ void inside_step4(JacobiRegs<4, E> &R, float tol2, SweepMax &mx) {
   const int m = threadIdx.x & 3;
   const bool hi = m >= 2;
-  auto gather_a = [&](C fx, C fy) {
-    const C u = dpp_mov<quad_perm(I0, I1, I0, I1)>(fx), w = dpp_mov<quad_perm(I0, I1, I0, I1)>(fy);
+  auto gather_a = [&](double fx, double fy) {
+    const double u = dpp_mov<quad_perm(I0, I1, I0, I1)>(fx), w = dpp_mov<quad_perm(I0, I1, I0, I1)>(fy);
     return hi ? w : u;
   };
-  auto gather_b = [&](C fx, C fy) {
-    const C u = dpp_mov<quad_perm(J0, J1, J0, J1)>(fx), w = dpp_mov<quad_perm(J0, J1, J0, J1)>(fy);
+  auto gather_b = [&](double fx, double fy) {
+    const double u = dpp_mov<quad_perm(J0, J1, J0, J1)>(fx), w = dpp_mov<quad_perm(J0, J1, J0, J1)>(fy);
     return hi ? w : u;
   };
-  C al = gather_a(R.al, R.be), da = gather_a(R.da, R.db), be = gather_b(R.al, R.be), db = gather_b(R.da, R.db);
-  C *a[4] = {R.x[I0], R.x[I1], R.y[I0], R.y[I1]};
-  C *b[4] = {R.x[J0], R.x[J1], R.y[J0], R.y[J1]};
+  double al = gather_a(R.al, R.be), da = gather_a(R.da, R.db), be = gather_b(R.al, R.be), db = gather_b(R.da, R.db);
+  double *a[4] = {R.x[I0], R.x[I1], R.y[I0], R.y[I1]};
+  double *b[4] = {R.x[J0], R.x[J1], R.y[J0], R.y[J1]};
   rotate_pairs<G, 4, E>(a, b, al, da, be, db, tol2, mx);
   // column m is the first or second member of pair 0 or 1
   constexpr int P0 = 0, P1 = (1 == I0 || 1 == J0) ? 0 : 1, P2 = (2 == I0 || 2 == J0) ? 0 : 1,
                 P3 = (3 == I0 || 3 == J0) ? 0 : 1;
   const bool second = m == J0 || m == J1;
-  auto scatter = [&](C fa, C fb, C &ox, C &oy) {
-    const C xa = dpp_mov<quad_perm(P0, P1, P2, P3)>(fa), xb = dpp_mov<quad_perm(P0, P1, P2, P3)>(fb);
-    const C ya = dpp_mov<quad_perm(2 + P0, 2 + P1, 2 + P2, 2 + P3)>(fa);
-    const C yb = dpp_mov<quad_perm(2 + P0, 2 + P1, 2 + P2, 2 + P3)>(fb);
+  auto scatter = [&](double fa, double fb, double &ox, double &oy) {
+    const double xa = dpp_mov<quad_perm(P0, P1, P2, P3)>(fa), xb = dpp_mov<quad_perm(P0, P1, P2, P3)>(fb);
+    const double ya = dpp_mov<quad_perm(2 + P0, 2 + P1, 2 + P2, 2 + P3)>(fa);
+    const double yb = dpp_mov<quad_perm(2 + P0, 2 + P1, 2 + P2, 2 + P3)>(fb);
     ox = second ? xb : xa;
     oy = second ? yb : ya;
   };
@@ -218,8 +225,8 @@ __device__ __forceinline__ void inside_step4(JacobiRegs<C, 4, E> &R, float tol2,
 }
 
 // The pairs inside the blocks, once per sweep.
-template <int G, int NB, int E, typename C>
-__device__ __forceinline__ void inside_pairs(JacobiRegs<C, NB, E> &R, float tol2, SweepMax &mx) {
+template <int G, int NB, int E>
+__device__ __forceinline__ void inside_pairs(JacobiRegs<NB, E> &R, float tol2, SweepMax &mx) {
   if constexpr (NB == 4) {
     inside_step4<G, E, 0, 1, 2, 3>(R, tol2, mx);
     inside_step4<G, E, 0, 2, 1, 3>(R, tol2, mx);
@@ -227,12 +234,12 @@ __device__ __forceinline__ void inside_pairs(JacobiRegs<C, NB, E> &R, float tol2
   } else {
     // even lanes: (x0, x1), odd lanes: (y0, y1)
     const bool odd = threadIdx.x & 1;
-    const C al2 = dpp_mov<DPP_XOR1>(R.al), da2 = dpp_mov<DPP_XOR1>(R.da);
-    const C be2 = dpp_mov<DPP_XOR1>(R.be), db2 = dpp_mov<DPP_XOR1>(R.db);
-    C al = odd ? be2 : R.al, da = odd ? db2 : R.da, be = odd ? R.be : al2, db = odd ? R.db : da2;
-    C *a[2] = {R.x[0], R.y[0]}, *b[2] = {R.x[1], R.y[1]};
+    const double al2 = dpp_mov<DPP_XOR1>(R.al), da2 = dpp_mov<DPP_XOR1>(R.da);
+    const double be2 = dpp_mov<DPP_XOR1>(R.be), db2 = dpp_mov<DPP_XOR1>(R.db);
+    double al = odd ? be2 : R.al, da = odd ? db2 : R.da, be = odd ? R.be : al2, db = odd ? R.db : da2;
+    double *a[2] = {R.x[0], R.y[0]}, *b[2] = {R.x[1], R.y[1]};
     rotate_pairs<G, 2, E>(a, b, al, da, be, db, tol2, mx);
-    const C pa = dpp_mov<DPP_XOR1>(al), pda = dpp_mov<DPP_XOR1>(da), pb = dpp_mov<DPP_XOR1>(be), pdb = dpp_mov<DPP_XOR1>(db);
+    const double pa = dpp_mov<DPP_XOR1>(al), pda = dpp_mov<DPP_XOR1>(da), pb = dpp_mov<DPP_XOR1>(be), pdb = dpp_mov<DPP_XOR1>(db);
     R.al = odd ? pb : al;
     R.da = odd ? pdb : da;
     R.be = odd ? be : pa;
@@ -241,14 +248,14 @@ __device__ __forceinline__ void inside_pairs(JacobiRegs<C, NB, E> &R, float tol2
 }
 
 // A block whose scale became small or large is rescaled by a power of two (exact).
-template <int NB, int E, typename C> __device__ __forceinline__ void rescale(C (&col)[NB][E], C &D) {
-  const bool low = D < (C)0.0009765625, high = D > (C)1024;   // 2^-10, 2^10
+template <int NB, int E> __device__ __forceinline__ void rescale(double (&col)[NB][E], double &D) {
+  const bool low = D < 0.0009765625, high = D > 1024.0;   // 2^-10, 2^10
   if (__ballot(low || high) == 0) return;
-  const C f = low ? (C)0.03125 : high ? (C)32 : (C)1;
-  D = low ? D * (C)1024 : high ? D * (C)0.0009765625 : D;
+  const double f = low ? 0.03125 : high ? 32.0 : 1.0;
+  D = low ? D * 1024.0 : high ? D * 0.0009765625 : D;
 #pragma unroll
   for (int q = 0; q < NB; ++q) {
-    const C fq = lane_value<NB>(f, q);
+    const double fq = lane_value<NB>(f, q);
 #pragma unroll
     for (int e = 0; e < E; ++e) col[q][e] *= fq;
   }
@@ -256,11 +263,12 @@ template <int NB, int E, typename C> __device__ __forceinline__ void rescale(C (
 
 // When a solve's sweeps end.  tol2: pairs with a squared cosine below it are
 // not rotated.  A sweep that rotated nothing ends them; so does one after
-// which the couplings that its rotations can have left behind, at most
-// p max|tan| max|cos|, are below stop (they mix a rotated pair's remainder
-// with another pair's coupling).  At most max_sweeps sweeps, or, with
-// coarse2 > 0, max_sweeps until the largest squared cosine is below coarse2
-// and then up to max_fine more.
+// which the couplings left are below stop: they are no larger than the
+// largest that it met (max|cos|), nor than what its rotations can have left
+// behind, p max|tan| max|cos| (they mix a rotated pair's remainder with
+// another pair's coupling).  At most max_sweeps sweeps, or, with coarse2 > 0,
+// max_sweeps until the largest squared cosine is below coarse2 and then up to
+// max_fine more.
 struct SweepRule {
   float tol2, stop, coarse2;
   int max_sweeps, max_fine;
@@ -270,59 +278,81 @@ struct SweepCount {
   bool converged;
 };
 
-// Sweeps over the order-p block in W (jacobi_cols<NB>(p) columns of leading
-// dimension ld, rows p .. ld - 1 and columns from p on zero; scale brings its
-// column norms to order one); leaves in W the normalised columns and in lamd
-// their norms times scale.  scal: 2 * jacobi_cols<NB>(p) elements (may be
-// lamd), mx_s: 6 zeroed ints.  Starts and ends with a barrier.
 template <int NB> __host__ __device__ constexpr int jacobi_cols(int p) { return (p + 2 * NB - 1) / (2 * NB) * (2 * NB); }
 
-template <typename C, int G, int NB, int PE, int NCH>
-__device__ __forceinline__ SweepCount jacobi_sweeps(C *W, C *scal, C scale, int p, int ld, const SweepRule &rule, double *lamd,
-                                    int *mx_s) {
-  constexpr int E = PE * NCH;
-  typedef C V __attribute__((ext_vector_type(PE)));
-  const int tid = threadIdx.x, grp = tid / G, gl = tid % G, q = tid % NB;
-  const int ng = jacobi_cols<NB>(p) / (2 * NB);
-  const bool act = grp < ng, first = grp == 0, last = grp == ng - 1;
-  const bool busy = __builtin_amdgcn_readfirstlane(grp) < ng;   // waves past the last group only keep the barriers
-  const int pe = (p + PE - 1) / PE * PE;
-  const int row0 = PE * gl;
-  const bool tail = row0 + PE * G * (NCH - 1) < pe;   // this lane's last piece lies inside the block
-  C *bufL = W, *bufR = W + NB * ng * ld;              // ng slots of NB columns each
-  C *scL = scal, *scR = scal + 2 * NB * ng;           // per slot: squared norms of its columns, then their D
-  JacobiRegs<C, NB, E> R;
-  auto load = [&](const C *src, C (&dst)[NB][E]) {
+// Sweeps that met no squared cosine above this leave the order as it is: the
+// norms are the eigenvalues to half the digits by then.
+constexpr float ORDER2 = 1e-6f;
+
+// Exchange buffer for blocks of E pieces per lane in a class of orders up to
+// PMAX: groups, lanes that hold a last piece, elements.
+template <int G, int NB, int E, int PMAX> struct Exchange {
+  static constexpr int NG = (G * E < PMAX ? jacobi_cols<NB>(G * E) : jacobi_cols<NB>(PMAX)) / (2 * NB);
+  static constexpr int TW = PMAX - G * (E - 1) < G ? PMAX - G * (E - 1) : G;
+  static constexpr int elems = NB * NG * (G * (E - 1) + TW);
+};
+
+// This thread's place: group, lane in it, whether its group holds columns.
+// busy is the same in a whole wave; waves past the last group only keep the
+// barriers.
+template <int G, int NB> struct JacobiPlace {
+  int ng, grp, gl;
+  bool act, busy;
+  __device__ __forceinline__ explicit JacobiPlace(int p) {
+    ng = jacobi_cols<NB>(p) / (2 * NB);
+    grp = threadIdx.x / G;
+    gl = threadIdx.x % G;
+    act = grp < ng;
+    busy = __builtin_amdgcn_readfirstlane(grp) < ng;
+  }
+};
+
+// First columns of the blocks that this group holds between sweeps.
+struct BlockCols {
+  int x, y;
+};
+template <int G, int NB> __device__ __forceinline__ BlockCols block_cols(const JacobiPlace<G, NB> &at, int rev) {
+  const int bx = rev ? 2 * at.ng - 1 - 2 * at.grp : 2 * at.grp;
+  return {NB * bx, NB * (rev ? bx - 1 : bx + 1)};
+}
+
+// Sweeps over the order-p block whose columns 2 NB g .. 2 NB g + NB - 1 are
+// group g's X and the next NB its Y, zero past the block, column norms of
+// order one; idle groups hold zeros.  Ends with column blocks at their
+// positions, reversed after an odd number of sweeps (rev).  xb:
+// Exchange::elems, sc: jacobi_cols<NB>(p) elements, rk: as many, mx_s: 7
+// zeroed ints; all are free to use from the first barrier on, which is the
+// first thing.  put(column, row, value) and get(column, row) reach a store of
+// jacobi_cols<NB>(p) columns and p rows in which columns are put in order
+// (put past column p - 1 may be dropped, get gives zeros there); it may
+// overlap xb.  ordered: the columns start in order (a warm start's).
+template <int NT, int G, int NB, int E, int PMAX, typename Put, typename Get>
+__device__ __forceinline__ SweepCount jacobi_sweeps(JacobiRegs<NB, E> &R, const JacobiPlace<G, NB> &at, double *xb,
+                                                    double *sc, short *rk, int p, const SweepRule &rule, bool ordered,
+                                                    int *mx_s, int &rev, Put put, Get get) {
+  using X = Exchange<G, NB, E, PMAX>;
+  const int tid = threadIdx.x, q = tid % NB, grp = at.grp, gl = at.gl, ng = at.ng;
+  const bool act = at.act, busy = at.busy, last = grp == ng - 1;
+  const bool tail = G * (E - 1) + gl < p;   // this lane's last piece lies inside the block
+  double *xf = xb + tid, *xt = xb + NB * X::NG * G * (E - 1) + grp * X::TW + gl;   // whole pieces, last pieces
+  auto load = [&](int shift, double (&dst)[NB][E]) {   // from this group's slot or (shift = 1) the next
 #pragma unroll
-    for (int k = 0; k < NB; ++k)
+    for (int k = 0; k < NB; ++k) {
 #pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        V t = 0;
-        if (c < NCH - 1 || tail) t = *reinterpret_cast<const V *>(src + k * ld + row0 + PE * G * c);
-#pragma unroll
-        for (int e = 0; e < PE; ++e) dst[k][PE * c + e] = t[e];
-      }
+      for (int c = 0; c < E - 1; ++c) dst[k][c] = xf[(k * (E - 1) + c) * X::NG * G + shift * G];
+      dst[k][E - 1] = tail ? xt[k * X::NG * X::TW + shift * X::TW] : 0.0;
+    }
   };
-  auto store = [&](C *dst, const C (&src)[NB][E]) {
+  auto store = [&](int shift, const double (&src)[NB][E]) {
 #pragma unroll
-    for (int k = 0; k < NB; ++k)
+    for (int k = 0; k < NB; ++k) {
 #pragma unroll
-      for (int c = 0; c < NCH; ++c)
-        if (c < NCH - 1 || tail) {
-          V t;
-#pragma unroll
-          for (int e = 0; e < PE; ++e) t[e] = src[k][PE * c + e];
-          *reinterpret_cast<V *>(dst + k * ld + row0 + PE * G * c) = t;
-        }
+      for (int c = 0; c < E - 1; ++c) xf[(k * (E - 1) + c) * X::NG * G + shift * G] = src[k][c];
+      if (tail) xt[k * X::NG * X::TW + shift * X::TW] = src[k][E - 1];
+    }
   };
-  auto set_all = [&](C (&dst)[NB][E], C f) {   // times f; f = 0 clears
-#pragma unroll
-    for (int k = 0; k < NB; ++k)
-#pragma unroll
-      for (int e = 0; e < E; ++e) dst[k][e] = f == (C)0 ? (C)0 : dst[k][e] * f;
-  };
-  auto norms = [&](const C (&v)[NB][E]) {
-    C s[NB];
+  auto norms = [&](const double (&v)[NB][E]) {
+    double s[NB];
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       s[k] = v[k][0] * v[k][0];
@@ -331,30 +361,86 @@ __device__ __forceinline__ SweepCount jacobi_sweeps(C *W, C *scal, C scale, int 
     }
     return group_sums<G, NB>(s);
   };
+  double *sc_mine = sc + 2 * NB * grp + q, *sc_next = sc_mine + 2 * NB;   // squared norms, then D
   R.da = R.db = 1;
   R.al = R.be = 0;
   __syncthreads();
-  if (act) {
-    load(W + 2 * NB * grp * ld, R.x);
-    load(W + (2 * NB * grp + NB) * ld, R.y);
-    set_all(R.x, scale);
-    set_all(R.y, scale);
-  } else {
-    set_all(R.x, 0);
-    set_all(R.y, 0);
-  }
-  C *myL = bufL + NB * grp * ld, *myR = bufR + NB * grp * ld;
-  __syncthreads();   // every column is in registers before the buffers are written
   SweepCount n{0, 0, p == 1};
   bool fine = false, coarse_ok = true;
-  int rev = 0, total = 0;
+  bool order = !ordered;
+  int total = 0;
+  rev = 0;
   while (!n.converged && (fine ? n.fine < rule.max_fine : n.sweeps < rule.max_sweeps)) {
     SweepMax mx{0.f, 0.f};
     if (busy) {
       R.al = R.da * norms(R.x);
       R.be = R.db * norms(R.y);
-      inside_pairs<G, NB, E>(R, rule.tol2, mx);
     }
+    if (order) {   // the columns in descending order of their norms, in float32
+      const BlockCols b = block_cols<G, NB>(at, rev);
+      float *key = reinterpret_cast<float *>(sc);
+      if (act && gl < NB) {
+        key[b.x + q] = (float)R.al;
+        key[b.y + q] = (float)R.be;
+      }
+      __syncthreads();
+      // TPC threads to a column, each counting a part of those before it
+      constexpr int TPC = NT / jacobi_cols<NB>(PMAX) >= 4 ? 4 : 2;
+      static_assert(NT >= 2 * jacobi_cols<NB>(PMAX), "two threads to a column");
+      const int nc = 2 * NB * ng, col = tid / TPC;
+      if (col < nc) {
+        const int mine = __float_as_int(key[col]);   // (non-negative floats order like their bits)
+        int rank = 0;
+        for (int j = 4 * (tid % TPC); j < nc; j += 4 * TPC) {
+          const int4 other = *reinterpret_cast<const int4 *>(key + j);
+          rank += (other.x >= mine + (j >= col)) + (other.y >= mine + (j + 1 >= col)) +
+                  (other.z >= mine + (j + 2 >= col)) + (other.w >= mine + (j + 3 >= col));
+        }
+        rank += __builtin_amdgcn_update_dpp(0, rank, DPP_XOR1, 0xF, 0xF, true);
+        if constexpr (TPC == 4) rank += __builtin_amdgcn_update_dpp(0, rank, DPP_XOR2, 0xF, 0xF, true);
+        if (tid % TPC == 0) {
+          rk[col] = (short)rank;
+          if (rank != col) mx_s[6] = total + 1;
+        }
+      }
+      __syncthreads();
+      if (mx_s[6] == total + 1) {
+        if (act) {
+          auto move = [&](int col0, const double (&v)[NB][E], double D, double norm) {
+            const double f = sqrt(D);
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+              const int to = rk[col0 + k];
+              const double fk = lane_value<NB>(f, k);
+#pragma unroll
+              for (int c = 0; c < E; ++c)
+                if (c < E - 1 || tail) put(to, G * c + gl, v[k][c] * fk);
+            }
+            if (gl < NB) sc[rk[col0 + q]] = norm;
+          };
+          move(b.x, R.x, R.da, R.al);
+          move(b.y, R.y, R.db, R.be);
+        }
+        __syncthreads();
+        if (act) {
+          const int col0 = 2 * NB * grp;
+          auto fetch = [&](int col, double (&v)[NB][E]) {
+#pragma unroll
+            for (int k = 0; k < NB; ++k)
+#pragma unroll
+              for (int c = 0; c < E; ++c) v[k][c] = c < E - 1 || tail ? get(col + k, G * c + gl) : 0.0;
+          };
+          fetch(col0, R.x);
+          fetch(col0 + NB, R.y);
+          R.al = sc[col0 + q];
+          R.be = sc[col0 + NB + q];
+          R.da = R.db = 1;
+        }
+        rev = 0;
+        __syncthreads();
+      }
+    }
+    if (busy) inside_pairs<G, NB, E>(R, rule.tol2, mx);
     for (int ph = 0; ph < ng; ++ph) {
       if (busy) {
         cross_pairs<G, NB, E>(R, rule.tol2, mx);
@@ -362,22 +448,25 @@ __device__ __forceinline__ SweepCount jacobi_sweeps(C *W, C *scal, C scale, int 
         rescale<NB, E>(R.y, R.db);
       }
       if (act) {
-        store(myL, R.y);
+        store(0, R.y);
         if (gl < NB) {
-          scL[2 * NB * grp + q] = R.be;
-          scL[2 * NB * grp + NB + q] = R.db;
+          sc_mine[0] = R.be;
+          sc_mine[NB] = R.db;
         }
       }
       __syncthreads();
       if (act) {
         if (last) {   // the right end: no partner in this phase
-          set_all(R.y, 0);
+#pragma unroll
+          for (int k = 0; k < NB; ++k)
+#pragma unroll
+            for (int e = 0; e < E; ++e) R.y[k][e] = 0;
           R.be = 0;
           R.db = 1;
         } else {
-          load(myL + NB * ld, R.y);
-          R.be = scL[2 * NB * (grp + 1) + q];
-          R.db = scL[2 * NB * (grp + 1) + NB + q];
+          load(1, R.y);
+          R.be = sc_next[0];
+          R.db = sc_next[NB];
         }
       }
       if (busy) {
@@ -385,11 +474,11 @@ __device__ __forceinline__ SweepCount jacobi_sweeps(C *W, C *scal, C scale, int 
         // the former left block moves right, to the group after
         rescale<NB, E>(R.x, R.da);
       }
-      if (act) {
-        store(myR, R.x);
+      if (act && !last) {
+        store(1, R.x);
         if (gl < NB) {
-          scR[2 * NB * grp + q] = R.al;
-          scR[2 * NB * grp + NB + q] = R.da;
+          sc_next[0] = R.al;
+          sc_next[NB] = R.da;
         }
       }
       __syncthreads();
@@ -403,11 +492,9 @@ __device__ __forceinline__ SweepCount jacobi_sweeps(C *W, C *scal, C scale, int 
           R.db = R.da;
         }
         // the left end takes back its own block of the phase before
-        const C *src = first ? bufL : myR - NB * ld;
-        const C *ssc = first ? scL : scR + 2 * NB * (grp - 1);
-        load(src, R.x);
-        R.al = ssc[q];
-        R.da = ssc[NB + q];
+        load(0, R.x);
+        R.al = sc_mine[0];
+        R.da = sc_mine[NB];
       }
     }
     rev ^= 1;
@@ -427,66 +514,98 @@ __device__ __forceinline__ SweepCount jacobi_sweeps(C *W, C *scal, C scale, int 
     if (tid == 0) next[0] = next[1] = 0;
     __syncthreads();
     const float c2 = __int_as_float(slot[0]), t2 = __int_as_float(slot[1]);
+    order = c2 > ORDER2;
     ++total;
     if (fine) ++n.fine;
     else ++n.sweeps;
-    n.converged = t2 == 0.f || (float)p * sqrtf(c2) * sqrtf(t2) <= rule.stop;
+    n.converged = t2 == 0.f || fminf(1.f, (float)p * sqrtf(t2)) * sqrtf(c2) <= rule.stop;
     if (!fine && rule.coarse2 > 0.f && (c2 <= rule.coarse2 || n.sweeps >= rule.max_sweeps)) {
       fine = true;
       coarse_ok = n.converged || c2 <= rule.coarse2;
     }
   }
   if (fine) n.converged = coarse_ok;
-  __syncthreads();
-  // normalised columns and their norms
-  auto norms64 = [&](const C (&v)[NB][E]) {
+  return n;
+}
+
+// The swept columns to unit length; their norms in the lanes of index q.
+struct ColumnNorms {
+  double x, y;
+};
+template <int G, int NB, int E> __device__ __forceinline__ ColumnNorms unit_columns(JacobiRegs<NB, E> &R) {
+  auto unit = [&](double (&v)[NB][E]) {
     double s[NB];
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
-      s[k] = 0;
+      s[k] = v[k][0] * v[k][0];
 #pragma unroll
-      for (int e = 0; e < E; ++e) s[k] = fma((double)v[k][e], (double)v[k][e], s[k]);
+      for (int e = 1; e < E; ++e) s[k] = fma(v[k][e], v[k][e], s[k]);
     }
-    return group_sums<G, NB>(s);
+    const double n2 = group_sums<G, NB>(s), n = sqrt(n2), f = n2 > 0.0 ? 1.0 / n : 0.0;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const double fk = lane_value<NB>(f, k);
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[k][e] *= fk;
+    }
+    return n;
   };
-  if (busy) {
-    const double sx = norms64(R.x), sy = norms64(R.y);
-    const double nx = sqrt(sx), ny = sqrt(sy);
-    const double ix = sx > 0.0 ? 1.0 / nx : 0.0, iy = sy > 0.0 ? 1.0 / ny : 0.0;
-    auto mul = [&](C (&v)[NB][E], double f) {
+  const double nx = unit(R.x), ny = unit(R.y);
+  return {sqrt(R.da) * nx, sqrt(R.db) * ny};
+}
+
+// The sweeps over a block that lies in LDS, with as many pieces per lane as
+// order p needs: W has jacobi_cols<NB>(p) columns of leading dimension ld,
+// rows p .. ld - 1 and columns from p on zero; scale brings its column norms
+// to order one.  Leaves in W the normalised columns and in lamd their norms
+// times scale.  W also holds the exchange buffer, lamd the moving scalars
+// (jacobi_cols<NB>(p) elements).  Starts and ends with a barrier.
+template <int NT, int G, int NB, int E, int EMAX, int PMAX>
+__device__ __forceinline__ SweepCount sweep_lds(double *W, double scale, int p, int ld, const SweepRule &rule,
+                                                bool ordered, double *lamd, short *rk, int *mx_s) {
+  if constexpr (E < EMAX) {
+    if (p > G * E) return sweep_lds<NT, G, NB, E + 1, EMAX, PMAX>(W, scale, p, ld, rule, ordered, lamd, rk, mx_s);
+  }
+  const JacobiPlace<G, NB> at(p);
+  const int q = threadIdx.x % NB;
+  const bool tail = G * (E - 1) + at.gl < p;
+  JacobiRegs<NB, E> R;
+  __syncthreads();
+  auto load = [&](const double *src, double (&dst)[NB][E]) {
 #pragma unroll
-      for (int k = 0; k < NB; ++k) {
-        const double fk = lane_value<NB>(f, k);
+    for (int k = 0; k < NB; ++k)
 #pragma unroll
-        for (int e = 0; e < E; ++e) v[k][e] = (C)((double)v[k][e] * fk);
-      }
-    };
-    mul(R.x, ix);
-    mul(R.y, iy);
-    if (act) {
-      // position i holds block i, or block 2 ng - 1 - i after an odd number of sweeps
-      const int bx = rev ? 2 * ng - 1 - 2 * grp : 2 * grp, by = rev ? bx - 1 : bx + 1;
-      store(W + NB * bx * ld, R.x);
-      store(W + NB * by * ld, R.y);
-      if (gl < NB) {
-        if (NB * bx + q < p) lamd[NB * bx + q] = sqrt((double)R.da) * nx;
-        if (NB * by + q < p) lamd[NB * by + q] = sqrt((double)R.db) * ny;
+      for (int c = 0; c < E; ++c)
+        dst[k][c] = at.act && (c < E - 1 || tail) ? src[k * ld + at.gl + G * c] * scale : 0.0;
+  };
+  load(W + 2 * NB * at.grp * ld, R.x);
+  load(W + (2 * NB * at.grp + NB) * ld, R.y);
+  int rev;
+  const SweepCount n = jacobi_sweeps<NT, G, NB, E, PMAX>(
+      R, at, W, lamd, rk, p, rule, ordered, mx_s, rev, [&](int col, int row, double v) { W[col * ld + row] = v; },
+      [&](int col, int row) { return W[col * ld + row]; });
+  __syncthreads();
+  if (at.busy) {
+    const ColumnNorms nm = unit_columns<G, NB, E>(R);
+    if (at.act) {
+      const BlockCols b = block_cols<G, NB>(at, rev);
+      auto store = [&](double *dst, const double (&src)[NB][E]) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+#pragma unroll
+          for (int c = 0; c < E; ++c)
+            if (c < E - 1 || tail) dst[k * ld + at.gl + G * c] = src[k][c];
+      };
+      store(W + b.x * ld, R.x);
+      store(W + b.y * ld, R.y);
+      if (at.gl < NB) {
+        if (b.x + q < p) lamd[b.x + q] = nm.x;
+        if (b.y + q < p) lamd[b.y + q] = nm.y;
       }
     }
   }
   __syncthreads();
   return n;
-}
-
-// The sweeps with as many column pieces per lane as order p needs.
-template <typename C, int G, int NB, int PE, int NCH, int NMAX>
-__device__ __forceinline__ SweepCount run_sweeps(C *W, C *scal, C scale, int p, int ld, const SweepRule &rule, double *lamd,
-                                        int *mx_s) {
-  if constexpr (NCH < NMAX) {
-    if (p > PE * G * NCH)
-      return run_sweeps<C, G, NB, PE, NCH + 1, NMAX>(W, scal, scale, p, ld, rule, lamd, mx_s);
-  }
-  return jacobi_sweeps<C, G, NB, PE, NCH>(W, scal, scale, p, ld, rule, lamd, mx_s);
 }
 
 }  // namespace

@@ -15,6 +15,7 @@
 // Reconstruction Pi = U diag(max(lam, 0)) U' and the four products of the DK
 // rule U (L o (U' T U)) U' run on the matrix cores (v_mfma 16x16x4, FP32 or
 // FP64; helpers in mma_tiles.h), on 16 x 16 output tiles, one wave per tile.
+#include <algorithm>
 #include <type_traits>
 
 #include "cosmo_internal.h"
@@ -43,45 +44,10 @@ template <typename T, int NT> __device__ inline T wg_max(T v, T *red) {
 // A p x p block in LDS is column-major; its columns are padded to whole pairs
 // of Jacobi blocks (zero columns).  The leading dimension makes the groups of
 // a wave, which work on consecutive column blocks, hit different LDS banks:
-// 4 modulo 8 doubles (8 modulo 16 for two-column blocks of 16-lane groups),
-// 8 modulo 16 floats.  Rows p to ld - 1 are zero.  Where that does not fit a
-// workgroup's LDS (float64 orders 137 to 140) ld is p.  p * ld does not
-// decrease with p.
-template <typename C, int G, int NB, int PMAX> __host__ __device__ constexpr int eig_ld(int p) {
-  if (sizeof(C) == 8 && PMAX > 128 && p > 136) return p;
-  return sizeof(C) == 8 && (NB == 4 || G == 8) ? ((p + 3) & ~7) + 4 : ((p + 7) & ~15) + 8;
-}
-
-// Two 16 x 16 tiles C1 = A B1, C2 = A B2 sharing the A operand.
-template <typename T, typename FA, typename FB1, typename FB2>
-__device__ inline void tile_mma2(int I0, int J0, int kdim, FA fa, FB1 fb1, FB2 fb2, typename Mma<T>::v4 &c1,
-                                 typename Mma<T>::v4 &c2) {
-  const int lane = threadIdx.x & 63;
-  const int r = lane & 15, kk = lane >> 4;
-  c1 = typename Mma<T>::v4{0, 0, 0, 0};
-  c2 = typename Mma<T>::v4{0, 0, 0, 0};
-  int k0 = 0;
-  for (; k0 + 16 <= kdim; k0 += 16) {
-    T a[4], b1[4], b2[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int k = k0 + 4 * u + kk;
-      a[u] = fa(I0 + r, k);
-      b1[u] = fb1(k, J0 + r);
-      b2[u] = fb2(k, J0 + r);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      c1 = Mma<T>::op(a[u], b1[u], c1);
-      c2 = Mma<T>::op(a[u], b2[u], c2);
-    }
-  }
-  for (; k0 < kdim; k0 += 4) {
-    const int k = k0 + kk;
-    const T a = fa(I0 + r, k);
-    c1 = Mma<T>::op(a, fb1(k, J0 + r), c1);
-    c2 = Mma<T>::op(a, fb2(k, J0 + r), c2);
-  }
+// 4 modulo 8 doubles (8 modulo 16 for two-column blocks of 16-lane groups).
+// Rows p to ld - 1 are zero.  p * ld does not decrease with p.
+template <int G, int NB> __host__ __device__ constexpr int eig_ld(int p) {
+  return NB == 4 || G == 8 ? ((p + 3) & ~7) + 4 : ((p + 7) & ~15) + 8;
 }
 
 // Runs comp(t) for the tiles t = wave, wave + nw, ... below ntiles and stores
@@ -110,64 +76,133 @@ __device__ inline void tile_pass(int ntiles, int wave, int nw, Fc comp, Fw wr) {
   __syncthreads();
 }
 
-struct Acc2d {
-  Mma<double>::v4 g, h;
+// What the eigensolver kernels share.  mode 0: COSMO step on the block (s+
+// and y+ rows); mode 1: projection only.  rscratch: per block 3 p^2 doubles,
+// the first p^2 for the float64 eigenvectors; a warm start reads those of the
+// previous step there (warm_read), and leaves its own (warm_write).
+template <typename T> struct EigArgs {
+  const PsdDesc *descs;
+  int32_t max_sweeps;
+  double tol;
+  int32_t mode;
+  const T *rho_hat, *vin, *sh, *y;
+  T *s_new, *y_new, *U, *lam;
+  cosmo_stats *stats;
+  int32_t refine;
+  double *rscratch;
+  int32_t warm_read, warm_write;
 };
 
-// Refinement pair tag: the lowest mantissa bit of a stored E entry marks a
-// pair on one side of the positive / non-positive split that was rotated.
-__device__ inline float pair_tag(float e, bool rotated) {
-  const unsigned int u = __float_as_uint(e);
-  return __uint_as_float(rotated ? (u | 1u) : (u & ~1u));
+// When the sweeps end (jacobi_sweeps.h).  tol is the column cosine that
+// counts as orthogonal: the caller's, or 4 eps sqrt(p) of the data's type.  A
+// refined float32 solve sweeps to a cosine of 1e-3 within max_sweeps, then on
+// until what is left is below 2e-8, a third of float32's unit roundoff.
+// Repeated eigenvalues, which float32 data hold as clusters 1e-8 wide, are
+// what sets this: with a quarter of them equal at order 138, the couplings
+// left after sweeps 7 to 11 are 1.4e-7, 1.7e-8, 3.7e-9, 1.7e-11 and 7e-15.
+template <typename T> __device__ __forceinline__ SweepRule sweep_rule(const EigArgs<T> &a, int p) {
+  const double tol = a.tol > 0.0 ? a.tol : 4.0 * (double)Unit<T>::eps * sqrt((double)p);
+  SweepRule rule{(float)(tol * tol), (float)tol, 0.f, a.max_sweeps, 0};
+  if (std::is_same<T, float>::value && a.refine > 0) {
+    const float fine = (float)fmin(a.tol > 0.0 ? a.tol : 1.0, 2e-8);
+    rule = SweepRule{fmaxf(1e-30f, 1e-4f * fine * fine), fine, 1e-6f, a.max_sweeps, 8};
+  }
+  return rule;
 }
-__device__ inline bool pair_rotated(float e) { return (__float_as_uint(e) & 1u) != 0; }
 
-// mode 0: COSMO step on the block (s+ and y+ rows); mode 1: projection only.
-// T: type of the data, C: type the sweeps run in.  Orders up to 128 of a
-// float32 plan sweep in float64: the vector units issue float64 multiply-adds
-// at the rate of (unpacked) float32 ones, a sweep costs about a quarter more
-// (LDS traffic, cross-lane moves), and the eigenpairs need no refinement
-// afterwards (245 us of 979 at order 100 when they were swept in float32).
-// Larger float32 blocks do not fit the LDS in float64: they sweep in float32
-// and are refined (below).
-//   warm: this plan's float64 eigenvectors (row-major) of the previous step
-//   (read when warm_read, written when warm_write; C = double), in the
-//   block's part of the scratch; Uprev: the same from the tape (C = float).
-template <typename T, typename C, int NT, int G, int NB, int PE, int PMAX>
-__global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ descs, int32_t max_sweeps, double tol_base,
-                                                int32_t mode, const T *__restrict__ rho_hat,
-                                                const T *__restrict__ vin, const T *__restrict__ sh,
-                                                const T *__restrict__ y, T *__restrict__ s_new,
-                                                T *__restrict__ y_new, T *__restrict__ Uout,
-                                                T *__restrict__ lamout, cosmo_stats *stats, int32_t refine,
-                                                double *__restrict__ rscratch, const T *__restrict__ Uprev,
-                                                int32_t warm_read, int32_t warm_write) {
-  constexpr bool WIDE = std::is_same<C, double>::value;   // float64 sweeps, no refinement
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  C *W = reinterpret_cast<C *>(smem_raw);
-  __shared__ C red[NT / 64];
-  __shared__ double redd[2 * (NT / 64)];
-  // eigenvalues; during the sweeps the scalars that travel with the columns
-  __shared__ double lamd[PMAX * sizeof(C) / 4];
-  __shared__ short pos_idx[PMAX + 16];
-  __shared__ short posof[WIDE ? 1 : PMAX];
-  __shared__ signed char cls[WIDE ? 1 : PMAX];
-  __shared__ int mx_s[6];
-  __shared__ int npos_s;
-  __shared__ int again_s;
+// Power of two that brings the columns of a block shifted by c to order one.
+__device__ __forceinline__ double column_scale(double c) {
+  int e = 0;
+  (void)frexp(c, &e);
+  return ldexp(1.0, e > 120 ? -120 : (e < -120 ? 120 : -e));
+}
 
-  const PsdDesc d = descs[blockIdx.x];
+// A non-finite block yields a non-finite projection (never a clipped one).
+template <typename T, int NT> __device__ inline void put_nan(const EigArgs<T> &a, const PsdDesc &d) {
   const int p = d.p;
-  const int ld = eig_ld<C, G, NB, PMAX>(p), nc = jacobi_cols<NB>(p);
+  for (int idx = threadIdx.x; idx < p * (p + 1) / 2; idx += NT) {
+    a.s_new[d.row0 + idx] = (T)NAN;
+    if (a.mode == 0) a.y_new[d.row0 + idx] = (T)NAN;
+  }
+  if (a.lam)
+    for (int i = threadIdx.x; i < p; i += NT) a.lam[d.loff + i] = (T)NAN;
+  for (int e = threadIdx.x; e < p * p; e += NT) {
+    if (a.U) a.U[d.uoff + e] = (T)NAN;
+    if (a.warm_write) a.rscratch[3 * (size_t)d.uoff + e] = NAN;
+  }
+}
+
+// svec entry (row, col), row <= col, of the projection, and the y+ row.
+template <typename T> struct PutEntry {
+  const EigArgs<T> &a;
+  int64_t row0;
+  T rh;
+  __device__ __forceinline__ PutEntry(const EigArgs<T> &args, const PsdDesc &d)
+      : a(args), row0(d.row0), rh(args.mode == 0 ? args.rho_hat[d.row0] : (T)0) {}
+  __device__ __forceinline__ void operator()(int row, int col, double val) const {
+    const int64_t idx = row0 + col * (col + 1) / 2 + row;
+    const T o = (T)((row == col) ? val : val * SQRT2);
+    a.s_new[idx] = o;
+    if (a.mode == 0) a.y_new[idx] = a.y[idx] + rh * (a.sh[idx] - o);
+  }
+};
+
+template <typename T> __device__ inline void count_sweeps(const EigArgs<T> &a, const PsdDesc &d, const SweepCount &sw) {
+  if (!a.stats) return;
+  atomicMax(&a.stats[d.inst].eig_sweeps_max, sw.sweeps);
+  atomicAdd(&a.stats[d.inst].eig_sweeps_total, sw.sweeps);
+  atomicAdd(&a.stats[d.inst].eig_solves, 1);
+  if (!sw.converged) atomicAdd(&a.stats[d.inst].eig_not_converged, 1);
+  if (sw.fine) atomicAdd(&a.stats[d.inst].eig_refine_steps_total, sw.fine);
+}
+
+// Indices of the positive eigenvalues, in order, by the first wave; the list
+// is padded to whole groups of 16 with the last column.
+__device__ inline void list_positive(const double *lamd, int p, short *pos_idx, int *npos) {
+  const int lane = threadIdx.x;
+  if (lane >= 64) return;
+  int np = 0;
+  for (int base = 0; base < p; base += 64) {
+    const int i = base + lane;
+    const bool on = i < p && lamd[i] > 0.0;
+    const unsigned long long m = __ballot(on);
+    if (on) pos_idx[np + __popcll(m & ((1ull << lane) - 1))] = (short)i;
+    np += __popcll(m);
+  }
+  if (lane < 16) pos_idx[np + lane] = (short)(p - 1);
+  if (lane == 0) *npos = np;
+}
+
+// Blocks of order up to 128: the block lies in LDS before and after the
+// sweeps.  float32 data sweep in float64 too: the vector units issue float64
+// multiply-adds at the rate of (unpacked) float32 ones, a sweep costs about a
+// quarter more (LDS traffic, cross-lane moves), and the eigenpairs need no
+// refinement afterwards (245 us of 979 at order 100 when they were swept in
+// float32).
+template <typename T, int NT, int G, int NB, int PMAX>
+__global__ __launch_bounds__(NT) void k_psd_eig(const EigArgs<T> a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double *W = reinterpret_cast<double *>(smem_raw);
+  __shared__ double red[NT / 64];
+  // eigenvalues; during the sweeps the scalars that travel with the columns
+  __shared__ __align__(16) double lamd[jacobi_cols<NB>(PMAX)];
+  __shared__ short pos_idx[PMAX + 16];
+  __shared__ int mx_s[7];
+  __shared__ int npos_s;
+
+  const PsdDesc d = a.descs[blockIdx.x];
+  const int p = d.p;
+  const int ld = eig_ld<G, NB>(p), nc = jacobi_cols<NB>(p);
   const int nrows = p * (p + 1) / 2;
-  const T *v = vin + d.row0;
+  const T *v = a.vin + d.row0;
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
   constexpr int NWv = NT / 64;
+  double *Ut = a.rscratch + 3 * (size_t)d.uoff;   // used when a warm start reads or leaves it: row-major
 
   // S = smat(v) into W (column-major, full); ||S||_F^2 = ||v||^2 (svec is
   // isometric).  Four entries in flight per thread.
-  C fro2 = 0;
+  double fro2 = 0;
   for (int base = tid; base < nrows; base += 4 * NT) {
     T val[4];
 #pragma unroll
@@ -178,9 +213,9 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
       if (idx < nrows) {
         const int j = svec_col(idx);
         const int i = idx - j * (j + 1) / 2;
-        C x = (C)val[u];
+        double x = (double)val[u];
         fro2 += x * x;
-        if (i != j) x *= (C)RSQRT2;
+        if (i != j) x *= RSQRT2;
         W[i + j * ld] = x;
         W[j + i * ld] = x;
       }
@@ -190,41 +225,29 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
     const int npad = ld - p;
     for (int e = tid; e < npad * p; e += NT) {
       const int j = e / npad;
-      W[p + (e - j * npad) + j * ld] = (C)0;
+      W[p + (e - j * npad) + j * ld] = 0.0;
     }
-    for (int e = p * ld + tid; e < nc * ld; e += NT) W[e] = (C)0;
+    for (int e = p * ld + tid; e < nc * ld; e += NT) W[e] = 0.0;
   }
-  if (tid < 6) mx_s[tid] = 0;
-  fro2 = wg_sum<C, NT>(fro2, red);   // contains barriers: W complete after this
+  if (tid < 7) mx_s[tid] = 0;
+  fro2 = wg_sum<double, NT>(fro2, red);   // contains barriers: W complete after this
   if (!isfinite((T)fro2)) {
-    // a non-finite block yields a non-finite projection (never a clipped one)
-    for (int idx = tid; idx < nrows; idx += NT) {
-      s_new[d.row0 + idx] = (T)NAN;
-      if (mode == 0) y_new[d.row0 + idx] = (T)NAN;
-    }
-    if (lamout)
-      for (int i = tid; i < p; i += NT) lamout[d.loff + i] = (T)NAN;
-    if (Uout)
-      for (int e = tid; e < p * p; e += NT) Uout[d.uoff + e] = (T)NAN;
-    if (WIDE && warm_write) {
-      double *Ut = rscratch + 3 * (size_t)d.uoff;
-      for (int e = tid; e < p * p; e += NT) Ut[e] = NAN;
-    }
+    put_nan<T, NT>(a, d);
     return;   // fro2 is the same in every thread: the whole workgroup leaves
   }
   // largest column sum of |S|: 16 lanes per column
-  C colmax = 0;
+  double colmax = 0;
   for (int j = tid / 16; j < (p + NT / 16 - 1) / (NT / 16) * (NT / 16); j += NT / 16) {
-    C a = 0;
+    double sum = 0;
     if (j < p)
-      for (int i = tid % 16; i < p; i += 16) a += fabs(W[i + j * ld]);
+      for (int i = tid % 16; i < p; i += 16) sum += fabs(W[i + j * ld]);
 #pragma unroll
-    for (int off = 8; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
-    colmax = fmax(colmax, a);
+    for (int off = 8; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    colmax = fmax(colmax, sum);
   }
-  const C inf = wg_max<C, NT>(colmax, red);
-  C c = (C)1.1 * fmin(sqrt(fro2), inf);
-  if (!(c > (C)0)) c = (C)1;
+  const double inf = wg_max<double, NT>(colmax, red);
+  double c = 1.1 * fmin(sqrt(fro2), inf);
+  if (!(c > 0.0)) c = 1;
   // Warm start: W = (S + c I) U_prev, with U_prev the eigenvectors of the same
   // block at the previous unrolled step.  One-sided Jacobi on W computes the
   // same decomposition (W = G V with V orthogonal, W'W diagonal at the end);
@@ -232,428 +255,55 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
   const int nt = (p + 15) / 16;
   constexpr int NTMAX = (PMAX + 15) / 16;
   constexpr int HOLD = (NTMAX * NTMAX + NWv - 1) / NWv;
-  if constexpr (WIDE) {
-    if (warm_read) {
-      // S is in W, so the products are held in registers until all are done
-      const double *Ut = rscratch + 3 * (size_t)d.uoff;
-      tile_pass<HOLD, true>(
-          nt * nt, wave, NWv,
-          [&](int t) {
-            const int I = t / nt, J = t % nt;
-            return tile_mma<double>(
-                I * 16, J * 16, p, [&](int i, int k) -> double { return W[min(i, ld - 1) + min(k, p - 1) * ld]; },
-                [&](int k, int j) -> double { return (k < p && j < p) ? Ut[k * p + j] : 0.0; });
-          },
-          [&](int t, const Mma<double>::v4 &acc) {
-            const int I = t / nt, J = t % nt;
-            const int col = J * 16 + (lane & 15);
+  if (a.warm_read) {
+    // S is in W, so the products are held in registers until all are done
+    tile_pass<HOLD, true>(
+        nt * nt, wave, NWv,
+        [&](int t) {
+          const int I = t / nt, J = t % nt;
+          return tile_mma<double>(
+              I * 16, J * 16, p, [&](int i, int k) -> double { return W[min(i, ld - 1) + min(k, p - 1) * ld]; },
+              [&](int k, int j) -> double { return (k < p && j < p) ? Ut[k * p + j] : 0.0; });
+        },
+        [&](int t, const Mma<double>::v4 &acc) {
+          const int I = t / nt, J = t % nt;
+          const int col = J * 16 + (lane & 15);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int row = I * 16 + Mma<double>::row(lane, e);
-              if (row < p && col < p) W[row + col * ld] = acc[e] + c * Ut[row * p + col];
-            }
-          });
-    } else {
-      for (int i = tid; i < p; i += NT) W[i + i * ld] += c;
-    }
-  } else if (Uprev) {
-    const T *Up = Uprev + d.uoff;
-    for (int t = wave; t < nt * nt; t += NT / 64) {
-      const int I = t / nt, J = t % nt;
-      const typename Mma<T>::v4 acc = tile_mma<T>(
-          I * 16, J * 16, p,
-          [&](int i, int k) -> T {
-            if (i >= p || k >= p) return (T)0;
-            const int a = i < k ? i : k, b = i < k ? k : i;
-            const T val = v[b * (b + 1) / 2 + a];
-            return a == b ? val : val * (T)RSQRT2;
-          },
-          [&](int k, int j) -> T { return (k < p && j < p) ? Up[k + j * p] : (T)0; });
-      const int col = J * 16 + (lane & 15);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int row = I * 16 + Mma<T>::row(lane, e);
-        if (row < p && col < p) W[row + col * ld] = acc[e] + c * Up[row + col * p];
-      }
-    }
+          for (int e = 0; e < 4; ++e) {
+            const int row = I * 16 + Mma<double>::row(lane, e);
+            if (row < p && col < p) W[row + col * ld] = acc[e] + c * Ut[row * p + col];
+          }
+        });
   } else {
     for (int i = tid; i < p; i += NT) W[i + i * ld] += c;
   }
 
-  // When the sweeps end (jacobi_sweeps.h).  tol is the column cosine that
-  // counts as orthogonal: the caller's, or 4 eps sqrt(p) of the data's type.
-  // A refined float32 solve in float64 sweeps to a cosine of 1e-3 within
-  // max_sweeps, then on until what is left is below 1e-11 (float32 eigenpairs
-  // would need three refinement steps for as much).
-  const double tol = tol_base > 0.0 ? tol_base : 4.0 * (double)Unit<T>::eps * sqrt((double)p);
-  SweepRule rule{(float)(tol * tol), (float)tol, 0.f, max_sweeps, 0};
-  if (WIDE && std::is_same<T, float>::value && refine > 0) {
-    const float fine = (float)fmin(tol_base > 0.0 ? tol_base : 1.0, 1e-11);
-    rule = SweepRule{fmaxf(1e-30f, 1e-4f * fine * fine), fine, 1e-6f, max_sweeps, 8};
-  }
-  int ce = 0;
-  (void)frexp((double)c, &ce);
-  const C scale = (C)ldexp(1.0, ce > 120 ? -120 : (ce < -120 ? 120 : -ce));
-  constexpr int PMIN = PMAX <= 32 ? 1 : (PMAX <= 64 ? 33 : (PMAX <= 128 ? 65 : 129));   // smallest order of the class
-  constexpr int NMIN = (PMIN + PE * G - 1) / (PE * G), NMAX = (PMAX + PE * G - 1) / (PE * G);
-  const SweepCount sw =
-      run_sweeps<C, G, NB, PE, NMIN, NMAX>(W, reinterpret_cast<C *>(lamd), scale, p, ld, rule, lamd, mx_s);
+  const double scale = column_scale(c);
+  constexpr int PMIN = PMAX <= 32 ? 1 : (PMAX <= 64 ? 33 : 65);   // smallest order of the class
+  constexpr int EMIN = (PMIN + G - 1) / G, EMAX = (PMAX + G - 1) / G;
+  const SweepCount sw = sweep_lds<NT, G, NB, EMIN, EMAX, PMAX>(W, scale, p, ld, sweep_rule(a, p), a.warm_read != 0,
+                                                                   lamd, pos_idx, mx_s);
   // eigenvalues: column norms minus the shift
-  for (int i = tid; i < p; i += NT) lamd[i] = lamd[i] / (double)scale - (double)c;
+  for (int i = tid; i < p; i += NT) lamd[i] = lamd[i] / scale - c;
   __syncthreads();
 
-  const int ntiles = nt * (nt + 1) / 2;
-  const T *yb = y + d.row0;
-  const T *shb = sh + d.row0;
-  const T rh = (mode == 0) ? rho_hat[d.row0] : (T)0;
-  // svec entry (row, col), row <= col, of the projection, and the y+ row
-  auto put = [&](int row, int col, double val) {
-    const int idx = col * (col + 1) / 2 + row;
-    const T o = (T)((row == col) ? val : val * SQRT2);
-    s_new[d.row0 + idx] = o;
-    if (mode == 0) y_new[d.row0 + idx] = yb[idx] + rh * (shb[idx] - o);
-  };
-  auto count = [&](int fine) {
-    if (stats) {
-      atomicMax(&stats[d.inst].eig_sweeps_max, sw.sweeps);
-      atomicAdd(&stats[d.inst].eig_sweeps_total, sw.sweeps);
-      atomicAdd(&stats[d.inst].eig_solves, 1);
-      if (!sw.converged) atomicAdd(&stats[d.inst].eig_not_converged, 1);
-      if (fine) atomicAdd(&stats[d.inst].eig_refine_steps_total, fine);
-    }
-  };
-  // indices of the positive eigenvalues, in order, by the first wave; the list
-  // is padded to whole groups of 16 with the last column
-  auto list_positive = [&](auto positive) {
-    if (wave == 0) {
-      int np = 0;
-      for (int base = 0; base < p; base += 64) {
-        const int i = base + lane;
-        const bool on = i < p && positive(i);
-        const unsigned long long m = __ballot(on);
-        const int at = np + __popcll(m & ((1ull << lane) - 1));
-        if (on) pos_idx[at] = (short)i;
-        if constexpr (!WIDE)
-          if (i < p) posof[i] = on ? (short)at : (short)-1;
-        np += __popcll(m);
-      }
-      if (lane < 16) pos_idx[np + lane] = (short)(p - 1);
-      if (lane == 0) npos_s = np;
-    }
-  };
-
-  if constexpr (!WIDE) {
-    if (refine > 0) {
-      // Refinement of the float32 eigenpairs (after Ogita & Aishima,
-      // "Iterative refinement for symmetric eigenvalue decomposition", 2018)
-      // with float64-accumulated residual products, then the projection by
-      // Rayleigh-Ritz on the positive subspace.  One step, with X the current
-      // eigenvectors and lam~ the current eigenvalues:
-      //   D = S X - X diag(lam~)                       (small; stored in float32)
-      //   R = I - X'X,  S~ = X'S X = (X'X) diag(lam~) + X'D,  lam_i = S~_ii / (1 - R_ii)
-      //   a pair (i, j) is resolvable when its gap exceeds
-      //          delta = 2 (||S~ - diag(lam)||_F + ||S||_F ||R||_F) and its
-      //          coupling-to-gap ratio th = cpl / gap is at most 0.1;
-      //   E_ij = (S~_ij + lam_j R_ij) / (lam_j - lam_i)  for rotated pairs,
-      //   E_ij = R_ij / 2 otherwise (re-orthogonalisation only)
-      //   X <- X + X E.
-      // Every resolvable pair is rotated, on either side of the split: the
-      // projection needs only the positive subspace, but the Daleckii-Krein
-      // weights of a pair across the split depend on the individual
-      // eigenvalues on each side, so the taped eigenvectors must be
-      // eigenvectors, not just a basis of the right subspace.  A step is the
-      // last when every resolvable pair's second-order remainder
-      // th^2 max|lam| is below 1e-7 ||S||_F (else another step follows: the
-      // remainders shrink quadratically), at most REFINE_STEPS steps.  In the
-      // last step only pairs that meet that bound rotate; the others are
-      // re-orthogonalised and the projection's middle factor absorbs their
-      // coupling:
-      //   Pi = X+ M X+',  M = X+' S X+ to first order in E:
-      //          M_ii = lam_i,  M_ij = 0 for rotated pairs,
-      //          M_ij = S~_ij + (lam_i + lam_j) R_ij / 2 otherwise.
-      // E + E' = R entry by entry keeps X orthonormal to second order.  Only
-      // D and the products building S~ and R need float64 accumulation; the
-      // correction X E is small and runs in float32.
-      //
-      // Storage of a pair i < j in the p x p buffer SR: slot (j, i) holds
-      // E_ji.  Slot (i, j) holds E_ij when the pair rotates, else (pairs on
-      // one side of the split) M_ij; for pairs on one side the lowest
-      // mantissa bit of slot (j, i) says which (1: rotated, then M_ij = 0).
-      // One unit in the last place of E is far below what E corrects.
-      constexpr int REFINE_STEPS = 3;
-      float *Db = reinterpret_cast<float *>(rscratch + 3 * (size_t)d.uoff);
-      float *SR = Db + p * ld;   // S~ (upper) and R (lower), then E and M
-      auto Sget = [&](int i, int k) -> double {
-        const int a = i < k ? i : k, b = i < k ? k : i;
-        const double val = (double)v[b * (b + 1) / 2 + a];
-        return a == b ? val : val * RSQRT2;
-      };
-      const double thr2 = 1e-7 * sqrt((double)fro2);
-      // This block's part of the refinement scratch (3 p^2 doubles) beyond D,
-      // S~ and R: the refined eigenvalues of a step (float64), then L+ and C
-      // of the projection (below).
-      double *xs = rscratch + 3 * (size_t)d.uoff + (size_t)p * ld;
-      // E_kj from the pair storage (see above)
-      auto Eget = [&](int k, int j) -> float {
-        if (k >= j || cls[k] * cls[j] < 0) return SR[k + j * ld];
-        const float low = SR[j + k * ld];
-        return pair_rotated(low) ? SR[k + j * ld] : low;
-      };
-      const int wave_o = wave, lane_o = lane;
-      int rsteps = 0;
-#pragma nounroll
-      for (int rstep = 0; rstep < REFINE_STEPS; ++rstep) {
-        // The wave and lane numbers are re-read opaquely in every step so
-        // that the compiler does not hoist each tile's addresses out of the
-        // loop (which exhausts the registers).
-        int wave = wave_o, lane = lane_o;
-        asm volatile("" : "+v"(wave), "+v"(lane));
-        const bool last_allowed = rstep == REFINE_STEPS - 1;
-        // D = S X - X diag(lam~)
-        tile_pass<HOLD, false>(
-            nt * nt, wave, NWv,
-            [&](int t) {
-              const int I = t / nt, J = t % nt;
-              return tile_mma<double>(
-                  I * 16, J * 16, p, [&](int i, int k) -> double { return (i < p && k < p) ? Sget(i, k) : 0.0; },
-                  [&](int k, int j) -> double { return (k < p && j < p) ? (double)W[k + j * ld] : 0.0; });
-            },
-            [&](int t, const Mma<double>::v4 &acc) {
-              const int I = t / nt, J = t % nt;
-              const int col = J * 16 + (lane & 15);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const int row = I * 16 + Mma<double>::row(lane, e);
-                if (row < p && col < p) Db[row + col * ld] = (float)(acc[e] - (double)W[row + col * ld] * lamd[col]);
-              }
-            });
-        // S~ into the upper triangle, R into the lower, lam_i on the diagonal
-        double nS = 0, nR = 0;
-        tile_pass<1, false>(
-            ntiles, wave, NWv,
-            [&](int t) {
-              int I, J;
-              upper_tile(t, I, J);
-              Acc2d a;
-              tile_mma2<double>(
-                  I * 16, J * 16, p,
-                  [&](int i, int k) -> double { return (i < p && k < p) ? (double)W[k + i * ld] : 0.0; },
-                  [&](int k, int j) -> double { return (k < p && j < p) ? (double)W[k + j * ld] : 0.0; },
-                  [&](int k, int j) -> double { return (k < p && j < p) ? (double)Db[k + j * ld] : 0.0; }, a.g, a.h);
-              return a;
-            },
-            [&](int t, const Acc2d &a) {
-              int I, J;
-              upper_tile(t, I, J);
-              const int col = J * 16 + (lane & 15);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const int row = I * 16 + Mma<double>::row(lane, e);
-                if (row <= col && col < p) {
-                  const double st = a.h[e] + a.g[e] * lamd[col];
-                  if (row < col) {
-                    const double r = -a.g[e];
-                    SR[row + col * ld] = (float)st;
-                    SR[col + row * ld] = (float)r;
-                    nS += 2.0 * st * st;
-                    nR += 2.0 * r * r;
-                  } else {
-                    const double lam = a.g[e] > 0.0 ? st / a.g[e] : 0.0;
-                    const double r = 1.0 - a.g[e];
-                    xs[row] = lam;   // kept in float64
-                    nS += (st - lam) * (st - lam);
-                    nR += r * r;
-                  }
-                }
-              }
-            });
-        for (int off = 32; off > 0; off >>= 1) {
-          nS += __shfl_xor(nS, off, 64);
-          nR += __shfl_xor(nR, off, 64);
-        }
-        if (lane == 0) {
-          redd[wave] = nS;
-          redd[NWv + wave] = nR;
-        }
-        if (tid == 0) again_s = 0;
-        // refined eigenvalues, their signs, and E_ii = R_ii / 2 on the diagonal
-        for (int i = tid; i < p; i += NT) {
-          const double lam = xs[i];
-          double g = 0;
-          for (int k = 0; k < p; ++k) {
-            const double x = (double)W[k + i * ld];
-            g += x * x;
-          }
-          lamd[i] = lam;
-          cls[i] = lam > 0.0 ? 1 : (lam < 0.0 ? -1 : 0);
-          SR[i + i * ld] = (float)(0.5 * (1.0 - g));
-        }
-        __syncthreads();
-        double ts = 0, tr = 0;
-        for (int w = 0; w < NWv; ++w) {
-          ts += redd[w];
-          tr += redd[NWv + w];
-        }
-        const double delta = 2.0 * (sqrt(ts) + sqrt((double)fro2) * sqrt(tr));
-        // Pairs i < j: which rotate in this step if it is not the last, and
-        // whether any of them leaves a remainder above the bound (then this
-        // step is not the last).
-        int more = 0;
-        for (int e = tid; e < p * p; e += NT) {
-          const int j = e / p, i = e - j * p;
-          if (i >= j) continue;
-          const double s = (double)SR[i + j * ld], r = (double)SR[j + i * ld];
-          const double li = lamd[i], lj = lamd[j];
-          const double gap = lj - li;
-          const double th = (fabs(s) + fmax(fabs(li), fabs(lj)) * fabs(r)) / fabs(gap);
-          if (fabs(gap) > delta && th <= 0.1 && th * th * fmax(fabs(li), fabs(lj)) > thr2) more = 1;
-        }
-        if (more) again_s = 1;
-        __syncthreads();
-        const bool last = last_allowed || again_s == 0;
-        for (int e = tid; e < p * p; e += NT) {
-          const int j = e / p, i = e - j * p;
-          if (i >= j) continue;
-          const double s = (double)SR[i + j * ld], r = (double)SR[j + i * ld];
-          const double li = lamd[i], lj = lamd[j];
-          const double gap = lj - li;
-          const double th = (fabs(s) + fmax(fabs(li), fabs(lj)) * fabs(r)) / fabs(gap);
-          const bool ok = fabs(gap) > delta && th <= 0.1;
-          const bool fin = th * th * fmax(fabs(li), fabs(lj)) <= thr2;
-          const bool rot = ok && (fin || !last);
-          const float eij = (float)(rot ? (s + lj * r) / gap : 0.5 * r);
-          const float eji = (float)(rot ? (s + li * r) / (-gap) : 0.5 * r);
-          if (li * lj < 0.0) {
-            SR[i + j * ld] = eij;
-            SR[j + i * ld] = eji;
-          } else {
-            SR[i + j * ld] = rot ? eij : (float)(s + 0.5 * (li + lj) * r);
-            SR[j + i * ld] = pair_tag(eji, rot);
-          }
-        }
-        __syncthreads();
-        rsteps = rstep + 1;
-        if (last) break;
-        // X <- X + X E, in place in W (the last step's correction is kept apart, below)
-        tile_pass<HOLD, true>(
-            nt * nt, wave, NWv,
-            [&](int t) {
-              const int I = t / nt, J = t % nt;
-              return tile_mma<float>(
-                  I * 16, J * 16, p, [&](int i, int k) -> float { return (i < p && k < p) ? W[i + k * ld] : 0.f; },
-                  [&](int k, int j) -> float { return (k < p && j < p) ? Eget(k, j) : 0.f; });
-            },
-            [&](int t, const Mma<float>::v4 &acc) {
-              const int I = t / nt, J = t % nt;
-              const int col = J * 16 + (lane & 15);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const int row = I * 16 + Mma<float>::row(lane, e);
-                if (row < p && col < p) W[row + col * ld] += acc[e];
-              }
-            });
-      }
-      if (lamout)
-        for (int i = tid; i < p; i += NT) lamout[d.loff + i] = (float)lamd[i];
-      list_positive([&](int i) { return cls[i] > 0; });
-      if (tid == 0) count(rsteps);
-      __syncthreads();
-      const int npos = npos_s;
-      const int ntp = (npos + 15) / 16;
-      // The last step's correction L = X E is not rounded into X: the
-      // refined eigenvectors are X + L with both parts float32 (their sum is
-      // carried to about twice the float32 precision), and the projection is
-      // formed from them with float64 products,
-      //   C = (X+ + L+) M,   Pi = C (X+ + L+)',
-      // so its accuracy is that of the refinement, not that of float32
-      // eigenvectors.  The taped eigenvectors are X + L rounded to float32.
-      // L+ (p x npos, float32) and C (p x npos, float64) live in this
-      // block's part of the refinement scratch (xs).
-      float *Lg = reinterpret_cast<float *>(xs);
-      double *Cg = xs + ((size_t)p * npos + 1) / 2;
-      tile_pass<HOLD, false>(
-          nt * nt, wave, NWv,
-          [&](int t) {
-            const int I = t / nt, J = t % nt;
-            return tile_mma<float>(
-                I * 16, J * 16, p, [&](int i, int k) -> float { return (i < p && k < p) ? W[i + k * ld] : 0.f; },
-                [&](int k, int j) -> float { return (k < p && j < p) ? Eget(k, j) : 0.f; });
-          },
-          [&](int t, const Mma<float>::v4 &acc) {
-            const int I = t / nt, J = t % nt;
-            const int col = J * 16 + (lane & 15);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int row = I * 16 + Mma<float>::row(lane, e);
-              if (row < p && col < p) {
-                if (Uout) Uout[d.uoff + row + col * p] = W[row + col * ld] + acc[e];
-                const int q = posof[col];
-                if (q >= 0) Lg[row + q * p] = acc[e];
-              }
-            }
-          });
-      // M on the positive pairs: lam_i (float64) on the diagonal
-      auto Mget = [&](int a, int b) -> double {
-        if (a == b) return lamd[a];
-        const int lo = a < b ? a : b, hi = a < b ? b : a;
-        return pair_rotated(SR[hi + lo * ld]) ? 0.0 : (double)SR[lo + hi * ld];
-      };
-      auto Xp = [&](int i, int k) -> double { return (double)W[i + pos_idx[k] * ld] + (double)Lg[i + k * p]; };
-      // C = (X+ + L+) M  (p x npos)
-      tile_pass<HOLD, false>(
-          nt * ntp, wave, NWv,
-          [&](int t) {
-            const int I = t / ntp, J = t % ntp;
-            return tile_mma<double>(
-                I * 16, J * 16, npos, [&](int i, int k) -> double { return (i < p && k < npos) ? Xp(i, k) : 0.0; },
-                [&](int k, int j) -> double { return (k < npos && j < npos) ? Mget(pos_idx[k], pos_idx[j]) : 0.0; });
-          },
-          [&](int t, const Mma<double>::v4 &acc) {
-            const int I = t / ntp, J = t % ntp;
-            const int col = J * 16 + (lane & 15);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int row = I * 16 + Mma<double>::row(lane, e);
-              if (row < p && col < npos) Cg[row + col * p] = acc[e];
-            }
-          });
-      // Pi = C (X+ + L+)', upper-triangle tiles
-      for (int t = wave; t < ntiles; t += NWv) {
-        int I, J;
-        upper_tile(t, I, J);
-        const Mma<double>::v4 acc = tile_mma<double>(
-            I * 16, J * 16, npos, [&](int i, int k) -> double { return (i < p && k < npos) ? Cg[i + k * p] : 0.0; },
-            [&](int k, int j) -> double { return (j < p && k < npos) ? Xp(j, k) : 0.0; });
-        const int col = J * 16 + (lane & 15);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int row = I * 16 + Mma<double>::row(lane, e);
-          if (row <= col && col < p) put(row, col, acc[e]);
-        }
-      }
-      return;
-    }
-  }
-
   // Pi = sum_{lam_k > 0} lam_k u_k u_k' (upper-triangle tiles)
-  if (lamout)
-    for (int i = tid; i < p; i += NT) lamout[d.loff + i] = (T)lamd[i];
-  if (Uout)
+  const int ntiles = nt * (nt + 1) / 2;
+  const PutEntry<T> put(a, d);
+  if (a.lam)
+    for (int i = tid; i < p; i += NT) a.lam[d.loff + i] = (T)lamd[i];
+  if (a.U)
     for (int e = tid; e < p * p; e += NT) {
       const int j = e / p, i = e - j * p;
-      Uout[d.uoff + e] = (T)W[i + j * ld];
+      a.U[d.uoff + e] = (T)W[i + j * ld];
     }
-  if constexpr (WIDE) {
-    if (warm_write) {
-      double *Ut = rscratch + 3 * (size_t)d.uoff;
-      for (int e = tid; e < p * p; e += NT) {
-        const int i = e / p, j = e - i * p;
-        Ut[e] = W[i + j * ld];
-      }
+  if (a.warm_write)
+    for (int e = tid; e < p * p; e += NT) {
+      const int i = e / p, j = e - i * p;
+      Ut[e] = W[i + j * ld];
     }
-  }
-  list_positive([&](int i) { return lamd[i] > 0.0; });
-  if (tid == 0) count(sw.fine);
+  list_positive(lamd, p, pos_idx, &npos_s);
+  if (tid == 0) count_sweeps(a, d, sw);
   __syncthreads();
   const int npos = npos_s;
   for (int t = wave; t < ntiles; t += NWv) {
@@ -661,20 +311,242 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const PsdDesc *__restrict__ desc
     upper_tile(t, I, J);
     // rows past the block's end read the padding or its last row: only
     // entries of the result that are not stored depend on them
-    const typename Mma<C>::v4 acc = tile_mma<C>(
+    const Mma<double>::v4 acc = tile_mma<double>(
         I * 16, J * 16, npos,
-        [&](int i, int k) -> C {
+        [&](int i, int k) -> double {
           const int c2 = pos_idx[k];
-          return W[min(i, ld - 1) + c2 * ld] * (k < npos ? (C)lamd[c2] : (C)0);
+          return W[min(i, ld - 1) + c2 * ld] * (k < npos ? lamd[c2] : 0.0);
         },
-        [&](int k, int j) -> C { return W[min(j, ld - 1) + pos_idx[k] * ld]; });
+        [&](int k, int j) -> double { return W[min(j, ld - 1) + pos_idx[k] * ld]; });
     const int col = J * 16 + (lane & 15);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int row = I * 16 + Mma<C>::row(lane, e);
-      if (row <= col && col < p) put(row, col, (double)acc[e]);
+      const int row = I * 16 + Mma<double>::row(lane, e);
+      if (row <= col && col < p) put(row, col, acc[e]);
     }
   }
+}
+
+// Blocks of order above 128 (float32 to 200, float64 to 140).  In float64
+// such a block does not fit the LDS, but it fits the registers of seven waves
+// (sixteen lanes and eight columns to a group, 16 E rows, 4 E doubles a lane
+// for each of X and Y: 208 registers of 256 at E = 13), and the sweeps need
+// LDS only for the half of it that moves.  Before the sweeps LDS holds the
+// svec entries of S as they came, in the data's own type (off the diagonal
+// S is 1 / sqrt(2) times them, formed in float64 where they are used); after them the eigenvectors go to the scratch,
+// column-major, and the products read them from the L2.  The warm start's
+// product lands in the registers that the sweeps want it in: result rows of
+// the matrix cores' 16 x 16 x 4 are the columns of one block of the four
+// groups of a wave, result columns the sixteen lanes of a group.
+// Sixteen float32 blocks of orders 129 to 200: 2.1 ms; float32 sweeps with an
+// Ogita-Aishima refinement of the eigenpairs in float64 products (two to
+// three passes over global scratch, about 515 us each at order 200) took 3.6.
+constexpr int LARGE_NT = 448;
+
+// LDS elements in the data's type: S, its leading dimension a multiple of four.
+__host__ __device__ constexpr int large_ld(int p) { return (p + 3) & ~3; }
+
+template <typename T, int E, int PMAX>
+__device__ __forceinline__ void eig_large(const EigArgs<T> &a, const PsdDesc &d, unsigned char *smem, double *lamd,
+                                          short *pos_idx, double *red, int *mx_s, int *npos_s) {
+  constexpr int G = 16, NB = 4, NT = LARGE_NT;
+  typedef Mma<double>::v4 v4;
+  const int p = d.p, ld = large_ld(p);
+  const int nrows = p * (p + 1) / 2;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, kk = lane >> 4;
+  T *S = reinterpret_cast<T *>(smem);
+  double *Ut = a.rscratch + 3 * (size_t)d.uoff;   // eigenvectors, column-major
+  const T *v = a.vin + d.row0;
+
+  double fro2 = 0;
+  for (int base = tid; base < nrows; base += 4 * NT) {
+    T val[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) val[u] = v[min(base + u * NT, nrows - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int idx = base + u * NT;
+      if (idx < nrows) {
+        const int j = svec_col(idx);
+        const int i = idx - j * (j + 1) / 2;
+        const double x = (double)val[u];
+        fro2 += x * x;
+        S[i + j * ld] = val[u];
+        S[j + i * ld] = val[u];
+      }
+    }
+  }
+  for (int j = tid; j < p; j += NT)
+    for (int i = p; i < ld; ++i) S[i + j * ld] = (T)0;
+  if (tid < 7) mx_s[tid] = 0;
+  fro2 = wg_sum<double, NT>(fro2, red);   // contains barriers: S complete after this
+  if (!isfinite((T)fro2)) {
+    put_nan<T, NT>(a, d);
+    return;   // the same in every thread
+  }
+  double colmax = 0;
+  for (int j = tid / 16; j < (p + NT / 16 - 1) / (NT / 16) * (NT / 16); j += NT / 16) {
+    double sum = 0;
+    if (j < p)
+      for (int i = r; i < p; i += 16) sum += fabs((double)S[i + j * ld]) * (i == j ? 1.0 : RSQRT2);
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    colmax = fmax(colmax, sum);
+  }
+  const double inf = wg_max<double, NT>(colmax, red);
+  double c = 1.1 * fmin(sqrt(fro2), inf);
+  if (!(c > 0.0)) c = 1;
+  const double scale = column_scale(c);
+
+  const JacobiPlace<G, NB> at(p);
+  JacobiRegs<NB, E> R;
+  const bool tail = G * (E - 1) + r < p;
+  if (a.warm_read) {
+    // columns col0 .. col0 + 3 of (S + c I) U: operand row m = g + 4 e is
+    // column e of group g's block
+    auto product = [&](int side, double (&dst)[NB][E]) {
+      const int mcol = 2 * NB * (4 * wave + (r & 3)) + NB * side + (r >> 2);   // column of operand row r
+      const bool in = mcol < p;
+      const double *u = Ut + (size_t)min(mcol, p - 1) * p;
+      v4 acc[E];
+#pragma unroll
+      for (int t = 0; t < E; ++t) acc[t] = v4{0, 0, 0, 0};
+      for (int k0 = 0; k0 < p; k0 += 16) {
+        // lane quarter kk takes the k's k0 + 4 kk .. + 3, one per product
+        const int k = k0 + 4 * kk, ks = min(k, ld - 4);
+        double uk[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) uk[w] = in && k + w < p ? u[min(k + w, p - 1)] : 0.0;
+#pragma unroll
+        for (int t = 0; t < E; ++t) {
+          const T *sc = S + min(16 * t + r, p - 1) * ld + ks;
+          T sv[4];
+#pragma unroll
+          for (int w = 0; w < 4; ++w) sv[w] = sc[w];
+#pragma unroll
+          for (int w = 0; w < 4; ++w) acc[t] = Mma<double>::op(uk[w], (double)sv[w], acc[t]);
+        }
+      }
+      const int col0 = 2 * NB * at.grp + NB * side;
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+#pragma unroll
+        for (int t = 0; t < E; ++t) {
+          const int row = 16 * t + r, col = col0 + k;
+          const bool on = row < p && col < p;
+          const double uu = Ut[(on ? row : 0) + (size_t)(on ? col : 0) * p];
+          // S = svec entries / sqrt(2) + (1 - 1 / sqrt(2)) diagonal
+          const double dc = fma(1.0 - RSQRT2, (double)S[(on ? row : 0) * (ld + 1)], c);
+          dst[k][t] = on ? fma(RSQRT2, acc[t][k], dc * uu) * scale : 0.0;
+        }
+    };
+    product(0, R.x);
+    product(1, R.y);
+  } else {
+    auto column = [&](int col0, double (&dst)[NB][E]) {
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+#pragma unroll
+        for (int t = 0; t < E; ++t) {
+          const int row = 16 * t + r, col = col0 + k;
+          const bool on = row < p && col < p;
+          const double x = (double)S[(on ? row : 0) + (on ? col : 0) * ld];
+          dst[k][t] = on ? (row == col ? x + c : x * RSQRT2) * scale : 0.0;
+        }
+    };
+    column(2 * NB * at.grp, R.x);
+    column(2 * NB * at.grp + NB, R.y);
+  }
+  int rev;
+  __syncthreads();   // S and the previous eigenvectors have been read
+  double *order = Ut + p * p;   // the columns, on their way to their order
+  const SweepCount sw = jacobi_sweeps<NT, G, NB, E, PMAX>(
+      R, at, reinterpret_cast<double *>(smem), lamd, pos_idx, p, sweep_rule(a, p), a.warm_read != 0, mx_s, rev,
+      [&](int col, int row, double x) {
+        if (col < p) order[col * p + row] = x;
+      },
+      [&](int col, int row) { return col < p ? order[col * p + row] : 0.0; });
+  __syncthreads();
+  if (at.busy) {
+    const ColumnNorms nm = unit_columns<G, NB, E>(R);
+    if (at.act) {
+      const BlockCols b = block_cols<G, NB>(at, rev);
+      auto store = [&](int col0, const double (&src)[NB][E]) {
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+          if (col0 + k < p)
+#pragma unroll
+            for (int t = 0; t < E; ++t)
+              if (t < E - 1 || tail) {
+                const size_t e = (size_t)(col0 + k) * p + 16 * t + r;
+                Ut[e] = src[k][t];
+                if (a.U) a.U[d.uoff + e] = (T)src[k][t];
+              }
+      };
+      store(b.x, R.x);
+      store(b.y, R.y);
+      if (r < NB) {
+        if (b.x + r < p) lamd[b.x + r] = nm.x / scale - c;
+        if (b.y + r < p) lamd[b.y + r] = nm.y / scale - c;
+      }
+    }
+  }
+  __syncthreads();
+  if (a.lam)
+    for (int i = tid; i < p; i += NT) a.lam[d.loff + i] = (T)lamd[i];
+  list_positive(lamd, p, pos_idx, npos_s);
+  if (tid == 0) count_sweeps(a, d, sw);
+  __syncthreads();
+  // Pi = sum_{lam_k > 0} lam_k u_k u_k': a wave takes the row strips wave and
+  // E - 1 - wave, E + 1 upper-triangle tiles together
+  const int npos = *npos_s;
+  const PutEntry<T> put(a, d);
+  for (int h = 0; h < 2; ++h) {
+    const int I = h == 0 ? wave : E - 1 - wave;
+    if (h == 0 ? 2 * wave > E - 1 : 2 * wave >= E - 1) break;
+    v4 acc[E];
+#pragma unroll
+    for (int t = 0; t < E; ++t) acc[t] = v4{0, 0, 0, 0};
+    for (int k0 = 0; k0 < npos; k0 += 4) {
+      const int k = pos_idx[k0 + kk];
+      const double *u = Ut + (size_t)k * p;
+      const double ai = u[min(16 * I + r, p - 1)] * (k0 + kk < npos ? lamd[k] : 0.0);
+#pragma unroll
+      for (int t = 0; t < E; ++t)
+        if (t >= I) acc[t] = Mma<double>::op(ai, u[min(16 * t + r, p - 1)], acc[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < E; ++t)
+      if (t >= I) {
+        const int col = 16 * t + r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int row = 16 * I + Mma<double>::row(lane, e);
+          if (row <= col && col < p) put(row, col, acc[t][e]);
+        }
+      }
+  }
+}
+
+template <typename T, int E, int PMAX>
+__device__ __forceinline__ void eig_large_by_order(const EigArgs<T> &a, const PsdDesc &d, unsigned char *smem,
+                                                   double *lamd, short *pos_idx, double *red, int *mx_s, int *npos_s) {
+  if constexpr (16 * E < PMAX) {
+    if (d.p > 16 * E) return eig_large_by_order<T, E + 1, PMAX>(a, d, smem, lamd, pos_idx, red, mx_s, npos_s);
+  }
+  eig_large<T, E, PMAX>(a, d, smem, lamd, pos_idx, red, mx_s, npos_s);
+}
+
+template <typename T, int PMAX>
+__global__ __launch_bounds__(LARGE_NT) void k_psd_eig_large(const EigArgs<T> a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ double red[LARGE_NT / 64];
+  __shared__ __align__(16) double lamd[jacobi_cols<4>(PMAX)];   // eigenvalues; the moving scalars during the sweeps
+  __shared__ short pos_idx[PMAX + 16];
+  __shared__ int mx_s[7];
+  __shared__ int npos_s;
+  const PsdDesc d = a.descs[blockIdx.x];
+  eig_large_by_order<T, 9, PMAX>(a, d, smem_raw, lamd, pos_idx, red, mx_s, &npos_s);
 }
 
 // Leading dimension of the DK VJP's LDS buffers: the smallest stride >= p
@@ -834,20 +706,36 @@ size_t set_dyn_lds_cap(const void *fn) {
   return LDS_LIMIT - stat;
 }
 
-template <typename T, typename C, int NT, int G, int NB, int PE, int PMAX>
-void run_eig(const PsdDesc *d, int32_t n, int32_t max_p, const PsdLaunchCfg &cfg, int32_t mode, const T *rho_hat,
-             const T *vv, const T *sh, const T *y, T *s_new, T *y_new, T *U, T *lam, cosmo_stats *stats,
-             double *rscratch, const T *Uprev, hipStream_t st) {
-  const int refine = (std::is_same<T, float>::value && rscratch) ? cfg.refine : 0;
-  const size_t dyn = (size_t)jacobi_cols<NB>(max_p) * (size_t)eig_ld<C, G, NB, PMAX>(max_p) * sizeof(C);
+// Elements of the exchange buffer for a launch whose largest order is p.
+template <int G, int NB, int E, int EMAX, int PMAX> constexpr int exchange_elems(int p) {
+  if constexpr (E < EMAX) {
+    if (p > G * E) return exchange_elems<G, NB, E + 1, EMAX, PMAX>(p);
+  }
+  return Exchange<G, NB, E, PMAX>::elems;
+}
+
+template <typename T, int NT, int G, int NB, int PMAX>
+void run_eig(const EigArgs<T> &a, int32_t n, int32_t max_p, hipStream_t st) {
+  const size_t block = (size_t)jacobi_cols<NB>(max_p) * (size_t)eig_ld<G, NB>(max_p);
+  const size_t exch = (size_t)exchange_elems<G, NB, 1, (PMAX + G - 1) / G, PMAX>(max_p);
   static bool attr_set = false;
   if (!attr_set) {
-    set_dyn_lds_cap(reinterpret_cast<const void *>(&k_psd_eig<T, C, NT, G, NB, PE, PMAX>));
+    set_dyn_lds_cap(reinterpret_cast<const void *>(&k_psd_eig<T, NT, G, NB, PMAX>));
     attr_set = true;
   }
-  k_psd_eig<T, C, NT, G, NB, PE, PMAX><<<n, NT, dyn, st>>>(
-      d, cfg.max_sweeps, cfg.tol, mode, rho_hat, vv, sh, y, s_new, y_new, U, lam, stats, refine, rscratch, Uprev,
-      Uprev && rscratch ? 1 : 0, cfg.keep_warm && rscratch ? 1 : 0);
+  k_psd_eig<T, NT, G, NB, PMAX><<<n, NT, std::max(block, exch) * sizeof(double), st>>>(a);
+}
+
+template <typename T, int PMAX>
+void run_eig_large(const EigArgs<T> &a, int32_t n, int32_t max_p, hipStream_t st) {
+  const size_t block = (size_t)max_p * large_ld(max_p) * sizeof(T);
+  const size_t exch = (size_t)exchange_elems<16, 4, 9, (PMAX + 15) / 16, PMAX>(max_p) * sizeof(double);
+  static bool attr_set = false;
+  if (!attr_set) {
+    set_dyn_lds_cap(reinterpret_cast<const void *>(&k_psd_eig_large<T, PMAX>));
+    attr_set = true;
+  }
+  k_psd_eig_large<T, PMAX><<<n, LARGE_NT, std::max(block, exch), st>>>(a);
 }
 
 }  // namespace
@@ -857,34 +745,31 @@ void run_eig(const PsdDesc *d, int32_t n, int32_t max_p, const PsdLaunchCfg &cfg
 // columns per block while that fills at most one wave per SIMD (a sweep is
 // then its ~p dependent steps, each as short as its rows are spread); four
 // above order 64, where the exchange of blocks between the groups costs as
-// much as the rotations (order 100: 51 us per sweep against 64 us with two).
+// much as the rotations (order 100: 55 us per sweep against 64 us with two).
+// The largest class's configuration is named by kEigThreads[3]; it has no
+// other, and runs seven waves (above).
 template <typename T>
 void launch_psd_step(const PsdDesc *d, int32_t n, const PsdLaunchCfg &cfg, const T *rho_hat, const T *vv,
                      const T *sh, const T *y, T *s_new, T *y_new, T *U, T *lam, double *rscratch,
                      const T *Uprev, cosmo_stats *stats, hipStream_t st) {
   if (n <= 0) return;
-  const int mode = (y_new != nullptr) ? 0 : 1;
   const int mp = cfg.max_p;
   const int cls = mp <= 32 ? 0 : mp <= 64 ? 1 : mp <= 128 ? 2 : 3;
   const bool alt = cfg.threads != 0 && cfg.threads == kEigThreadsAlt[cls] && cfg.threads != kEigThreads[cls];
-#define COSMO_EIG(C_, NT_, G_, NB_, PE_, PMAX_)                                                                 \
-  run_eig<T, C_, NT_, G_, NB_, PE_, PMAX_>(d, n, mp, cfg, mode, rho_hat, vv, sh, y, s_new, y_new, U, lam, stats, \
-                                           rscratch, Uprev, st)
+  const EigArgs<T> a{d, cfg.max_sweeps, cfg.tol, y_new != nullptr ? 0 : 1, rho_hat, vv, sh, y, s_new, y_new, U, lam,
+                     stats, cfg.refine, rscratch, Uprev && rscratch ? 1 : 0, cfg.keep_warm && rscratch ? 1 : 0};
   static_assert(kEigThreads[0] == 64 && kEigThreads[1] == 256 && kEigThreads[2] == 512 && kEigThreads[3] == 1024,
                 "class defaults");
   static_assert(kEigThreadsAlt[0] == 128 && kEigThreadsAlt[1] == 512 && kEigThreadsAlt[2] == 1024, "class alternatives");
   if (cls == 0) {
-    if (alt) COSMO_EIG(double, 128, 16, 2, 1, 32); else COSMO_EIG(double, 64, 8, 2, 1, 32);
+    if (alt) run_eig<T, 128, 16, 2, 32>(a, n, mp, st); else run_eig<T, 64, 8, 2, 32>(a, n, mp, st);
   } else if (cls == 1) {
-    if (alt) COSMO_EIG(double, 512, 16, 2, 1, 64); else COSMO_EIG(double, 256, 16, 2, 1, 64);
+    if (alt) run_eig<T, 512, 16, 2, 64>(a, n, mp, st); else run_eig<T, 256, 16, 2, 64>(a, n, mp, st);
   } else if (cls == 2) {
-    if (alt) COSMO_EIG(double, 1024, 16, 2, 1, 128); else COSMO_EIG(double, 512, 16, 4, 1, 128);
-  } else if constexpr (std::is_same<T, float>::value) {
-    COSMO_EIG(float, 1024, 16, 2, 2, COSMO_MAX_PSD_ORDER_F32);
+    if (alt) run_eig<T, 1024, 16, 2, 128>(a, n, mp, st); else run_eig<T, 512, 16, 4, 128>(a, n, mp, st);
   } else {
-    COSMO_EIG(double, 1024, 16, 2, 1, COSMO_MAX_PSD_ORDER_F64);
+    run_eig_large<T, std::is_same<T, float>::value ? COSMO_MAX_PSD_ORDER_F32 : COSMO_MAX_PSD_ORDER_F64>(a, n, mp, st);
   }
-#undef COSMO_EIG
 }
 
 // 16 waves by default: a block of order ~100 has 49 output tiles per

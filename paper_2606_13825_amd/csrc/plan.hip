@@ -2221,7 +2221,7 @@ cosmo_status psd_proj(int32_t nblk, const int32_t *order, const int64_t *offset,
                              (float *)eigvecs, (float *)eigvals, rs, nullptr, nullptr, st);
     else
       launch_psd_step<double>(d + cb[c], n, cfg, nullptr, (const double *)in, nullptr, nullptr, (double *)out,
-                              nullptr, (double *)eigvecs, (double *)eigvals, nullptr, nullptr, nullptr, st);
+                              nullptr, (double *)eigvecs, (double *)eigvals, rs, nullptr, nullptr, st);
   }
   HIPCHK(hipGetLastError());
   return COSMO_OK;
