@@ -2,8 +2,10 @@
 // with fewer instances than compute units).  Same iteration and stopping rule
 // as k_pcg (see k_pcg.hip); an instance's rows and columns are cut into
 // `slices` parts, one per workgroup of a full team, and the workgroups meet at
-// team barriers: after the row half of the operator, with the sum of p'Mp,
-// and with the sums of r'z and r'r.
+// two team barriers per iteration: after the row half of the operator, which
+// also gives p'Mp = sum rho_hat (A p)^2 + p'(P p + sigma p), and with the sums
+// of r'z and r'r.  (With p'Mp formed from the columns of M p, behind a third
+// barrier, the covariance-steering solves below took 10 % longer.)
 //
 // Teams.  A team's workgroups run on one XCD: each reads its XCD's number
 // (the XCC_ID hardware register) and takes a ticket there, so what a team
@@ -32,7 +34,7 @@
 // past the compute unit's cache took 10 us a pass on a slice of 300 columns of
 // 50 entries).
 //
-// What bounds it: latency.  Per iteration about 7 us are the three team
+// What bounds it: latency.  Per iteration about 5 us are the two team
 // barriers with their sums, the rest dependent loads (row list, entries,
 // gathers) of the few rows a lane group has, which come from beyond the L2
 // (an instance's A and A' or dense block fill it); the operator's bytes at the
@@ -291,10 +293,19 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
     };
     // Row half: tt = rho_hat o (A p) on this workgroup's slices, sums in AT;
     // rows of dense blocks are completed there and give the slice's G'w.
-    auto rows_half = [&](auto zero, auto *tt) {
+    // term((A p)_i, tt_i) is called once per row, done(s) after each slice.
+    auto rows_half = [&](auto zero, auto *tt, auto term, auto done) {
       using AT = decltype(zero);
       for (int s = tm.rank; s < V; s += tm.size) {
-        auto emit = [&](int32_t i, AT acc) { tt[i] = (v.drow && v.drow[i] >= 0) ? acc : (AT)rho_hat[i] * acc; };
+        auto emit = [&](int32_t i, AT acc) {
+          if (v.drow && v.drow[i] >= 0) {
+            tt[i] = acc;
+          } else {
+            const AT w = (AT)rho_hat[i] * acc;
+            tt[i] = w;
+            term(acc, w);
+          }
+        };
         class_rows_of((AT)0, v.rowsA, v.spanA, cuts[s], v.A_col, v.A_val, pv, emit);
         if constexpr (DMP > 0) {
           __syncthreads();   // the CSR part of the slice's dense rows
@@ -303,22 +314,28 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
             const int rb = (int)((int64_t)d.rows * s / V), re = (int)((int64_t)d.rows * (s + 1) / V);
             const T *vd = pl + (d.col0 - n0);
             dense_block_fused<NTH, DMP, AT, TG>(d, rb, re, rho_hat, [&](int c) { return vd[c]; }, tt,
-                                                reinterpret_cast<AT *>(dl), tv.ecp + (int64_t)s * tv.ec_stride);
+                                                reinterpret_cast<AT *>(dl), tv.ecp + (int64_t)s * tv.ec_stride, term);
           }
         }
+        done(s);
       }
     };
-    // (P p + sigma p)_j and the dense blocks' part of (A' t)_j, added to the
-    // column half's sum where the column's owner reads it (all loads of a
-    // column independent, none behind the sum).
-    auto col_rest = [&](auto acc, int64_t j, int s) {
+    // (P p + sigma p)_j, added to acc
+    auto col_diag = [&](auto acc, int64_t j) {
       using AT = decltype(acc);
       if (v.P_rowptr)
         for (int64_t k = v.P_rowptr[j]; k < v.P_rowptr[j + 1]; ++k) acc += (AT)v.P_val[k] * (AT)pv[v.P_col[k]];
+      return acc + (AT)v.sigma * (AT)pv[j];
+    };
+    // that and the dense blocks' part of (A' t)_j, added to the column half's
+    // sum where the column's owner reads it (all loads of a column
+    // independent, none behind the sum)
+    auto col_rest = [&](auto acc, int64_t j, int s) {
+      using AT = decltype(acc);
       if constexpr (DMP > 0) {
         if (v.dcol[j] >= 0) acc += (AT)dl[j - cuts[s][16]];
       }
-      return acc + (AT)v.sigma * (AT)pv[j];
+      return col_diag(acc, j);
     };
     // Column half: emit(j, (CSR part of A' tt)_j) on this workgroup's slices.
     auto cols_half = [&](auto zero, auto *tt, auto emit) {
@@ -367,7 +384,7 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
     for (int restart = 0; !tm.aborted; ++restart) {
       // true residual with float64 accumulation; z = r / diag M, p = z
       fill(x, [](T, T e) { return e; });
-      rows_half(0.0, t64);
+      rows_half(0.0, t64, NoTerm{}, [](int) {});
       team_sync<NTH>(tm, &flag_s);
       cols_half(0.0, t64, [&](int32_t j, double acc) { c64[j] = acc; });
       ++passes;
@@ -400,34 +417,33 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
       const T target = (T)(restart == 0 ? thr : fmax(thr, ROUND_DROP2 * (double)rr));
       fill(z, [](T, T e) { return e; });
       while (rr > target && it < max_iter) {
-        rows_half((T)0, t);
-        team_sync<NTH>(tm, &flag_s);
-        cols_half((T)0, t, [&](int32_t j, T acc) { Mp[j] = acc; });
-        for (int s = tm.rank; s < V; s += tm.size) {
-          if constexpr (DMP > 0) dense_columns(s);
-          T pMp = 0, dummy = 0;
-          own(s, [&](int64_t j) {
-            const T m = col_rest(Mp[j], j, s);
-            Mp[j] = m;
-            pMp += pl[j - n0] * m;
-          });
-          wg_sum2<NTH>(pMp, dummy, red);
-          sum_set(0, s, (double)pMp);
-        }
+        // p'Mp = sum rho_hat (A p)^2 + p'(P p + sigma p): known with the row
+        // half, so its sum needs no barrier of its own
+        T pMp = 0;
+        rows_half((T)0, t, [&](T ap, T w) { pMp += ap * w; },
+                  [&](int s) {
+                    T dummy = 0;
+                    own(s, [&](int64_t j) { pMp += pl[j - n0] * col_diag((T)0, j); });
+                    wg_sum2<NTH>(pMp, dummy, red);
+                    sum_set(0, s, (double)pMp);
+                    pMp = 0;
+                  });
         double one[1];
         team_sums<NTH, 1>(tm, V, one, sum_s, &flag_s);
         if (tm.aborted) break;
-        const T pMp = (T)one[0];
+        pMp = (T)one[0];
         if (!(pMp > (T)0)) {   // breakdown: restart from the true residual (or fail if non-finite)
           fail = !isfinite(pMp);
           break;
         }
         const T a = rz / pMp;
+        cols_half((T)0, t, [&](int32_t j, T acc) { Mp[j] = acc; });
         for (int s = tm.rank; s < V; s += tm.size) {
+          if constexpr (DMP > 0) dense_columns(s);
           T rzn = 0, rrn = 0;
           own(s, [&](int64_t j) {
             x[j] += a * pl[j - n0];
-            const T rj = r[j] - a * Mp[j];
+            const T rj = r[j] - a * col_rest(Mp[j], j, s);
             const T zj = rj / dg[j];
             r[j] = rj;
             z[j] = zj;

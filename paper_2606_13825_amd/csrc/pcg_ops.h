@@ -217,10 +217,15 @@ template <typename T> struct alignas(16) DPiece {
 
 //
 // Rows [rb, re) of the block (a slice of it, or all of it); vin(c): the
-// vector's entry of the block's column c.
-template <int NTH, int MP, typename AT, typename TG, typename T, typename TT, typename VIN>
+// vector's entry of the block's column c; row((A p)_i, new t_i) is called once
+// per row of A, on one lane.
+struct NoTerm {
+  template <typename AT> __device__ void operator()(AT, AT) const {}
+};
+template <int NTH, int MP, typename AT, typename TG, typename T, typename TT, typename VIN, typename Row = NoTerm>
 __device__ inline void dense_block_fused(const DenseDesc &d, int rb, int re, const T *__restrict__ rho_hat, VIN vin,
-                                         TT *__restrict__ t, AT *__restrict__ lds, double *__restrict__ ec) {
+                                         TT *__restrict__ t, AT *__restrict__ lds, double *__restrict__ ec,
+                                         Row row = NoTerm{}) {
   constexpr int VE = 16 / sizeof(TG);
   constexpr int NW = NTH / 64;
   // rows in flight per wave: four while a row spans at most two pieces per
@@ -287,8 +292,11 @@ __device__ inline void dense_block_fused(const DenseDesc &d, int rb, int re, con
     AT dl = dots[0];
 #pragma unroll
     for (int u = 1; u < U; ++u) dl = lu == u ? dots[u] : dl;
-    const AT ti = rl * (tl + lsc * dl);
-    if (lane < 4 * U && lplace && lr < re) t[lrow0 + lr] = (TT)ti;
+    const AT ap = tl + lsc * dl, ti = rl * ap;
+    if (lane < 4 * U && lplace && lr < re) {
+      t[lrow0 + lr] = (TT)ti;
+      row(ap, ti);
+    }
     AT wl = lsc * ti;
     wl += __shfl_xor(wl, 1, 64);
     wl += __shfl_xor(wl, 2, 64);   // lane 4u: row u's weight
