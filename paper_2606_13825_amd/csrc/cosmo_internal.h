@@ -255,24 +255,40 @@ constexpr int32_t TEAM_XCDS = 8;            // accelerator dies of the device
 constexpr int32_t TEAM_MAX_SLICES = 32;     // compute units of one die
 constexpr int32_t TEAM_MID_ROW = 256;       // entries of a row 16 lanes still handle well
 constexpr uint32_t TEAM_NONE = 0xffffffffu;
-constexpr int32_t TEAM_MAX_LDS = 153600;    // dynamic LDS a team workgroup may use
+constexpr int32_t TEAM_MAX_LDS = 158208;    // dynamic LDS a team workgroup may use
 struct TeamView {
   int32_t slices = 0;          // 0: no teams, one workgroup per instance
   int32_t teams_per_xcd = 0;
   int32_t grid = 0;            // workgroups of a launch
   int64_t max_n = 0;           // columns of the largest instance
-  int64_t tcap = 0;            // bytes of a workgroup's LDS for the rows a slice's columns use
   const int64_t *sliceA = nullptr, *sliceAt = nullptr, *midA = nullptr, *midAt = nullptr, *colcut = nullptr;
-  const int64_t *trange = nullptr;  // [2 (b slices + s)]: first row and end of the rows slice s's columns use
+  // the rows slice s's columns use, as far as the LDS copy of them is
+  // concerned: [2 (b slices + s)] the first of a range, or -1 - (offset of
+  // their list in uses), and how many; At_loc: A's transposed indices in it
+  // (what fits the LDS has 16-bit indices)
+  const int64_t *used = nullptr;
+  const int32_t *uses = nullptr;
+  const uint16_t *At_loc = nullptr;
   const int32_t *order = nullptr;   // instances, most work first
   void *state = nullptr;       // control words (team_state_bytes), zeroed once per call
-  int64_t tl_off = 0;          // where tcap's bytes begin (set at the launch)
+  // the copy of a slice that a workgroup keeps in LDS during a solve: per
+  // listed row where its entries begin in it, and per slice its entries
+  const int32_t *keptA = nullptr, *keptAt = nullptr;   // [rowsA / rowsAt]
+  const int32_t *entries = nullptr;                    // [2 (b slices + s)]: of the slice's rows, of its columns
+  int64_t cap = 0;             // bytes of LDS for both copies
+  int64_t cap_off = 0;         // where they begin (set at the launch)
   double *ecp = nullptr;       // per slice, the dense blocks' column products
   int64_t ec_stride = 0;       // their length
 };
 size_t team_state_bytes(int32_t teams_per_xcd);
-size_t team_lds_bytes(size_t esz, int64_t max_n, int32_t dense_maxcols);   // without tcap
+size_t team_lds_bytes(size_t esz, int64_t max_n, int32_t dense_maxcols);   // without cap
 void launch_team_reset(const TeamView &tv, hipStream_t st);
+// Bytes of such a copy (16-byte multiple): row ids, where their entries
+// begin, rho_hat (rows) or nothing (columns), values, 16-bit indices.
+__host__ __device__ inline int64_t team_kept_bytes(int64_t rows, int64_t entries, int64_t esz, bool rho) {
+  return ((rows + 1) * 8 + 15) / 16 * 16 + (rho ? (rows * esz + 15) / 16 * 16 : 0) + (entries * esz + 15) / 16 * 16 +
+         (entries * 2 + 15) / 16 * 16;
+}
 template <typename T> void launch_pcg_team(const View<T> &v, const TeamView &tv, const T *rho_hat, const T *dg,
                                            const double *rhs, T *x, T *r, T *z, T *Mp, T *t, double *t64,
                                            double *c64, double tol, int32_t max_iter, const T *alpha_k, const T *xold, T *xnew,

@@ -29,20 +29,28 @@
 //
 // p (in the residual pass: x) is kept whole in every workgroup's LDS: the row
 // half gathers from there, and p = z + beta p needs no barrier of its own.
-// The column half first copies the span of rows its columns use, where that
-// fits (a coalesced copy with all loads in flight; gathers of single entries
+// The column half first copies the rows that its columns use, where they
+// fit (a coalesced copy with all loads in flight; gathers of single entries
 // past the compute unit's cache took 10 us a pass on a slice of 300 columns of
 // 50 entries).
 //
+// A workgroup keeps its slice of A in LDS through a solve's iterations, and
+// its slice of A' where that still fits: an instance's A and A' do not fit the
+// die's L2 together with its vectors, and read from behind it they took 8 to
+// 11 us a half (covariance steering with 290,000 entries, a program with
+// 500,000); from LDS a half takes 3 to 4.  Slices of A' that do not fit are
+// read with 16-bit indices and eight lanes per row of 50 to 256 entries (16
+// lanes left most of their loads without an entry: 11 us, now 7).
+//
 // What bounds it: latency.  Per iteration about 5 us are the two team
-// barriers with their sums, the rest dependent loads (row list, entries,
-// gathers) of the few rows a lane group has, which come from beyond the L2
-// (an instance's A and A' or dense block fill it); the operator's bytes at the
-// rate of one XCD are 4 to 8 us.  Measured per iteration, one workgroup per
+// barriers with their sums and 2 to 3 the copies of p and t; the rest is the
+// operator, by the LDS's rate and, for what is not kept, by dependent loads of
+// the few rows a lane group has.  Measured per iteration, one workgroup per
 // instance or the device-wide form against teams of 32: 4 Huber instances of
-// 2000 x 500 in float64 137 -> 20 us; 16 covariance-steering instances 97 ->
-// 30 us; one program with 500,000 nonzeros 83 -> 28 us.
+// 2000 x 500 in float64 137 -> 19 us; 16 covariance-steering instances 97 ->
+// 20 us; one program with 500,000 nonzeros 83 -> 18 us.
 #include <algorithm>
+#include <type_traits>
 
 #include "pcg_ops.h"
 
@@ -72,6 +80,140 @@ template <typename T> struct Local {
   __device__ T operator[](int32_t c) const { return p[c - n0]; }
 };
 
+extern __shared__ double dyn_lds[];
+
+// Sum of a row's products by L lanes, four entries per lane in flight.  The
+// order of the additions, and so the result, depends on L and the row alone.
+template <int L, typename AT, typename V, typename G> __device__ inline AT strided_sum(int len, V val, G gather) {
+  AT a = 0;
+  for (int k = threadIdx.x % L; k < len; k += 4 * L) {
+    AT e[4], g[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int ku = min(k + u * L, len - 1);   // past the end: the last entry again, not counted
+      e[u] = (AT)val(ku);
+      g[u] = (AT)gather(ku);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) a = k + u * L < len ? fma(e[u], g[u], a) : a;
+  }
+  return sub_sum(a, L);
+}
+
+// Eight waves: the kernel's state does not fit the 128 registers of sixteen
+// (with 1024 threads 16 covariance-steering instances took 8.5 ms per training
+// step instead of 6.9, one program with 500,000 nonzeros 3.8 instead of 3.2).
+constexpr int NTH = 512;
+
+// Where the length classes of a slice end in its list, from its list ranges
+// (class 0, class 1, class 2: short, long rows).
+__device__ inline void class_ends(const int64_t *cut, int32_t (&end)[4]) {
+  auto uni = [](int64_t x) { return __builtin_amdgcn_readfirstlane((int32_t)x); };
+  end[0] = uni(cut[1] - cut[0]);
+  end[1] = end[0] + uni(cut[3] - cut[2]);
+  end[2] = end[1] + uni(cut[5] - cut[4]);
+  end[3] = end[2] + uni(cut[6] - cut[5]);
+}
+__device__ inline int64_t list_at(const int64_t *cut, const int32_t (&end)[4], int q) {
+  return q < end[0] ? cut[0] + q : q < end[1] ? cut[2] + (q - end[0]) : cut[4] + (q - end[1]);
+}
+
+// A slice's rows (or columns) in LDS: per listed row its id and where its
+// entries begin, for rows rho_hat, then values and 16-bit indices.  Offsets
+// into the dynamic LDS, the same in every thread (scalar registers).
+template <typename T> struct Kept {
+  int32_t o_first = 0, o_rho = 0, o_val = 0, o_idx = 0, o_row = 0;
+  int32_t end[4] = {0, 0, 0, 0};   // where each length class ends
+  bool on = false;
+  __device__ void place(int64_t at, const int64_t *cut, int32_t entries, bool with_rho) {
+    on = true;
+    class_ends(cut, end);
+    auto uni = [](int64_t x) { return __builtin_amdgcn_readfirstlane((int32_t)x); };
+    o_row = uni(at);
+    o_first = o_row + 4 * end[3];
+    o_rho = o_row + ((end[3] + 1) * 8 + 15) / 16 * 16;
+    o_val = o_rho + (with_rho ? (end[3] * (int32_t)sizeof(T) + 15) / 16 * 16 : 0);
+    o_idx = o_val + (uni(entries) * (int32_t)sizeof(T) + 15) / 16 * 16;
+  }
+  template <typename X> static __device__ X *lds(int32_t off) {
+    return reinterpret_cast<X *>(reinterpret_cast<char *>(dyn_lds) + off);
+  }
+  __device__ int32_t *row() const { return lds<int32_t>(o_row); }
+  __device__ int32_t *first() const { return lds<int32_t>(o_first); }
+  __device__ T *rho() const { return lds<T>(o_rho); }
+  // 16 lanes per row; id(row) is what is kept as the row's id; base: the index
+  // kept as 0.  Ends with a barrier.
+  template <bool RHO, typename CT, typename Id>
+  __device__ void fill(const int64_t *cut, int32_t entries, const int32_t *rows, const RowSpan *span,
+                       const int32_t *begin, const CT *col, const T *v, const T *rho_hat, int64_t base, Id id) {
+    const int lane = threadIdx.x % 16;
+    T *val = lds<T>(o_val);
+    uint16_t *idx = lds<uint16_t>(o_idx);
+    for (int q0 = threadIdx.x / 16; q0 < end[3]; q0 += 4 * (NTH / 16)) {   // four rows in flight per 16 lanes
+      int32_t r[4], o[4];
+      RowSpan sp[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int q = min(q0 + u * (NTH / 16), end[3] - 1);   // past the end: the last row again, not stored
+        const int64_t li = list_at(cut, end, q);
+        r[u] = rows[li];
+        o[u] = begin[li];
+        sp[u] = span[li];
+      }
+      T e[4], rh[4];
+      CT c[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool on = lane < sp[u].k1 - sp[u].kb;
+        e[u] = on ? v[sp[u].kb + lane] : (T)0;
+        c[u] = on ? col[sp[u].kb + lane] : (CT)0;
+        rh[u] = RHO ? rho_hat[r[u]] : (T)0;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int q = q0 + u * (NTH / 16), len = (int)(sp[u].k1 - sp[u].kb);
+        if (q >= end[3]) continue;
+        if (lane < len) {
+          val[o[u] + lane] = e[u];
+          idx[o[u] + lane] = (uint16_t)(c[u] - base);
+        }
+        for (int k = lane + 16; k < len; k += 16) {
+          val[o[u] + k] = v[sp[u].kb + k];
+          idx[o[u] + k] = (uint16_t)(col[sp[u].kb + k] - base);
+        }
+        if (lane == 0) {
+          row()[q] = id(r[u]);
+          first()[q] = o[u];
+          if (RHO) rho()[q] = rh[u];
+        }
+      }
+    }
+    if (threadIdx.x == 0) first()[end[3]] = entries;
+    __syncthreads();
+  }
+  // Row q of the list, L lanes: its sum, on every lane.  x: the vector by kept
+  // index.
+  template <int L, typename AT, typename X> __device__ AT row_sum(int q, const X *x) const {
+    const T *val = lds<T>(o_val);
+    const uint16_t *idx = lds<uint16_t>(o_idx);
+    const int o = first()[q];
+    return strided_sum<L, AT>(first()[q + 1] - o, [&](int k) { return val[o + k]; }, [&](int k) { return x[idx[o + k]]; });
+  }
+};
+
+// Length classes of a slice's rows, by rows [q0, q1) of its list and the lanes
+// that one of them takes; f<L>(q) runs on those lanes.
+template <typename F> __device__ inline void strided_rows(const int32_t (&end)[4], F f) {
+  auto pass = [&](auto lanes, int q0, int q1) {
+    constexpr int L = decltype(lanes)::value;
+    for (int q = q0 + threadIdx.x / L; q < q1; q += NTH / L) f(lanes, q);
+  };
+  pass(std::integral_constant<int, 64>{}, end[2], end[3]);
+  pass(std::integral_constant<int, 16>{}, end[1], end[2]);
+  pass(std::integral_constant<int, 4>{}, end[0], end[1]);
+  pass(std::integral_constant<int, 1>{}, 0, end[0]);
+}
+
 // Control words of one launch, zero before it and left zero by it.
 struct TeamHead {
   uint32_t queue, exits;
@@ -99,7 +241,7 @@ struct Team {
 };
 
 // All members' stores before it are visible to Shared reads after it.
-template <int NTH> __device__ inline void team_sync(Team &tm, int32_t *flag_s) {
+__device__ inline void team_sync(Team &tm, int32_t *flag_s) {
   __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's stores are in L2
   __syncthreads();
   const uint32_t target = tm.gen + 1;
@@ -129,9 +271,9 @@ template <int NTH> __device__ inline void team_sync(Team &tm, int32_t *flag_s) {
 // Team sums of up to three values whose slice partials this workgroup has
 // stored (by thread 0) in the record's current set; same bits in every thread
 // of every member.
-template <int NTH, int NV> __device__ inline void team_sums(Team &tm, int slices, double (&out)[NV], double *sum_s,
+template <int NV> __device__ inline void team_sums(Team &tm, int slices, double (&out)[NV], double *sum_s,
                                                             int32_t *flag_s) {
-  team_sync<NTH>(tm, flag_s);
+  team_sync(tm, flag_s);
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
 #pragma unroll
@@ -148,19 +290,14 @@ template <int NTH, int NV> __device__ inline void team_sums(Team &tm, int slices
   tm.parity ^= 1;
 }
 
-// threads per workgroup: as in the one-workgroup form
-template <typename T, int DMP> constexpr int TT = (DMP == 0 && sizeof(T) == 4) ? 1024 : 512;
-
 template <typename T, int DMP, typename TG>
-__global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView tv, const T *__restrict__ rho_hat,
+__global__ __launch_bounds__(NTH) void k_pcg_team(View<T> v, TeamView tv, const T *__restrict__ rho_hat,
                                                            const T *__restrict__ dg, const double *__restrict__ rhs,
                                                            T *x, T *r, T *z, T *Mp, T *t, double *t64,
                                                            double *c64, T tol, int32_t max_iter, const T *__restrict__ alpha_k,
                                                            const T *__restrict__ xold, T *__restrict__ xnew,
                                                            const T *__restrict__ gx_in, T *__restrict__ gx_out,
                                                            int32_t mode, cosmo_stats *stats) {
-  constexpr int NTH = TT<T, DMP>;
-  extern __shared__ double dyn_lds[];
   __shared__ T red[2 * (NTH / 64)];
   __shared__ double redd[2 * (NTH / 64)];
   __shared__ double sum_s[3];
@@ -206,7 +343,7 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
     // ---- the next instance of the queue ------------------------------------------
     if (tm.rank == 0 && tid == 0)
       st_agent(&tm.rec->inst, __hip_atomic_fetch_add(&head->queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    team_sync<NTH>(tm, &flag_s);
+    team_sync(tm, &flag_s);
     if (tid == 0) sum_s[0] = (double)ld_agent(&tm.rec->inst);
     __syncthreads();
     const uint32_t pos = (uint32_t)sum_s[0];
@@ -218,20 +355,67 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
     double *dl = dyn_lds + ((size_t)n * sizeof(T) + 7) / 8;   // the waves' partials of the dense product
     const int64_t BV = (int64_t)v.B * V, bV = (int64_t)b * V;
     const Local<T> pv{pl, (int32_t)n0};
-    char *tl = reinterpret_cast<char *>(dyn_lds) + tv.tl_off;   // the copied span of rows
+    char *tl = reinterpret_cast<char *>(dyn_lds) + tv.cap_off;   // the copied rows of t, then a kept slice
 
     // where this workgroup's slices begin and end: list ranges of the rows
     // (0-6: three classes, the last one's short and long rows) and of the
-    // columns (7-13), the columns' span of rows (14, 15), the columns (16, 17)
+    // columns (7-13), the rows the columns use (14, 15), the columns (16, 17)
     for (int e = tid; e < 18 * V; e += NTH) {
       const int s = e / 18, k = e % 18;
       if (s % (int)tm.size != (int)tm.rank) continue;
       const int64_t *sl = (k < 7 ? tv.sliceA : tv.sliceAt) + bV + s, *mid = (k < 7 ? tv.midA : tv.midAt) + bV + s;
       const int q = k < 7 ? k : k - 7;
-      cuts[s][k] = k >= 16 ? tv.colcut[bV + s + k - 16] : k >= 14 ? tv.trange[2 * (bV + s) + k - 14]
+      cuts[s][k] = k >= 16 ? tv.colcut[bV + s + k - 16] : k >= 14 ? tv.used[2 * (bV + s) + k - 14]
                    : q == 5 ? *mid : q == 6 ? sl[2 * (BV + 1) + 1] : sl[(q / 2) * (BV + 1) + (q & 1)];
     }
     __syncthreads();
+
+    // A slice's entries are read again in every iteration: a workgroup with one
+    // slice keeps them in LDS where they fit, the rows first, behind the copied
+    // rows of t.  Set up before the first iteration of a round (a residual
+    // pass in float64 uses the same LDS).  A smaller team adds the rows of
+    // slices that would fit in the same order, from memory.
+    Kept<T> keptA, keptAt;
+    auto t_bytes = [&](int s) { return (cuts[s][15] * (int64_t)sizeof(T) + 15) / 16 * 16; };
+    auto fits = [&](int s, int64_t &at, int64_t &na) {   // bit 0: the rows, bit 1: the columns
+      const int64_t *cut = cuts[s];
+      na = team_kept_bytes(cut[1] - cut[0] + cut[3] - cut[2] + cut[6] - cut[4], tv.entries[2 * (bV + s)], sizeof(T), true);
+      const int64_t nat = team_kept_bytes(cut[8] - cut[7] + cut[10] - cut[9] + cut[13] - cut[11],
+                                          tv.entries[2 * (bV + s) + 1], sizeof(T), false);
+      at = t_bytes(s) <= tv.cap ? t_bytes(s) : 0;
+      if (at + na > tv.cap || n > 65536) return 0;
+      return t_bytes(s) > tv.cap || at + na + nat > tv.cap ? 1 : 3;
+    };
+    auto keep_slice = [&]() {
+      if ((int)tm.size != V || keptA.on) return;
+      const int s = tm.rank;
+      int64_t at, na;
+      const int kept = fits(s, at, na);
+      if (kept == 0) return;
+      const int32_t ea = tv.entries[2 * (bV + s)], eat = tv.entries[2 * (bV + s) + 1];
+      keptA.place(tv.cap_off + at, cuts[s], ea, true);
+      keptA.template fill<true>(cuts[s], ea, v.rowsA, v.spanA, tv.keptA, v.A_col, v.A_val, rho_hat, n0,
+                                [&](int32_t r) { return DMP > 0 && v.drow && v.drow[r] >= 0 ? ~r : r; });
+      if (kept == 1) return;
+      keptAt.place(tv.cap_off + at + na, cuts[s] + 7, eat, false);
+      keptAt.template fill<false>(cuts[s] + 7, eat, v.rowsAt, v.spanAt, tv.keptAt, tv.At_loc, v.At_val, rho_hat, 0,
+                                  [](int32_t j) { return j; });
+    };
+    // a fitting slice's rows from memory: emit(id, sum) on a row's first lane
+    auto strided_from_memory = [&](auto zero, const int64_t *cut, const int32_t *rows, const RowSpan *span,
+                                   const auto *col, const T *val, auto vin, auto emit) {
+      using AT = decltype(zero);
+      int32_t end[4];
+      class_ends(cut, end);
+      strided_rows(end, [&](auto lanes, int q) {
+        constexpr int L = decltype(lanes)::value;
+        const int64_t li = list_at(cut, end, q);
+        const RowSpan sp = span[li];
+        const AT acc = strided_sum<L, AT>((int)(sp.k1 - sp.kb), [&](int k) { return val[sp.kb + k]; },
+                                          [&](int k) { return vin[col[sp.kb + k]]; });
+        if (threadIdx.x % L == 0) emit(rows[li], acc);
+      });
+    };
 
     // this workgroup's columns of slice s
     auto own = [&](int s, auto f) {
@@ -243,12 +427,12 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
     // LDS copy of a vector the team's members wrote; f(old LDS value, new entry)
     auto fill = [&](const T *src, auto f) {
       const Shared<T> sv{src + n0};
-      for (int j = tid; j < n; j += 4 * NTH) {   // past the end: the last entry again, not stored
-        T e[4];
+      for (int j = tid; j < n; j += 8 * NTH) {   // past the end: the last entry again, not stored
+        T e[8];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) e[u] = sv[min(j + u * NTH, n - 1)];
+        for (int u = 0; u < 8; ++u) e[u] = sv[min(j + u * NTH, n - 1)];
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 8; ++u)
           if (j + u * NTH < n) pl[j + u * NTH] = f(pl[j + u * NTH], e[u]);
       }
       __syncthreads();
@@ -257,12 +441,12 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
     // group, so the time is the dependent loads of the rows one after another:
     // few lanes per row, all of a row's pieces in flight at once.
     auto class_rows_of = [&](auto zero, const int32_t *rows, const RowSpan *span, const int64_t *cut,
-                             const int32_t *col, const T *val, auto vin, auto emit) {
+                             const auto *col, const T *val, auto vin, auto emit) {
       using AT = decltype(zero);
       constexpr int U = 16 / sizeof(AT);
       row_pass<1, AT>(rows, span, cut[0], cut[1], tid, NTH, col, val, vin, all, emit);
       row_pass<4, AT, U>(rows, span, cut[2], cut[3], tid / 4, NTH / 4, col, val, vin, all, emit);
-      row_pass<16, AT, U>(rows, span, cut[4], cut[5], tid / 16, NTH / 16, col, val, vin, all, emit);
+      row_pass<8, AT, U>(rows, span, cut[4], cut[5], tid / 8, NTH / 8, col, val, vin, all, emit);
       row_pass<64, AT>(rows, span, cut[5], cut[6], tid / 64, NTH / 64, col, val, vin, all, emit);
     };
     // The dense blocks' column products of slice s's columns, summed over the
@@ -296,6 +480,7 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
     // term((A p)_i, tt_i) is called once per row, done(s) after each slice.
     auto rows_half = [&](auto zero, auto *tt, auto term, auto done) {
       using AT = decltype(zero);
+      constexpr bool ITER = !std::is_same<decltype(term), NoTerm>::value;   // an iteration, not the residual
       for (int s = tm.rank; s < V; s += tm.size) {
         auto emit = [&](int32_t i, AT acc) {
           if (v.drow && v.drow[i] >= 0) {
@@ -306,7 +491,27 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
             term(acc, w);
           }
         };
-        class_rows_of((AT)0, v.rowsA, v.spanA, cuts[s], v.A_col, v.A_val, pv, emit);
+        int64_t at, na;
+        if (ITER && keptA.on) {
+          strided_rows(keptA.end, [&](auto lanes, int q) {
+            constexpr int L = decltype(lanes)::value;
+            const AT acc = keptA.template row_sum<L, AT>(q, pl);
+            if (tid % L == 0) {
+              const int32_t i = keptA.row()[q];
+              if (DMP > 0 && i < 0) {
+                tt[~i] = acc;
+              } else {
+                const AT w = (AT)keptA.rho()[q] * acc;
+                tt[i] = w;
+                term(acc, w);
+              }
+            }
+          });
+        } else if (ITER && (int)tm.size != V && fits(s, at, na) != 0) {
+          strided_from_memory((AT)0, cuts[s], v.rowsA, v.spanA, v.A_col, v.A_val, pv, emit);
+        } else {
+          class_rows_of((AT)0, v.rowsA, v.spanA, cuts[s], v.A_col, v.A_val, pv, emit);
+        }
         if constexpr (DMP > 0) {
           __syncthreads();   // the CSR part of the slice's dense rows
           for (int k = v.dense_inst[b]; k < v.dense_inst[b + 1]; ++k) {
@@ -338,25 +543,47 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
       return col_diag(acc, j);
     };
     // Column half: emit(j, (CSR part of A' tt)_j) on this workgroup's slices.
-    auto cols_half = [&](auto zero, auto *tt, auto emit) {
+    auto cols_half = [&](bool iter, auto zero, auto *tt, auto emit) {
       using AT = decltype(zero);
       const Shared<AT> tsh{tt};
       for (int s = tm.rank; s < V; s += tm.size) {
-        const int64_t i0 = cuts[s][14], i1 = cuts[s][15];
-        if ((i1 - i0) * (int64_t)sizeof(AT) <= tv.tcap) {
+        const int64_t i0 = cuts[s][14];
+        const int cnt = (int)cuts[s][15];
+        if (cnt * (int64_t)sizeof(AT) <= tv.cap) {
           AT *tc = reinterpret_cast<AT *>(tl);
-          const int cnt = (int)(i1 - i0);
-          const Shared<AT> src{tt + i0};
-          for (int i = tid; i < cnt; i += 4 * NTH) {
-            AT e[4];
+          if (sizeof(AT) != sizeof(T)) {   // wider than the place left for it
+            __syncthreads();
+            keptA.on = keptAt.on = false;
+          }
+          auto copy = [&](auto entry) {
+            for (int i = tid; i < cnt; i += 4 * NTH) {
+              AT e[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) e[u] = src[min(i + u * NTH, cnt - 1)];
+              for (int u = 0; u < 4; ++u) e[u] = entry(min(i + u * NTH, cnt - 1));
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-              if (i + u * NTH < cnt) tc[i + u * NTH] = e[u];
+              for (int u = 0; u < 4; ++u)
+                if (i + u * NTH < cnt) tc[i + u * NTH] = e[u];
+            }
+          };
+          if (i0 >= 0) {
+            const Shared<AT> src{tt + i0};
+            copy([&](int k) { return src[k]; });
+          } else {
+            const int32_t *list = tv.uses + (-1 - i0);
+            copy([&](int k) { return tsh[list[k]]; });
           }
           __syncthreads();
-          class_rows_of((AT)0, v.rowsAt, v.spanAt, cuts[s] + 7, v.At_col, v.At_val, Local<AT>{tc, (int32_t)i0}, emit);
+          int64_t at, na;
+          if (iter && keptAt.on)
+            strided_rows(keptAt.end, [&](auto lanes, int q) {
+              constexpr int L = decltype(lanes)::value;
+              const AT acc = keptAt.template row_sum<L, AT>(q, tc);
+              if (tid % L == 0) emit(keptAt.row()[q], acc);
+            });
+          else if (iter && (int)tm.size != V && (fits(s, at, na) & 2) != 0)
+            strided_from_memory((AT)0, cuts[s] + 7, v.rowsAt, v.spanAt, tv.At_loc, v.At_val, Local<AT>{tc, 0}, emit);
+          else
+            class_rows_of((AT)0, v.rowsAt, v.spanAt, cuts[s] + 7, tv.At_loc, v.At_val, Local<AT>{tc, 0}, emit);
           __syncthreads();   // the next slice's copy may overwrite it
         } else {
           class_rows_of((AT)0, v.rowsAt, v.spanAt, cuts[s] + 7, v.At_col, v.At_val, tsh, emit);
@@ -374,7 +601,7 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
     double tot[3];
     {
       double one[1];
-      team_sums<NTH, 1>(tm, V, one, sum_s, &flag_s);
+      team_sums<1>(tm, V, one, sum_s, &flag_s);
       tot[0] = one[0];
     }
     const double thr = (double)tol * (double)tol * tot[0];
@@ -385,8 +612,8 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
       // true residual with float64 accumulation; z = r / diag M, p = z
       fill(x, [](T, T e) { return e; });
       rows_half(0.0, t64, NoTerm{}, [](int) {});
-      team_sync<NTH>(tm, &flag_s);
-      cols_half(0.0, t64, [&](int32_t j, double acc) { c64[j] = acc; });
+      team_sync(tm, &flag_s);
+      cols_half(false, 0.0, t64, [&](int32_t j, double acc) { c64[j] = acc; });
       ++passes;
       for (int s = tm.rank; s < V; s += tm.size) {
         if constexpr (DMP > 0) dense_columns(s);
@@ -407,7 +634,7 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
         sum_set(1, s, (double)rr);
         sum_set(2, s, rt);
       }
-      team_sums<NTH, 3>(tm, V, tot, sum_s, &flag_s);
+      team_sums<3>(tm, V, tot, sum_s, &flag_s);
       T rz = (T)tot[0], rr = (T)tot[1];
       rrt = tot[2];
       fail = fail || !isfinite(rrt);
@@ -416,6 +643,7 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
       rrt_prev = rrt;
       const T target = (T)(restart == 0 ? thr : fmax(thr, ROUND_DROP2 * (double)rr));
       fill(z, [](T, T e) { return e; });
+      keep_slice();
       while (rr > target && it < max_iter) {
         // p'Mp = sum rho_hat (A p)^2 + p'(P p + sigma p): known with the row
         // half, so its sum needs no barrier of its own
@@ -429,7 +657,7 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
                     pMp = 0;
                   });
         double one[1];
-        team_sums<NTH, 1>(tm, V, one, sum_s, &flag_s);
+        team_sums<1>(tm, V, one, sum_s, &flag_s);
         if (tm.aborted) break;
         pMp = (T)one[0];
         if (!(pMp > (T)0)) {   // breakdown: restart from the true residual (or fail if non-finite)
@@ -437,14 +665,20 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
           break;
         }
         const T a = rz / pMp;
-        cols_half((T)0, t, [&](int32_t j, T acc) { Mp[j] = acc; });
+        // this thread's first column: what its update reads is on its way
+        // while the column half runs
+        const int64_t jf = cuts[tm.rank][16] + tid;
+        const bool has = jf < cuts[tm.rank][17];
+        const T xf = has ? x[jf] : (T)0, rf = has ? r[jf] : (T)0, df = has ? dg[jf] : (T)1;
+        cols_half(true, (T)0, t, [&](int32_t j, T acc) { Mp[j] = acc; });
         for (int s = tm.rank; s < V; s += tm.size) {
           if constexpr (DMP > 0) dense_columns(s);
           T rzn = 0, rrn = 0;
           own(s, [&](int64_t j) {
-            x[j] += a * pl[j - n0];
-            const T rj = r[j] - a * col_rest(Mp[j], j, s);
-            const T zj = rj / dg[j];
+            const bool pre = j == jf;
+            x[j] = (pre ? xf : x[j]) + a * pl[j - n0];
+            const T rj = (pre ? rf : r[j]) - a * col_rest(Mp[j], j, s);
+            const T zj = rj / (pre ? df : dg[j]);
             r[j] = rj;
             z[j] = zj;
             rzn += rj * zj;
@@ -455,7 +689,7 @@ __global__ __launch_bounds__((TT<T, DMP>)) void k_pcg_team(View<T> v, TeamView t
           sum_set(1, s, (double)rrn);
         }
         double two[2];
-        team_sums<NTH, 2>(tm, V, two, sum_s, &flag_s);
+        team_sums<2>(tm, V, two, sum_s, &flag_s);
         if (tm.aborted) break;
         const T rz_new = (T)two[0];
         rr = (T)two[1];
@@ -541,28 +775,28 @@ void launch_pcg_team(const View<T> &v, const TeamView &tv, const T *rho_hat, con
                      const T *xold, T *xnew, const T *gx_in, T *gx_out, int32_t mode, cosmo_stats *stats,
                      hipStream_t st) {
   TeamView tvl = tv;
-  tvl.tl_off = team_lds_bytes(sizeof(T), tv.max_n, v.n_dense > 0 ? v.dense_maxcols : 0);
-  auto go = [&](auto kern, int threads) {
+  tvl.cap_off = (int64_t)(team_lds_bytes(sizeof(T), tv.max_n, v.n_dense > 0 ? v.dense_maxcols : 0) + 15) / 16 * 16;
+  auto go = [&](auto kern) {
     static bool attr_set = false;   // more than the default 64 KiB of dynamic LDS may be needed
     if (!attr_set) {
       (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 TEAM_MAX_LDS);
       attr_set = true;
     }
-    kern<<<tv.grid, threads, tvl.tl_off + tv.tcap, st>>>(v, tvl, rho_hat, dg, rhs, x, r, z, Mp, t, t64, c64, (T)tol,
+    kern<<<tv.grid, NTH, tvl.cap_off + tv.cap, st>>>(v, tvl, rho_hat, dg, rhs, x, r, z, Mp, t, t64, c64, (T)tol,
                                                          max_iter, alpha_k, xold, xnew, gx_in, gx_out, mode, stats);
   };
   if (v.n_dense <= 0) {
-    go(&k_pcg_team<T, 0, T>, TT<T, 0>);
+    go(&k_pcg_team<T, 0, T>);
     return;
   }
   auto pick = [&](auto tg) {
     using TG = decltype(tg);
     constexpr int VE = 16 / sizeof(TG), MAXPC = COSMO_DENSE_MAX_COLS / (64 * VE);
     const int pieces = (v.dense_maxcols + 64 * VE - 1) / (64 * VE);
-    if (pieces <= MAXPC / 4) go(&k_pcg_team<T, MAXPC / 4, TG>, 512);
-    else if (pieces <= MAXPC / 2) go(&k_pcg_team<T, MAXPC / 2, TG>, 512);
-    else go(&k_pcg_team<T, MAXPC, TG>, 512);
+    if (pieces <= MAXPC / 4) go(&k_pcg_team<T, MAXPC / 4, TG>);
+    else if (pieces <= MAXPC / 2) go(&k_pcg_team<T, MAXPC / 2, TG>);
+    else go(&k_pcg_team<T, MAXPC, TG>);
   };
   if (sizeof(T) == 8 && v.dense_g32) pick(float{});
   else pick(T{});

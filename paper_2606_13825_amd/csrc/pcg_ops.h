@@ -48,9 +48,9 @@ template <int NTH, typename T> __device__ inline void wg_sum2(T &a, T &b, T *red
 // Short rows (at most 4 nonzeros, one lane each): four rows per lane per
 // pass, all entries read with clamped indices and masks so the whole gather is
 // in flight at once.
-template <typename AT, typename T, typename VIN, typename Act, typename F>
+template <typename AT, typename CT, typename T, typename VIN, typename Act, typename F>
 __device__ inline void short_rows(const int32_t *__restrict__ rows, const RowSpan *__restrict__ span, int64_t first,
-                                  int64_t r1, int64_t stride, const int32_t *__restrict__ col,
+                                  int64_t r1, int64_t stride, const CT *__restrict__ col,
                                   const T *__restrict__ val, VIN vin, Act active, F emit) {
   for (int64_t base = first; base < r1; base += 4 * stride) {
     int32_t rw[4];
@@ -90,12 +90,12 @@ __device__ inline void short_rows(const int32_t *__restrict__ rows, const RowSpa
   }
 }
 
-// 16-byte pieces of a row: VE = 16 / sizeof(T) values and VE column indices.
+// Pieces of a row: VE = 16 / sizeof(T) values and VE column indices.
 template <typename T> struct alignas(16) ValPiece {
   T v[16 / sizeof(T)];
 };
-template <int N> struct alignas(4 * N) ColPiece {
-  int32_t c[N];
+template <typename CT, int N> struct alignas(sizeof(CT) * N) ColPiece {
+  CT c[N];
 };
 
 // L lanes per row.  The row's entries are read in 16-byte pieces (the CSR
@@ -106,16 +106,17 @@ template <int N> struct alignas(4 * N) ColPiece {
 // loaded while the current row is summed, so the index loads are off the
 // critical path.  gsub / nsub: this thread's row group and the number of row
 // groups of the pass.
-template <int L, typename AT, int U = 2, typename T, typename VIN, typename Act, typename F>
+template <int L, typename AT, int U = 2, typename CT, typename T, typename VIN, typename Act, typename F>
 __device__ inline void row_pass(const int32_t *__restrict__ rows, const RowSpan *__restrict__ span, int64_t r0,
-                                int64_t r1, int64_t gsub, int64_t nsub, const int32_t *__restrict__ col,
+                                int64_t r1, int64_t gsub, int64_t nsub, const CT *__restrict__ col,
                                 const T *__restrict__ val, VIN vin, Act active, F emit) {
   if constexpr (L == 1) {
     short_rows<AT>(rows, span, r0 + gsub, r1, nsub, col, val, vin, active, emit);
   } else {
     constexpr int VE = 16 / sizeof(T);
+    static_assert(L >= VE - 1, "a lane for each entry before the first whole piece");
     using VP = ValPiece<T>;
-    using CP = ColPiece<VE>;
+    using CP = ColPiece<CT, VE>;
     const int lane = threadIdx.x % L;
     int64_t ri = r0 + gsub;
     int32_t nrow = 0;
@@ -211,10 +212,6 @@ __device__ inline void class_passes(const int32_t *rows, const RowSpan *span, co
 // its partial of G'w -- so G is read once per operator application.  The
 // waves' partials are added in wave order into ec (the column passes add
 // ec to the CSR part of A' t).  MP: 16-byte pieces of a row per lane.
-template <typename T> struct alignas(16) DPiece {
-  T v[16 / sizeof(T)];
-};
-
 //
 // Rows [rb, re) of the block (a slice of it, or all of it); vin(c): the
 // vector's entry of the block's column c; row((A p)_i, new t_i) is called once
@@ -260,10 +257,14 @@ __device__ inline void dense_block_fused(const DenseDesc &d, int rb, int re, con
       lsc = (AT)d.scale[q];
     }
   if (!lplace) lsc = (AT)0;
-  const DPiece<TG> *G = static_cast<const DPiece<TG> *>(d.val);
+  // (the block's address comes out of memory: said to be global memory, its
+  // loads do not also wait for the LDS)
+  typedef TG Piece __attribute__((ext_vector_type(VE)));
+  typedef const __attribute__((address_space(1))) Piece *GlobalPieces;
+  GlobalPieces G = (GlobalPieces)d.val;
   const int64_t ldp = d.ld / VE;
   for (int r0 = rb + wave; r0 < re; r0 += U * NW) {
-    DPiece<TG> g[U][MP];
+    Piece g[U][MP];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int r = min(r0 + u * NW, re - 1);   // clamped; surplus rows change nothing
@@ -286,7 +287,7 @@ __device__ inline void dense_block_fused(const DenseDesc &d, int rb, int re, con
 #pragma unroll
       for (int q = 0; q < MP; ++q)
 #pragma unroll
-        for (int e = 0; e < VE; ++e) dots[u] += (AT)g[u][q].v[e] * xv[q][e];   // xv is 0 past the row's end
+        for (int e = 0; e < VE; ++e) dots[u] += (AT)g[u][q][e] * xv[q][e];   // xv is 0 past the row's end
     }
     wave_sums<U>(dots);
     AT dl = dots[0];
@@ -307,7 +308,7 @@ __device__ inline void dense_block_fused(const DenseDesc &d, int rb, int re, con
 #pragma unroll
         for (int q = 0; q < MP; ++q)
 #pragma unroll
-          for (int e = 0; e < VE; ++e) acc[q][e] += w * (AT)g[u][q].v[e];   // entries past cols are never read
+          for (int e = 0; e < VE; ++e) acc[q][e] += w * (AT)g[u][q][e];   // entries past cols are never read
       }
     }
   }

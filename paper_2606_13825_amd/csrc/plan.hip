@@ -613,8 +613,9 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   // CG teams: slices of every instance's rows and columns, cut by their
   // entries; the rows of a dense block (all its placements) go with the
   // block's row, so a slice completes its part of the block by itself
-  std::vector<int64_t> sliceA, sliceAt, midA, midAt, colcut, trange;
-  std::vector<int32_t> order;
+  std::vector<int64_t> sliceA, sliceAt, midA, midAt, colcut, used;
+  std::vector<int32_t> order, keptA, keptAt, entries, uses;
+  std::vector<uint16_t> At_loc;
   if (!pl->diag_M) {
     int dev = 0, ncu = 0;
     HIPCHK(hipGetDevice(&dev));
@@ -673,23 +674,66 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
         }
       }
       colcut[(size_t)pl->B * V] = n;
-      // the span of rows each slice's columns use, and the LDS left for it
-      // (float64 in the residual pass; spans that do not fit are gathered)
-      const size_t room = (size_t)TEAM_MAX_LDS - team_lds_bytes(sizeof(T), max_n, pl->dense_maxcols);
+      // The rows each slice's columns use, copied to LDS for the column half:
+      // the range they span, or a list of them where they fill less than half
+      // of it (a few columns of a covariance-steering instance reach rows of
+      // every stage).
+      const size_t room = ((size_t)TEAM_MAX_LDS - team_lds_bytes(sizeof(T), max_n, pl->dense_maxcols)) / 16 * 16;
+      At_loc.resize(nnz);
+      std::vector<int32_t> place(m, -1);
+      std::vector<int64_t> seen(m, -1);
       for (size_t q = 0; q < (size_t)pl->B * V; ++q) {
-        int64_t lo = m, hi = 0;
-        for (int64_t j = colcut[q]; j < colcut[q + 1]; ++j)
-          if (trp[j + 1] > trp[j]) {   // rows of a column are in increasing order
-            lo = std::min<int64_t>(lo, tcol[trp[j]]);
-            hi = std::max<int64_t>(hi, tcol[trp[j + 1] - 1] + 1);
+        const int64_t ka = trp[colcut[q]], ke = trp[colcut[q + 1]];
+        std::vector<int32_t> rows;
+        for (int64_t k = ka; k < ke; ++k)
+          if (seen[tcol[k]] != (int64_t)q) {
+            seen[tcol[k]] = (int64_t)q;
+            rows.push_back(tcol[k]);
           }
-        trange.push_back(std::min(lo, hi));
-        trange.push_back(hi);
-        const size_t wide = (size_t)std::max<int64_t>(hi - lo, 0) * 8, narrow = (size_t)std::max<int64_t>(hi - lo, 0) * sizeof(T);
-        pl->team.tcap = std::max<int64_t>(pl->team.tcap, (int64_t)(wide <= room ? wide : narrow <= room ? narrow : 0));
+        std::sort(rows.begin(), rows.end());
+        const int64_t cnt = (int64_t)rows.size(), lo = cnt ? rows.front() : 0, range = cnt ? rows.back() + 1 - lo : 0;
+        if (range <= 2 * cnt) {
+          used.push_back(lo);
+          used.push_back(range);
+          for (int64_t k = ka; k < ke; ++k) At_loc[k] = (uint16_t)(tcol[k] - lo);
+        } else {
+          used.push_back(-1 - (int64_t)uses.size());
+          used.push_back(cnt);
+          for (int64_t i = 0; i < cnt; ++i) place[rows[i]] = (int32_t)i;
+          for (int64_t k = ka; k < ke; ++k) At_loc[k] = (uint16_t)place[tcol[k]];
+          uses.insert(uses.end(), rows.begin(), rows.end());
+        }
       }
       sliceA = sort_by_slice(rowsA, pl->bkA, rp, rinst, rslice, pl->B, V, midA);
       sliceAt = sort_by_slice(rowsAt, pl->bkAt, trp, cinst, cslice, pl->B, V, midAt);
+      // where the entries of a slice's listed rows begin in its LDS copy, and
+      // the LDS that the copies want: the used rows (float64 in the residual
+      // pass) and, next to them in the data's type, the slice's rows, then
+      // also its columns
+      const int64_t BV = (int64_t)pl->B * V;
+      entries.assign(2 * (size_t)BV, 0);
+      std::vector<int64_t> listed(2 * (size_t)BV, 0);
+      auto keep = [&](const std::vector<int32_t> &rows, const std::vector<int64_t> &cut, const std::vector<int64_t> &ptr,
+                      int side, std::vector<int32_t> &begin) {
+        begin.resize(rows.size());
+        for (int64_t q = 0; q < BV; ++q)
+          for (int c = 0; c < 3; ++c)
+            for (int64_t k = cut[c * (BV + 1) + q]; k < cut[c * (BV + 1) + q + 1]; ++k) {
+              begin[k] = entries[2 * q + side];
+              entries[2 * q + side] += (int32_t)(ptr[rows[k] + 1] - ptr[rows[k]]);
+              ++listed[2 * q + side];
+            }
+      };
+      keep(rowsA, sliceA, rp, 0, keptA);
+      keep(rowsAt, sliceAt, trp, 1, keptAt);
+      for (int64_t q = 0; q < BV; ++q) {
+        const int64_t t = (used[2 * q + 1] * (int64_t)sizeof(T) + 15) / 16 * 16, wide = used[2 * q + 1] * 8;
+        const int64_t a = t + team_kept_bytes(listed[2 * q], entries[2 * q], sizeof(T), true);
+        const int64_t both = a + team_kept_bytes(listed[2 * q + 1], entries[2 * q + 1], sizeof(T), false);
+        for (int64_t want : {t, wide, a, both})
+          if (want <= (int64_t)room) pl->team.cap = std::max(pl->team.cap, want);
+      }
+      pl->team.cap = (pl->team.cap + 15) / 16 * 16;
       order.resize(pl->B);
       std::iota(order.begin(), order.end(), 0);
       std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return work[a] > work[b]; });
@@ -729,9 +773,14 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   const size_t o_slAt = take(std::max<size_t>(sliceAt.size(), 1) * sizeof(int64_t));
   const size_t o_mA = take(std::max<size_t>(midA.size(), 1) * sizeof(int64_t));
   const size_t o_mAt = take(std::max<size_t>(midAt.size(), 1) * sizeof(int64_t));
-  const size_t o_tr = take(std::max<size_t>(trange.size(), 1) * sizeof(int64_t));
+  const size_t o_used = take(std::max<size_t>(used.size(), 1) * sizeof(int64_t));
+  const size_t o_uses = take(std::max<size_t>(uses.size(), 1) * sizeof(int32_t));
+  const size_t o_loc = take(std::max<size_t>(At_loc.size(), 1) * sizeof(uint16_t));
   const size_t o_cut = take(std::max<size_t>(colcut.size(), 1) * sizeof(int64_t));
   const size_t o_ord = take(std::max<size_t>(order.size(), 1) * sizeof(int32_t));
+  const size_t o_kA = take(std::max<size_t>(keptA.size(), 1) * sizeof(int32_t));
+  const size_t o_kAt = take(std::max<size_t>(keptAt.size(), 1) * sizeof(int32_t));
+  const size_t o_ent = take(std::max<size_t>(entries.size(), 1) * sizeof(int32_t));
   if (hipMalloc(&pl->mem.ptr, off) != hipSuccess) {
     pl->mem.ptr = nullptr;
     FAIL(COSMO_ENOMEM, "plan allocation of " + std::to_string(off) + " bytes failed");
@@ -768,16 +817,26 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   HIPCHK(up(o_slAt, sliceAt.data(), sliceAt.size() * sizeof(int64_t)));
   HIPCHK(up(o_mA, midA.data(), midA.size() * sizeof(int64_t)));
   HIPCHK(up(o_mAt, midAt.data(), midAt.size() * sizeof(int64_t)));
-  HIPCHK(up(o_tr, trange.data(), trange.size() * sizeof(int64_t)));
+  HIPCHK(up(o_used, used.data(), used.size() * sizeof(int64_t)));
+  HIPCHK(up(o_uses, uses.data(), uses.size() * sizeof(int32_t)));
+  HIPCHK(up(o_loc, At_loc.data(), At_loc.size() * sizeof(uint16_t)));
   HIPCHK(up(o_cut, colcut.data(), colcut.size() * sizeof(int64_t)));
   HIPCHK(up(o_ord, order.data(), order.size() * sizeof(int32_t)));
+  HIPCHK(up(o_kA, keptA.data(), keptA.size() * sizeof(int32_t)));
+  HIPCHK(up(o_kAt, keptAt.data(), keptAt.size() * sizeof(int32_t)));
+  HIPCHK(up(o_ent, entries.data(), entries.size() * sizeof(int32_t)));
   pl->team.sliceA = reinterpret_cast<int64_t *>(base + o_slA);
   pl->team.sliceAt = reinterpret_cast<int64_t *>(base + o_slAt);
   pl->team.midA = reinterpret_cast<int64_t *>(base + o_mA);
   pl->team.midAt = reinterpret_cast<int64_t *>(base + o_mAt);
-  pl->team.trange = reinterpret_cast<int64_t *>(base + o_tr);
+  pl->team.used = reinterpret_cast<int64_t *>(base + o_used);
+  pl->team.uses = reinterpret_cast<int32_t *>(base + o_uses);
+  pl->team.At_loc = reinterpret_cast<uint16_t *>(base + o_loc);
   pl->team.colcut = reinterpret_cast<int64_t *>(base + o_cut);
   pl->team.order = reinterpret_cast<int32_t *>(base + o_ord);
+  pl->team.keptA = reinterpret_cast<int32_t *>(base + o_kA);
+  pl->team.keptAt = reinterpret_cast<int32_t *>(base + o_kAt);
+  pl->team.entries = reinterpret_cast<int32_t *>(base + o_ent);
   pl->d_n_off = reinterpret_cast<int64_t *>(base + o_noff);
   pl->d_m_off = reinterpret_cast<int64_t *>(base + o_moff);
   pl->d_At_rowptr = reinterpret_cast<int64_t *>(base + o_trp);
