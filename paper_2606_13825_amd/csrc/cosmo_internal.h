@@ -105,7 +105,7 @@ template <typename T> struct View {
   // call's workspace (block rows, block columns, block columns).
   const DenseDesc *dense; const int32_t *dense_inst;
   const int32_t *drow; const double *dscale; const int32_t *dcol;
-  int32_t n_dense, dense_maxcols, dense_wg_rows, dense_wg_cols, dense_g32;
+  int32_t n_dense, dense_maxcols, dense_wg_rows, dense_wg_cols, dense_g32, dense_strip;
   double *dn; double *ec; double *ed;
 };
 
@@ -231,7 +231,8 @@ enum DenseColMode : int32_t {
 };
 template <typename T> void launch_dense_rows(const View<T> &v, const T *vin, hipStream_t st);
 int32_t dense_row_workgroups(int32_t rows);
-int32_t dense_col_workgroups(int32_t cols, size_t esz);
+int32_t dense_col_workgroups(int32_t cols, size_t esz, int32_t pieces);
+constexpr int32_t DENSE_STRIP = 64, DENSE_NARROW = 8;   // 16-byte pieces of a column strip
 template <typename T> void launch_dense_cols(const View<T> &v, int32_t mode, const T *rho_hat, const T *u,
                                             const T *s, hipStream_t st);
 

@@ -10,12 +10,16 @@
 //   flight per wave, float64 accumulation, the four rows summed over the
 //   wave together (fixed order).
 // Column products ec[coff + c] = sum_r G_rc w_r  (and ed = sum_r G_rc^2 wd_r)
-//   one workgroup per (block, 64-piece column strip); the workgroup first
-//   forms the row weights of a tile of 2048 rows in LDS (w_r sums the
-//   placements' scale times the mode's per-row value), then its four waves
-//   walk a quarter of the tile each, every lane owning one piece of the
-//   strip; the four waves' partial sums are added in wave order.  Sums are
-//   float64 and deterministic.
+//   one workgroup per (block, column strip); the workgroup first forms the
+//   row weights of a tile of 2048 rows in LDS (w_r sums the placements' scale
+//   times the mode's per-row value), then its four waves walk a quarter of
+//   the tile each, every lane owning one piece of the strip; the partial sums
+//   of the waves' lane groups are added in order.  Sums are float64 and
+//   deterministic.  What bounds it is the loads a workgroup keeps in flight,
+//   so few strips leave the device idle: a strip is 64 pieces (one row per
+//   wave at a time) where that gives at least one workgroup per compute unit,
+//   else 8 pieces (a 128-byte line of eight rows at a time).  4 blocks of 2000
+//   x 500 in float32: 8 workgroups took 196 us, 64 take 39 us.
 #include "cosmo_internal.h"
 #include "wave_ops.h"
 
@@ -129,7 +133,7 @@ __device__ inline void row_weights(const DenseDesc &d, const ColArgs &a, int r, 
   }
 }
 
-template <typename T, typename TG>
+template <typename T, typename TG, int LP>   // LP: pieces of a strip
 __global__ __launch_bounds__(NT) void k_dense_cols(const DenseDesc *__restrict__ dd, int32_t nd, ColArgs a,
                                                    double *__restrict__ ec, double *__restrict__ ed) {
   constexpr int VE = 16 / sizeof(TG);
@@ -139,7 +143,9 @@ __global__ __launch_bounds__(NT) void k_dense_cols(const DenseDesc *__restrict__
   const bool diag = a.mode == DC_XI || a.mode == DC_GST;
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
   const int npieces = (d.cols + VE - 1) / VE;
-  const int pc = (int)(blockIdx.x - d.wg_cols0) * 64 + lane;   // this lane's piece of the strip
+  constexpr int SUB = 64 / LP;   // rows a wave reads at a time
+  const int sub = lane / LP;
+  const int pc = (int)(blockIdx.x - d.wg_cols0) * LP + lane % LP;   // this lane's piece of the strip
   const bool has = pc < npieces;
   const Piece<TG> *G = static_cast<const Piece<TG> *>(d.val);
   const int64_t ldp = d.ld / VE;
@@ -159,17 +165,17 @@ __global__ __launch_bounds__(NT) void k_dense_cols(const DenseDesc *__restrict__
     const int q0 = wave * (TILE / NW);
     const int q1 = min(nr, q0 + TILE / NW);
     constexpr int U = 8;
-    for (int q = q0; q < q1; q += U) {
+    for (int q = q0 + sub; q < q1; q += U * SUB) {
       Piece<TG> g[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int r = min(q + u, q1 - 1);
+        const int r = min(q + u * SUB, q1 - 1);
         if (has) g[u] = G[(int64_t)(t0 + r) * ldp + pc];
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        if (q + u < q1 && has) {
-          const double w = wt[q + u], wd = wdt[q + u];
+        if (q + u * SUB < q1 && has) {
+          const double w = wt[q + u * SUB], wd = wdt[q + u * SUB];
 #pragma unroll
           for (int e = 0; e < VE; ++e) {
             const double gv = (double)g[u].v[e];
@@ -186,14 +192,15 @@ __global__ __launch_bounds__(NT) void k_dense_cols(const DenseDesc *__restrict__
     part[1][wave][lane * VE + e] = accd[e];
   }
   __syncthreads();
-  for (int k = threadIdx.x; k < 64 * VE; k += NT) {
-    const int c = ((int)(blockIdx.x - d.wg_cols0) * 64) * VE + k;
+  for (int k = threadIdx.x; k < LP * VE; k += NT) {
+    const int c = ((int)(blockIdx.x - d.wg_cols0) * LP) * VE + k;
     if (c >= d.cols) continue;
     double s0 = 0.0, s1 = 0.0;
-    for (int w = 0; w < NW; ++w) {
-      s0 += part[0][w][k];
-      s1 += part[1][w][k];
-    }
+    for (int w = 0; w < NW; ++w)
+      for (int q = 0; q < SUB; ++q) {
+        s0 += part[0][w][q * LP * VE + k];
+        s1 += part[1][w][q * LP * VE + k];
+      }
     ec[d.coff + c] = s0;
     if (diag) ed[d.coff + c] = s1;
   }
@@ -213,17 +220,22 @@ template <typename T>
 void launch_dense_cols(const View<T> &v, int32_t mode, const T *rho_hat, const T *u, const T *s, hipStream_t st) {
   if (v.n_dense <= 0 || v.dense_wg_cols <= 0) return;
   ColArgs a{mode, rho_hat, u, s, v.b};
-  if (sizeof(T) == 8 && v.dense_g32)
-    k_dense_cols<T, float><<<v.dense_wg_cols, NT, 0, st>>>(v.dense, v.n_dense, a, v.ec, v.ed);
-  else
-    k_dense_cols<T, T><<<v.dense_wg_cols, NT, 0, st>>>(v.dense, v.n_dense, a, v.ec, v.ed);
+  auto go = [&](auto kern) { kern<<<v.dense_wg_cols, NT, 0, st>>>(v.dense, v.n_dense, a, v.ec, v.ed); };
+  auto pick = [&](auto tg) {
+    using TG = decltype(tg);
+    if (v.dense_strip == DENSE_STRIP) go(&k_dense_cols<T, TG, DENSE_STRIP>);
+    else go(&k_dense_cols<T, TG, DENSE_NARROW>);
+  };
+  if (sizeof(T) == 8 && v.dense_g32) pick(float{});
+  else pick(T{});
 }
 
 // Workgroup counts of the two launches for a block (the host lays out
-// DenseDesc::wg_rows0 / wg_cols0 with these); esz: bytes per stored value.
+// DenseDesc::wg_rows0 / wg_cols0 with these); esz: bytes per stored value,
+// pieces: of a column strip.
 int32_t dense_row_workgroups(int32_t rows) { return (rows + ROWS_PER_WG - 1) / ROWS_PER_WG; }
-int32_t dense_col_workgroups(int32_t cols, size_t esz) {
-  const int32_t strip = 64 * (int32_t)(16 / esz);
+int32_t dense_col_workgroups(int32_t cols, size_t esz, int32_t pieces) {
+  const int32_t strip = pieces * (int32_t)(16 / esz);
   return (cols + strip - 1) / strip;
 }
 

@@ -104,7 +104,7 @@ struct cosmo_plan {
   RowBuckets bkA, bkAt;
   int64_t sum_p = 0, sum_p2 = 0, sum_p2_large = 0;
   // dense sub-blocks of A (descriptors ordered by instance)
-  int32_t n_dense = 0, dense_maxcols = 0, dense_wg_rows = 0, dense_wg_cols = 0;
+  int32_t n_dense = 0, dense_maxcols = 0, dense_wg_rows = 0, dense_wg_cols = 0, dense_strip = DENSE_STRIP;
   bool dense_g32 = false;   // the blocks' values are stored as float32
   int64_t dense_rows_tot = 0, dense_cols_tot = 0;
   DenseDesc *d_dense = nullptr;
@@ -207,6 +207,7 @@ template <typename T> View<T> make_view(const cosmo_plan *pl) {
   v.dense_maxcols = pl->dense_maxcols;
   v.dense_wg_rows = pl->dense_wg_rows;
   v.dense_wg_cols = pl->dense_wg_cols;
+  v.dense_strip = pl->dense_strip;
   v.dense_g32 = pl->dense_g32 ? 1 : 0;
   v.dn = v.ec = v.ed = nullptr;   // set per call from the call's workspace
   return v;
@@ -563,7 +564,12 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
     }
     std::stable_sort(dens.begin(), dens.end(), [](const DenseDesc &a, const DenseDesc &b) { return a.inst < b.inst; });
     int64_t doff = 0, coff = 0;
-    int32_t wr = 0, wc = 0;
+    int32_t wr = 0, wc = 0, wide = 0, dev = 0, ncu = 0;
+    const size_t dsz = pl->dense_g32 ? 4 : sizeof(T);
+    HIPCHK(hipGetDevice(&dev));
+    HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    for (const DenseDesc &d : dens) wide += dense_col_workgroups(d.cols, dsz, DENSE_STRIP);
+    pl->dense_strip = wide >= ncu ? DENSE_STRIP : DENSE_NARROW;
     for (size_t k = 0; k < dens.size(); ++k) {
       DenseDesc &d = dens[k];
       d.doff = doff;
@@ -579,7 +585,7 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
       doff += d.rows;
       coff += d.cols;
       wr += dense_row_workgroups(d.rows);
-      wc += dense_col_workgroups(d.cols, pl->dense_g32 ? 4 : sizeof(T));
+      wc += dense_col_workgroups(d.cols, dsz, pl->dense_strip);
       pl->dense_maxcols = std::max(pl->dense_maxcols, d.cols);
       dinst[d.inst + 1]++;
     }
