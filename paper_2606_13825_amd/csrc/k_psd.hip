@@ -694,6 +694,153 @@ __global__ __launch_bounds__(NT) void k_psd_vjp(const PsdDesc *__restrict__ desc
   }
 }
 
+// The same for orders above 128, where U and B1 do not fit the LDS beside B0:
+// a wave takes a strip of 16 result columns, E tiles in registers, so the
+// strip's operand is read once, and each lane takes four consecutive k of a
+// group of 16 (one 16-byte load where the operand is stored along k).  Bound
+// by the matrix cores at 13 waves on four of them and the operands' latency;
+// tile by tile, each reading both its operands in single strided entries,
+// 16 blocks of orders 129 to 200 in float32 took 612 us, so 238.
+template <typename T, int E>
+__device__ __forceinline__ void vjp_large(const PsdDesc &d, const T *__restrict__ U, const T *lam_s,
+                                          const T *__restrict__ gb, T *__restrict__ ob, T *B1, T *B0, int rule,
+                                          T eps, int NT) {
+  typedef typename Mma<T>::v4 v4;
+  const int p = d.p, l0 = large_ld(p);
+  const int tid = threadIdx.x, J = tid >> 6, lane = tid & 63, r = lane & 15, kk = lane >> 4;
+  const int nrows = p * (p + 1) / 2;
+  for (int idx = tid; idx < nrows; idx += NT) {
+    const int j = svec_col(idx);
+    const int i = idx - j * (j + 1) / 2;
+    T val = gb[idx];
+    if (i != j) val *= (T)RSQRT2;
+    B0[i + j * l0] = val;
+    B0[j + i * l0] = val;
+  }
+  for (int j = tid; j < p; j += NT)
+    for (int i = p; i < l0; ++i) B0[i + j * l0] = (T)0;
+  __syncthreads();
+  const bool act = J < E;
+  const int col = 16 * J + r;   // this lane's column of the strip
+  const bool in = act && col < p;
+  const int cs = in ? col : 0;
+  v4 acc[E];
+  // acc[t] = sum_k a(t, k..k+3) b(k..k+3) for the tiles t that `tiles` wants;
+  // both are zero from k = p on
+  auto strip = [&](auto tiles, auto a4, auto b4) {
+#pragma unroll
+    for (int t = 0; t < E; ++t) acc[t] = v4{0, 0, 0, 0};
+    for (int k0 = 0; k0 < p; k0 += 16) {
+      const int k = k0 + 4 * kk;
+      T b[4];
+      b4(k, b);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) b[w] = in ? b[w] : (T)0;
+#pragma unroll
+      for (int t = 0; t < E; ++t)
+        if (tiles(t)) {
+          T a[4];
+          a4(min(16 * t + r, p - 1), k, a);
+#pragma unroll
+          for (int w = 0; w < 4; ++w) acc[t] = Mma<T>::op(a[w], b[w], acc[t]);
+        }
+    }
+  };
+  // four entries along k of column c of a p x p matrix, of its row c, and of B0
+  auto along = [&](const T *M, int c, int k, T (&x)[4]) {
+    if (k + 4 <= p) {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) x[w] = M[k + w + c * p];
+    } else {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) x[w] = k + w < p ? M[k + w + c * p] : (T)0;
+    }
+  };
+  auto across = [&](const T *M, int c, int k, T (&x)[4]) {
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const T e = M[c + min(k + w, p - 1) * p];
+      x[w] = k + w < p ? e : (T)0;
+    }
+  };
+  auto lds4 = [&](int c, int k, T (&x)[4]) {   // B0 is symmetric; its rows p to l0 - 1 are zero
+#pragma unroll
+    for (int w = 0; w < 4; ++w) x[w] = 0;
+    if (k < p) {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) x[w] = B0[k + w + c * l0];
+    }
+  };
+  auto all = [](int) { return true; };
+  auto upper = [&](int t) { return t <= J; };
+  auto put_b1 = [&]() {
+#pragma unroll
+    for (int t = 0; t < E; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = 16 * t + Mma<T>::row(lane, e);
+        if (row < p && in) B1[row + col * p] = acc[t][e];
+      }
+  };
+  if (act) {   // B1 = B0 U
+    strip(all, lds4, [&](int k, T (&x)[4]) { along(U, cs, k, x); });
+    put_b1();
+  }
+  __syncthreads();
+  if (act) {   // B0 = W o (U' B1), upper tiles; one lane writes an entry to both places
+    strip(upper, [&](int i, int k, T (&x)[4]) { along(U, i, k, x); }, [&](int k, T (&x)[4]) { along(B1, cs, k, x); });
+#pragma unroll
+    for (int t = 0; t < E; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = 16 * t + Mma<T>::row(lane, e);
+        if (t <= J && row <= col && in) {
+          const T val = vjp_weight<T>(rule, lam_s[row], lam_s[col], row == col, eps) * acc[t][e];
+          B0[row + col * l0] = val;
+          B0[col + row * l0] = val;
+        }
+      }
+  }
+  __syncthreads();
+  if (act) {   // B1 = U B0
+    strip(all, [&](int i, int k, T (&x)[4]) { across(U, i, k, x); }, [&](int k, T (&x)[4]) { lds4(cs, k, x); });
+    put_b1();
+  }
+  __syncthreads();
+  if (act) {   // out = svec(B1 U'), upper tiles
+    strip(upper, [&](int i, int k, T (&x)[4]) { across(B1, i, k, x); }, [&](int k, T (&x)[4]) { across(U, cs, k, x); });
+#pragma unroll
+    for (int t = 0; t < E; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = 16 * t + Mma<T>::row(lane, e);
+        if (t <= J && row <= col && in)
+          ob[col * (col + 1) / 2 + row] = row == col ? acc[t][e] : acc[t][e] * (T)SQRT2;
+      }
+  }
+}
+
+template <typename T, int E, int EMAX, typename... A>
+__device__ __forceinline__ void vjp_large_by_order(const PsdDesc &d, A... args) {
+  if constexpr (E < EMAX) {
+    if (d.p > 16 * E) return vjp_large_by_order<T, E + 1, EMAX>(d, args...);
+  }
+  vjp_large<T, E>(d, args...);
+}
+
+template <typename T, int EMAX>
+__global__ __launch_bounds__(64 * EMAX) void k_psd_vjp_large(const PsdDesc *__restrict__ descs,
+                                                             const T *__restrict__ Ug, const T *__restrict__ lam,
+                                                             const T *__restrict__ g, T *__restrict__ out,
+                                                             T *__restrict__ scratch, int32_t rule, T eps) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ T lam_s[MAXP];
+  const PsdDesc d = descs[blockIdx.x];
+  for (int i = threadIdx.x; i < d.p; i += 64 * EMAX) lam_s[i] = lam[d.loff + i];
+  vjp_large_by_order<T, 9, EMAX>(d, Ug + d.uoff, lam_s, g + d.row0, out + d.row0, scratch + d.uoff,
+                                 reinterpret_cast<T *>(smem_raw), rule, eps, 64 * EMAX);
+}
+
 constexpr size_t LDS_LIMIT = 163840;
 
 // Allow a kernel the whole LDS of a workgroup minus its static allocation;
@@ -799,10 +946,24 @@ bool run_vjp(const PsdDesc *d, int32_t n, int32_t max_p, const T *U, const T *la
 }
 
 template <typename T>
+bool run_vjp_large(const PsdDesc *d, int32_t n, int32_t max_p, const T *U, const T *lam, const T *g, T *out, T *scratch,
+                   hipStream_t st, int32_t rule, double eps) {
+  constexpr int PMAX = std::is_same<T, float>::value ? COSMO_MAX_PSD_ORDER_F32 : COSMO_MAX_PSD_ORDER_F64;
+  constexpr int EMAX = (PMAX + 15) / 16;
+  static size_t dyn_bytes = 0;
+  if (dyn_bytes == 0) dyn_bytes = set_dyn_lds_cap(reinterpret_cast<const void *>(&k_psd_vjp_large<T, EMAX>));
+  const size_t need = (size_t)max_p * large_ld(max_p) * sizeof(T);
+  if (max_p > PMAX || need > dyn_bytes) return false;
+  k_psd_vjp_large<T, EMAX><<<n, 64 * EMAX, need, st>>>(d, U, lam, g, out, scratch, rule, (T)eps);
+  return true;
+}
+
+template <typename T>
 bool launch_psd_vjp(const PsdDesc *d, int32_t n, int32_t max_p, const T *U, const T *lam, const T *g, T *out,
                     T *scratch, hipStream_t st, int32_t rule, double eps, int32_t threads) {
   if (n <= 0) return true;
   static_assert(kVjpThreads == 1024 && kVjpThreadsAlt == 512, "VJP shapes");
+  if (max_p > 128) return run_vjp_large<T>(d, n, max_p, U, lam, g, out, scratch, st, rule, eps);
   if (threads == kVjpThreadsAlt) return run_vjp<T, 512>(d, n, max_p, U, lam, g, out, scratch, st, rule, eps);
   return run_vjp<T, 1024>(d, n, max_p, U, lam, g, out, scratch, st, rule, eps);
 }
