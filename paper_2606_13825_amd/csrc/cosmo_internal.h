@@ -325,6 +325,11 @@ template <typename T> void launch_psd_step(const PsdDesc *d, int32_t n, const Ps
                                            const T *rho_hat, const T *vv, const T *sh, const T *y, T *s_new,
                                            T *y_new, T *U, T *lam, double *rscratch, const T *Uprev,
                                            cosmo_stats *stats, hipStream_t st);
+// A projection without a plan: blocks of the classes up to order 128, in class
+// order (begin: of the three classes and their end; maxp: their largest).
+template <typename T> void launch_psd_proj(const PsdDesc *d, const int32_t *begin, const int32_t *maxp,
+                                           const PsdLaunchCfg &cfg, const T *in, T *out, T *U, T *lam,
+                                           double *rscratch, int32_t ncu, hipStream_t st);
 // rule 0 = Daleckii-Krein, 1 = eigendecomposition rule as autograd forms it,
 // 2 = rule 1 at the eigenvalues shifted by eps (Tikhonov).  Returns false
 // (nothing launched) when a block of order max_p does not fit in LDS.

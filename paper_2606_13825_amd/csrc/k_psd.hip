@@ -179,18 +179,22 @@ __device__ inline void list_positive(const double *lamd, int p, short *pos_idx, 
 // quarter more (LDS traffic, cross-lane moves), and the eigenpairs need no
 // refinement afterwards (245 us of 979 at order 100 when they were swept in
 // float32).
-template <typename T, int NT, int G, int NB, int PMAX>
-__global__ __launch_bounds__(NT) void k_psd_eig(const EigArgs<T> a) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  double *W = reinterpret_cast<double *>(smem_raw);
-  __shared__ double red[NT / 64];
-  // eigenvalues; during the sweeps the scalars that travel with the columns
-  __shared__ __align__(16) double lamd[jacobi_cols<NB>(PMAX)];
-  __shared__ short pos_idx[PMAX + 16];
-  __shared__ int mx_s[7];
-  __shared__ int npos_s;
+// Static LDS of the kernels that follow: eigenvalues (the scalars that travel
+// with the columns during the sweeps), positive indices, sums.
+template <int NT, int PMAX> struct EigShared {
+  __attribute__((aligned(16))) double lamd[PMAX];   // (a multiple of whole pairs of column blocks)
+  double red[NT / 64];
+  short pos_idx[PMAX + 16];
+  int mx_s[7];
+  int npos;
+};
 
-  const PsdDesc d = a.descs[blockIdx.x];
+template <typename T, int NT, int G, int NB, int PMAX, int SMAX>
+__device__ __forceinline__ void eig_block(const EigArgs<T> &a, const PsdDesc &d, double *W, EigShared<NT, SMAX> &sm) {
+  static_assert(jacobi_cols<NB>(PMAX) == PMAX && PMAX <= SMAX, "one scalar per column");
+  double *lamd = sm.lamd, *red = sm.red;
+  short *pos_idx = sm.pos_idx;
+  int *mx_s = sm.mx_s;
   const int p = d.p;
   const int ld = eig_ld<G, NB>(p), nc = jacobi_cols<NB>(p);
   const int nrows = p * (p + 1) / 2;
@@ -302,10 +306,10 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const EigArgs<T> a) {
       const int i = e / p, j = e - i * p;
       Ut[e] = W[i + j * ld];
     }
-  list_positive(lamd, p, pos_idx, &npos_s);
+  list_positive(lamd, p, pos_idx, &sm.npos);
   if (tid == 0) count_sweeps(a, d, sw);
   __syncthreads();
-  const int npos = npos_s;
+  const int npos = sm.npos;
   for (int t = wave; t < ntiles; t += NWv) {
     int I, J;
     upper_tile(t, I, J);
@@ -325,6 +329,30 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const EigArgs<T> a) {
       if (row <= col && col < p) put(row, col, acc[e]);
     }
   }
+}
+
+template <typename T, int NT, int G, int NB, int PMAX>
+__global__ __launch_bounds__(NT) void k_psd_eig(const EigArgs<T> a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ EigShared<NT, PMAX> sm;
+  const PsdDesc d = a.descs[blockIdx.x];
+  eig_block<T, NT, G, NB, PMAX>(a, d, reinterpret_cast<double *>(smem_raw), sm);
+}
+
+// Blocks of several of those classes in one launch, all with the threads of
+// the largest (the smaller ones' sweeps leave waves at the barriers).  For
+// calls whose blocks do not fill the device: class after class, such a launch
+// takes as long as its largest block, three times over (48 float64 blocks of
+// orders 20 to 100: 82 + 214 + 502 us; together 502).
+template <typename T>
+__global__ __launch_bounds__(512) void k_psd_eig_mixed(const EigArgs<T> a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  __shared__ EigShared<512, 128> sm;
+  const PsdDesc d = a.descs[blockIdx.x];
+  double *W = reinterpret_cast<double *>(smem_raw);
+  if (d.p <= 32) eig_block<T, 512, 8, 2, 32>(a, d, W, sm);
+  else if (d.p <= 64) eig_block<T, 512, 16, 2, 64>(a, d, W, sm);
+  else eig_block<T, 512, 16, 4, 128>(a, d, W, sm);
 }
 
 // Blocks of order above 128 (float32 to 200, float64 to 140).  In float64
@@ -861,16 +889,21 @@ template <int G, int NB, int E, int EMAX, int PMAX> constexpr int exchange_elems
   return Exchange<G, NB, E, PMAX>::elems;
 }
 
+// Dynamic LDS of a block of order p in a class.
+template <int G, int NB, int PMAX> size_t eig_lds(int32_t p) {
+  const size_t block = (size_t)jacobi_cols<NB>(p) * (size_t)eig_ld<G, NB>(p);
+  const size_t exch = (size_t)exchange_elems<G, NB, 1, (PMAX + G - 1) / G, PMAX>(p);
+  return std::max(block, exch) * sizeof(double);
+}
+
 template <typename T, int NT, int G, int NB, int PMAX>
 void run_eig(const EigArgs<T> &a, int32_t n, int32_t max_p, hipStream_t st) {
-  const size_t block = (size_t)jacobi_cols<NB>(max_p) * (size_t)eig_ld<G, NB>(max_p);
-  const size_t exch = (size_t)exchange_elems<G, NB, 1, (PMAX + G - 1) / G, PMAX>(max_p);
   static bool attr_set = false;
   if (!attr_set) {
     set_dyn_lds_cap(reinterpret_cast<const void *>(&k_psd_eig<T, NT, G, NB, PMAX>));
     attr_set = true;
   }
-  k_psd_eig<T, NT, G, NB, PMAX><<<n, NT, std::max(block, exch) * sizeof(double), st>>>(a);
+  k_psd_eig<T, NT, G, NB, PMAX><<<n, NT, eig_lds<G, NB, PMAX>(max_p), st>>>(a);
 }
 
 template <typename T, int PMAX>
@@ -916,6 +949,37 @@ void launch_psd_step(const PsdDesc *d, int32_t n, const PsdLaunchCfg &cfg, const
     if (alt) run_eig<T, 1024, 16, 2, 128>(a, n, mp, st); else run_eig<T, 512, 16, 4, 128>(a, n, mp, st);
   } else {
     run_eig_large<T, std::is_same<T, float>::value ? COSMO_MAX_PSD_ORDER_F32 : COSMO_MAX_PSD_ORDER_F64>(a, n, mp, st);
+  }
+}
+
+// Classes 0 to 2 of a projection without a plan, descriptors in class order;
+// begin, maxp: of the three classes.  One launch for all where more than one
+// has blocks and all of them together do not fill the device.
+template <typename T>
+void launch_psd_proj(const PsdDesc *d, const int32_t *begin, const int32_t *maxp, const PsdLaunchCfg &cfg, const T *in,
+                     T *out, T *U, T *lam, double *rscratch, int32_t ncu, hipStream_t st) {
+  const int32_t n = begin[3] - begin[0];
+  const int classes = (begin[1] > begin[0]) + (begin[2] > begin[1]) + (begin[3] > begin[2]);
+  if (classes > 1 && n <= ncu) {
+    const EigArgs<T> a{d + begin[0], cfg.max_sweeps, cfg.tol, 1, nullptr, in, nullptr, nullptr, out, nullptr, U, lam,
+                       nullptr, cfg.refine, rscratch, 0, 0};
+    size_t lds = 0;
+    if (begin[1] > begin[0]) lds = std::max(lds, eig_lds<8, 2, 32>(maxp[0]));
+    if (begin[2] > begin[1]) lds = std::max(lds, eig_lds<16, 2, 64>(maxp[1]));
+    if (begin[3] > begin[2]) lds = std::max(lds, eig_lds<16, 4, 128>(maxp[2]));
+    static bool attr_set = false;
+    if (!attr_set) {
+      set_dyn_lds_cap(reinterpret_cast<const void *>(&k_psd_eig_mixed<T>));
+      attr_set = true;
+    }
+    k_psd_eig_mixed<T><<<n, 512, lds, st>>>(a);
+    return;
+  }
+  for (int c = 0; c < 3; ++c) {
+    PsdLaunchCfg one = cfg;
+    one.max_p = maxp[c];
+    launch_psd_step<T>(d + begin[c], begin[c + 1] - begin[c], one, nullptr, in, nullptr, nullptr, out, nullptr, U, lam,
+                       rscratch, nullptr, nullptr, st);
   }
 }
 
@@ -974,6 +1038,10 @@ template void launch_psd_step<float>(const PsdDesc *, int32_t, const PsdLaunchCf
 template void launch_psd_step<double>(const PsdDesc *, int32_t, const PsdLaunchCfg &, const double *,
                                       const double *, const double *, const double *, double *, double *, double *,
                                       double *, double *, const double *, cosmo_stats *, hipStream_t);
+template void launch_psd_proj<float>(const PsdDesc *, const int32_t *, const int32_t *, const PsdLaunchCfg &,
+                                     const float *, float *, float *, float *, double *, int32_t, hipStream_t);
+template void launch_psd_proj<double>(const PsdDesc *, const int32_t *, const int32_t *, const PsdLaunchCfg &,
+                                      const double *, double *, double *, double *, double *, int32_t, hipStream_t);
 template bool launch_psd_vjp<float>(const PsdDesc *, int32_t, int32_t, const float *, const float *, const float *,
                                     float *, float *, hipStream_t, int32_t, double, int32_t);
 template bool launch_psd_vjp<double>(const PsdDesc *, int32_t, int32_t, const double *, const double *,

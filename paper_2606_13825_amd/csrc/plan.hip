@@ -2277,16 +2277,20 @@ cosmo_status psd_proj(int32_t nblk, const int32_t *order, const int64_t *offset,
   double *rs = reinterpret_cast<double *>(static_cast<char *>(ws) +
                                           align_up((size_t)nblk * std::max(sizeof(PsdDesc), sizeof(SocDesc)), 256));
   const int rf = dtype == COSMO_F32 ? refine : 0;
-  for (int c = 0; c < 4; ++c) {
-    const int n = cb[c + 1] - cb[c];
-    if (!n) continue;
-    PsdLaunchCfg cfg{max_sweeps, eig_tol, rf, cm[c]};
-    if (dtype == COSMO_F32)
-      launch_psd_step<float>(d + cb[c], n, cfg, nullptr, (const float *)in, nullptr, nullptr, (float *)out, nullptr,
-                             (float *)eigvecs, (float *)eigvals, rs, nullptr, nullptr, st);
-    else
-      launch_psd_step<double>(d + cb[c], n, cfg, nullptr, (const double *)in, nullptr, nullptr, (double *)out,
-                              nullptr, (double *)eigvecs, (double *)eigvals, rs, nullptr, nullptr, st);
+  int dev = 0, ncu = 0;
+  HIPCHK(hipGetDevice(&dev));
+  HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+  PsdLaunchCfg cfg{max_sweeps, eig_tol, rf, cm[3]};
+  const int large = cb[4] - cb[3];
+  if (dtype == COSMO_F32) {
+    launch_psd_proj<float>(d, cb, cm, cfg, (const float *)in, (float *)out, (float *)eigvecs, (float *)eigvals, rs, ncu, st);
+    launch_psd_step<float>(d + cb[3], large, cfg, nullptr, (const float *)in, nullptr, nullptr, (float *)out, nullptr,
+                           (float *)eigvecs, (float *)eigvals, rs, nullptr, nullptr, st);
+  } else {
+    launch_psd_proj<double>(d, cb, cm, cfg, (const double *)in, (double *)out, (double *)eigvecs, (double *)eigvals, rs,
+                            ncu, st);
+    launch_psd_step<double>(d + cb[3], large, cfg, nullptr, (const double *)in, nullptr, nullptr, (double *)out,
+                            nullptr, (double *)eigvecs, (double *)eigvals, rs, nullptr, nullptr, st);
   }
   HIPCHK(hipGetLastError());
   return COSMO_OK;
