@@ -51,20 +51,28 @@ PEAK_HBM_GBS = 8000.0
 # Algorithmic work of one PSD block of order p: 9 p^3 for a textbook symmetric
 # eigendecomposition (eigenvectors included) + 2 p^3 for U max(L, 0) U'.
 EIG_FLOPS_PER_P3 = 11.0
-# The library's PSD order classes: lanes per Jacobi pair, largest order (per
-# dtype for the last class) and the orders they hold.
-EIG_CLASSES = {0: (4, "32", "orders <= 32"), 1: (8, "64", "orders 33-64"), 2: (8, "128", "orders 65-128"),
-               3: (8, None, "orders above 128")}
+# The library's PSD order classes: by threads, lanes and columns of a column
+# block; largest order and the orders they hold.
+EIG_CLASSES = {0: ({64: (8, 2), 128: (16, 2)}, "32", "orders <= 32"),
+               1: ({256: (16, 2), 512: (16, 2)}, "64", "orders 33-64"),
+               2: ({512: (16, 4), 1024: (16, 2)}, "128", "orders 65-128")}
 
 
 def eig_kernel_name(cls: int, threads: int, f32: bool) -> str:
     """Instantiation of the eigensolve kernel that ran order class cls."""
-    g, pmax, what = EIG_CLASSES[cls]
-    pmax = pmax or ("200" if f32 else "140")
-    return f"k_psd_eig<{'float' if f32 else 'double'},{threads},{g},{pmax}> ({what})"
+    t = "float" if f32 else "double"
+    if cls == 3:
+        return f"k_psd_eig_large<{t},{200 if f32 else 140}> (orders above 128)"
+    shapes, pmax, what = EIG_CLASSES[cls]
+    g, nb = shapes[threads]
+    return f"k_psd_eig<{t},{threads},{g},{nb},{pmax}> ({what})"
+
+
 EIG_PROFILE = os.path.join(ROOT, "profiles", "k_psd_eig_maxcut64_pmc.md")
-# the eigensolve kernels are built from k_psd.hip and the shared tile helpers
+# the eigensolve kernels are built from k_psd.hip, the sweeps and the shared
+# tile helpers
 EIG_SOURCE = [os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "k_psd.hip"),
+              os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "jacobi_sweeps.h"),
               os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "mma_tiles.h")]
 PCG_PROFILE = os.path.join(ROOT, "profiles", "k_pcg_huber256_pmc.md")
 PCG_C5_PROFILE = os.path.join(ROOT, "profiles", "k_pcg_coop_covsteer128_pmc.md")
@@ -73,6 +81,7 @@ NS_SOURCE = [os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "k_ns.hip"),
              os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "mma_tiles.h")]
 APPB_PROFILE = os.path.join(ROOT, "profiles", "k_pcg_coop_appb_pmc.md")
 PCG_SOURCE = [os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "k_pcg.hip"),
+              os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "pcg_ops.h"),
               os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "wave_ops.h")]
 
 
@@ -491,11 +500,12 @@ def appb_study(ns=(1000, 2000, 5000, 10000, 20000, 50000), reps=3, seed=8, dense
                                  "pcg_form": 4, "cg_tol": APPB_CG_TOL, "reps": reps,
                                  "dense_baselines": dense_baselines},
                       "rows": rows,
-                      "roofline": {"kernel": "k_pcg_coop<float> (backward adjoint solve)", "n": last["n"],
+                      "roofline": {"kernel": "k_pcg_team<float> or, above 64 MB per application, k_pcg_coop<float> "
+                                             "(backward adjoint solve)", "n": last["n"],
                                    "bound": "hbm", "achieved": last["bwd_cg_gbs"], "peak": PEAK_HBM_GBS,
                                    "unit": "GB/s", "frac": last["bwd_cg_gbs"] / PEAK_HBM_GBS,
                                    "traffic": traffic_from_profile(APPB_PROFILE, PCG_SOURCE, n=last["n"]),
-                                   "traffic_per": "one backward adjoint solve (one k_pcg_coop launch)"}}))
+                                   "traffic_per": "one backward adjoint solve (one launch)"}}))
 
 
 def psd_trajectory_study(K=100, seed=5, alpha=1.6, ns_iters=40, fd_rel_step=1e-6):
@@ -1049,7 +1059,7 @@ def main():
         ach = total / n_pcg / (avg_ms * 1e-3) / 1e9
         form = batch.pcg_form()
         tn = "float" if esz == 4 else "double"
-        kname = (f"k_pcg_coop<{tn}> (cooperative, <= {form} workgroups per CU)" if form > 0
+        kname = (f"k_pcg_team<{tn}> or, above 64 MB per application, k_pcg_coop<{tn}> (form {form})" if form > 0
                  else f"k_pcg<{tn}> (one workgroup per instance"
                       + ((", dense blocks fused" + (", stored float32)" if gsz < esz else ")"))
                          if batch.n_dense else ")"))
