@@ -280,9 +280,15 @@ struct TeamView {
   int64_t cap_off = 0;         // where they begin (set at the launch)
   double *ecp = nullptr;       // per slice, the dense blocks' column products
   int64_t ec_stride = 0;       // their length
+  // the dense columns of slice s of instance b, in column order:
+  // dense_list[dense_cut[b slices + s] .. next) are their entries of ecp, and
+  // dense_slot[j] is column j's place among them (-1: not a dense column)
+  const int64_t *dense_cut = nullptr;
+  const int32_t *dense_list = nullptr, *dense_slot = nullptr;
+  int32_t dense_slots = 0;     // most of them in a slice
 };
 size_t team_state_bytes(int32_t teams_per_xcd);
-size_t team_lds_bytes(size_t esz, int64_t max_n, int32_t dense_maxcols);   // without cap
+size_t team_lds_bytes(size_t esz, int64_t max_n, int32_t dense_maxcols, int32_t dense_slots);   // without cap
 void launch_team_reset(const TeamView &tv, hipStream_t st);
 // Bytes of such a copy (16-byte multiple): row ids, where their entries
 // begin, rho_hat (rows) or nothing (columns), values, 16-bit indices.

@@ -303,7 +303,7 @@ __global__ __launch_bounds__(NTH) void k_pcg_team(View<T> v, TeamView tv, const 
   __shared__ double sum_s[3];
   __shared__ int32_t flag_s;
   __shared__ uint32_t join_s[3];
-  __shared__ int64_t cuts[TEAM_MAX_SLICES][18];
+  __shared__ int64_t cuts[TEAM_MAX_SLICES][20];
   const int tid = threadIdx.x;
   const int V = tv.slices;
   TeamHead *head = static_cast<TeamHead *>(tv.state);
@@ -352,20 +352,23 @@ __global__ __launch_bounds__(NTH) void k_pcg_team(View<T> v, TeamView tv, const 
     const int b = tv.order[pos];
     const int64_t n0 = v.n_off[b], n1 = v.n_off[b + 1];
     const int n = (int)(n1 - n0);
-    double *dl = dyn_lds + ((size_t)n * sizeof(T) + 7) / 8;   // the waves' partials of the dense product
+    // the waves' partials of the dense product, then the sums of a slice's dense columns
+    double *dl = dyn_lds + ((size_t)n * sizeof(T) + 7) / 8;
     const int64_t BV = (int64_t)v.B * V, bV = (int64_t)b * V;
     const Local<T> pv{pl, (int32_t)n0};
     char *tl = reinterpret_cast<char *>(dyn_lds) + tv.cap_off;   // the copied rows of t, then a kept slice
 
     // where this workgroup's slices begin and end: list ranges of the rows
     // (0-6: three classes, the last one's short and long rows) and of the
-    // columns (7-13), the rows the columns use (14, 15), the columns (16, 17)
-    for (int e = tid; e < 18 * V; e += NTH) {
-      const int s = e / 18, k = e % 18;
+    // columns (7-13), the rows the columns use (14, 15), the columns (16, 17),
+    // the dense ones among them (18, 19)
+    for (int e = tid; e < 20 * V; e += NTH) {
+      const int s = e / 20, k = e % 20;
       if (s % (int)tm.size != (int)tm.rank) continue;
       const int64_t *sl = (k < 7 ? tv.sliceA : tv.sliceAt) + bV + s, *mid = (k < 7 ? tv.midA : tv.midAt) + bV + s;
       const int q = k < 7 ? k : k - 7;
-      cuts[s][k] = k >= 16 ? tv.colcut[bV + s + k - 16] : k >= 14 ? tv.used[2 * (bV + s) + k - 14]
+      cuts[s][k] = k >= 18 ? (DMP > 0 ? tv.dense_cut[bV + s + k - 18] : 0) : k >= 16 ? tv.colcut[bV + s + k - 16]
+                   : k >= 14 ? tv.used[2 * (bV + s) + k - 14]
                    : q == 5 ? *mid : q == 6 ? sl[2 * (BV + 1) + 1] : sl[(q / 2) * (BV + 1) + (q & 1)];
     }
     __syncthreads();
@@ -450,17 +453,19 @@ __global__ __launch_bounds__(NTH) void k_pcg_team(View<T> v, TeamView tv, const 
       row_pass<64, AT>(rows, span, cut[5], cut[6], tid / 64, NTH / 64, col, val, vin, all, emit);
     };
     // The dense blocks' column products of slice s's columns, summed over the
-    // slices in order, into dl (by column of the slice): half a wave per column.
+    // slices in order, into dl (by place among the slice's dense columns, of
+    // which dl has room for the most a slice has): half a wave per column.
     auto dense_columns = [&](int s) {
-      const int64_t c0 = cuts[s][16], c1 = cuts[s][17];
+      const int32_t *list = tv.dense_list + cuts[s][18];
+      const int cnt = (int)(cuts[s][19] - cuts[s][18]);
       const int lane = tid % 32;
-      for (int64_t base = c0; base < c1; base += 4 * (NTH / 32)) {
+      for (int base = 0; base < cnt; base += 4 * (NTH / 32)) {
         int32_t e[4];
         double x[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int64_t j = base + u * (NTH / 32) + tid / 32;
-          e[u] = j < c1 ? v.dcol[j] : -1;
+          const int k = base + u * (NTH / 32) + tid / 32;
+          e[u] = k < cnt ? list[k] : -1;
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -471,7 +476,7 @@ __global__ __launch_bounds__(NTH) void k_pcg_team(View<T> v, TeamView tv, const 
           for (int u = 0; u < 4; ++u) x[u] += __shfl_xor(x[u], off, 64);
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          if (e[u] >= 0 && lane == 0) dl[base + u * (NTH / 32) + tid / 32 - c0] = x[u];
+          if (e[u] >= 0 && lane == 0) dl[base + u * (NTH / 32) + tid / 32] = x[u];
       }
       __syncthreads();
     };
@@ -535,10 +540,11 @@ __global__ __launch_bounds__(NTH) void k_pcg_team(View<T> v, TeamView tv, const 
     // that and the dense blocks' part of (A' t)_j, added to the column half's
     // sum where the column's owner reads it (all loads of a column
     // independent, none behind the sum)
-    auto col_rest = [&](auto acc, int64_t j, int s) {
+    auto col_rest = [&](auto acc, int64_t j) {
       using AT = decltype(acc);
       if constexpr (DMP > 0) {
-        if (v.dcol[j] >= 0) acc += (AT)dl[j - cuts[s][16]];
+        const int32_t q = tv.dense_slot[j];
+        if (q >= 0) acc += (AT)dl[q];
       }
       return col_diag(acc, j);
     };
@@ -620,7 +626,7 @@ __global__ __launch_bounds__(NTH) void k_pcg_team(View<T> v, TeamView tv, const 
         T rz = 0, rr = 0;
         double rt = 0, dd = 0;
         own(s, [&](int64_t j) {
-          const T rj = (T)(rhs[j] - col_rest(c64[j], j, s));
+          const T rj = (T)(rhs[j] - col_rest(c64[j], j));
           r[j] = rj;
           const T zj = rj / dg[j];
           z[j] = zj;
@@ -677,7 +683,7 @@ __global__ __launch_bounds__(NTH) void k_pcg_team(View<T> v, TeamView tv, const 
           own(s, [&](int64_t j) {
             const bool pre = j == jf;
             x[j] = (pre ? xf : x[j]) + a * pl[j - n0];
-            const T rj = (pre ? rf : r[j]) - a * col_rest(Mp[j], j, s);
+            const T rj = (pre ? rf : r[j]) - a * col_rest(Mp[j], j);
             const T zj = rj / (pre ? df : dg[j]);
             r[j] = rj;
             z[j] = zj;
@@ -763,10 +769,12 @@ void launch_team_reset(const TeamView &tv, hipStream_t st) {
   k_team_reset<<<(int)std::min<int64_t>((n + 255) / 256, 64), 256, 0, st>>>(static_cast<uint32_t *>(tv.state), n);
 }
 
-// Dynamic LDS of a workgroup: the longest instance's vector, and the waves'
-// partials of the dense product (float64 in the residual pass).
-size_t team_lds_bytes(size_t esz, int64_t max_n, int32_t dense_maxcols) {
-  return (size_t)(max_n * (int64_t)esz + 7) / 8 * 8 + (dense_maxcols > 0 ? (size_t)(512 / 64) * dense_maxcols * 8 : 0);
+// Dynamic LDS of a workgroup: the longest instance's vector, and one region
+// for the waves' partials of the dense product (float64 in the residual pass)
+// and for the sums of a slice's dense columns.
+size_t team_lds_bytes(size_t esz, int64_t max_n, int32_t dense_maxcols, int32_t dense_slots) {
+  const int64_t dense = std::max<int64_t>((int64_t)(NTH / 64) * dense_maxcols, dense_slots);
+  return (size_t)(max_n * (int64_t)esz + 7) / 8 * 8 + (size_t)dense * 8;
 }
 
 template <typename T>
@@ -775,7 +783,7 @@ void launch_pcg_team(const View<T> &v, const TeamView &tv, const T *rho_hat, con
                      const T *xold, T *xnew, const T *gx_in, T *gx_out, int32_t mode, cosmo_stats *stats,
                      hipStream_t st) {
   TeamView tvl = tv;
-  tvl.cap_off = (int64_t)(team_lds_bytes(sizeof(T), tv.max_n, v.n_dense > 0 ? v.dense_maxcols : 0) + 15) / 16 * 16;
+  tvl.cap_off = (int64_t)(team_lds_bytes(sizeof(T), tv.max_n, v.n_dense > 0 ? v.dense_maxcols : 0, tv.dense_slots) + 15) / 16 * 16;
   auto go = [&](auto kern) {
     static bool attr_set = false;   // more than the default 64 KiB of dynamic LDS may be needed
     if (!attr_set) {

@@ -619,8 +619,8 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   // CG teams: slices of every instance's rows and columns, cut by their
   // entries; the rows of a dense block (all its placements) go with the
   // block's row, so a slice completes its part of the block by itself
-  std::vector<int64_t> sliceA, sliceAt, midA, midAt, colcut, used;
-  std::vector<int32_t> order, keptA, keptAt, entries, uses;
+  std::vector<int64_t> sliceA, sliceAt, midA, midAt, colcut, used, dense_cut;
+  std::vector<int32_t> order, keptA, keptAt, entries, uses, dense_list, dense_slot;
   std::vector<uint16_t> At_loc;
   if (!pl->diag_M) {
     int dev = 0, ncu = 0;
@@ -638,18 +638,12 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
       bytes = std::max(bytes, nz * 2 * (4 + sizeof(T)) + gb);
       max_n = std::max(max_n, pl->n_off[b + 1] - pl->n_off[b]);
     }
-    const bool fits = team_lds_bytes(sizeof(T), max_n, pl->dense_maxcols) <= (size_t)TEAM_MAX_LDS;
-    const int32_t V = fits ? team_slices(work, ncu) : 0;
+    auto lds = [&](int32_t dense_slots) { return team_lds_bytes(sizeof(T), max_n, pl->dense_maxcols, dense_slots); };
+    int32_t V = lds(0) <= (size_t)TEAM_MAX_LDS ? team_slices(work, ncu) : 0;
+    std::vector<int32_t> rslice, cslice;
     if (V > 0) {
-      pl->team.slices = V;
-      pl->team.teams_per_xcd = (TEAM_MAX_SLICES + V - 1) / V;
-      pl->team.grid = (int32_t)std::min<int64_t>(ncu, (int64_t)TEAM_XCDS * V * ((pl->B + TEAM_XCDS - 1) / TEAM_XCDS));
-      pl->team.max_n = max_n;
-      pl->team.ec_stride = pl->dense_cols_tot;
-      // one die reads about 1 TB/s; the device-wide form reads the whole
-      // device's 4 TB/s but pays about 60 us of grid barriers per iteration
-      pl->team_wide = bytes > 64e6;
-      std::vector<int32_t> rslice(m), cslice(n);
+      rslice.resize(m);
+      cslice.resize(n);
       colcut.assign((size_t)pl->B * V + 1, 0);
       for (int b = 0; b < pl->B; ++b) {
         auto cut = [&](int64_t i0, int64_t i1, auto weight, std::vector<int32_t> &out) {   // weight < 0: placed already
@@ -680,11 +674,43 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
         }
       }
       colcut[(size_t)pl->B * V] = n;
+      // the dense columns of each slice; no teams where the most of them that
+      // a slice has do not fit the LDS
+      if (!dcolm.empty()) {
+        dense_slot.assign(n, -1);
+        dense_cut.assign(colcut.size(), 0);
+        for (size_t q = 0; q + 1 < colcut.size(); ++q) {
+          for (int64_t j = colcut[q]; j < colcut[q + 1]; ++j)
+            if (dcolm[j] >= 0) {
+              dense_slot[j] = (int32_t)(dense_list.size() - dense_cut[q]);
+              dense_list.push_back(dcolm[j]);
+            }
+          dense_cut[q + 1] = (int64_t)dense_list.size();
+          pl->team.dense_slots = std::max(pl->team.dense_slots, (int32_t)(dense_cut[q + 1] - dense_cut[q]));
+        }
+      }
+      if (lds(pl->team.dense_slots) > (size_t)TEAM_MAX_LDS) {
+        V = pl->team.dense_slots = 0;
+        colcut.clear();
+        dense_cut.clear();
+        dense_list.clear();
+        dense_slot.clear();
+      }
+    }
+    if (V > 0) {
+      pl->team.slices = V;
+      pl->team.teams_per_xcd = (TEAM_MAX_SLICES + V - 1) / V;
+      pl->team.grid = (int32_t)std::min<int64_t>(ncu, (int64_t)TEAM_XCDS * V * ((pl->B + TEAM_XCDS - 1) / TEAM_XCDS));
+      pl->team.max_n = max_n;
+      pl->team.ec_stride = pl->dense_cols_tot;
+      // one die reads about 1 TB/s; the device-wide form reads the whole
+      // device's 4 TB/s but pays about 60 us of grid barriers per iteration
+      pl->team_wide = bytes > 64e6;
       // The rows each slice's columns use, copied to LDS for the column half:
       // the range they span, or a list of them where they fill less than half
       // of it (a few columns of a covariance-steering instance reach rows of
       // every stage).
-      const size_t room = ((size_t)TEAM_MAX_LDS - team_lds_bytes(sizeof(T), max_n, pl->dense_maxcols)) / 16 * 16;
+      const size_t room = ((size_t)TEAM_MAX_LDS - lds(pl->team.dense_slots)) / 16 * 16;
       At_loc.resize(nnz);
       std::vector<int32_t> place(m, -1);
       std::vector<int64_t> seen(m, -1);
@@ -787,6 +813,9 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   const size_t o_kA = take(std::max<size_t>(keptA.size(), 1) * sizeof(int32_t));
   const size_t o_kAt = take(std::max<size_t>(keptAt.size(), 1) * sizeof(int32_t));
   const size_t o_ent = take(std::max<size_t>(entries.size(), 1) * sizeof(int32_t));
+  const size_t o_dcut = take(std::max<size_t>(dense_cut.size(), 1) * sizeof(int64_t));
+  const size_t o_dlist = take(std::max<size_t>(dense_list.size(), 1) * sizeof(int32_t));
+  const size_t o_dslot = take(std::max<size_t>(dense_slot.size(), 1) * sizeof(int32_t));
   if (hipMalloc(&pl->mem.ptr, off) != hipSuccess) {
     pl->mem.ptr = nullptr;
     FAIL(COSMO_ENOMEM, "plan allocation of " + std::to_string(off) + " bytes failed");
@@ -831,6 +860,12 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   HIPCHK(up(o_kA, keptA.data(), keptA.size() * sizeof(int32_t)));
   HIPCHK(up(o_kAt, keptAt.data(), keptAt.size() * sizeof(int32_t)));
   HIPCHK(up(o_ent, entries.data(), entries.size() * sizeof(int32_t)));
+  HIPCHK(up(o_dcut, dense_cut.data(), dense_cut.size() * sizeof(int64_t)));
+  HIPCHK(up(o_dlist, dense_list.data(), dense_list.size() * sizeof(int32_t)));
+  HIPCHK(up(o_dslot, dense_slot.data(), dense_slot.size() * sizeof(int32_t)));
+  pl->team.dense_cut = reinterpret_cast<int64_t *>(base + o_dcut);
+  pl->team.dense_list = reinterpret_cast<int32_t *>(base + o_dlist);
+  pl->team.dense_slot = reinterpret_cast<int32_t *>(base + o_dslot);
   pl->team.sliceA = reinterpret_cast<int64_t *>(base + o_slA);
   pl->team.sliceAt = reinterpret_cast<int64_t *>(base + o_slAt);
   pl->team.midA = reinterpret_cast<int64_t *>(base + o_mA);
