@@ -110,11 +110,14 @@ template <typename T> __device__ __forceinline__ SweepRule sweep_rule(const EigA
   return rule;
 }
 
-// Power of two that brings the columns of a block shifted by c to order one.
+// Power of two that brings the columns of a block shifted by c to order one,
+// whatever c is: the sweeps judge a pair of columns by the product of their
+// squared norms, which for larger or smaller columns leaves the range it is
+// formed in.
 __device__ __forceinline__ double column_scale(double c) {
   int e = 0;
   (void)frexp(c, &e);
-  return ldexp(1.0, e > 120 ? -120 : (e < -120 ? 120 : -e));
+  return ldexp(1.0, -e);   // c is positive and finite, the root of a float64 sum at most: |e| < 540
 }
 
 // A non-finite block yields a non-finite projection (never a clipped one).
