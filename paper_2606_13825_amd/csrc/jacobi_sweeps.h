@@ -11,9 +11,11 @@
 // four operations.  Squared norms are carried along (|a|^2 - t g, |b|^2 + t g
 // with g = a'b) and formed afresh at every sweep, so one inner product per
 // pair remains.  The scalars of pair q sit in the lanes with lane % NB == q,
-// so the NB pairs' rotations cost one evaluation.  The angle is computed in
-// float32 (any t gives an orthogonal rotation; an inexact one leaves a little
-// more for the next sweep); 1 / (1 + t^2) is formed to working precision.
+// so the NB pairs' rotations cost one evaluation.  The angle, the test whether
+// a pair is rotated and the measures that end the sweeps are formed in the
+// data's own type (Sc; any t gives an orthogonal rotation, an inexact one
+// leaves a little more for the next sweep); 1 / (1 + t^2) is formed to working
+// precision.  In float32 for float64 data they would save 2.5 %.
 //
 // Blocks stand in a row of positions; a sweep is one odd-even transposition
 // pass: the blocks at positions (0,1), (2,3), .. are rotated and change
@@ -47,6 +49,8 @@
 // projection of an order-100 float64 block, this 487 us; two-column blocks at
 // order 100 (twice the exchanges, two waves per SIMD) 64 us per sweep.
 #pragma once
+
+#include <type_traits>
 
 #include "cosmo_internal.h"
 
@@ -108,17 +112,43 @@ __device__ __forceinline__ double full_rcp(double x) {
   return fma(fma(-x, y, 1.0), y, y);
 }
 
+// 1 / x and 1 / sqrt(x) for the angles: the hardware's in float32; in float64
+// one Newton step on it (47 bits or more).
+__device__ __forceinline__ float angle_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ __forceinline__ double angle_rcp(double x) {
+  const double y = __builtin_amdgcn_rcp(x);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ __forceinline__ float angle_rsq(float x) { return __builtin_amdgcn_rsqf(x); }
+__device__ __forceinline__ double angle_rsq(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+
 // What a sweep has seen: the largest squared cosine of a column pair and the
 // largest squared tangent of a rotation.
-struct SweepMax {
-  float cos2, tan2;
+template <typename Sc> struct SweepMax {
+  Sc cos2, tan2;
+};
+// The same over the workgroup, three sweeps in turn (non-negative numbers
+// order like their bits), and whether the columns were put in another order.
+template <typename Sc> struct SweepShared {
+  using Bits = std::conditional_t<sizeof(Sc) == 8, unsigned long long, unsigned int>;
+  Bits cos2[3], tan2[3];
+  int moved;
+  __device__ __forceinline__ void clear() {   // by the first threads, before a barrier
+    if (threadIdx.x < 3) cos2[threadIdx.x] = tan2[threadIdx.x] = 0;
+    if (threadIdx.x == 3) moved = 0;
+  }
+  static __device__ __forceinline__ Bits bits(Sc x) { return __builtin_bit_cast(Bits, x); }
+  static __device__ __forceinline__ Sc value(Bits b) { return __builtin_bit_cast(Sc, b); }
 };
 
 // Rotates NB disjoint pairs (a[q], b[q]); al, da, be, db: squared norms and D
 // of pair q's columns in the lanes of index q.
-template <int G, int NB, int E>
-__device__ __forceinline__ void rotate_pairs(double *const (&a)[NB], double *const (&b)[NB], double &al, double &da, double &be, double &db, float tol2,
-                                    SweepMax &mx) {
+template <int G, int NB, int E, typename Sc>
+__device__ __forceinline__ void rotate_pairs(double *const (&a)[NB], double *const (&b)[NB], double &al, double &da,
+                                             double &be, double &db, Sc tol2, SweepMax<Sc> &mx) {
   double dots[NB];
 #pragma unroll
   for (int q = 0; q < NB; ++q) dots[q] = a[q][0] * b[q][0];
@@ -128,16 +158,16 @@ __device__ __forceinline__ void rotate_pairs(double *const (&a)[NB], double *con
     for (int q = 0; q < NB; ++q) dots[q] = fma(a[q][e], b[q][e], dots[q]);
   const double g = group_sums<G, NB>(dots);
   const double P = da * db, Pg = P * g;
-  const float gf = (float)g, g2 = gf * (float)Pg;   // (a'b)^2
-  const float ab = (float)al * (float)be;
+  const Sc gs = (Sc)g, g2 = gs * (Sc)Pg;   // (a'b)^2
+  const Sc ab = (Sc)al * (Sc)be;
   const bool rot = g2 > tol2 * ab;
   if constexpr (E * NB >= 20) {
     if (__ballot(rot) == 0) return;   // nothing to rotate in this wave
   }
-  const float d = (float)(be - al);
-  const float r2 = fmaf(4.f, g2, d * d);
-  float tau = 2.f * gf * __builtin_amdgcn_rcpf(fmaf(r2, __builtin_amdgcn_rsqf(r2), fabsf(d)));
-  tau = rot ? copysignf(1.f, d) * tau : 0.f;   // t / (d_a d_b); 0 where r2 = 0
+  const Sc d = (Sc)(be - al);
+  const Sc r2 = fma((Sc)4, g2, d * d);
+  Sc tau = 2 * gs * angle_rcp(fma(r2, angle_rsq(r2), fabs(d)));
+  tau = rot ? copysign((Sc)1, d) * tau : (Sc)0;   // t / (d_a d_b); 0 where r2 = 0
   const double cx = (double)tau * db, cy = (double)tau * da;
   const double t2 = cx * cy, sec2 = 1.0 + t2, k = (double)tau * Pg;
   const double cs2 = rot ? full_rcp(sec2) : 1.0;
@@ -158,8 +188,8 @@ __device__ __forceinline__ void rotate_pairs(double *const (&a)[NB], double *con
   be += k;
   da *= cs2;
   db *= sec2;
-  mx.cos2 = fmaxf(mx.cos2, g2 * __builtin_amdgcn_rcpf(ab));   // (a zero column's NaN is dropped)
-  mx.tan2 = fmaxf(mx.tan2, (float)t2);
+  mx.cos2 = fmax(mx.cos2, g2 * angle_rcp(ab));   // (a zero column's NaN is dropped)
+  mx.tan2 = fmax(mx.tan2, (Sc)t2);
 }
 
 template <int NB, int E> struct JacobiRegs {
@@ -169,8 +199,8 @@ template <int NB, int E> struct JacobiRegs {
 };
 
 // The cross pairs of blocks X and Y: step S pairs (x_q, y_(q+S)).
-template <int G, int NB, int E, int S>
-__device__ __forceinline__ void cross_step(JacobiRegs<NB, E> &R, float tol2, SweepMax &mx) {
+template <int G, int NB, int E, int S, typename Sc>
+__device__ __forceinline__ void cross_step(JacobiRegs<NB, E> &R, Sc tol2, SweepMax<Sc> &mx) {
   double *a[NB], *b[NB];
 #pragma unroll
   for (int q = 0; q < NB; ++q) {
@@ -181,8 +211,8 @@ __device__ __forceinline__ void cross_step(JacobiRegs<NB, E> &R, float tol2, Swe
   R.be = next_lane<NB>(R.be);
   R.db = next_lane<NB>(R.db);
 }
-template <int G, int NB, int E>
-__device__ __forceinline__ void cross_pairs(JacobiRegs<NB, E> &R, float tol2, SweepMax &mx) {
+template <int G, int NB, int E, typename Sc>
+__device__ __forceinline__ void cross_pairs(JacobiRegs<NB, E> &R, Sc tol2, SweepMax<Sc> &mx) {
   cross_step<G, NB, E, 0>(R, tol2, mx);
   cross_step<G, NB, E, 1>(R, tol2, mx);
   if constexpr (NB == 4) {
@@ -193,8 +223,8 @@ __device__ __forceinline__ void cross_pairs(JacobiRegs<NB, E> &R, float tol2, Sw
 
 // The pairs (I0, J0), (I1, J1) of X and of Y at once (NB = 4); lanes 0 and 1
 // of a quad take X's scalars, lanes 2 and 3 Y's.
-template <int G, int E, int I0, int J0, int I1, int J1>
-__device__ __forceinline__ void inside_step4(JacobiRegs<4, E> &R, float tol2, SweepMax &mx) {
+template <int G, int E, int I0, int J0, int I1, int J1, typename Sc>
+__device__ __forceinline__ void inside_step4(JacobiRegs<4, E> &R, Sc tol2, SweepMax<Sc> &mx) {
   const int m = threadIdx.x & 3;
   const bool hi = m >= 2;
   auto gather_a = [&](double fx, double fy) {
@@ -225,8 +255,8 @@ __device__ __forceinline__ void inside_step4(JacobiRegs<4, E> &R, float tol2, Sw
 }
 
 // The pairs inside the blocks, once per sweep.
-template <int G, int NB, int E>
-__device__ __forceinline__ void inside_pairs(JacobiRegs<NB, E> &R, float tol2, SweepMax &mx) {
+template <int G, int NB, int E, typename Sc>
+__device__ __forceinline__ void inside_pairs(JacobiRegs<NB, E> &R, Sc tol2, SweepMax<Sc> &mx) {
   if constexpr (NB == 4) {
     inside_step4<G, E, 0, 1, 2, 3>(R, tol2, mx);
     inside_step4<G, E, 0, 2, 1, 3>(R, tol2, mx);
@@ -266,11 +296,13 @@ template <int NB, int E> __device__ __forceinline__ void rescale(double (&col)[N
 // which the couplings left are below stop: they are no larger than the
 // largest that it met (max|cos|), nor than what its rotations can have left
 // behind, p max|tan| max|cos| (they mix a rotated pair's remainder with
-// another pair's coupling).  At most max_sweeps sweeps, or, with coarse2 > 0,
+// another pair's coupling).  (Sweeping on until nothing is rotated took 12 %
+// longer in an unroll of order-20 float64 blocks, 3 % at orders up to 100, for
+// the same errors against 80-bit arithmetic.)  At most max_sweeps sweeps, or, with coarse2 > 0,
 // max_sweeps until the largest squared cosine is below coarse2 and then up to
 // max_fine more.
-struct SweepRule {
-  float tol2, stop, coarse2;
+template <typename Sc> struct SweepRule {
+  Sc tol2, stop, coarse2;
   int max_sweeps, max_fine;
 };
 struct SweepCount {
@@ -320,16 +352,16 @@ template <int G, int NB> __device__ __forceinline__ BlockCols block_cols(const J
 // group g's X and the next NB its Y, zero past the block, column norms of
 // order one; idle groups hold zeros.  Ends with column blocks at their
 // positions, reversed after an odd number of sweeps (rev).  xb:
-// Exchange::elems, sc: jacobi_cols<NB>(p) elements, rk: as many, mx_s: 7
-// zeroed ints; all are free to use from the first barrier on, which is the
+// Exchange::elems, sc: jacobi_cols<NB>(p) elements, rk: as many, mx_s:
+// cleared; all are free to use from the first barrier on, which is the
 // first thing.  put(column, row, value) and get(column, row) reach a store of
 // jacobi_cols<NB>(p) columns and p rows in which columns are put in order
 // (put past column p - 1 may be dropped, get gives zeros there); it may
 // overlap xb.  ordered: the columns start in order (a warm start's).
-template <int NT, int G, int NB, int E, int PMAX, typename Put, typename Get>
+template <int NT, int G, int NB, int E, int PMAX, typename Sc, typename Put, typename Get>
 __device__ __forceinline__ SweepCount jacobi_sweeps(JacobiRegs<NB, E> &R, const JacobiPlace<G, NB> &at, double *xb,
-                                                    double *sc, short *rk, int p, const SweepRule &rule, bool ordered,
-                                                    int *mx_s, int &rev, Put put, Get get) {
+                                                    double *sc, short *rk, int p, const SweepRule<Sc> &rule, bool ordered,
+                                                    SweepShared<Sc> &mx_s, int &rev, Put put, Get get) {
   using X = Exchange<G, NB, E, PMAX>;
   const int tid = threadIdx.x, q = tid % NB, grp = at.grp, gl = at.gl, ng = at.ng;
   const bool act = at.act, busy = at.busy, last = grp == ng - 1;
@@ -371,7 +403,7 @@ __device__ __forceinline__ SweepCount jacobi_sweeps(JacobiRegs<NB, E> &R, const 
   int total = 0;
   rev = 0;
   while (!n.converged && (fine ? n.fine < rule.max_fine : n.sweeps < rule.max_sweeps)) {
-    SweepMax mx{0.f, 0.f};
+    SweepMax<Sc> mx{0, 0};
     if (busy) {
       R.al = R.da * norms(R.x);
       R.be = R.db * norms(R.y);
@@ -400,11 +432,11 @@ __device__ __forceinline__ SweepCount jacobi_sweeps(JacobiRegs<NB, E> &R, const 
         if constexpr (TPC == 4) rank += __builtin_amdgcn_update_dpp(0, rank, DPP_XOR2, 0xF, 0xF, true);
         if (tid % TPC == 0) {
           rk[col] = (short)rank;
-          if (rank != col) mx_s[6] = total + 1;
+          if (rank != col) mx_s.moved = total + 1;
         }
       }
       __syncthreads();
-      if (mx_s[6] == total + 1) {
+      if (mx_s.moved == total + 1) {
         if (act) {
           auto move = [&](int col0, const double (&v)[NB][E], double D, double norm) {
             const double f = sqrt(D);
@@ -498,28 +530,29 @@ __device__ __forceinline__ SweepCount jacobi_sweeps(JacobiRegs<NB, E> &R, const 
       }
     }
     rev ^= 1;
-    // the sweep's maxima over the workgroup (non-negative floats order like their bits)
-    int *slot = mx_s + 2 * (total % 3), *next = mx_s + 2 * ((total + 1) % 3);
+    // the sweep's maxima over the workgroup
+    using Shared = SweepShared<Sc>;
+    const int slot = total % 3, next = (total + 1) % 3;
     if (busy) {
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) {
-        mx.cos2 = fmaxf(mx.cos2, __shfl_xor(mx.cos2, off, 64));
-        mx.tan2 = fmaxf(mx.tan2, __shfl_xor(mx.tan2, off, 64));
+        mx.cos2 = fmax(mx.cos2, __shfl_xor(mx.cos2, off, 64));
+        mx.tan2 = fmax(mx.tan2, __shfl_xor(mx.tan2, off, 64));
       }
       if (tid % 64 == 0) {
-        atomicMax(&slot[0], __float_as_int(mx.cos2));
-        atomicMax(&slot[1], __float_as_int(mx.tan2));
+        atomicMax(&mx_s.cos2[slot], Shared::bits(mx.cos2));
+        atomicMax(&mx_s.tan2[slot], Shared::bits(mx.tan2));
       }
     }
-    if (tid == 0) next[0] = next[1] = 0;
+    if (tid == 0) mx_s.cos2[next] = mx_s.tan2[next] = 0;
     __syncthreads();
-    const float c2 = __int_as_float(slot[0]), t2 = __int_as_float(slot[1]);
+    const Sc c2 = Shared::value(mx_s.cos2[slot]), t2 = Shared::value(mx_s.tan2[slot]);
     order = c2 > ORDER2;
     ++total;
     if (fine) ++n.fine;
     else ++n.sweeps;
-    n.converged = t2 == 0.f || fminf(1.f, (float)p * sqrtf(t2)) * sqrtf(c2) <= rule.stop;
-    if (!fine && rule.coarse2 > 0.f && (c2 <= rule.coarse2 || n.sweeps >= rule.max_sweeps)) {
+    n.converged = t2 == 0 || fmin((Sc)1, (Sc)p * sqrt(t2)) * sqrt(c2) <= rule.stop;
+    if (!fine && rule.coarse2 > 0 && (c2 <= rule.coarse2 || n.sweeps >= rule.max_sweeps)) {
       fine = true;
       coarse_ok = n.converged || c2 <= rule.coarse2;
     }
@@ -560,9 +593,9 @@ template <int G, int NB, int E> __device__ __forceinline__ ColumnNorms unit_colu
 // to order one.  Leaves in W the normalised columns and in lamd their norms
 // times scale.  W also holds the exchange buffer, lamd the moving scalars
 // (jacobi_cols<NB>(p) elements).  Starts and ends with a barrier.
-template <int NT, int G, int NB, int E, int EMAX, int PMAX>
-__device__ __forceinline__ SweepCount sweep_lds(double *W, double scale, int p, int ld, const SweepRule &rule,
-                                                bool ordered, double *lamd, short *rk, int *mx_s) {
+template <int NT, int G, int NB, int E, int EMAX, int PMAX, typename Sc>
+__device__ __forceinline__ SweepCount sweep_lds(double *W, double scale, int p, int ld, const SweepRule<Sc> &rule,
+                                                bool ordered, double *lamd, short *rk, SweepShared<Sc> &mx_s) {
   if constexpr (E < EMAX) {
     if (p > G * E) return sweep_lds<NT, G, NB, E + 1, EMAX, PMAX>(W, scale, p, ld, rule, ordered, lamd, rk, mx_s);
   }

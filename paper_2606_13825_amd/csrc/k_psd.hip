@@ -100,12 +100,12 @@ template <typename T> struct EigArgs {
 // Repeated eigenvalues, which float32 data hold as clusters 1e-8 wide, are
 // what sets this: with a quarter of them equal at order 138, the couplings
 // left after sweeps 7 to 11 are 1.4e-7, 1.7e-8, 3.7e-9, 1.7e-11 and 7e-15.
-template <typename T> __device__ __forceinline__ SweepRule sweep_rule(const EigArgs<T> &a, int p) {
+template <typename T> __device__ __forceinline__ SweepRule<T> sweep_rule(const EigArgs<T> &a, int p) {
   const double tol = a.tol > 0.0 ? a.tol : 4.0 * (double)Unit<T>::eps * sqrt((double)p);
-  SweepRule rule{(float)(tol * tol), (float)tol, 0.f, a.max_sweeps, 0};
+  SweepRule<T> rule{(T)(tol * tol), (T)tol, 0, a.max_sweeps, 0};
   if (std::is_same<T, float>::value && a.refine > 0) {
     const float fine = (float)fmin(a.tol > 0.0 ? a.tol : 1.0, 2e-8);
-    rule = SweepRule{fmaxf(1e-30f, 1e-4f * fine * fine), fine, 1e-6f, a.max_sweeps, 8};
+    rule = SweepRule<T>{(T)fmaxf(1e-30f, 1e-4f * fine * fine), (T)fine, (T)1e-6f, a.max_sweeps, 8};
   }
   return rule;
 }
@@ -184,20 +184,19 @@ __device__ inline void list_positive(const double *lamd, int p, short *pos_idx, 
 // float32).
 // Static LDS of the kernels that follow: eigenvalues (the scalars that travel
 // with the columns during the sweeps), positive indices, sums.
-template <int NT, int PMAX> struct EigShared {
+template <typename T, int NT, int PMAX> struct EigShared {
   __attribute__((aligned(16))) double lamd[PMAX];   // (a multiple of whole pairs of column blocks)
   double red[NT / 64];
   short pos_idx[PMAX + 16];
-  int mx_s[7];
+  SweepShared<T> mx_s;
   int npos;
 };
 
 template <typename T, int NT, int G, int NB, int PMAX, int SMAX>
-__device__ __forceinline__ void eig_block(const EigArgs<T> &a, const PsdDesc &d, double *W, EigShared<NT, SMAX> &sm) {
+__device__ __forceinline__ void eig_block(const EigArgs<T> &a, const PsdDesc &d, double *W, EigShared<T, NT, SMAX> &sm) {
   static_assert(jacobi_cols<NB>(PMAX) == PMAX && PMAX <= SMAX, "one scalar per column");
   double *lamd = sm.lamd, *red = sm.red;
   short *pos_idx = sm.pos_idx;
-  int *mx_s = sm.mx_s;
   const int p = d.p;
   const int ld = eig_ld<G, NB>(p), nc = jacobi_cols<NB>(p);
   const int nrows = p * (p + 1) / 2;
@@ -236,7 +235,7 @@ __device__ __forceinline__ void eig_block(const EigArgs<T> &a, const PsdDesc &d,
     }
     for (int e = p * ld + tid; e < nc * ld; e += NT) W[e] = 0.0;
   }
-  if (tid < 7) mx_s[tid] = 0;
+  sm.mx_s.clear();
   fro2 = wg_sum<double, NT>(fro2, red);   // contains barriers: W complete after this
   if (!isfinite((T)fro2)) {
     put_nan<T, NT>(a, d);
@@ -289,7 +288,7 @@ __device__ __forceinline__ void eig_block(const EigArgs<T> &a, const PsdDesc &d,
   constexpr int PMIN = PMAX <= 32 ? 1 : (PMAX <= 64 ? 33 : 65);   // smallest order of the class
   constexpr int EMIN = (PMIN + G - 1) / G, EMAX = (PMAX + G - 1) / G;
   const SweepCount sw = sweep_lds<NT, G, NB, EMIN, EMAX, PMAX>(W, scale, p, ld, sweep_rule(a, p), a.warm_read != 0,
-                                                                   lamd, pos_idx, mx_s);
+                                                                   lamd, pos_idx, sm.mx_s);
   // eigenvalues: column norms minus the shift
   for (int i = tid; i < p; i += NT) lamd[i] = lamd[i] / scale - c;
   __syncthreads();
@@ -337,7 +336,7 @@ __device__ __forceinline__ void eig_block(const EigArgs<T> &a, const PsdDesc &d,
 template <typename T, int NT, int G, int NB, int PMAX>
 __global__ __launch_bounds__(NT) void k_psd_eig(const EigArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ EigShared<NT, PMAX> sm;
+  __shared__ EigShared<T, NT, PMAX> sm;
   const PsdDesc d = a.descs[blockIdx.x];
   eig_block<T, NT, G, NB, PMAX>(a, d, reinterpret_cast<double *>(smem_raw), sm);
 }
@@ -350,7 +349,7 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const EigArgs<T> a) {
 template <typename T>
 __global__ __launch_bounds__(512) void k_psd_eig_mixed(const EigArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  __shared__ EigShared<512, 128> sm;
+  __shared__ EigShared<T, 512, 128> sm;
   const PsdDesc d = a.descs[blockIdx.x];
   double *W = reinterpret_cast<double *>(smem_raw);
   if (d.p <= 32) eig_block<T, 512, 8, 2, 32>(a, d, W, sm);
@@ -379,7 +378,7 @@ __host__ __device__ constexpr int large_ld(int p) { return (p + 3) & ~3; }
 
 template <typename T, int E, int PMAX>
 __device__ __forceinline__ void eig_large(const EigArgs<T> &a, const PsdDesc &d, unsigned char *smem, double *lamd,
-                                          short *pos_idx, double *red, int *mx_s, int *npos_s) {
+                                          short *pos_idx, double *red, SweepShared<T> &mx_s, int *npos_s) {
   constexpr int G = 16, NB = 4, NT = LARGE_NT;
   typedef Mma<double>::v4 v4;
   const int p = d.p, ld = large_ld(p);
@@ -409,7 +408,7 @@ __device__ __forceinline__ void eig_large(const EigArgs<T> &a, const PsdDesc &d,
   }
   for (int j = tid; j < p; j += NT)
     for (int i = p; i < ld; ++i) S[i + j * ld] = (T)0;
-  if (tid < 7) mx_s[tid] = 0;
+  mx_s.clear();
   fro2 = wg_sum<double, NT>(fro2, red);   // contains barriers: S complete after this
   if (!isfinite((T)fro2)) {
     put_nan<T, NT>(a, d);
@@ -561,7 +560,7 @@ __device__ __forceinline__ void eig_large(const EigArgs<T> &a, const PsdDesc &d,
 
 template <typename T, int E, int PMAX>
 __device__ __forceinline__ void eig_large_by_order(const EigArgs<T> &a, const PsdDesc &d, unsigned char *smem,
-                                                   double *lamd, short *pos_idx, double *red, int *mx_s, int *npos_s) {
+                                                   double *lamd, short *pos_idx, double *red, SweepShared<T> &mx_s, int *npos_s) {
   if constexpr (16 * E < PMAX) {
     if (d.p > 16 * E) return eig_large_by_order<T, E + 1, PMAX>(a, d, smem, lamd, pos_idx, red, mx_s, npos_s);
   }
@@ -574,7 +573,7 @@ __global__ __launch_bounds__(LARGE_NT) void k_psd_eig_large(const EigArgs<T> a) 
   __shared__ double red[LARGE_NT / 64];
   __shared__ __align__(16) double lamd[jacobi_cols<4>(PMAX)];   // eigenvalues; the moving scalars during the sweeps
   __shared__ short pos_idx[PMAX + 16];
-  __shared__ int mx_s[7];
+  __shared__ SweepShared<T> mx_s;
   __shared__ int npos_s;
   const PsdDesc d = a.descs[blockIdx.x];
   eig_large_by_order<T, 9, PMAX>(a, d, smem_raw, lamd, pos_idx, red, mx_s, &npos_s);
