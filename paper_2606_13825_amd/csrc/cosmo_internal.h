@@ -374,6 +374,13 @@ template <typename T> void launch_ns_forward(const NsDesc *d, int32_t nblk, int3
 template <typename T> void launch_ns_vjp(const NsDesc *d, int32_t nblk, int32_t ntiles, int32_t tile, int32_t K,
                                          const T *g, T *gin, T *base, const double *cnorm, hipStream_t st);
 
+// Allows a kernel the whole LDS of a workgroup minus its static part on the
+// current device; returns the dynamic LDS it may use.  Asked once per kernel
+// (its address: kernels of one signature share their type) and device; any
+// thread may call it.
+constexpr size_t LDS_BYTES = 163840, DEFAULT_DYN_LDS = 65536;
+size_t allow_dyn_lds(const void *kernel);
+
 // bookkeeping for profiling: kernel-family events
 void set_last_error(const std::string &msg);
 

@@ -566,15 +566,7 @@ void launch_pcg(const View<T> &v, const T *rho_hat, const T *dg, const double *r
   // (float64 in the residual pass)
   const size_t lds = (size_t)(512 / 64) * v.dense_maxcols * sizeof(double);
   auto go = [&](auto kern) {
-    static bool attr_set = false;   // more than the default 64 KiB of dynamic LDS may be needed
-    if (!attr_set) {
-      hipFuncAttributes a{};
-      size_t stat = 4096;
-      if (hipFuncGetAttributes(&a, reinterpret_cast<const void *>(kern)) == hipSuccess) stat = a.sharedSizeBytes;
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)(163840 - stat));
-      attr_set = true;
-    }
+    (void)allow_dyn_lds(reinterpret_cast<const void *>(kern));
     kern<<<v.B, 512, lds, st>>>(v, rho_hat, dg, rhs, x, r, z, p, Mp, t, t64, (T)tol, max_iter, alpha_k, xold, xnew,
                                   gx_in, gx_out, mode, stats);
   };

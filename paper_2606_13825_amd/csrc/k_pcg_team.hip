@@ -785,12 +785,7 @@ void launch_pcg_team(const View<T> &v, const TeamView &tv, const T *rho_hat, con
   TeamView tvl = tv;
   tvl.cap_off = (int64_t)(team_lds_bytes(sizeof(T), tv.max_n, v.n_dense > 0 ? v.dense_maxcols : 0, tv.dense_slots) + 15) / 16 * 16;
   auto go = [&](auto kern) {
-    static bool attr_set = false;   // more than the default 64 KiB of dynamic LDS may be needed
-    if (!attr_set) {
-      (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                TEAM_MAX_LDS);
-      attr_set = true;
-    }
+    (void)allow_dyn_lds(reinterpret_cast<const void *>(kern));
     kern<<<tv.grid, NTH, tvl.cap_off + tv.cap, st>>>(v, tvl, rho_hat, dg, rhs, x, r, z, Mp, t, t64, c64, (T)tol,
                                                          max_iter, alpha_k, xold, xnew, gx_in, gx_out, mode, stats);
   };

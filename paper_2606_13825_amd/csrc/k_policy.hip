@@ -672,12 +672,7 @@ inline int grid_of(int64_t n, int nt) {
 }
 
 template <typename K> void allow_row_lds(K kern, size_t bytes) {
-  static bool done = false;   // one attribute call per kernel instantiation
-  if (!done && bytes > 65536) {
-    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)bytes);
-  }
-  done = true;
+  if (bytes > DEFAULT_DYN_LDS) (void)allow_dyn_lds(reinterpret_cast<const void *>(kern));
 }
 
 }  // namespace

@@ -871,18 +871,6 @@ __global__ __launch_bounds__(64 * EMAX) void k_psd_vjp_large(const PsdDesc *__re
                                  reinterpret_cast<T *>(smem_raw), rule, eps, 64 * EMAX);
 }
 
-constexpr size_t LDS_LIMIT = 163840;
-
-// Allow a kernel the whole LDS of a workgroup minus its static allocation;
-// returns the dynamic LDS bytes it may use.
-size_t set_dyn_lds_cap(const void *fn) {
-  hipFuncAttributes a{};
-  size_t stat = 4096;
-  if (hipFuncGetAttributes(&a, fn) == hipSuccess) stat = a.sharedSizeBytes;
-  (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(LDS_LIMIT - stat));
-  return LDS_LIMIT - stat;
-}
-
 // Elements of the exchange buffer for a launch whose largest order is p.
 template <int G, int NB, int E, int EMAX, int PMAX> constexpr int exchange_elems(int p) {
   if constexpr (E < EMAX) {
@@ -900,11 +888,7 @@ template <int G, int NB, int PMAX> size_t eig_lds(int32_t p) {
 
 template <typename T, int NT, int G, int NB, int PMAX>
 void run_eig(const EigArgs<T> &a, int32_t n, int32_t max_p, hipStream_t st) {
-  static bool attr_set = false;
-  if (!attr_set) {
-    set_dyn_lds_cap(reinterpret_cast<const void *>(&k_psd_eig<T, NT, G, NB, PMAX>));
-    attr_set = true;
-  }
+  (void)allow_dyn_lds(reinterpret_cast<const void *>(&k_psd_eig<T, NT, G, NB, PMAX>));
   k_psd_eig<T, NT, G, NB, PMAX><<<n, NT, eig_lds<G, NB, PMAX>(max_p), st>>>(a);
 }
 
@@ -912,11 +896,7 @@ template <typename T, int PMAX>
 void run_eig_large(const EigArgs<T> &a, int32_t n, int32_t max_p, hipStream_t st) {
   const size_t block = (size_t)max_p * large_ld(max_p) * sizeof(T);
   const size_t exch = (size_t)exchange_elems<16, 4, 9, (PMAX + 15) / 16, PMAX>(max_p) * sizeof(double);
-  static bool attr_set = false;
-  if (!attr_set) {
-    set_dyn_lds_cap(reinterpret_cast<const void *>(&k_psd_eig_large<T, PMAX>));
-    attr_set = true;
-  }
+  (void)allow_dyn_lds(reinterpret_cast<const void *>(&k_psd_eig_large<T, PMAX>));
   k_psd_eig_large<T, PMAX><<<n, LARGE_NT, std::max(block, exch), st>>>(a);
 }
 
@@ -969,11 +949,7 @@ void launch_psd_proj(const PsdDesc *d, const int32_t *begin, const int32_t *maxp
     if (begin[1] > begin[0]) lds = std::max(lds, eig_lds<8, 2, 32>(maxp[0]));
     if (begin[2] > begin[1]) lds = std::max(lds, eig_lds<16, 2, 64>(maxp[1]));
     if (begin[3] > begin[2]) lds = std::max(lds, eig_lds<16, 4, 128>(maxp[2]));
-    static bool attr_set = false;
-    if (!attr_set) {
-      set_dyn_lds_cap(reinterpret_cast<const void *>(&k_psd_eig_mixed<T>));
-      attr_set = true;
-    }
+    (void)allow_dyn_lds(reinterpret_cast<const void *>(&k_psd_eig_mixed<T>));
     k_psd_eig_mixed<T><<<n, 512, lds, st>>>(a);
     return;
   }
@@ -993,8 +969,7 @@ void launch_psd_proj(const PsdDesc *d, const int32_t *begin, const int32_t *maxp
 template <typename T, int NT>
 bool run_vjp(const PsdDesc *d, int32_t n, int32_t max_p, const T *U, const T *lam, const T *g, T *out, T *scratch,
              hipStream_t st, int32_t rule, double eps) {
-  static size_t dyn_bytes = 0;
-  if (dyn_bytes == 0) dyn_bytes = set_dyn_lds_cap(reinterpret_cast<const void *>(&k_psd_vjp<T, NT>));
+  const size_t dyn_bytes = allow_dyn_lds(reinterpret_cast<const void *>(&k_psd_vjp<T, NT>));
   // LDS holds B0 (and B1, then U) at the padded stride while they fit; the
   // largest orders keep only B0, unpadded (order 200 in float32: 160,000
   // bytes), with B1 in the global scratch.
@@ -1016,8 +991,7 @@ bool run_vjp_large(const PsdDesc *d, int32_t n, int32_t max_p, const T *U, const
                    hipStream_t st, int32_t rule, double eps) {
   constexpr int PMAX = std::is_same<T, float>::value ? COSMO_MAX_PSD_ORDER_F32 : COSMO_MAX_PSD_ORDER_F64;
   constexpr int EMAX = (PMAX + 15) / 16;
-  static size_t dyn_bytes = 0;
-  if (dyn_bytes == 0) dyn_bytes = set_dyn_lds_cap(reinterpret_cast<const void *>(&k_psd_vjp_large<T, EMAX>));
+  const size_t dyn_bytes = allow_dyn_lds(reinterpret_cast<const void *>(&k_psd_vjp_large<T, EMAX>));
   const size_t need = (size_t)max_p * large_ld(max_p) * sizeof(T);
   if (max_p > PMAX || need > dyn_bytes) return false;
   k_psd_vjp_large<T, EMAX><<<n, 64 * EMAX, need, st>>>(d, U, lam, g, out, scratch, rule, (T)eps);

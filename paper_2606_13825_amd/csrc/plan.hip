@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <map>
 #include <sstream>
 #include <mutex>
 #include <numeric>
@@ -19,6 +20,23 @@ namespace cosmo {
 
 static thread_local std::string g_last_error;
 void set_last_error(const std::string &msg) { g_last_error = msg; }
+
+size_t allow_dyn_lds(const void *kernel) {
+  static std::mutex mu;
+  static std::map<std::pair<const void *, int>, size_t> allowed;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return DEFAULT_DYN_LDS;
+  const std::lock_guard<std::mutex> lock(mu);
+  const auto known = allowed.find({kernel, dev});
+  if (known != allowed.end()) return known->second;
+  hipFuncAttributes a{};
+  if (hipFuncGetAttributes(&a, kernel) != hipSuccess) return DEFAULT_DYN_LDS;
+  const size_t bytes = LDS_BYTES - a.sharedSizeBytes;
+  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
+    return DEFAULT_DYN_LDS;   // (asked again by the next launch, which reports the error)
+  allowed[{kernel, dev}] = bytes;
+  return bytes;
+}
 
 }  // namespace cosmo
 

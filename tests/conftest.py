@@ -22,3 +22,10 @@ def pytest_collection_modifyitems(config, items):
     for item in items:
         if "gpu" in item.keywords:
             item.add_marker(skip)
+
+
+@pytest.fixture(scope="session")
+def host_lib(tmp_path_factory):
+    """The library's host code over a runtime without a GPU (host_runtime.py)."""
+    from host_runtime import build
+    return build(str(tmp_path_factory.mktemp("host")))

@@ -19,12 +19,6 @@ LAYOUTS = [   # instances, dtype, (sparse columns before, rows, columns, sparse 
 ]
 
 
-@pytest.fixture(scope="module")
-def host_lib(tmp_path_factory):
-    from host_runtime import build
-    return build(str(tmp_path_factory.mktemp("host")))
-
-
 @pytest.mark.parametrize("B,dtype,shape", LAYOUTS, ids=[f"{b}x{np.dtype(d).name}-{s}" for b, d, s in LAYOUTS])
 def test_dense_columns_stay_in_their_region(host_lib, monkeypatch, B, dtype, shape):
     rt = load(None, monkeypatch, host_lib)
