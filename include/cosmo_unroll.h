@@ -443,6 +443,16 @@ cosmo_status socp_proj_vjp(int32_t ncones, const int32_t *dim, const int64_t *of
 cosmo_status cosmo_plan_set_pcg_form(cosmo_plan *plan, int32_t form);
 cosmo_status cosmo_plan_get_pcg_form(const cosmo_plan *plan, int32_t *form);
 
+/* Teams of workgroups per instance in the CG.  members: the most workgroups
+ * one team has (0, the default: as many as the plan cut its instances for;
+ * more than those are not used).  Fewer leave compute units to other streams;
+ * results are bitwise the same.  wait_ns: how long a workgroup waits for
+ * another of its team before it gives the instance up (0, the default: 2 s).
+ * Solutions of instances given up, and of those that then no team was left
+ * for, are non-finite and counted in cg_not_converged.  Negative values are
+ * COSMO_EINVAL; on plans without teams the call has no effect. */
+cosmo_status cosmo_plan_set_cg_team(cosmo_plan *plan, int32_t members, int64_t wait_ns);
+
 /* Graph mode (enable = 0 or 1, default 0).  When on, cosmo_unroll_forward and
  * cosmo_unroll_backward record their whole launch sequence (all K steps, the
  * order-class streams included) into a HIP graph on the first call with a

@@ -468,6 +468,11 @@ class CosmoBatch:
         L.check(L.lib().cosmo_plan_get_pcg_form(self._plan, ctypes.byref(f)), "cosmo_plan_get_pcg_form")
         return f.value
 
+    def set_cg_team(self, members: int = 0, wait_ns: int = 0):
+        """Most workgroups that share an instance's CG on plans with teams, and
+        how long one waits for another (cosmo_plan_set_cg_team; 0: the defaults)."""
+        L.check(L.lib().cosmo_plan_set_cg_team(self._plan, int(members), int(wait_ns)), "cosmo_plan_set_cg_team")
+
     def set_graph(self, enable: bool):
         """Graph mode: forward and backward calls record their launch
         sequence once per set of buffers and replay it afterwards."""

@@ -256,11 +256,14 @@ constexpr int32_t TEAM_XCDS = 8;            // accelerator dies of the device
 constexpr int32_t TEAM_MAX_SLICES = 32;     // compute units of one die
 constexpr int32_t TEAM_MID_ROW = 256;       // entries of a row 16 lanes still handle well
 constexpr uint32_t TEAM_NONE = 0xffffffffu;
+constexpr uint64_t TEAM_WAIT_TICKS = 200000000ull;   // 2 s of the 100 MHz real-time counter
 constexpr int32_t TEAM_MAX_LDS = 158208;    // dynamic LDS a team workgroup may use
 struct TeamView {
   int32_t slices = 0;          // 0: no teams, one workgroup per instance
   int32_t teams_per_xcd = 0;
   int32_t grid = 0;            // workgroups of a launch
+  int32_t members = 0;         // most workgroups of a team, at most slices
+  uint64_t wait_ticks = TEAM_WAIT_TICKS;   // how long one waits for another before the solve is given up
   int64_t max_n = 0;           // columns of the largest instance
   const int64_t *sliceA = nullptr, *sliceAt = nullptr, *midA = nullptr, *midAt = nullptr, *colcut = nullptr;
   // the rows slice s's columns use, as far as the LDS copy of them is
@@ -287,9 +290,9 @@ struct TeamView {
   const int32_t *dense_list = nullptr, *dense_slot = nullptr;
   int32_t dense_slots = 0;     // most of them in a slice
 };
-size_t team_state_bytes(int32_t teams_per_xcd);
+size_t team_state_bytes(int32_t teams_per_xcd, int32_t B);
 size_t team_lds_bytes(size_t esz, int64_t max_n, int32_t dense_maxcols, int32_t dense_slots);   // without cap
-void launch_team_reset(const TeamView &tv, hipStream_t st);
+void launch_team_reset(const TeamView &tv, int32_t B, hipStream_t st);
 // Bytes of such a copy (16-byte multiple): row ids, where their entries
 // begin, rho_hat (rows) or nothing (columns), values, 16-bit indices.
 __host__ __device__ inline int64_t team_kept_bytes(int64_t rows, int64_t entries, int64_t esz, bool rho) {

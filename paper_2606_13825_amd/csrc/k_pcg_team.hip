@@ -25,7 +25,10 @@
 // one queue, largest first, until it is empty.  Sums are formed per slice and
 // added in slice order: the result does not depend on the teams' sizes.
 // Waits inside a closed team end because all its members are running; each is
-// bounded in time all the same and then marks the solutions non-finite.
+// bounded in time all the same.  A member whose wait runs out, and with it its
+// team, gives its instance up and leaves; the last workgroup of the launch
+// then marks the instances given up, and those that no team took, as
+// non-finite and not converged.
 //
 // p (in the residual pass: x) is kept whole in every workgroup's LDS: the row
 // half gathers from there, and p = z + beta p needs no barrier of its own.
@@ -58,7 +61,6 @@ namespace cosmo {
 namespace {
 
 constexpr uint64_t FORM_TICKS = 5000;           // 50 us of the 100 MHz real-time counter
-constexpr uint64_t WAIT_TICKS = 200000000ull;   // 2 s
 
 __device__ inline uint32_t ld_agent(const uint32_t *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -214,10 +216,12 @@ template <typename F> __device__ inline void strided_rows(const int32_t (&end)[4
   pass(std::integral_constant<int, 1>{}, 0, end[0]);
 }
 
-// Control words of one launch, zero before it and left zero by it.
+// Control words of one launch, zero before it and left zero by it: a head, a
+// record per team, and per queue position whether its instance was given up.
 struct TeamHead {
   uint32_t queue, exits;
-  uint32_t pad[62];
+  uint32_t aborted;   // a team gave up
+  uint32_t pad[61];
   uint32_t ticket[TEAM_XCDS * 64];   // one line per XCD
 };
 struct TeamRec {
@@ -236,6 +240,7 @@ constexpr uint32_t CLOSED = 0x80000000u;
 
 struct Team {
   TeamRec *rec;
+  uint64_t wait_ticks;
   uint32_t rank, size, gen, parity;
   bool aborted;
 };
@@ -254,7 +259,7 @@ __device__ inline void team_sync(Team &tm, int32_t *flag_s) {
         const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
         while (ld_agent(&tm.rec->gen) < target) {
           if (ld_agent(&tm.rec->abort) != 0) break;
-          if (__builtin_amdgcn_s_memrealtime() - t0 > WAIT_TICKS) {
+          if (__builtin_amdgcn_s_memrealtime() - t0 > tm.wait_ticks) {
             st_agent(&tm.rec->abort, 1u);
             break;
           }
@@ -308,23 +313,25 @@ __global__ __launch_bounds__(NTH) void k_pcg_team(View<T> v, TeamView tv, const 
   const int V = tv.slices;
   TeamHead *head = static_cast<TeamHead *>(tv.state);
   TeamRec *recs = reinterpret_cast<TeamRec *>(head + 1);
+  uint32_t *given_up = reinterpret_cast<uint32_t *>(recs + TEAM_XCDS * tv.teams_per_xcd);
 
   // ---- join a team --------------------------------------------------------------
   if (tid == 0) {
     const uint32_t xcc = (uint32_t)__builtin_amdgcn_s_getreg(20 | (3 << 11)) % TEAM_XCDS;   // XCC_ID, bits 3:0
     const uint32_t ticket = __hip_atomic_fetch_add(&head->ticket[64 * xcc], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     uint32_t team = TEAM_NONE, rank = 0, size = 0;
-    if (ticket < (uint32_t)(tv.teams_per_xcd * V)) {
-      TeamRec *rec = recs + xcc * tv.teams_per_xcd + ticket / V;
+    const uint32_t M = tv.members;
+    if (ticket < (uint32_t)tv.teams_per_xcd * M) {
+      TeamRec *rec = recs + xcc * tv.teams_per_xcd + ticket / M;
       const uint32_t old = __hip_atomic_fetch_add(&rec->joined, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (!(old & CLOSED)) {
-        team = xcc * tv.teams_per_xcd + ticket / V;
+        team = xcc * tv.teams_per_xcd + ticket / M;
         rank = old;
         auto close = [&]() {
           const uint32_t was = __hip_atomic_fetch_or(&rec->joined, CLOSED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           if (!(was & CLOSED)) st_agent(&rec->size, was);
         };
-        if (rank == (uint32_t)V - 1) close();
+        if (rank == M - 1) close();
         const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
         while ((size = ld_agent(&rec->size)) == 0)
           if (__builtin_amdgcn_s_memrealtime() - t0 > FORM_TICKS) close();
@@ -335,20 +342,27 @@ __global__ __launch_bounds__(NTH) void k_pcg_team(View<T> v, TeamView tv, const 
     join_s[2] = size;
   }
   __syncthreads();
-  Team tm{recs + (join_s[0] == TEAM_NONE ? 0 : join_s[0]), join_s[1], join_s[2], 0, 0, false};
+  Team tm{recs + (join_s[0] == TEAM_NONE ? 0 : join_s[0]), tv.wait_ticks, join_s[1], join_s[2], 0, 0, false};
 
   T *pl = reinterpret_cast<T *>(dyn_lds);
   auto all = [](int32_t) { return true; };
   while (join_s[0] != TEAM_NONE) {
     // ---- the next instance of the queue ------------------------------------------
-    if (tm.rank == 0 && tid == 0)
-      st_agent(&tm.rec->inst, __hip_atomic_fetch_add(&head->queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    uint32_t popped = (uint32_t)v.B;   // what this thread took from the queue
+    if (tm.rank == 0 && tid == 0) {
+      popped = __hip_atomic_fetch_add(&head->queue, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      st_agent(&tm.rec->inst, popped);
+    }
     team_sync(tm, &flag_s);
-    if (tid == 0) sum_s[0] = (double)ld_agent(&tm.rec->inst);
+    if (tid == 0) sum_s[0] = (double)(tm.aborted ? popped : ld_agent(&tm.rec->inst));
     __syncthreads();
     const uint32_t pos = (uint32_t)sum_s[0];
     __syncthreads();   // sum_s is written again below
-    if (pos >= (uint32_t)v.B || tm.aborted) break;
+    if (pos >= (uint32_t)v.B) break;
+    if (tm.aborted) {
+      if (tid == 0) st_agent(&given_up[pos], 1u);
+      break;
+    }
     const int b = tv.order[pos];
     const int64_t n0 = v.n_off[b], n1 = v.n_off[b + 1];
     const int n = (int)(n1 - n0);
@@ -710,8 +724,13 @@ __global__ __launch_bounds__(NTH) void k_pcg_team(View<T> v, TeamView tv, const 
       }
       if (fail) break;
     }
+    // A team that gives up: whichever of its members misses another, the one
+    // that took the instance or a member that worked on it says so here or above.
+    if (tm.aborted) {
+      if (tid == 0) st_agent(&given_up[pos], 1u);
+      break;
+    }
     // ---- epilogue on this workgroup's columns --------------------------------------
-    if (tm.aborted) fail = true;
     const T al = alpha_k ? alpha_k[b] : (T)1;
     for (int s = tm.rank; s < V; s += tm.size)
       own(s, [&](int64_t j) {
@@ -728,15 +747,38 @@ __global__ __launch_bounds__(NTH) void k_pcg_team(View<T> v, TeamView tv, const 
       atomicAdd(&stats[b].cg_passes_total, passes);
       if (!(rrt <= thr)) atomicAdd(&stats[b].cg_not_converged, 1);
     }
-    if (tm.aborted) break;
   }
 
-  // ---- the last workgroup out leaves the control words zero -------------------------
+  // ---- the last workgroup out: instances given up; control words left zero ----------
+  if (tm.aborted) {   // what this workgroup stored is in memory before it counts as gone
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+    __syncthreads();
+    if (tid == 0) {
+      st_agent(&head->aborted, 1u);
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    }
+  }
   __syncthreads();
   if (tid == 0)
     flag_s = __hip_atomic_fetch_add(&head->exits, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
   __syncthreads();
   if (flag_s) {
+    if (ld_agent(&head->aborted) != 0) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      const uint32_t taken = ld_agent(&head->queue);
+      for (uint32_t q = 0; q < (uint32_t)v.B; ++q) {
+        if (q < taken && ld_agent(&given_up[q]) == 0) continue;
+        const int b = tv.order[q];
+        T *out = mode == 0 ? xnew : gx_out;
+        for (int64_t j = v.n_off[b] + tid; j < v.n_off[b + 1]; j += NTH) {
+          x[j] = (T)NAN;
+          if (out) out[j] = (T)NAN;
+        }
+        if (stats && tid == 0) atomicAdd(&stats[b].cg_not_converged, 1);
+      }
+      __syncthreads();   // the words have been read
+      for (int q = tid; q < v.B; q += NTH) st_agent(&given_up[q], 0);
+    }
     for (int i = tid; i < TEAM_XCDS * tv.teams_per_xcd; i += NTH) {
       TeamRec &rec = recs[i];
       st_agent(&rec.joined, 0);
@@ -749,6 +791,7 @@ __global__ __launch_bounds__(NTH) void k_pcg_team(View<T> v, TeamView tv, const 
     if (tid == 0) {
       st_agent(&head->queue, 0);
       st_agent(&head->exits, 0);
+      st_agent(&head->aborted, 0);
     }
   }
 }
@@ -760,12 +803,12 @@ __global__ __launch_bounds__(256) void k_team_reset(uint32_t *words, int64_t n) 
 
 }  // namespace
 
-size_t team_state_bytes(int32_t teams_per_xcd) {
-  return sizeof(TeamHead) + (size_t)TEAM_XCDS * teams_per_xcd * sizeof(TeamRec);
+size_t team_state_bytes(int32_t teams_per_xcd, int32_t B) {
+  return sizeof(TeamHead) + (size_t)TEAM_XCDS * teams_per_xcd * sizeof(TeamRec) + ((size_t)B + 1) / 2 * 8;
 }
 
-void launch_team_reset(const TeamView &tv, hipStream_t st) {
-  const int64_t n = (int64_t)team_state_bytes(tv.teams_per_xcd) / 4;
+void launch_team_reset(const TeamView &tv, int32_t B, hipStream_t st) {
+  const int64_t n = (int64_t)team_state_bytes(tv.teams_per_xcd, B) / 4;
   k_team_reset<<<(int)std::min<int64_t>((n + 255) / 256, 64), 256, 0, st>>>(static_cast<uint32_t *>(tv.state), n);
 }
 

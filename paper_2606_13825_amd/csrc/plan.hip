@@ -130,6 +130,7 @@ struct cosmo_plan {
   double *d_dscale = nullptr;
   // teams of workgroups per instance in the CG (k_pcg_team.hip); slices = 0: none
   TeamView team;
+  int32_t team_cus = 0;     // compute units of the device
   bool team_wide = false;   // the device-wide form reads the largest instance faster than one die does
   // M = P + sigma I + A' D A is diagonal when every row of A has at most one
   // nonzero and P is diagonal; the linear solves are then done in the
@@ -432,6 +433,14 @@ std::vector<int64_t> sort_by_slice(std::vector<int32_t> &rows, const RowBuckets 
   return off;
 }
 
+// Teams of at most `members` workgroups, and as many workgroups in a launch as
+// can find one and an instance.
+void set_team_members(cosmo_plan *pl, int32_t members) {
+  pl->team.members = members;
+  pl->team.grid = (int32_t)std::min<int64_t>(
+      pl->team_cus, (int64_t)TEAM_XCDS * members * ((pl->B + TEAM_XCDS - 1) / TEAM_XCDS));
+}
+
 template <typename T>
 cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   const int64_t n = pl->n_tot, m = pl->m_tot, nnz = p->A_nnz;
@@ -718,7 +727,8 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
     if (V > 0) {
       pl->team.slices = V;
       pl->team.teams_per_xcd = (TEAM_MAX_SLICES + V - 1) / V;
-      pl->team.grid = (int32_t)std::min<int64_t>(ncu, (int64_t)TEAM_XCDS * V * ((pl->B + TEAM_XCDS - 1) / TEAM_XCDS));
+      pl->team_cus = ncu;
+      set_team_members(pl, V);
       pl->team.max_n = max_n;
       pl->team.ec_stride = pl->dense_cols_tot;
       // one die reads about 1 TB/s; the device-wide form reads the whole
@@ -943,7 +953,7 @@ void build_layouts(cosmo_plan *pl) {
   f.t = take(m);
   f.t64 = take(2 * m);                     // float64 residual pass of the CG (m doubles)
   f.cg = take(16 * ((size_t)pl->B + 1) + 256);  // per-instance state of the CG (cooperative form)
-  const size_t team_elems = pl->team.slices > 0 ? team_state_bytes(pl->team.teams_per_xcd) / pl->esz : 0;
+  const size_t team_elems = pl->team.slices > 0 ? team_state_bytes(pl->team.teams_per_xcd, pl->B) / pl->esz : 0;
   const size_t ecp_elems = (size_t)pl->team.slices * pl->dense_cols_tot * 8 / pl->esz;
   f.tm = take(team_elems);                 // control words of the CG teams
   f.c64 = take(pl->team.slices > 0 ? n * 8 / pl->esz : 0);   // float64 column sums of their residual pass
@@ -1206,7 +1216,7 @@ template <typename T> struct CgRun {
     teams = tv.slices > 0 && (pl->pcg_form == 0 || !pl->team_wide);
     tv.state = ws + f.tm;
     tv.ecp = reinterpret_cast<double *>(ws + f.ecp);
-    if (teams) launch_team_reset(tv, st);
+    if (teams) launch_team_reset(tv, v.B, st);
   }
   void operator()(const T *rho_hat, const T *dg, const double *rhs, T *x, const T *al, const T *xold, T *xnew,
                   const T *gx_in, T *gx_out, int32_t mode, cosmo_stats *stats) const {
@@ -1845,6 +1855,18 @@ cosmo_status cosmo_plan_get_pcg_form(const cosmo_plan *plan, int32_t *form) {
   if (s != COSMO_OK) return s;
   if (!form) FAIL(COSMO_EINVAL, "form is NULL");
   *form = plan->pcg_form;
+  return COSMO_OK;
+}
+
+cosmo_status cosmo_plan_set_cg_team(cosmo_plan *plan, int32_t members, int64_t wait_ns) {
+  cosmo_status s = check_plan(plan);
+  if (s != COSMO_OK) return s;
+  if (members < 0 || wait_ns < 0) FAIL(COSMO_EINVAL, "members and wait_ns must be >= 0");
+  if (plan->team.slices == 0) return COSMO_OK;   // nothing runs in teams
+  plan->drop_graphs();   // recorded sequences hold the previous launch shape
+  const int32_t V = plan->team.slices;
+  set_team_members(plan, members == 0 ? V : std::min(members, V));
+  plan->team.wait_ticks = wait_ns == 0 ? TEAM_WAIT_TICKS : (uint64_t)(wait_ns + 9) / 10;
   return COSMO_OK;
 }
 
