@@ -431,9 +431,10 @@ cosmo_status socp_proj_vjp(int32_t ncones, const int32_t *dim, const int64_t *of
  * creation from the instances' sizes); form f = 1..4 = one cooperative launch
  * over the whole device with at most f workgroups per compute unit, the
  * operator passes of all instances spread over every workgroup and grid
- * barriers between phases, on plans where no instance or a very large one is
- * in the teams' reach (else, and where cooperative launch is not available,
- * as form 0).  All compute the same iteration with the same stopping rule;
+ * barriers between phases, on plans without teams and on those with an
+ * instance of more than 64 MB per operator application (on others, and where
+ * cooperative launch is not available, the kernel of form 0 runs;
+ * cosmo_plan_get_cg_kernel tells).  All compute the same iteration with the same stopping rule;
  * their sums are taken in different orders, each deterministic.
  * set_pcg_form: form outside 0..4 is COSMO_EINVAL; a cooperative form while
  * graph mode is on, or on a plan with dense blocks, is COSMO_EUNSUPPORTED.
@@ -442,6 +443,17 @@ cosmo_status socp_proj_vjp(int32_t ncones, const int32_t *dim, const int64_t *of
  * G'(D (A v)) are fused per row of G inside the instance's workgroup. */
 cosmo_status cosmo_plan_set_pcg_form(cosmo_plan *plan, int32_t form);
 cosmo_status cosmo_plan_get_pcg_form(const cosmo_plan *plan, int32_t *form);
+
+/* The kernel that runs the plan's CG solves in its current form, and how many
+ * workgroups share an instance in it (may be NULL; 0 where they all do, or
+ * none). */
+typedef enum {
+  COSMO_CG_NONE = 0,         /* M is diagonal: no CG                                    */
+  COSMO_CG_WORKGROUP = 1,    /* one workgroup per instance                              */
+  COSMO_CG_TEAM = 2,         /* a team of workgroups per instance                       */
+  COSMO_CG_COOPERATIVE = 3   /* one cooperative launch over the whole device            */
+} cosmo_cg_kernel;
+cosmo_status cosmo_plan_get_cg_kernel(const cosmo_plan *plan, int32_t *kernel, int32_t *workgroups);
 
 /* Teams of workgroups per instance in the CG.  members: the most workgroups
  * one team has (0, the default: as many as the plan cut its instances for;
@@ -480,10 +492,11 @@ cosmo_status cosmo_plan_get_graph(const cosmo_plan *plan, int32_t *enabled);
  * keeps the faster (an error in that phase leaves the PSD shapes the plan
  * had).  A setup call, not for the hot path: it allocates scratch buffers
  * and waits for the stream, and it discards the plan's profiling records
- * (cosmo_plan_profile_read counts from zero afterwards).  ms (host, nullable) [4] receives the CG
- * timings in that order (-1 for schedules not run: problems whose reduced
- * matrix is diagonal have no CG, and only the eager and graph runs of form
- * 0 are timed for them); cosmo_plan_psd_tune_ms returns the PSD timings. */
+ * (cosmo_plan_profile_read counts from zero afterwards).  ms (host, nullable)
+ * [4] receives the CG timings in that order (-1 for schedules not run: only
+ * the eager and graph runs of form 0 are timed where the other forms would not
+ * launch cooperatively -- plans with teams, with dense blocks, or without a
+ * CG); cosmo_plan_psd_tune_ms returns the PSD timings. */
 cosmo_status cosmo_plan_autotune(cosmo_plan *plan, const void *rho, const void *alpha, void *ws, void *stream,
                                  double *ms);
 

@@ -22,7 +22,7 @@ EXPORTED = [
     "cosmo_unroll_forward", "cosmo_unroll_backward", "cosmo_residual_loss",
     "cosmo_proj_workspace_size", "psd_proj", "psd_proj_static_scratch", "psd_proj_vjp", "socp_proj", "socp_proj_vjp",
     "cosmo_plan_set_profiling", "cosmo_plan_profile_read", "cosmo_plan_set_tap",
-    "cosmo_plan_set_pcg_form", "cosmo_plan_get_pcg_form", "cosmo_plan_set_cg_team", "cosmo_plan_autotune",
+    "cosmo_plan_set_pcg_form", "cosmo_plan_get_pcg_form", "cosmo_plan_get_cg_kernel", "cosmo_plan_set_cg_team", "cosmo_plan_autotune",
     "cosmo_plan_set_graph", "cosmo_plan_get_graph",
     "cosmo_plan_set_psd_schedule", "cosmo_plan_get_psd_schedule", "cosmo_plan_psd_tune_ms",
     "cosmo_plan_get_schedule", "cosmo_plan_set_schedule", "cosmo_plan_signature",
@@ -205,6 +205,8 @@ def _sig(lib):
     lib.cosmo_plan_set_pcg_form.argtypes = [vp, i32]
     lib.cosmo_plan_get_pcg_form.restype = ctypes.c_int
     lib.cosmo_plan_get_pcg_form.argtypes = [vp, ctypes.POINTER(i32)]
+    lib.cosmo_plan_get_cg_kernel.restype = ctypes.c_int
+    lib.cosmo_plan_get_cg_kernel.argtypes = [vp, P32, P32]
     lib.cosmo_plan_set_cg_team.restype = ctypes.c_int
     lib.cosmo_plan_set_cg_team.argtypes = [vp, i32, i64]
     lib.cosmo_plan_set_graph.restype = ctypes.c_int

@@ -459,14 +459,22 @@ class CosmoBatch:
 
     # -- schedules ----------------------------------------------------------------
     def set_pcg_form(self, form: int):
-        """CG schedule: 0 one workgroup per instance, 1..4 cooperative (that
-        many workgroups per compute unit at most)."""
+        """CG schedule: 0 one workgroup per instance or a team of them, 1..4
+        cooperative (that many workgroups per compute unit at most) where the
+        plan has no teams or its largest instance is read faster so."""
         L.check(L.lib().cosmo_plan_set_pcg_form(self._plan, int(form)), "cosmo_plan_set_pcg_form")
 
     def pcg_form(self) -> int:
         f = ctypes.c_int32()
         L.check(L.lib().cosmo_plan_get_pcg_form(self._plan, ctypes.byref(f)), "cosmo_plan_get_pcg_form")
         return f.value
+
+    def cg_kernel(self):
+        """The kernel that runs the CG solves now ("none", "workgroup", "team"
+        or "cooperative") and how many workgroups share an instance in it."""
+        k, w = ctypes.c_int32(), ctypes.c_int32()
+        L.check(L.lib().cosmo_plan_get_cg_kernel(self._plan, ctypes.byref(k), ctypes.byref(w)), "cosmo_plan_get_cg_kernel")
+        return ("none", "workgroup", "team", "cooperative")[k.value], w.value
 
     def set_cg_team(self, members: int = 0, wait_ns: int = 0):
         """Most workgroups that share an instance's CG on plans with teams, and

@@ -246,6 +246,10 @@ template <typename T> void launch_pcg(const View<T> &v, const T *rho_hat, const 
                                       int32_t mode, cosmo_stats *stats, void *state, int32_t form,
                                       hipStream_t st);
 
+// Workgroups of a cooperative launch with at most per_cu per compute unit; 0
+// where the device has no cooperative launch.
+template <typename T> int pcg_coop_grid(int per_cu);
+
 // PCG with a team of workgroups per instance (k_pcg_team.hip).  An instance's
 // rows and columns are cut into `slices` parts; rowsA / rowsAt list every
 // instance's rows of a length class slice by slice:

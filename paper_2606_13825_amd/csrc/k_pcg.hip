@@ -582,6 +582,8 @@ void launch_pcg(const View<T> &v, const T *rho_hat, const T *dg, const double *r
   else pick(T{});
 }
 
+template int pcg_coop_grid<float>(int);
+template int pcg_coop_grid<double>(int);
 template void launch_pcg<float>(const View<float> &, const float *, const float *, const double *, float *, float *,
                                 float *, float *, float *, float *, double *, double, int32_t, const float *,
                                 const float *, float *, const float *, float *, int32_t, cosmo_stats *, void *,

@@ -1192,8 +1192,18 @@ void policy_bwd_at(cosmo_plan *pl, const View<T> &v, const PolRun<T> &P, int k, 
   launch_pol_resid_adjoint<T>(v, pl->bkA, pl->bkAt, ub, pb, wb, gx, gy, st);
 }
 
-// The CG solves of a call: a team of workgroups per instance where the plan
-// has teams and the device-wide form is not both asked for and faster.
+// The kernel that runs the CG solves in a form: a team of workgroups per
+// instance where the plan has teams and the device-wide form is not both asked
+// for and faster.
+int32_t cg_kernel(const cosmo_plan *pl, int32_t form) {
+  if (pl->diag_M) return COSMO_CG_NONE;
+  if (pl->team.slices > 0 && (form == 0 || !pl->team_wide)) return COSMO_CG_TEAM;
+  if (form == 0 || pl->n_dense > 0) return COSMO_CG_WORKGROUP;
+  const int grid = pl->opt.dtype == COSMO_F32 ? pcg_coop_grid<float>(form) : pcg_coop_grid<double>(form);
+  return grid > 0 ? COSMO_CG_COOPERATIVE : COSMO_CG_WORKGROUP;
+}
+
+// The CG solves of a call.
 template <typename T> struct CgRun {
   cosmo_plan *pl;
   const View<T> &v;
@@ -1213,7 +1223,7 @@ template <typename T> struct CgRun {
     t64 = reinterpret_cast<double *>(ws + f.t64);
     c64 = reinterpret_cast<double *>(ws + f.c64);
     state = ws + f.cg;
-    teams = tv.slices > 0 && (pl->pcg_form == 0 || !pl->team_wide);
+    teams = cg_kernel(pl, pl->pcg_form) == COSMO_CG_TEAM;
     tv.state = ws + f.tm;
     tv.ecp = reinterpret_cast<double *>(ws + f.ecp);
     if (teams) launch_team_reset(tv, v.B, st);
@@ -1870,6 +1880,16 @@ cosmo_status cosmo_plan_set_cg_team(cosmo_plan *plan, int32_t members, int64_t w
   return COSMO_OK;
 }
 
+cosmo_status cosmo_plan_get_cg_kernel(const cosmo_plan *plan, int32_t *kernel, int32_t *workgroups) {
+  cosmo_status s = check_plan(plan);
+  if (s != COSMO_OK) return s;
+  if (!kernel) FAIL(COSMO_EINVAL, "kernel is NULL");
+  *kernel = cg_kernel(plan, plan->pcg_form);
+  if (workgroups)
+    *workgroups = *kernel == COSMO_CG_TEAM ? plan->team.members : *kernel == COSMO_CG_WORKGROUP ? 1 : 0;
+  return COSMO_OK;
+}
+
 cosmo_status cosmo_plan_set_psd_schedule(cosmo_plan *plan, const int32_t *eig_threads, int32_t vjp_threads) {
   cosmo_status s = check_plan(plan);
   if (s != COSMO_OK) return s;
@@ -1982,7 +2002,8 @@ cosmo_status cosmo_plan_autotune(cosmo_plan *plan, const void *rho, const void *
   double best = -1.0;
   int best_c = -1;
   for (int c = 0; c < 4 && s == COSMO_OK; ++c) {
-    if ((plan->diag_M || plan->n_dense > 0) && cand_form[c] != 0) continue;   // no CG to schedule, or form 0 only
+    // a form that would not launch cooperatively is form 0 under another name
+    if (cand_form[c] != 0 && cg_kernel(plan, cand_form[c]) != COSMO_CG_COOPERATIVE) continue;
     plan->drop_graphs();
     plan->pcg_form = cand_form[c];
     plan->graph = cand_graph[c];
