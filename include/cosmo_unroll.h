@@ -348,7 +348,8 @@ size_t cosmo_proj_workspace_size(int32_t nblk, const int32_t *order_or_dim);
  * eigvals (d, nullable) [sum p], in no particular order inside a block;
  * eigvecs (d, nullable) [sum p^2], block b column-major p x p at offset
  * sum_{b'<b} p_{b'}^2, column i paired with eigvals i.  `refine` as in
- * cosmo_options.eig_refine. */
+ * cosmo_options.eig_refine.  A block's results are bitwise the same whatever
+ * other blocks the call has. */
 cosmo_status psd_proj(int32_t nblk, const int32_t *order, const int64_t *offset, cosmo_dtype dtype,
                       const void *in, void *out, void *eigvals, void *eigvecs, int32_t max_sweeps,
                       double eig_tol, int32_t refine, void *ws, void *stream);

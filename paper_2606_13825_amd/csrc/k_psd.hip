@@ -206,9 +206,7 @@ __device__ __forceinline__ void eig_block(const EigArgs<T> &a, const PsdDesc &d,
   constexpr int NWv = NT / 64;
   double *Ut = a.rscratch + 3 * (size_t)d.uoff;   // used when a warm start reads or leaves it: row-major
 
-  // S = smat(v) into W (column-major, full); ||S||_F^2 = ||v||^2 (svec is
-  // isometric).  Four entries in flight per thread.
-  double fro2 = 0;
+  // S = smat(v) into W (column-major, full).  Four entries in flight per thread.
   for (int base = tid; base < nrows; base += 4 * NT) {
     T val[4];
 #pragma unroll
@@ -220,7 +218,6 @@ __device__ __forceinline__ void eig_block(const EigArgs<T> &a, const PsdDesc &d,
         const int j = svec_col(idx);
         const int i = idx - j * (j + 1) / 2;
         double x = (double)val[u];
-        fro2 += x * x;
         if (i != j) x *= RSQRT2;
         W[i + j * ld] = x;
         W[j + i * ld] = x;
@@ -236,22 +233,33 @@ __device__ __forceinline__ void eig_block(const EigArgs<T> &a, const PsdDesc &d,
     for (int e = p * ld + tid; e < nc * ld; e += NT) W[e] = 0.0;
   }
   sm.mx_s.clear();
-  fro2 = wg_sum<double, NT>(fro2, red);   // contains barriers: W complete after this
+  __syncthreads();   // W complete
+  // Largest column sum of |S| and ||S||_F^2, 16 lanes per column.  The sums of
+  // squares are then added in an order that depends on p alone: a block has
+  // the same bits whatever workgroup it is solved in, by itself or in a
+  // launch with other classes.
+  double colmax = 0;
+  for (int j = tid / 16; j < (p + NT / 16 - 1) / (NT / 16) * (NT / 16); j += NT / 16) {
+    double part[2] = {0, 0};
+    if (j < p)
+      for (int i = tid % 16; i < p; i += 16) {
+        const double x = W[i + j * ld];
+        part[0] += fabs(x);
+        part[1] = fma(x, x, part[1]);
+      }
+    const double sum = group_sums<16, 2>(part);   // of the magnitudes in even lanes, of the squares in odd ones
+    if (tid % 2 == 0) colmax = fmax(colmax, sum);
+    if (j < p && tid % 16 == 1) lamd[j] = sum;
+  }
+  const double inf = wg_max<double, NT>(colmax, red);   // contains a barrier: lamd complete after this
+  double fro2 = 0;
+  for (int j = lane; j < p; j += 64) fro2 += lamd[j];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) fro2 += __shfl_xor(fro2, off, 64);
   if (!isfinite((T)fro2)) {
     put_nan<T, NT>(a, d);
     return;   // fro2 is the same in every thread: the whole workgroup leaves
   }
-  // largest column sum of |S|: 16 lanes per column
-  double colmax = 0;
-  for (int j = tid / 16; j < (p + NT / 16 - 1) / (NT / 16) * (NT / 16); j += NT / 16) {
-    double sum = 0;
-    if (j < p)
-      for (int i = tid % 16; i < p; i += 16) sum += fabs(W[i + j * ld]);
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    colmax = fmax(colmax, sum);
-  }
-  const double inf = wg_max<double, NT>(colmax, red);
   double c = 1.1 * fmin(sqrt(fro2), inf);
   if (!(c > 0.0)) c = 1;
   // Warm start: W = (S + c I) U_prev, with U_prev the eigenvectors of the same
