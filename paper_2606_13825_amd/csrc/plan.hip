@@ -8,6 +8,7 @@
 #include <cstring>
 #include <fstream>
 #include <map>
+#include <memory>
 #include <sstream>
 #include <mutex>
 #include <numeric>
@@ -358,19 +359,31 @@ cosmo_status validate_problem_host(const cosmo_problem *p, const cosmo_options *
   return COSMO_OK;
 }
 
+// A host array whose entries are all written before they are read: nothing is
+// filled first (a plan's creation spent a fifth of its time on that).
+template <typename V> struct HostArray {
+  std::unique_ptr<V[]> p;
+  size_t n;
+  explicit HostArray(size_t n_) : p(new V[n_]), n(n_) {}
+  V *data() { return p.get(); }
+  size_t size() const { return n; }
+  V &operator[](size_t i) { return p[i]; }
+  const V &operator[](size_t i) const { return p[i]; }
+};
+
+constexpr int64_t LONG_ROW = 48;   // entries of a row of the middle class at most
 void build_buckets(const std::vector<int64_t> &rowptr, int64_t nrows, std::vector<int32_t> &rows_out,
                    RowBuckets &bk) {
-  std::vector<int32_t> cls[3];
-  for (int64_t r = 0; r < nrows; ++r) {
+  auto cls = [&](int64_t r) {
     const int64_t len = rowptr[r + 1] - rowptr[r];
-    cls[len <= 4 ? 0 : (len <= 48 ? 1 : 2)].push_back((int32_t)r);
-  }
-  rows_out.clear();
-  for (int c = 0; c < 3; ++c) {
-    bk.begin[c] = (int64_t)rows_out.size();
-    rows_out.insert(rows_out.end(), cls[c].begin(), cls[c].end());
-  }
-  bk.begin[3] = (int64_t)rows_out.size();
+    return (len > 4) + (len > LONG_ROW);
+  };
+  int64_t at[3], count[3] = {0, 0, 0};
+  for (int64_t r = 0; r < nrows; ++r) count[cls(r)]++;
+  bk.begin[0] = 0;
+  for (int c = 0; c < 3; ++c) bk.begin[c + 1] = (at[c] = bk.begin[c]) + count[c];
+  rows_out.resize(nrows);
+  for (int64_t r = 0; r < nrows; ++r) rows_out[at[cls(r)]++] = (int32_t)r;
   bk.lanes[0] = 1;
   bk.lanes[1] = 8;
   bk.lanes[2] = 64;
@@ -404,34 +417,54 @@ int32_t team_slices(const std::vector<double> &work_us, int32_t ncu) {
   return best;
 }
 
-// Lists an instance's rows of each length class slice by slice (rows of a
+// Lists the rows of each length class slice by slice (slice[r] of BV; rows of a
 // slice stay in increasing order, in the longest class those of up to
-// TEAM_MID_ROW entries first); returns the list ranges of (class, instance,
-// slice), mid: where the longest class's long rows begin.
+// TEAM_MID_ROW entries first); returns the list ranges of (class, slice), mid:
+// where the longest class's long rows begin.  Rows come in increasing order,
+// so mostly in that of their slices too, and then stay as they are.
 std::vector<int64_t> sort_by_slice(std::vector<int32_t> &rows, const RowBuckets &bk, const std::vector<int64_t> &ptr,
-                                   const std::vector<int32_t> &inst, const std::vector<int32_t> &slice, int32_t B,
-                                   int32_t V, std::vector<int64_t> &mid) {
-  const int64_t BV = (int64_t)B * V;
+                                   const std::vector<int32_t> &slice, int64_t BV, std::vector<int64_t> &mid) {
+  static_assert(LONG_ROW < TEAM_MID_ROW, "long rows are in the longest class only");
   std::vector<int64_t> off(3 * (BV + 1), 0);
-  std::vector<int32_t> out(rows.size());
+  std::vector<int32_t> out;
   for (int c = 0; c < 3; ++c) {
     // two keys per slice: rows up to TEAM_MID_ROW entries, longer ones
     auto key = [&](int32_t r) {
-      return 2 * ((int64_t)inst[r] * V + slice[r]) + (ptr[r + 1] - ptr[r] > TEAM_MID_ROW ? 1 : 0);
+      return 2 * (int64_t)slice[r] + (c == 2 && ptr[r + 1] - ptr[r] > TEAM_MID_ROW ? 1 : 0);
     };
     std::vector<int64_t> at(2 * BV + 1, 0);
-    for (int64_t k = bk.begin[c]; k < bk.begin[c + 1]; ++k) at[key(rows[k]) + 1]++;
+    int64_t before = 0;
+    bool ordered = true;
+    for (int64_t k = bk.begin[c]; k < bk.begin[c + 1]; ++k) {
+      const int64_t q = key(rows[k]);
+      ordered = ordered && q >= before;
+      before = q;
+      at[q + 1]++;
+    }
     at[0] = bk.begin[c];
     for (int64_t q = 0; q < 2 * BV; ++q) at[q + 1] += at[q];
     int64_t *o = off.data() + c * (BV + 1);
     for (int64_t q = 0; q <= BV; ++q) o[q] = at[2 * q];
     if (c == 2)
       for (int64_t q = 0; q < BV; ++q) mid.push_back(at[2 * q + 1]);
-    for (int64_t k = bk.begin[c]; k < bk.begin[c + 1]; ++k) out[at[key(rows[k])]++] = rows[k];
+    if (ordered) continue;
+    out.resize(bk.begin[c + 1] - bk.begin[c]);
+    for (int64_t k = bk.begin[c]; k < bk.begin[c + 1]; ++k) out[at[key(rows[k])]++ - bk.begin[c]] = rows[k];
+    std::copy(out.begin(), out.end(), rows.begin() + bk.begin[c]);
   }
-  rows.swap(out);
   return off;
 }
+
+// Tables that go to the device in one copy: each at an offset of it.
+struct Staged {
+  std::vector<char> bytes;
+  template <typename V> size_t add(const std::vector<V> &v) {
+    const size_t o = align_up(bytes.size(), 256);
+    bytes.resize(o + std::max<size_t>(v.size(), 1) * sizeof(V));
+    std::copy(v.begin(), v.end(), reinterpret_cast<V *>(bytes.data() + o));
+    return o;
+  }
+};
 
 // Teams of at most `members` workgroups, and as many workgroups in a launch as
 // can find one and an instance.
@@ -450,17 +483,20 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   if (rp[0] != 0 || rp[m] != nnz) FAIL(COSMO_EINVAL, "A_rowptr[0] must be 0 and A_rowptr[m_tot] must equal A_nnz");
   for (int64_t i = 0; i < m; ++i)
     if (rp[i + 1] < rp[i]) FAIL(COSMO_EINVAL, "A_rowptr must be non-decreasing");
-  std::vector<int32_t> col(nnz);
-  std::vector<T> val(nnz);
+  HostArray<int32_t> col(nnz);
+  HostArray<T> val(nnz);
   if (nnz > 0) {
     HIPCHK(hipMemcpy(col.data(), p->A_col, nnz * sizeof(int32_t), hipMemcpyDeviceToHost));
     HIPCHK(hipMemcpy(val.data(), p->A_val, nnz * sizeof(T), hipMemcpyDeviceToHost));
   }
+  std::vector<int64_t> trp(n + 1, 0);   // entries per column, then where A's columns begin
   for (int b = 0; b < pl->B; ++b)
     for (int64_t i = pl->m_off[b]; i < pl->m_off[b + 1]; ++i)
-      for (int64_t k = rp[i]; k < rp[i + 1]; ++k)
+      for (int64_t k = rp[i]; k < rp[i + 1]; ++k) {
         if (col[k] < pl->n_off[b] || col[k] >= pl->n_off[b + 1])
           FAIL(COSMO_EINVAL, "A has an entry outside its instance's column block (row " + std::to_string(i) + ")");
+        trp[col[k] + 1]++;
+      }
   std::vector<T> pdiag(n, (T)0);
   std::vector<int64_t> prp;
   if (p->P_nnz > 0) {
@@ -484,12 +520,10 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
     prp.assign(n + 1, 0);
   }
   // --- transpose of A (counting sort by column; rows stay increasing)
-  std::vector<int64_t> trp(n + 1, 0);
-  for (int64_t k = 0; k < nnz; ++k) trp[col[k] + 1]++;
   for (int64_t j = 0; j < n; ++j) trp[j + 1] += trp[j];
   std::vector<int64_t> fill(trp.begin(), trp.end() - 1);
-  std::vector<int32_t> tcol(nnz);
-  std::vector<T> tval(nnz);
+  HostArray<int32_t> tcol(nnz);
+  HostArray<T> tval(nnz);
   for (int64_t i = 0; i < m; ++i)
     for (int64_t k = rp[i]; k < rp[i + 1]; ++k) {
       const int64_t dst = fill[col[k]]++;
@@ -648,7 +682,7 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   // block's row, so a slice completes its part of the block by itself
   std::vector<int64_t> sliceA, sliceAt, midA, midAt, colcut, used, dense_cut;
   std::vector<int32_t> order, keptA, keptAt, entries, uses, dense_list, dense_slot;
-  std::vector<uint16_t> At_loc;
+  HostArray<uint16_t> At_loc(0);
   if (!pl->diag_M) {
     int dev = 0, ncu = 0;
     HIPCHK(hipGetDevice(&dev));
@@ -673,23 +707,34 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
       cslice.resize(n);
       colcut.assign((size_t)pl->B * V + 1, 0);
       for (int b = 0; b < pl->B; ++b) {
-        auto cut = [&](int64_t i0, int64_t i1, auto weight, std::vector<int32_t> &out) {   // weight < 0: placed already
-          double tot = 0, at = 0;
-          for (int64_t i = i0; i < i1; ++i) tot += std::max(weight(i), 0.0);
+        const int32_t bV = b * V;   // (slices are numbered through the instances)
+        auto cut = [&](int64_t i0, int64_t i1, double tot, auto weight, std::vector<int32_t> &out) {   // weight < 0: placed already
+          double at = 0;
           for (int64_t i = i0; i < i1; ++i) {
-            if (weight(i) < 0) continue;
-            out[i] = std::min<int32_t>(V - 1, (int32_t)(at * V / tot));
-            at += weight(i);
+            const double w = weight(i);
+            if (w < 0) continue;
+            out[i] = bV + std::min<int32_t>(V - 1, (int32_t)(at * V / tot));
+            at += w;
           }
         };
         for (int k = dinst[b]; k < dinst[b + 1]; ++k)
           for (int q = 0; q < dens[k].nplace; ++q)
             for (int32_t sl = 0; sl < V; ++sl)
               for (int64_t r = (int64_t)dens[k].rows * sl / V; r < (int64_t)dens[k].rows * (sl + 1) / V; ++r)
-                rslice[dens[k].row0[q] + r] = sl;
-        cut(pl->m_off[b], pl->m_off[b + 1],
+                rslice[dens[k].row0[q] + r] = bV + sl;
+        const int64_t i0 = pl->m_off[b], i1 = pl->m_off[b + 1], j0 = pl->n_off[b], j1 = pl->n_off[b + 1];
+        int64_t weight_A = 2 * (i1 - i0) + rp[i1] - rp[i0];   // of the instance's rows, of its columns
+        int64_t weight_At = 4 * (j1 - j0) + trp[j1] - trp[j0] + prp[j1] - prp[j0];
+        for (int k = dinst[b]; k < dinst[b + 1]; ++k) {
+          weight_At += 12 * (int64_t)dens[k].cols;
+          for (int q = 0; q < dens[k].nplace; ++q) {
+            const int64_t r = dens[k].row0[q];
+            weight_A -= 2 * (int64_t)dens[k].rows + rp[r + dens[k].rows] - rp[r];
+          }
+        }
+        cut(i0, i1, (double)weight_A,
             [&](int64_t i) { return !drow.empty() && drow[i] >= 0 ? -1.0 : 2.0 + (double)(rp[i + 1] - rp[i]); }, rslice);
-        cut(pl->n_off[b], pl->n_off[b + 1],
+        cut(j0, j1, (double)weight_At,
             [&](int64_t j) {   // a dense column also sums its products over the slices
               return 4.0 + (double)(trp[j + 1] - trp[j]) + (double)(prp[j + 1] - prp[j]) +
                      (!dcolm.empty() && dcolm[j] >= 0 ? 12.0 : 0.0);
@@ -697,7 +742,7 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
         int64_t j = pl->n_off[b];
         for (int32_t sl = 0; sl < V; ++sl) {
           colcut[(size_t)b * V + sl] = j;
-          while (j < pl->n_off[b + 1] && cslice[j] == sl) ++j;
+          while (j < pl->n_off[b + 1] && cslice[j] == bV + sl) ++j;
         }
       }
       colcut[(size_t)pl->B * V] = n;
@@ -737,52 +782,75 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
       // The rows each slice's columns use, copied to LDS for the column half:
       // the range they span, or a list of them where they fill less than half
       // of it (a few columns of a covariance-steering instance reach rows of
-      // every stage).
+      // every stage).  Nothing is made for a slice whose rows do not fit.  A
+      // slice's rows are marked one byte each and read off the range they
+      // span: sorted lists of them took longer than the rest of a plan's
+      // creation (14 of 20 ms for a program with 500,000 nonzeros).
       const size_t room = ((size_t)TEAM_MAX_LDS - lds(pl->team.dense_slots)) / 16 * 16;
-      At_loc.resize(nnz);
-      std::vector<int32_t> place(m, -1);
-      std::vector<int64_t> seen(m, -1);
+      At_loc = HostArray<uint16_t>(nnz);
+      std::vector<unsigned char> mark(align_up(m, 8) + 8, 0);
+      std::vector<uint16_t> place(m);
       for (size_t q = 0; q < (size_t)pl->B * V; ++q) {
         const int64_t ka = trp[colcut[q]], ke = trp[colcut[q + 1]];
-        std::vector<int32_t> rows;
-        for (int64_t k = ka; k < ke; ++k)
-          if (seen[tcol[k]] != (int64_t)q) {
-            seen[tcol[k]] = (int64_t)q;
-            rows.push_back(tcol[k]);
+        int64_t lo = m, hi = -1;   // a column's rows are increasing
+        for (int64_t j = colcut[q]; j < colcut[q + 1]; ++j)
+          if (trp[j] < trp[j + 1]) {
+            lo = std::min<int64_t>(lo, tcol[trp[j]]);
+            hi = std::max<int64_t>(hi, tcol[trp[j + 1] - 1]);
           }
-        std::sort(rows.begin(), rows.end());
-        const int64_t cnt = (int64_t)rows.size(), lo = cnt ? rows.front() : 0, range = cnt ? rows.back() + 1 - lo : 0;
-        if (range <= 2 * cnt) {
-          used.push_back(lo);
-          used.push_back(range);
-          for (int64_t k = ka; k < ke; ++k) At_loc[k] = (uint16_t)(tcol[k] - lo);
-        } else {
-          used.push_back(-1 - (int64_t)uses.size());
-          used.push_back(cnt);
-          for (int64_t i = 0; i < cnt; ++i) place[rows[i]] = (int32_t)i;
-          for (int64_t k = ka; k < ke; ++k) At_loc[k] = (uint16_t)place[tcol[k]];
-          uses.insert(uses.end(), rows.begin(), rows.end());
+        if (hi < 0) lo = 0;
+        const int64_t range = hi + 1 - lo;
+        for (int64_t k = ka; k < ke; ++k) mark[tcol[k]] = 1;
+        int64_t cnt = 0;
+        for (int64_t i = lo; i < hi + 1; i += 8) {   // (nothing is marked behind the last row)
+          uint64_t eight;
+          std::memcpy(&eight, &mark[i], 8);
+          cnt += __builtin_popcountll(eight);
         }
+        const bool listed = range > 2 * cnt, fits = (listed ? cnt : range) * sizeof(T) <= room;
+        used.push_back(listed && fits ? -1 - (int64_t)uses.size() : lo);
+        used.push_back(listed ? cnt : range);
+        if (listed && fits) {
+          uint16_t at = 0;
+          for (int64_t i = lo; i <= hi; i += 8) {
+            uint64_t eight;
+            std::memcpy(&eight, &mark[i], 8);
+            for (; eight != 0; eight &= eight - 1) {
+              const int64_t r = i + __builtin_ctzll(eight) / 8;
+              place[r] = at++;
+              uses.push_back((int32_t)r);
+            }
+          }
+          for (int64_t k = ka; k < ke; ++k) At_loc[k] = place[tcol[k]];
+        } else {   // (not read where they do not fit)
+          for (int64_t k = ka; k < ke; ++k) At_loc[k] = (uint16_t)(tcol[k] - lo);
+        }
+        std::fill(mark.begin() + lo, mark.begin() + hi + 1, 0);
       }
-      sliceA = sort_by_slice(rowsA, pl->bkA, rp, rinst, rslice, pl->B, V, midA);
-      sliceAt = sort_by_slice(rowsAt, pl->bkAt, trp, cinst, cslice, pl->B, V, midAt);
+      const int64_t BV = (int64_t)pl->B * V;
+      sliceA = sort_by_slice(rowsA, pl->bkA, rp, rslice, BV, midA);
+      sliceAt = sort_by_slice(rowsAt, pl->bkAt, trp, cslice, BV, midAt);
       // where the entries of a slice's listed rows begin in its LDS copy, and
       // the LDS that the copies want: the used rows (float64 in the residual
       // pass) and, next to them in the data's type, the slice's rows, then
       // also its columns
-      const int64_t BV = (int64_t)pl->B * V;
       entries.assign(2 * (size_t)BV, 0);
       std::vector<int64_t> listed(2 * (size_t)BV, 0);
       auto keep = [&](const std::vector<int32_t> &rows, const std::vector<int64_t> &cut, const std::vector<int64_t> &ptr,
                       int side, std::vector<int32_t> &begin) {
         begin.resize(rows.size());
-        for (int64_t q = 0; q < BV; ++q)
-          for (int c = 0; c < 3; ++c)
-            for (int64_t k = cut[c * (BV + 1) + q]; k < cut[c * (BV + 1) + q + 1]; ++k) {
-              begin[k] = entries[2 * q + side];
-              entries[2 * q + side] += (int32_t)(ptr[rows[k] + 1] - ptr[rows[k]]);
-              ++listed[2 * q + side];
+        for (int64_t q = 0; q < BV; ++q) {
+          int32_t at = 0;
+          for (int c = 0; c < 3; ++c) {
+            const int64_t k0 = cut[c * (BV + 1) + q], k1 = cut[c * (BV + 1) + q + 1];
+            for (int64_t k = k0; k < k1; ++k) {
+              begin[k] = at;
+              at += (int32_t)(ptr[rows[k] + 1] - ptr[rows[k]]);
             }
+            listed[2 * q + side] += k1 - k0;
+          }
+          entries[2 * q + side] = at;
+        }
       };
       keep(rowsA, sliceA, rp, 0, keptA);
       keep(rowsAt, sliceAt, trp, 1, keptAt);
@@ -817,11 +885,11 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   const size_t o_bA = take(std::max<size_t>(rowsA.size(), 1) * sizeof(int32_t));
   const size_t o_bAt = take(std::max<size_t>(rowsAt.size(), 1) * sizeof(int32_t));
   auto spans = [](const std::vector<int32_t> &rows, const std::vector<int64_t> &ptr) {
-    std::vector<RowSpan> sp(rows.size());
+    HostArray<RowSpan> sp(rows.size());
     for (size_t i = 0; i < rows.size(); ++i) sp[i] = RowSpan{ptr[rows[i]], ptr[rows[i] + 1]};
     return sp;
   };
-  const std::vector<RowSpan> spA = spans(rowsA, rp), spAt = spans(rowsAt, trp);
+  HostArray<RowSpan> spA = spans(rowsA, rp), spAt = spans(rowsAt, trp);
   const size_t o_sA = take(std::max<size_t>(spA.size(), 1) * sizeof(RowSpan));
   const size_t o_sAt = take(std::max<size_t>(spAt.size(), 1) * sizeof(RowSpan));
   const size_t o_dense = take(std::max<size_t>(dens.size(), 1) * sizeof(DenseDesc));
@@ -829,21 +897,17 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   const size_t o_drow = take(std::max<size_t>(drow.size(), 1) * sizeof(int32_t));
   const size_t o_dscale = take(std::max<size_t>(dscale.size(), 1) * sizeof(double));
   const size_t o_dcol = take(std::max<size_t>(dcolm.size(), 1) * sizeof(int32_t));
-  const size_t o_slA = take(std::max<size_t>(sliceA.size(), 1) * sizeof(int64_t));
-  const size_t o_slAt = take(std::max<size_t>(sliceAt.size(), 1) * sizeof(int64_t));
-  const size_t o_mA = take(std::max<size_t>(midA.size(), 1) * sizeof(int64_t));
-  const size_t o_mAt = take(std::max<size_t>(midAt.size(), 1) * sizeof(int64_t));
-  const size_t o_used = take(std::max<size_t>(used.size(), 1) * sizeof(int64_t));
-  const size_t o_uses = take(std::max<size_t>(uses.size(), 1) * sizeof(int32_t));
+  Staged team;
+  team.bytes.reserve(4096 + 8 * (sliceA.size() + sliceAt.size() + midA.size() + midAt.size() + used.size() + colcut.size() +
+                                 dense_cut.size()) +
+                     4 * (uses.size() + order.size() + keptA.size() + keptAt.size() + entries.size() + dense_list.size() +
+                          dense_slot.size()));
+  const size_t o_slA = team.add(sliceA), o_slAt = team.add(sliceAt), o_mA = team.add(midA), o_mAt = team.add(midAt);
+  const size_t o_used = team.add(used), o_uses = team.add(uses), o_cut = team.add(colcut), o_ord = team.add(order);
+  const size_t o_kA = team.add(keptA), o_kAt = team.add(keptAt), o_ent = team.add(entries);
+  const size_t o_dcut = team.add(dense_cut), o_dlist = team.add(dense_list), o_dslot = team.add(dense_slot);
+  const size_t o_team = take(team.bytes.size());
   const size_t o_loc = take(std::max<size_t>(At_loc.size(), 1) * sizeof(uint16_t));
-  const size_t o_cut = take(std::max<size_t>(colcut.size(), 1) * sizeof(int64_t));
-  const size_t o_ord = take(std::max<size_t>(order.size(), 1) * sizeof(int32_t));
-  const size_t o_kA = take(std::max<size_t>(keptA.size(), 1) * sizeof(int32_t));
-  const size_t o_kAt = take(std::max<size_t>(keptAt.size(), 1) * sizeof(int32_t));
-  const size_t o_ent = take(std::max<size_t>(entries.size(), 1) * sizeof(int32_t));
-  const size_t o_dcut = take(std::max<size_t>(dense_cut.size(), 1) * sizeof(int64_t));
-  const size_t o_dlist = take(std::max<size_t>(dense_list.size(), 1) * sizeof(int32_t));
-  const size_t o_dslot = take(std::max<size_t>(dense_slot.size(), 1) * sizeof(int32_t));
   if (hipMalloc(&pl->mem.ptr, off) != hipSuccess) {
     pl->mem.ptr = nullptr;
     FAIL(COSMO_ENOMEM, "plan allocation of " + std::to_string(off) + " bytes failed");
@@ -876,36 +940,27 @@ cosmo_status build_plan(cosmo_plan *pl, const cosmo_problem *p) {
   HIPCHK(up(o_drow, drow.data(), drow.size() * sizeof(int32_t)));
   HIPCHK(up(o_dscale, dscale.data(), dscale.size() * sizeof(double)));
   HIPCHK(up(o_dcol, dcolm.data(), dcolm.size() * sizeof(int32_t)));
-  HIPCHK(up(o_slA, sliceA.data(), sliceA.size() * sizeof(int64_t)));
-  HIPCHK(up(o_slAt, sliceAt.data(), sliceAt.size() * sizeof(int64_t)));
-  HIPCHK(up(o_mA, midA.data(), midA.size() * sizeof(int64_t)));
-  HIPCHK(up(o_mAt, midAt.data(), midAt.size() * sizeof(int64_t)));
-  HIPCHK(up(o_used, used.data(), used.size() * sizeof(int64_t)));
-  HIPCHK(up(o_uses, uses.data(), uses.size() * sizeof(int32_t)));
-  HIPCHK(up(o_loc, At_loc.data(), At_loc.size() * sizeof(uint16_t)));
-  HIPCHK(up(o_cut, colcut.data(), colcut.size() * sizeof(int64_t)));
-  HIPCHK(up(o_ord, order.data(), order.size() * sizeof(int32_t)));
-  HIPCHK(up(o_kA, keptA.data(), keptA.size() * sizeof(int32_t)));
-  HIPCHK(up(o_kAt, keptAt.data(), keptAt.size() * sizeof(int32_t)));
-  HIPCHK(up(o_ent, entries.data(), entries.size() * sizeof(int32_t)));
-  HIPCHK(up(o_dcut, dense_cut.data(), dense_cut.size() * sizeof(int64_t)));
-  HIPCHK(up(o_dlist, dense_list.data(), dense_list.size() * sizeof(int32_t)));
-  HIPCHK(up(o_dslot, dense_slot.data(), dense_slot.size() * sizeof(int32_t)));
-  pl->team.dense_cut = reinterpret_cast<int64_t *>(base + o_dcut);
-  pl->team.dense_list = reinterpret_cast<int32_t *>(base + o_dlist);
-  pl->team.dense_slot = reinterpret_cast<int32_t *>(base + o_dslot);
-  pl->team.sliceA = reinterpret_cast<int64_t *>(base + o_slA);
-  pl->team.sliceAt = reinterpret_cast<int64_t *>(base + o_slAt);
-  pl->team.midA = reinterpret_cast<int64_t *>(base + o_mA);
-  pl->team.midAt = reinterpret_cast<int64_t *>(base + o_mAt);
-  pl->team.used = reinterpret_cast<int64_t *>(base + o_used);
-  pl->team.uses = reinterpret_cast<int32_t *>(base + o_uses);
-  pl->team.At_loc = reinterpret_cast<uint16_t *>(base + o_loc);
-  pl->team.colcut = reinterpret_cast<int64_t *>(base + o_cut);
-  pl->team.order = reinterpret_cast<int32_t *>(base + o_ord);
-  pl->team.keptA = reinterpret_cast<int32_t *>(base + o_kA);
-  pl->team.keptAt = reinterpret_cast<int32_t *>(base + o_kAt);
-  pl->team.entries = reinterpret_cast<int32_t *>(base + o_ent);
+  if (pl->team.slices > 0) {
+    HIPCHK(up(o_team, team.bytes.data(), team.bytes.size()));
+    HIPCHK(up(o_loc, At_loc.data(), At_loc.size() * sizeof(uint16_t)));
+    auto wide = [&](size_t o) { return reinterpret_cast<const int64_t *>(base + o_team + o); };
+    auto narrow = [&](size_t o) { return reinterpret_cast<const int32_t *>(base + o_team + o); };
+    pl->team.sliceA = wide(o_slA);
+    pl->team.sliceAt = wide(o_slAt);
+    pl->team.midA = wide(o_mA);
+    pl->team.midAt = wide(o_mAt);
+    pl->team.used = wide(o_used);
+    pl->team.uses = narrow(o_uses);
+    pl->team.At_loc = reinterpret_cast<const uint16_t *>(base + o_loc);
+    pl->team.colcut = wide(o_cut);
+    pl->team.order = narrow(o_ord);
+    pl->team.keptA = narrow(o_kA);
+    pl->team.keptAt = narrow(o_kAt);
+    pl->team.entries = narrow(o_ent);
+    pl->team.dense_cut = wide(o_dcut);
+    pl->team.dense_list = narrow(o_dlist);
+    pl->team.dense_slot = narrow(o_dslot);
+  }
   pl->d_n_off = reinterpret_cast<int64_t *>(base + o_noff);
   pl->d_m_off = reinterpret_cast<int64_t *>(base + o_moff);
   pl->d_At_rowptr = reinterpret_cast<int64_t *>(base + o_trp);

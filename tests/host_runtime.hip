@@ -76,7 +76,9 @@ void host_runtime_team(int i, long long *out) {   // the team tables of a k_pcg_
   const cosmo::View<double> &v = launches[i].view;
   const auto at = [](const void *p) { return (long long)reinterpret_cast<uintptr_t>(p); };
   const long long f[] = {v.B, v.n_tot, t.slices, t.max_n, t.cap_off, t.cap, at(t.colcut), at(v.dcol),
-                         at(t.dense_cut), at(t.dense_list), at(t.dense_slot), t.dense_slots};
+                         at(t.dense_cut), at(t.dense_list), at(t.dense_slot), t.dense_slots,
+                         at(t.used), at(t.uses), at(t.At_loc), at(v.At_rowptr), at(v.At_col), at(t.sliceA), at(v.rowsA),
+                         v.m_tot};
   std::memcpy(out, f, sizeof f);
 }
 

@@ -43,16 +43,19 @@ class HostRuntime:
     def team(self, launch):
         """The team tables of a k_pcg_team launch (views of the plan's memory)."""
         names = ("B", "n", "slices", "max_n", "cap_off", "cap", "colcut", "dcol", "dense_cut", "dense_list", "dense_slot",
-                 "dense_slots")
+                 "dense_slots", "used", "uses", "At_loc", "At_rowptr", "At_col", "sliceA", "rowsA", "m")
         v = (ctypes.c_longlong * len(names))()
         self.lib.host_runtime_team(launch.index, v)
         t = dict(zip(names, v))
         BV = t["B"] * t["slices"]
         for k, n, dt in (("colcut", BV + 1, np.int64), ("dcol", t["n"], np.int32), ("dense_cut", BV + 1, np.int64),
-                         ("dense_slot", t["n"], np.int32)):
+                         ("dense_slot", t["n"], np.int32), ("used", 2 * BV, np.int64), ("At_rowptr", t["n"] + 1, np.int64),
+                         ("sliceA", 3 * (BV + 1), np.int64), ("rowsA", t["m"], np.int32)):
             t[k] = array(t[k], n, dt) if t[k] else None
         if t["dense_cut"] is not None:
             t["dense_list"] = array(t["dense_list"], int(t["dense_cut"][-1]), np.int32)
+        nnz = int(t["At_rowptr"][-1])
+        t["At_loc"], t["At_col"] = array(t["At_loc"], nnz, np.uint16), array(t["At_col"], nnz, np.int32)
         return t
 
 
