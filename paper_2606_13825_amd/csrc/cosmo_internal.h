@@ -318,7 +318,8 @@ template <typename T> void launch_soc_proj(const SocDesc *d, int32_t n, const T 
 
 // PSD (k_psd.hip).  Blocks are processed by order class; `d` lists blocks
 // [0, n).  Forward step: eig of smat(vv_blk), Pi, s+ and y+ rows, eigenpairs
-// to (U, lam).  Standalone: the same with no y update.
+// to (U, lam).  Standalone: the same with no y update.  warm: start from the
+// float64 eigenvectors that the previous step left in rscratch (keep_warm).
 struct PsdLaunchCfg {
   int32_t max_sweeps;
   double tol;
@@ -336,7 +337,7 @@ constexpr int32_t kEigThreadsAlt[4] = {128, 512, 1024, 1024};
 constexpr int32_t kVjpThreads = 1024, kVjpThreadsAlt = 512;
 template <typename T> void launch_psd_step(const PsdDesc *d, int32_t n, const PsdLaunchCfg &cfg,
                                            const T *rho_hat, const T *vv, const T *sh, const T *y, T *s_new,
-                                           T *y_new, T *U, T *lam, double *rscratch, const T *Uprev,
+                                           T *y_new, T *U, T *lam, double *rscratch, bool warm,
                                            cosmo_stats *stats, hipStream_t st);
 // A projection without a plan: blocks of the classes up to order 128, in class
 // order (begin: of the three classes and their end; maxp: their largest).

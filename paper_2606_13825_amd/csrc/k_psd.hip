@@ -921,13 +921,13 @@ void run_eig_large(const EigArgs<T> &a, int32_t n, int32_t max_p, hipStream_t st
 template <typename T>
 void launch_psd_step(const PsdDesc *d, int32_t n, const PsdLaunchCfg &cfg, const T *rho_hat, const T *vv,
                      const T *sh, const T *y, T *s_new, T *y_new, T *U, T *lam, double *rscratch,
-                     const T *Uprev, cosmo_stats *stats, hipStream_t st) {
+                     bool warm, cosmo_stats *stats, hipStream_t st) {
   if (n <= 0) return;
   const int mp = cfg.max_p;
   const int cls = mp <= 32 ? 0 : mp <= 64 ? 1 : mp <= 128 ? 2 : 3;
   const bool alt = cfg.threads != 0 && cfg.threads == kEigThreadsAlt[cls] && cfg.threads != kEigThreads[cls];
   const EigArgs<T> a{d, cfg.max_sweeps, cfg.tol, y_new != nullptr ? 0 : 1, rho_hat, vv, sh, y, s_new, y_new, U, lam,
-                     stats, cfg.refine, rscratch, Uprev && rscratch ? 1 : 0, cfg.keep_warm && rscratch ? 1 : 0};
+                     stats, cfg.refine, rscratch, warm && rscratch ? 1 : 0, cfg.keep_warm && rscratch ? 1 : 0};
   static_assert(kEigThreads[0] == 64 && kEigThreads[1] == 256 && kEigThreads[2] == 512 && kEigThreads[3] == 1024,
                 "class defaults");
   static_assert(kEigThreadsAlt[0] == 128 && kEigThreadsAlt[1] == 512 && kEigThreadsAlt[2] == 1024, "class alternatives");
@@ -965,7 +965,7 @@ void launch_psd_proj(const PsdDesc *d, const int32_t *begin, const int32_t *maxp
     PsdLaunchCfg one = cfg;
     one.max_p = maxp[c];
     launch_psd_step<T>(d + begin[c], begin[c + 1] - begin[c], one, nullptr, in, nullptr, nullptr, out, nullptr, U, lam,
-                       rscratch, nullptr, nullptr, st);
+                       rscratch, false, nullptr, st);
   }
 }
 
@@ -1018,10 +1018,10 @@ bool launch_psd_vjp(const PsdDesc *d, int32_t n, int32_t max_p, const T *U, cons
 
 template void launch_psd_step<float>(const PsdDesc *, int32_t, const PsdLaunchCfg &, const float *, const float *,
                                      const float *, const float *, float *, float *, float *, float *, double *,
-                                     const float *, cosmo_stats *, hipStream_t);
+                                     bool, cosmo_stats *, hipStream_t);
 template void launch_psd_step<double>(const PsdDesc *, int32_t, const PsdLaunchCfg &, const double *,
                                       const double *, const double *, const double *, double *, double *, double *,
-                                      double *, double *, const double *, cosmo_stats *, hipStream_t);
+                                      double *, double *, bool, cosmo_stats *, hipStream_t);
 template void launch_psd_proj<float>(const PsdDesc *, const int32_t *, const int32_t *, const PsdLaunchCfg &,
                                      const float *, float *, float *, float *, double *, int32_t, hipStream_t);
 template void launch_psd_proj<double>(const PsdDesc *, const int32_t *, const int32_t *, const PsdLaunchCfg &,

@@ -1025,7 +1025,10 @@ void build_layouts(cosmo_plan *pl) {
   f.lam = take(pl->sum_p);
   f.rp = take(m);
   f.rd = take(n);
-  f.rs = take(3 * (size_t)pl->sum_p2 * 8 / pl->esz);   // eigensolver refinement scratch
+  // eigensolver scratch, 3 p^2 doubles per block: the first p^2 hold its
+  // float64 eigenvectors and must survive to the next step, which starts from
+  // them (warm start)
+  f.rs = take(3 * (size_t)pl->sum_p2 * 8 / pl->esz);
   // float64 scratch of the dense sub-blocks: row products, column products, Jacobi terms
   f.dn = take((size_t)pl->dense_rows_tot * 8 / pl->esz);
   f.ec = take((size_t)pl->dense_cols_tot * 8 / pl->esz);
@@ -1099,7 +1102,7 @@ template <typename F> void fork_classes(cosmo_plan *pl, hipStream_t st, F &&laun
 
 template <typename T>
 void launch_psd_classes(cosmo_plan *pl, const T *rho_hat, const T *vv, const T *sh, const T *y, T *s_new, T *y_new,
-                        T *U, T *lam, double *rscratch, const T *Uprev, cosmo_stats *stats, hipStream_t st) {
+                        T *U, T *lam, double *rscratch, bool warm, cosmo_stats *stats, hipStream_t st) {
   ProfScope ps(pl, 0, st);
   const bool refine = pl->opt.dtype == COSMO_F32 && pl->opt.eig_refine > 0;
   fork_classes(pl, st, [&](int c, hipStream_t s) {
@@ -1108,7 +1111,7 @@ void launch_psd_classes(cosmo_plan *pl, const T *rho_hat, const T *vv, const T *
                      pl->eig_threads[c], pl->opt.eig_warm_start != 0};
     ProfScope pc(pl, 4 + c, s);   // this class's kernel alone, on the stream it runs on
     launch_psd_step<T>(pl->d_psd + pl->psd_cls_begin[c], n, cfg, rho_hat, vv, sh, y, s_new, y_new, U, lam,
-                       rscratch, Uprev, stats, s);
+                       rscratch, warm, stats, s);
   });
 }
 
@@ -1355,13 +1358,13 @@ cosmo_status forward_impl(cosmo_plan *pl, const T *rho, const T *alpha, const T 
       launch_rows_post<T>(v, pl->bkA, rh, al, xt, s, y, ST(k), ws + f.sh, ws + f.vv, sn, yn, st);
     }
     launch_soc_step<T>(pl->d_soc, pl->n_soc, rh, ws + f.vv, ws + f.sh, y, sn, yn, st);
-    // warm start from the previous step's eigenvectors of the same blocks (the
-    // tape keeps them; without a tape the single buffer is updated in place,
-    // each block reading its own slot before overwriting it)
-    const T *Uprev = (pl->opt.eig_warm_start && (k > 0 || (continues && !tape))) ? (tape ? UU(k - 1) : UU(k))
-                                                                                  : nullptr;
+    // warm start from the previous step's eigenvectors of the same blocks, kept
+    // in float64 in the workspace's eigensolver scratch (f.rs), each block
+    // reading its own before overwriting them; a call that continues the
+    // previous one without a tape finds that call's last ones there
+    const bool warm = pl->opt.eig_warm_start && (k > 0 || (continues && !tape));
     launch_psd_classes<T>(pl, rh, ws + f.vv, ws + f.sh, y, sn, yn, UU(k), LAM(k),
-                          reinterpret_cast<double *>(ws + f.rs), Uprev, stats, st);
+                          reinterpret_cast<double *>(ws + f.rs), warm, stats, st);
   }
   if (pol) policy_fwd_at<T>(pl, v, *pol, K, X(K), S(K), Y(K), nullptr, nullptr, rho_hat, st);
   launch_nonfinite_check<T>(v, X(K), S(K), Y(K), stats, st);
@@ -2436,12 +2439,12 @@ cosmo_status psd_proj(int32_t nblk, const int32_t *order, const int64_t *offset,
   if (dtype == COSMO_F32) {
     launch_psd_proj<float>(d, cb, cm, cfg, (const float *)in, (float *)out, (float *)eigvecs, (float *)eigvals, rs, ncu, st);
     launch_psd_step<float>(d + cb[3], large, cfg, nullptr, (const float *)in, nullptr, nullptr, (float *)out, nullptr,
-                           (float *)eigvecs, (float *)eigvals, rs, nullptr, nullptr, st);
+                           (float *)eigvecs, (float *)eigvals, rs, false, nullptr, st);
   } else {
     launch_psd_proj<double>(d, cb, cm, cfg, (const double *)in, (double *)out, (double *)eigvecs, (double *)eigvals, rs,
                             ncu, st);
     launch_psd_step<double>(d + cb[3], large, cfg, nullptr, (const double *)in, nullptr, nullptr, (double *)out,
-                            nullptr, (double *)eigvecs, (double *)eigvals, rs, nullptr, nullptr, st);
+                            nullptr, (double *)eigvecs, (double *)eigvals, rs, false, nullptr, st);
   }
   HIPCHK(hipGetLastError());
   return COSMO_OK;
