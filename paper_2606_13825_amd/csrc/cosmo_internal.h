@@ -323,7 +323,7 @@ template <typename T> void launch_soc_proj(const SocDesc *d, int32_t n, const T 
 struct PsdLaunchCfg {
   int32_t max_sweeps;
   double tol;
-  int32_t refine;          // float64 refinement steps after the Jacobi sweeps
+  int32_t refine;          // float32: sweeps go on until the couplings are below float32's accuracy
   int32_t max_p;           // largest order in the list
   int32_t threads = 0;     // threads per workgroup of the eigensolve; 0 = the class default
   bool keep_warm = false;  // keep the float64 eigenvectors in the scratch for the next step's warm start

@@ -105,6 +105,9 @@ template <int L, typename AT, typename V, typename G> __device__ inline AT strid
 // Eight waves: the kernel's state does not fit the 128 registers of sixteen
 // (with 1024 threads 16 covariance-steering instances took 8.5 ms per training
 // step instead of 6.9, one program with 500,000 nonzeros 3.8 instead of 3.2).
+// In the 256 of eight it fits without dense blocks (185 to 201) and with
+// narrow ones; the instantiations for the widest blocks of a stored type spill
+// 18 to 73, those that run 2000 x 500 blocks stored in float32 27.
 constexpr int NTH = 512;
 
 // Where the length classes of a slice end in its list, from its list ranges

@@ -51,27 +51,22 @@ template <int G, int NB> __host__ __device__ constexpr int eig_ld(int p) {
 }
 
 // Runs comp(t) for the tiles t = wave, wave + nw, ... below ntiles and stores
-// each result with wr(t, result).  INPL: the wave keeps all its results in
-// registers until every wave has finished computing (one barrier), so wr may
-// overwrite what comp reads; HOLD must cover the tiles of one wave.  Ends
-// with a barrier.
-template <int HOLD, bool INPL, typename Fc, typename Fw>
+// each result with wr(t, result).  A wave keeps all its results in registers
+// until every wave has finished computing (one barrier), so wr may overwrite
+// what comp reads; HOLD must cover the tiles of one wave.  Ends with a barrier.
+template <int HOLD, typename Fc, typename Fw>
 __device__ inline void tile_pass(int ntiles, int wave, int nw, Fc comp, Fw wr) {
-  if constexpr (INPL) {
-    decltype(comp(0)) hold[HOLD];
+  decltype(comp(0)) hold[HOLD];
 #pragma unroll
-    for (int h = 0; h < HOLD; ++h) {
-      const int t = wave + h * nw;
-      if (t < ntiles) hold[h] = comp(t);
-    }
-    __syncthreads();
+  for (int h = 0; h < HOLD; ++h) {
+    const int t = wave + h * nw;
+    if (t < ntiles) hold[h] = comp(t);
+  }
+  __syncthreads();
 #pragma unroll
-    for (int h = 0; h < HOLD; ++h) {
-      const int t = wave + h * nw;
-      if (t < ntiles) wr(t, hold[h]);
-    }
-  } else {
-    for (int t = wave; t < ntiles; t += nw) wr(t, comp(t));
+  for (int h = 0; h < HOLD; ++h) {
+    const int t = wave + h * nw;
+    if (t < ntiles) wr(t, hold[h]);
   }
   __syncthreads();
 }
@@ -271,7 +266,7 @@ __device__ __forceinline__ void eig_block(const EigArgs<T> &a, const PsdDesc &d,
   constexpr int HOLD = (NTMAX * NTMAX + NWv - 1) / NWv;
   if (a.warm_read) {
     // S is in W, so the products are held in registers until all are done
-    tile_pass<HOLD, true>(
+    tile_pass<HOLD>(
         nt * nt, wave, NWv,
         [&](int t) {
           const int I = t / nt, J = t % nt;
@@ -614,10 +609,10 @@ template <typename T> __device__ inline T vjp_weight(int rule, T li, T lj, bool 
   return fb / (b - a) + fa / (a - b);
 }
 
-// PSD VJP: out = svec(U (W o (U' smat(g) U)) U'), W from vjp_weight.  Buffers:
-// B0 and B1 (p x p, stride dk_ld(p)) in LDS when they fit, else B1 in global
-// scratch (stride p); U read from LDS when a third buffer fits, else from
-// global memory.
+// PSD VJP of orders up to 128: out = svec(U (W o (U' smat(g) U)) U'), W from
+// vjp_weight.  Buffers: B0 (p x p, stride dk_ld(p)) in LDS, B1 too when both
+// fit, else in global scratch (stride p); U read from LDS when a third buffer
+// fits, else from global memory.
 template <typename T, int NT>
 __global__ __launch_bounds__(NT) void k_psd_vjp(const PsdDesc *__restrict__ descs, const T *__restrict__ Ug,
                                                 const T *__restrict__ lam, const T *__restrict__ g,
@@ -625,13 +620,12 @@ __global__ __launch_bounds__(NT) void k_psd_vjp(const PsdDesc *__restrict__ desc
                                                 int32_t rule, T eps) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   T *lds = reinterpret_cast<T *>(smem_raw);
-  __shared__ T lam_s[MAXP];
+  __shared__ T lam_s[128];
   const PsdDesc d = descs[blockIdx.x];
   const int p = d.p, pp = p * p, lp = dk_ld(p), ppl = p * lp;
   const int tid = threadIdx.x;
   T *B0 = lds;
-  // B0 keeps the padded stride when it fits, else p (the largest orders)
-  const int l0 = ppl <= lds_elems ? lp : p;
+  const int l0 = lp;
   const bool b1_lds = 2 * ppl <= lds_elems;
   T *B1 = b1_lds ? lds + ppl : scratch + d.uoff;
   const int l1 = b1_lds ? lp : p;
@@ -978,18 +972,12 @@ template <typename T, int NT>
 bool run_vjp(const PsdDesc *d, int32_t n, int32_t max_p, const T *U, const T *lam, const T *g, T *out, T *scratch,
              hipStream_t st, int32_t rule, double eps) {
   const size_t dyn_bytes = allow_dyn_lds(reinterpret_cast<const void *>(&k_psd_vjp<T, NT>));
-  // LDS holds B0 (and B1, then U) at the padded stride while they fit; the
-  // largest orders keep only B0, unpadded (order 200 in float32: 160,000
-  // bytes), with B1 in the global scratch.
+  // LDS holds B0, then B1, then U while they fit; B0 alone always does (order
+  // 128 in float64: 135,168 bytes)
   const size_t ppl = (size_t)max_p * dk_ld(max_p);   // p dk_ld(p) does not decrease with p
-  const size_t pp = (size_t)max_p * max_p;
   const size_t budget = dyn_bytes / sizeof(T);
-  size_t elems;
-  if (3 * ppl <= budget) elems = 3 * ppl;
-  else if (2 * ppl <= budget) elems = 2 * ppl;
-  else if (ppl <= budget) elems = ppl;
-  else if (pp <= budget) elems = pp;   // every order the validation admits fits here
-  else return false;
+  if (max_p > 128 || ppl > budget) return false;
+  const size_t elems = std::min<size_t>(3, budget / ppl) * ppl;
   k_psd_vjp<T, NT><<<n, NT, elems * sizeof(T), st>>>(d, U, lam, g, out, scratch, (int32_t)elems, rule, (T)eps);
   return true;
 }
