@@ -75,7 +75,7 @@ EIG_SOURCE = [os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "k_psd.hip"),
               os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "jacobi_sweeps.h"),
               os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "mma_tiles.h")]
 PCG_PROFILE = os.path.join(ROOT, "profiles", "k_pcg_huber256_pmc.md")
-PCG_C5_PROFILE = os.path.join(ROOT, "profiles", "k_pcg_coop_covsteer128_pmc.md")
+PCG_TEAM_PROFILE = os.path.join(ROOT, "profiles", "k_pcg_team_covsteer128_pmc.md")
 NS_PROFILE = os.path.join(ROOT, "profiles", "k_ns_gemm_appc_pmc.md")
 NS_SOURCE = [os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "k_ns.hip"),
              os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "mma_tiles.h")]
@@ -83,6 +83,19 @@ APPB_PROFILE = os.path.join(ROOT, "profiles", "k_pcg_coop_appb_pmc.md")
 PCG_SOURCE = [os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "k_pcg.hip"),
               os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "pcg_ops.h"),
               os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "wave_ops.h")]
+
+
+PCG_TEAM_SOURCE = [os.path.join(ROOT, "paper_2606_13825_amd", "csrc", "k_pcg_team.hip")] + PCG_SOURCE[1:]
+
+
+def pcg_kernel_name(kernel, workgroups, f32, stored_f32=False):
+    """The kernel that runs the CG solves (CosmoBatch.cg_kernel), by name and
+    what shares an instance in it."""
+    t = "float" if f32 else "double"
+    dense = ", dense blocks fused, stored float32" if stored_f32 else ""
+    return {"team": f"k_pcg_team<{t}> (teams of up to {workgroups} workgroups per instance{dense})",
+            "cooperative": f"k_pcg_coop<{t}> (one cooperative launch over the device)",
+            "workgroup": f"k_pcg<{t}> (one workgroup per instance{dense})"}[kernel]
 
 
 def psd_order_class(orders):
@@ -454,6 +467,7 @@ def appb_study(ns=(1000, 2000, 5000, 10000, 20000, 50000), reps=3, seed=8, dense
         batch.set_pcg_form(4)
         rho = torch.from_numpy(rho_row.astype(np.float32)[None, :].copy()).to(dev)
         alpha = torch.ones((1, 1), dtype=torch.float32, device=dev)
+        kernel = batch.cg_kernel()
         tape, fws, bws = batch.new_tape(), batch.new_fwd_ws(), batch.new_bwd_ws()
         stats = batch.new_stats()
         fw = batch.forward(rho, alpha, tape=tape, ws=fws, stats=stats)
@@ -475,7 +489,7 @@ def appb_study(ns=(1000, 2000, 5000, 10000, 20000, 50000), reps=3, seed=8, dense
         sd = batch.stats_dict(st2)
         ops = float(sd["cg_iters_total"].sum() + sd["cg_passes_total"].sum()) / reps
         cg_bytes = ops * pcg_bytes_per_iteration(inst, 4)
-        row = {"n": n, "m": m, "nnz_A": int(inst.A.nnz), "peak_hbm_bytes": int(peak), "plan_bytes": int(plan_bytes),
+        row = {"n": n, "m": m, "nnz_A": int(inst.A.nnz), "cg_kernel": kernel[0], "peak_hbm_bytes": int(peak), "plan_bytes": int(plan_bytes),
                "bwd_ms": ms, "bwd_cg_operator_applications": ops, "bwd_cg_bytes": cg_bytes,
                "bwd_cg_gbs": cg_bytes / (ms * 1e-3) / 1e9,
                "dense_reduced_matrix_bytes": 4 * n * n, "dense_kkt_bytes": 4 * (n + m) ** 2}
@@ -500,8 +514,7 @@ def appb_study(ns=(1000, 2000, 5000, 10000, 20000, 50000), reps=3, seed=8, dense
                                  "pcg_form": 4, "cg_tol": APPB_CG_TOL, "reps": reps,
                                  "dense_baselines": dense_baselines},
                       "rows": rows,
-                      "roofline": {"kernel": "k_pcg_team<float> or, above 64 MB per application, k_pcg_coop<float> "
-                                             "(backward adjoint solve)", "n": last["n"],
+                      "roofline": {"kernel": pcg_kernel_name(*kernel, True) + ", backward adjoint solve", "n": last["n"],
                                    "bound": "hbm", "achieved": last["bwd_cg_gbs"], "peak": PEAK_HBM_GBS,
                                    "unit": "GB/s", "frac": last["bwd_cg_gbs"] / PEAK_HBM_GBS,
                                    "traffic": traffic_from_profile(APPB_PROFILE, PCG_SOURCE, n=last["n"]),
@@ -1057,17 +1070,15 @@ def main():
                     for i, inst in enumerate(insts))
         avg_ms = ms_pcg / n_pcg
         ach = total / n_pcg / (avg_ms * 1e-3) / 1e9
-        form = batch.pcg_form()
-        tn = "float" if esz == 4 else "double"
-        kname = (f"k_pcg_team<{tn}> or, above 64 MB per application, k_pcg_coop<{tn}> (form {form})" if form > 0
-                 else f"k_pcg<{tn}> (one workgroup per instance"
-                      + ((", dense blocks fused" + (", stored float32)" if gsz < esz else ")"))
-                         if batch.n_dense else ")"))
+        kernel, workgroups = batch.cg_kernel()
+        kname = pcg_kernel_name(kernel, workgroups, esz == 4, batch.n_dense > 0 and gsz < esz)
+        # counter summaries of the workloads' kernels: c4's one workgroup per
+        # instance, c5's teams
+        profile = {("c4", "workgroup"): (PCG_PROFILE, PCG_SOURCE),
+                   ("c5", "team"): (PCG_TEAM_PROFILE, PCG_TEAM_SOURCE)}.get((args.workload, kernel))
         rooflines["pcg"] = {"kernel": kname, "bound": "hbm", "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                             "frac": ach / PEAK_HBM_GBS,
-                            "traffic": ({"c4": lambda: traffic_from_profile(PCG_PROFILE, PCG_SOURCE, pcg_form=form),
-                                         "c5": lambda: traffic_from_profile(PCG_C5_PROFILE, PCG_SOURCE, pcg_form=form)}
-                                        .get(args.workload, lambda: None)()),
+                            "traffic": traffic_from_profile(*profile, pcg_form=0) if profile else None,
                             "bytes_per_launch": total / n_pcg, "avg_launch_ms": avg_ms, "launches": n_pcg,
                             "mean_cg_iterations": float(iters.sum() / (n_pcg * B)),
                             "mean_residual_passes": float(passes.sum() / (n_pcg * B)),

@@ -42,11 +42,11 @@
 // cycles), about as many instructions again for the reduction, the rotation
 // and the broadcasts, and their latency; above order 128, two waves to a
 // SIMD, also the LDS traffic of the exchange (320 KB a phase at order 200,
-// 2500 of its 10900 cycles).  Measured per sweep: 10 us at order 30, 23 us at
-// 60 (NB = 2), 55 us at 100, 73 us at 128, 150 us at 160, 230 us at 200 (NB =
-// 4).  Reading and writing both columns of every pair in LDS for each
+// 2500 of its 10900 cycles).  Measured per sweep: 10 us at order 30, 24 us at
+// 60 (NB = 2), 56 us at 100, 73 us at 128, 150 us at 160, 230 us at 200 (NB =
+// 4); with float64 angles 11, 24, 58 and 75 us, 134 us at 140.  Reading and writing both columns of every pair in LDS for each
 // rotation (the circle schedule, which this replaces) took 1542 us for the
-// projection of an order-100 float64 block, this 487 us; two-column blocks at
+// projection of an order-100 float64 block, this 500 us; two-column blocks at
 // order 100 (twice the exchanges, two waves per SIMD) 64 us per sweep.
 #pragma once
 

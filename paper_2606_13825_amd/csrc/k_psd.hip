@@ -348,7 +348,8 @@ __global__ __launch_bounds__(NT) void k_psd_eig(const EigArgs<T> a) {
 // the largest (the smaller ones' sweeps leave waves at the barriers).  For
 // calls whose blocks do not fill the device: class after class, such a launch
 // takes as long as its largest block, three times over (48 float64 blocks of
-// orders 20 to 100: 82 + 214 + 502 us; together 502).
+// orders 20 to 100: 82 + 214 + 502 us; together 502, and 510 with float64
+// angles).
 template <typename T>
 __global__ __launch_bounds__(512) void k_psd_eig_mixed(const EigArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -371,7 +372,7 @@ __global__ __launch_bounds__(512) void k_psd_eig_mixed(const EigArgs<T> a) {
 // product lands in the registers that the sweeps want it in: result rows of
 // the matrix cores' 16 x 16 x 4 are the columns of one block of the four
 // groups of a wave, result columns the sixteen lanes of a group.
-// Sixteen float32 blocks of orders 129 to 200: 2.1 ms; float32 sweeps with an
+// Sixteen float32 blocks of orders 129 to 200: 2.1 to 2.3 ms; float32 sweeps with an
 // Ogita-Aishima refinement of the eigenpairs in float64 products (two to
 // three passes over global scratch, about 515 us each at order 200) took 3.6.
 constexpr int LARGE_NT = 448;
